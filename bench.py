@@ -439,8 +439,8 @@ def main() -> int:
                                        "rotating inputs; d=8192 is the 80-layer point", **sweep}
 
     # ---- decode latency (config 2): fp16, T = 1 and 8.  Router weights are static at inference, so the
-    # serving loop's call is the one on pre-packed weights (automatic choice: the split-k form on the
-    # matrix cores, in one launch); the raw-weight call (fp32 W1, latency kernel, no packing pass) is timed beside it.
+    # serving loop's call is the one on pre-packed weights (automatic choice: the few-rows kernel on the
+    # matrix cores, one launch); the raw-weight call (fp32 W1, latency kernel, no packing pass) is timed beside it.
     if not args.no_decode:
         dec = {}
         evict_src = torch.empty(512 << 20, dtype=torch.uint8, device="cuda")
@@ -500,8 +500,8 @@ def main() -> int:
                 lat_g.append(time.perf_counter() - t0)
             lat_g.sort()
             dec[f"T{Td}"] = {"us_per_call": round(r_d["wall"] * 1e6, 2), "calls_per_s": round(1.0 / r_d["wall"], 1),
-                             "entry_point": "tide_select_exit_packed (fp16 packed weights; split-k form in one launch: 64 workgroups, "
-                                            "the last of each checkpoint's eight finishes its router)",
+                             "entry_point": "tide_select_exit_packed (fp16 packed weights; few-rows kernel: 64 workgroups of 16 columns "
+                                            "each, the last one adds their shares of every logit)",
                              "cache_state": "warm: the same 8 MiB of packed routers and the same rows are re-read back to back "
                                             "and stay in L2 / the last-level cache",
                              "us_per_call_hip_events": round(r_d["mean"] * 1e6, 2),

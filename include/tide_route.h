@@ -61,10 +61,11 @@
  *    (a caller-owned workspace: by the caller's next tide_workspace_init).
  *  - W1 / packed, w2, and b1 when given, must be 16-byte aligned (TIDE_ERR_ALIGNMENT).
  *  - Small batches (a decode step, or one checkpoint's call on a few hundred rows) run on kernels
- *    that split each router's contraction over the whole chip: a matrix-core split-k pair for
- *    packed weights, an fp32 latency kernel for raw weights up to 8 rows per checkpoint and, up
- *    to 32, for hidden sizes the pair does not cover; larger batches on the streaming kernels.
- *    All of them compute the same function.
+ *    that split each router's work over the whole chip: on packed weights the few-rows kernel
+ *    (a workgroup per 16 rows and 16 bottleneck columns) while its workgroups fit the chip, a
+ *    matrix-core split-k pair beyond; an fp32 latency kernel for raw weights up to 8 rows per
+ *    checkpoint (32 for hidden sizes that are not multiples of 128); larger batches on the
+ *    streaming kernels.  All of them compute the same function.
  */
 #ifndef TIDE_ROUTE_H
 #define TIDE_ROUTE_H
@@ -302,8 +303,8 @@ int tide_set_prefill_form(int form);
  * of a checkpoint possibly ragged).  kernel: 1 split-k pair, 2 wide-tile, 3 wide-tile fp32, 4 one-tile,
  * 5 / 6 streaming with 128 / 64 rows, 7 register-ring, 8 band (rows_per_tile = 32: the blocks its
  * bands are counted in, see tide_band_schedule), 9 split-k in one launch, 10 square.  Returns the number of launches (1 or 2) or a
- * negative tide_status_t.  Calls with at most 32 rows per checkpoint may take the latency kernel
- * instead (see the conventions); this function describes the prefill path only.              */
+ * negative tide_status_t.  Calls of few rows take the few-rows or the latency kernel
+ * instead under the automatic settings (see the conventions); this function describes the prefill path only.              */
 int tide_prefill_plan(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int cus, int form, int32_t* out);
 
 /* The persistent streaming kernels' schedule, for tests (host arithmetic, no GPU needed; the very

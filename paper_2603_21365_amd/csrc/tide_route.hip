@@ -18,6 +18,7 @@
 #include "compact_kernel.hpp"
 #include "cosine_kernel.hpp"
 #include "decode_kernel.hpp"
+#include "few_rows_kernel.hpp"
 #include "pack_kernel.hpp"
 #include "prefill_dma_kernel.hpp"
 #include "prefill_kernel.hpp"
@@ -56,6 +57,7 @@ constexpr size_t kCounterSlots = 64;       // per-checkpoint counters of the dec
 constexpr int kDecodeAutoMaxT = 32;
 constexpr int kDecodeRawMaxT = 8;          // raw weights where the split-k prefill form applies
 constexpr int kDecodeMaxT = 64;
+static_assert(kFewMaxTiles <= (int)kCounterSlots, "the few-rows kernel: a counter per row tile");
 constexpr int kSplitkMaxSlices = 8;        // workgroups that share a tile's k range in the split-k prefill form
 constexpr int kSplitkMaxTiles = 128;       // most 128-row tiles' worth of rows (x column halves) the split-k form is considered for ...
 constexpr int kSplitkForcedMaxTiles = 1024;   // ... and when it is forced (tide_set_prefill_form(5)): bounds the partial results at 512 MiB
@@ -684,9 +686,10 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     return plan;
 }
 
-int launch_prefill(const Scratch& sc, const PrefillPlan& plan, const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t d_mean,
-                   int64_t b, int64_t ckpt_stride, int64_t row_stride, const void* packed, float eps, const float* b1, const float* w2,
-                   const CheckpointTable& tab, int32_t min_layer, int32_t no_exit, const Outputs& o, hipStream_t st) {
+// What the prefill kernels and the few-rows kernel take, all but the tiling.
+PrefillParams prefill_params(const Scratch& sc, const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t d_mean, int64_t b,
+                             int64_t ckpt_stride, int64_t row_stride, const void* packed, float eps, const float* b1, const float* w2,
+                             const CheckpointTable& tab, int32_t min_layer, int32_t no_exit, const Outputs& o) {
     PrefillParams p;
     std::memset(&p, 0, sizeof(p));
     const size_t eb = elem_bytes(dtype);
@@ -712,6 +715,12 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, const void* hidde
     p.fire_mask = o.fire_mask;
     p.tab = tab;
     p.arrive = o.exit_layer ? sc.arrive : nullptr;
+    return p;
+}
+
+int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, int dtype, hipStream_t st) {
+    const int64_t b = p.b;
+    const size_t eb = elem_bytes(dtype);
     int rc = TIDE_OK;
     const bool two_halves = halves_of(b) == 2;
     const int ntile = (int)(p.dpad * (int64_t)eb / kTileBytes);
@@ -775,6 +784,32 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, const void* hidde
     return TIDE_OK;
 }
 
+// The few-rows kernel: a workgroup per 16 rows and 16 columns of the bottleneck.
+template <int DT> int launch_few(unsigned grid, hipStream_t st, const PrefillParams& p) {
+    static bool raised[kMaxDevices] = {};
+    int dev = 0;
+    TIDE_HIP(hipGetDevice(&dev));
+    if (!raised[dev]) {
+        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_few_rows_kernel<DT>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, few_lds_bytes(kFewRows)));
+        raised[dev] = true;
+    }
+    hipLaunchKernelGGL((tide_few_rows_kernel<DT>), dim3(grid), dim3(kFewThreads), few_lds_bytes(std::min(p.T, kFewRows)), st, p);
+    return TIDE_OK;
+}
+int launch_few_rows(const Scratch& sc, PrefillParams p, int dtype, hipStream_t st) {
+    p.tiles_per_ckpt = (p.T + kFewRows - 1) / kFewRows;
+    p.total_tiles = p.C * p.tiles_per_ckpt;
+    p.k_slices = p.b / kFewCols;
+    p.zpart = sc.part;
+    p.counters = sc.counters;
+    const unsigned grid = 8u * (unsigned)((p.total_tiles * p.k_slices + 7) / 8);
+    const int rc = by_dtype(dtype, [&](auto dt) { return launch_few<decltype(dt)::value>(grid, st, p); });
+    if (rc) return rc;
+    TIDE_HIP(hipGetLastError());
+    return TIDE_OK;
+}
+
 int launch_decode(const Scratch& sc, const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int64_t ckpt_stride,
                   int64_t row_stride, const float* gamma, const float* W1, const void* packed, float eps, const float* b1, const float* w2,
                   const CheckpointTable& tab, int32_t min_layer, int32_t no_exit, const Outputs& o, hipStream_t st) {
@@ -832,7 +867,8 @@ int launch_decode(const Scratch& sc, const void* hidden, int dtype, int64_t C, i
 // and 40 us at T = 32; fp32 rows: 13.3 / 14.7 us against 11.3 / 14.4 us at T = 1 and 13.6 / 16.4 us at
 // T = 8).  With raw weights that form needs the packing pass first (7.5 us at C = 8), so the latency
 // kernel, which reads W1 as it is, keeps T <= 8 (11-15 us against 17 us); it also keeps, up to
-// T = 32, what the split-k form does not cover (hidden sizes that are not multiples of 128).
+// T = 32, what the split-k form does not cover (hidden sizes that are not multiples of 128).  Calls that would pack or have
+// packed weights go to the few-rows kernel instead where use_few_rows says so.
 bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, int variant, int form_word) {
     if (variant == TIDE_VARIANT_DECODE) return T <= kDecodeMaxT;
     if (variant == TIDE_VARIANT_PREFILL) return false;
@@ -842,22 +878,41 @@ bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, i
     return !packed_given && T <= kDecodeRawMaxT;
 }
 
+// The few-rows kernel (a workgroup per 16 rows and 16 columns, all of k) or the paths above?  It is the faster one as long
+// as its workgroups fit the chip once, whatever the hidden size (256 CUs, packed weights, against the split-k forms, us:
+// C = 8, d = 4096: 8.7 -> 6.3 at T = 1, 9.5 -> 7.3 at 16, 11.3 -> 8.5 at 48, 11.3 -> 9.2 at 64 = 256 workgroups; d = 16384, T = 32:
+// 18.3 -> 17.2) and, with rows of up to 8 KiB, up to one and a half workgroups per CU (two are resident): 11.8 -> 11.4 at
+// T = 96, 11.6 -> 11.4 at C = 1, T = 768, level from there on; longer rows lose there (d = 8192, C = 10, T = 96: 15.8 -> 18.1).
+// Rows of 64 KiB (fp32, d = 16384) are level at best.  Every workgroup of a row tile ticks the tile's counter (14 ns each): from 256 of
+// them on that costs what the kernel gains (C = 32, width 128: 12.2 -> 12.6; C = 20: 10.2 -> 9.1).
+// Hidden sizes that are no multiple of 128 go to the register-ring kernel otherwise (18.9 -> 9.3 us at C = 8, T = 100, d = 1600):
+// there up to two workgroups per CU.
+bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus) {
+    const int64_t tiles = (T + kFewRows - 1) / kFewRows, nbk = b / kFewCols, row_bytes = d * (int64_t)elem_bytes(dtype);
+    if (tiles > kFewMaxTiles || C * nbk >= 256 || row_bytes > 32768) return false;
+    const int64_t W = C * tiles * nbk;
+    if (d % 128 != 0) return W <= 2 * (int64_t)cus;
+    return W <= (int64_t)cus || (row_bytes <= 8192 && 2 * W <= 3 * (int64_t)cus);
+}
+
 // ---- What a router call needs of scratch memory, and which path it takes: host arithmetic only.
 struct CallNeed {
     bool decode = false;            // the latency kernel takes the call, else the prefill path with `plan`
+    bool few = false;               // the few-rows kernel takes the call
     PrefillPlan plan;
     size_t state_bytes = 0;         // counters + arrival words, a multiple of 256
     size_t packed_bytes = 0;        // a multiple of 256
     size_t part_bytes = 0;          // a multiple of 256
     size_t rows_bytes = 0;          // generic fallback: the re-aligned copy of the hidden rows; a multiple of 256
     int64_t d_run = 0;              // the row length the kernels run on: d, or d padded to a multiple of 128 with rows_bytes
-    size_t data_bytes() const { return packed_bytes + part_bytes + rows_bytes; }
-    size_t total() const { return state_bytes + data_bytes(); }
+    size_t total() const { return state_bytes + packed_bytes + part_bytes + rows_bytes; }
+    bool leaves_data = false;       // whether a block counts as written behind the state words afterwards: as on the paths without
+                                    // the few-rows kernel, which itself leaves zeros where it wrote
 };
 size_t round256(size_t n) { return (n + 255) & ~size_t(255); }
 
 CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool raw_weights, bool want_exit, unsigned cus, int variant,
-                   int form_word) {
+                   int form_word, bool allow_few = true) {
     CallNeed n;
     n.state_bytes = round256(kCounterSlots * sizeof(uint32_t)) + (want_exit ? round256((size_t)T * sizeof(uint64_t)) : 0);
     const bool repack = needs_repack(dtype, d, b);
@@ -869,6 +924,14 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
     if (n.decode) {
         const size_t S = (size_t)((d + kDecodeSlice - 1) / kDecodeSlice);
         n.part_bytes = round256((size_t)C * S * (size_t)T * (size_t)(halves * kBottleneck + kPartPad) * sizeof(float));
+    }
+    // (the other paths' needs are counted all the same: what a caller has to bring does not depend on this choice)
+    n.few = allow_few && !(raw_weights && n.decode) && variant == TIDE_VARIANT_AUTO && form_word == 0 && use_few_rows(dtype, C, T, n.d_run, b, cus);
+    const size_t few_bytes = n.few ? round256((size_t)T * (size_t)C * (size_t)(b / kFewCols) * sizeof(float)) : 0;
+    if (n.decode) {
+        n.leaves_data = true;
+        n.part_bytes = std::max(n.part_bytes, few_bytes);
+        if (n.few) n.decode = false;
         return n;
     }
     if (raw_weights) n.packed_bytes = round256((size_t)C * tide_packed_router_bytes(dtype, d, b));
@@ -877,6 +940,8 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
         const PlannedLaunch& L = n.plan.launch[i];
         if (L.kernel == kKernelSplitK || L.kernel == kKernelSplitKFused) n.part_bytes = round256(splitk_part_bytes(L.rows_per_tile / 32, L.total_tiles, halves, L.k_slices));
     }
+    n.leaves_data = n.packed_bytes + n.part_bytes + n.rows_bytes > 0;
+    n.part_bytes = std::max(n.part_bytes, few_bytes);
     return n;
 }
 
@@ -931,7 +996,10 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
     rc = resident_cus(&cus);
     if (rc) return rc;
     const bool want_exit = o.exit_layer != nullptr;
-    const CallNeed need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form);
+    CallNeed need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form);
+    // a block that holds what the call needs on the other paths is enough
+    if (need.few && source != kScratchLibrary && need.total() > (source == kScratchCaller ? block_bytes : kStaticScratchBytes))
+        need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false);
 
     Scratch sc;
     Workspace* ws = nullptr;        // library workspace, if that is the source
@@ -987,7 +1055,7 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
         sc = carve(ss.ptr, need, want_exit);
     }
     // the data regions of this call overwrite whatever zero state lay behind its own state words
-    if (clean && need.data_bytes() > 0 && *clean > need.state_bytes) *clean = need.state_bytes;
+    if (clean && need.leaves_data && *clean > need.state_bytes) *clean = need.state_bytes;
 
     if (need.decode) {
         rc = launch_decode(sc, hidden, dtype, C, T, d, b, ckpt_stride, row_stride, gamma, W1, packed, eps, b1, w2, tab,
@@ -1020,9 +1088,12 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
             rc = launch_pack(dtype, C, d, b, gamma, W1, sc.packed, st);
             packed = sc.packed;
         }
+        auto params = [&]() {
+            return prefill_params(sc, hidden, dtype, C, T, need.d_run, d, b, ckpt_stride, row_stride, packed, eps, b1, w2, tab, min_layer,
+                                  no_exit, o);
+        };
         if (!rc)
-            rc = launch_prefill(sc, need.plan, hidden, dtype, C, T, need.d_run, d, b, ckpt_stride, row_stride, packed, eps, b1, w2,
-                                tab, min_layer, no_exit, o, st);
+            rc = need.few ? launch_few_rows(sc, params(), dtype, st) : launch_prefill(sc, need.plan, params(), dtype, st);
     }
     if (rc) {                       // a launch failed, possibly after an earlier one of this call was enqueued
         if (ws) ws->dirty = true;
