@@ -32,7 +32,7 @@
  *    only element alignment is required.
  *    Hidden sizes that are multiples of 128 (every model of the paper's Table 2) run on the tuned
  *    kernels; any other size on a generic fallback (Sec. 3.4): at widths 64 / 128 and rows of whole
- *    16-byte chunks, kernels that zero-fill the last partial tile; otherwise (rows that are not
+ *    16-byte chunks, variants of these kernels that fetch zeros beyond the end of a row; otherwise (rows that are not
  *    whole chunks, or width 256) the rows are first copied into aligned, zero-padded rows in the
  *    scratch memory -- C*T*roundup(d,128) elements -- and the tuned kernels run on the copy.
  *    tide_exit_project and tide_cosine_labels read rows in 16-byte chunks and accept only hidden
@@ -302,7 +302,9 @@ int tide_set_prefill_form(int form);
  * checkpoint-major list of tiles of rows_per_tile rows (tiles_per_ckpt per checkpoint, the last one
  * of a checkpoint possibly ragged).  kernel: 1 split-k pair, 2 wide-tile, 3 wide-tile fp32, 4 one-tile,
  * 5 / 6 streaming with 128 / 64 rows, 7 register-ring, 8 band (rows_per_tile = 32: the blocks its
- * bands are counted in, see tide_band_schedule), 9 split-k in one launch, 10 square.  Returns the number of launches (1 or 2) or a
+ * bands are counted in, see tide_band_schedule), 9 split-k in one launch, 10 square.  For hidden sizes
+ * that are not multiples of 128 this is the plan under a forced variant or form (the register-ring kernel); the automatic
+ * settings run the kernels of the plan for the next multiple.  Returns the number of launches (1 or 2) or a
  * negative tide_status_t.  Calls of few rows take the few-rows or the latency kernel
  * instead under the automatic settings (see the conventions); this function describes the prefill path only.              */
 int tide_prefill_plan(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int cus, int form, int32_t* out);

@@ -28,6 +28,9 @@ template <> struct Storage<kBF16> { static constexpr int kBytes = 2; static cons
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
 
+// Zeros: where a load beyond the packed weights (a 32-k group of the few-rows kernel: 8 KiB) or beyond the end of a row points.
+static __device__ __attribute__((aligned(16))) uint32_t g_zeros[2048];
+
 // Sum of squares of the elements of one chunk, accumulated in fp32.
 template <int DT> __device__ __forceinline__ float chunk_sumsq(u32x4 c, float acc);
 template <> __device__ __forceinline__ float chunk_sumsq<kF32>(u32x4 c, float acc) {

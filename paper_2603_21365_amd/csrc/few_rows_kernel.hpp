@@ -38,9 +38,6 @@ constexpr int few_lds_bytes(int rows) {
     return kFewWaves * ((rows + kFewRowsPerTransfer - 1) / kFewRowsPerTransfer * kFewRowsPerTransfer) * kFewChunks * 16;
 }
 
-// Zeros: where a load beyond the packed weights (a 32-k group: 8 KiB) or beyond the end of a row points.
-static __device__ __attribute__((aligned(16))) uint32_t g_zeros[2048];
-
 // acc[16x16] += A[16 x 32] * B[32 x 16]: lane l supplies row / column l % 16 and the 8 consecutive k of quarter l / 16.
 template <int DT> __device__ __forceinline__ f32x4 mma_k32(u32x4 a, u32x4 b, f32x4 acc);
 template <> __device__ __forceinline__ f32x4 mma_k32<kBF16>(u32x4 a, u32x4 b, f32x4 acc) {

@@ -19,7 +19,8 @@
 //     lane owns one row per block, so the epilogue needs no row-scale array and one barrier less;
 //   - a stage of a tile of n blocks is 4 n transfers of 8 rows x 128 bytes, 2 n per row producer;
 //     the producers' wait counts follow the tile the younger stage belongs to.
-// 16-bit storage types, bottleneck widths 64 / 128, d a multiple of 128.
+// 16-bit storage types, bottleneck widths 64 / 128.  kRagged: rows of whole 16-byte chunks whose length is no multiple of 128
+// elements -- the stages that reach beyond a row's end fetch zeros for the chunks past it (the packed weights are zero there too).
 #pragma once
 #include <type_traits>
 
@@ -97,7 +98,7 @@ __device__ __forceinline__ void band_wait_vmcnt(int n) {
 }
 
 // grid = any multiple of 8 (the host launches one workgroup per CU); p.tiles_per_ckpt = U = ceil(T / 32).
-template <int DT>
+template <int DT, bool kRagged = false>
 __global__ __launch_bounds__(kBandThreads, 1) void tide_prefill_band_kernel(const PrefillParams p) {
     static_assert(DT != kF32, "16-bit storage types only");
     typedef __attribute__((address_space(3))) char lds_char;
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(kBandThreads, 1) void tide_prefill_band_kernel(cons
     char* b_ring = smem + kBandStages * kBandABytes;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nstage = p.d * Storage<DT>::kBytes / kWideTileBytes;      // k-tiles of a row
+    const int nstage = p.dpad * Storage<DT>::kBytes / kWideTileBytes;      // k-tiles of a row
     BandWalk walk((int)blockIdx.x, (int)gridDim.x, p.C, p.tiles_per_ckpt);
     if (!walk.valid()) return;                                          // (the whole workgroup, before any barrier)
     // Each workgroup starts its k loop at a different k-tile and wraps (see prefill_kernel.hpp).  The rotation
@@ -118,7 +119,7 @@ __global__ __launch_bounds__(kBandThreads, 1) void tide_prefill_band_kernel(cons
     // equal of any other step measured; a step of 5 cost 10 % on tiles of 5 blocks at d = 4096.
     const unsigned band_index = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
     auto first_stage = [&](int nth_tile) { return (int)(((band_index + (unsigned)nth_tile) * 7u) % (unsigned)nstage); };
-    const size_t ckpt_chunks = (size_t)p.d * kBottleneck / Storage<DT>::kElems;
+    const size_t ckpt_chunks = (size_t)p.dpad * kBottleneck / Storage<DT>::kElems;
 
     if (wave == kBandConsumers + 2) {
         // ------------------------------------------------------------------ the W1' producer
@@ -183,6 +184,7 @@ __global__ __launch_bounds__(kBandThreads, 1) void tide_prefill_band_kernel(cons
         // stage's transfers are straight-line code with an immediate wait count, and the hand-overs of the
         // consumers' tile (two stages behind, possibly the tile before) are interleaved with them.
         int issued = 0, handed = 0, last_cnt = 0, in_tile = 0, f_tile = 0;
+        const int row_bytes = p.d * Storage<DT>::kBytes, whole = row_bytes / kWideTileBytes;   // kRagged: stages from `whole` on reach beyond the rows' end
         // one hand-over of the consumers' side: stage `handed` has landed once at most the younger stage's
         // transfers are outstanding (`younger` of them: the stage issued last)
         auto end_of_consumed_tile = [&]() {
@@ -218,9 +220,18 @@ __global__ __launch_bounds__(kBandThreads, 1) void tide_prefill_band_kernel(cons
                 ks = ks >= nstage ? ks - nstage : ks;
                 char* dst = a_ring + (issued % kBandStages) * kBandABytes + pw * 1024;
                 const int64_t koff = (int64_t)ks * kWideTileBytes;
+                if (kRagged && ks >= whole) {
 #pragma unroll
-                for (int i = 0; i < 2 * kN; ++i)
-                    __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + koff), (lds_char*)(dst + i * 2048), 16, 0, kStreamOnce);
+                    for (int i = 0; i < 2 * kN; ++i) {
+                        const int row = (2 * i + pw) * kWideRowsPerTransfer + rl;
+                        const bool inside = ks * kWideTileBytes + ((slot ^ wide_swizzle(row)) << 4) < row_bytes;
+                        __builtin_amdgcn_global_load_lds((glb_char*)(inside ? gp[i] + koff : reinterpret_cast<const char*>(g_zeros)), (lds_char*)(dst + i * 2048), 16, 0, 0);
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 2 * kN; ++i)
+                        __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + koff), (lds_char*)(dst + i * 2048), 16, 0, kStreamOnce);
+                }
                 ++issued;
                 if (hand) end_of_consumed_tile();
             }

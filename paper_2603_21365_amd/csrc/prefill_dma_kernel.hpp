@@ -100,7 +100,7 @@ struct TileWalk {
 
 // kCB = 128-column halves of the bottleneck each consumer wave covers: 1 (width 64 or 128) or 2
 // (width 256: wave w owns columns 32w..32w+31 of both halves, twice the accumulators).
-template <int DT, int kRowsM, int kCB>
+template <int DT, int kRowsM, int kCB, bool kRagged = false>
 __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_dma_kernel(const PrefillParams p) {
     typedef __attribute__((address_space(3))) char lds_char;
     typedef __attribute__((address_space(1))) const char glb_char;
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_dma_kernel(const 
     float* inv_rms = z_part + kDmaConsumers * kRowsM;                              // [kRowsM]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int ntile = p.d * Storage<DT>::kBytes / kTileBytes;
+    const int ntile = p.dpad * Storage<DT>::kBytes / kTileBytes;
     // An item of 1/s of the rows takes s k-tiles per stage: ntile / s stages.
     auto split_of = [&](const WorkItem& it) { return kBlocks / it.blocks; };
     // Rows are a power-of-two number of bytes apart and all workgroups start together: each
@@ -139,6 +139,8 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_dma_kernel(const 
         // producer's half of the item's rows; per_sub = kInstrPerProducer / s.
         const char* gp[kInstrPerProducer];     // source of transfer i at stage 0
         int doff[kInstrPerProducer];           // its place in the ring slot
+        [[maybe_unused]] int cx[kInstrPerProducer];   // kRagged: the byte of a stage's share of the row this lane fetches
+        const int row_bytes = p.d * Storage<DT>::kBytes;
         int f_rot = 0, f_k = 0, f_stages = 0, f_stage_bytes = 0;   // fetch cursor within its item
         TileWalk<kBlocks> fetch = walk;
         auto aim = [&](const WorkItem& it) {
@@ -153,7 +155,9 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_dma_kernel(const 
                 const int row = group * 4 + rl;                             // row within the item
                 int r = row0 + row;
                 r = r < p.T ? r : p.T - 1;                                  // ragged tail: re-read the last row
-                gp[i] = base + (int64_t)r * p.row_stride_bytes + ((slot ^ (row & 15)) << 4) + sub * kTileBytes;
+                const int x = ((slot ^ (row & 15)) << 4) + sub * kTileBytes;
+                gp[i] = base + (int64_t)r * p.row_stride_bytes + x;
+                if constexpr (kRagged) cx[i] = x;
                 doff[i] = sub * (kStageBytes / s) + group * 1024;
             }
             f_stages = ntile / s;
@@ -169,9 +173,17 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_dma_kernel(const 
             int ks = f_k + f_rot;
             ks = ks >= f_stages ? ks - f_stages : ks;
             char* dst = ring + (issued % kDmaStages) * kStageBytes;
+            if (kRagged && (ks + 1) * f_stage_bytes > row_bytes) {         // chunks beyond the end of the rows are zeros
 #pragma unroll
-            for (int i = 0; i < kInstrPerProducer; ++i)
-                __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + (int64_t)ks * f_stage_bytes), (lds_char*)(dst + doff[i]), 16, 0, kStreamOnce);
+                for (int i = 0; i < kInstrPerProducer; ++i)
+                    __builtin_amdgcn_global_load_lds((glb_char*)(ks * f_stage_bytes + cx[i] < row_bytes ? gp[i] + (int64_t)ks * f_stage_bytes
+                                                                                                        : reinterpret_cast<const char*>(g_zeros)),
+                                                     (lds_char*)(dst + doff[i]), 16, 0, 0);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kInstrPerProducer; ++i)
+                    __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + (int64_t)ks * f_stage_bytes), (lds_char*)(dst + doff[i]), 16, 0, kStreamOnce);
+            }
             ++issued;
             if (++f_k == f_stages) {
                 if (fetch.has_more()) {
@@ -211,13 +223,13 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_dma_kernel(const 
     const int a_base = r * kTileBytes;
     const int y16 = ((lane >> 5) ^ (r & 15)) << 4;
     const int yf16 = (((lane >> 5) << 1) ^ (r & 15)) << 4;     // fp32 rows: see the k loop
-    const size_t ckpt_chunks = (size_t)p.d * kBottleneck / Storage<DT>::kElems;
+    const size_t ckpt_chunks = (size_t)p.dpad * kBottleneck / Storage<DT>::kElems;
     auto b_pointer = [&](const WorkItem& it) {           // first (or only) column half of the item's checkpoint
         return p.packed + (size_t)(it.tile / p.tiles_per_ckpt) * kCB * ckpt_chunks + wave * 64 + lane;
     };
     constexpr int kMmaGroups = Compute<DT>::kMmaGroups, kPlanes = Compute<DT>::kPlanes;
     constexpr int kFrags = kMmaGroups * kPlanes;   // W1' fragments of one k-tile: 8 either way
-    const size_t plane_chunks = (size_t)p.d * 16;
+    const size_t plane_chunks = (size_t)p.dpad * 16;
     u32x4 breg[kFrags];                            // [g * kPlanes + plane]
     // Two column halves: half a k-tile of fragments per column half, refilled half a k-tile
     // ahead (the same number of matrix instructions between fetch and use as with one half).

@@ -21,7 +21,7 @@
 // 128 rows) and S (2, 4 or 8) are the host's choice per call: short tiles and many slices while
 // the workgroups fit the chip once, fewer slices and taller tiles beyond.
 // Every storage type (fp32 rows as two bf16 terms, as in the streaming kernel), d a multiple of
-// 128; at bottleneck width 256 each 128-column half of a tile is a workgroup of its own in the
+// 128 (kRagged: any rows of whole 16-byte chunks, zeros fetched beyond their end); at bottleneck width 256 each 128-column half of a tile is a workgroup of its own in the
 // first launch.
 #pragma once
 #include <type_traits>
@@ -42,7 +42,7 @@ template <int kBlocks> constexpr int splitk_part_floats() { return kBlocks * 32 
 
 // First launch: blockIdx.x = (tile * halves + half) * p.k_slices + slice; tiles of kBlocks*32 rows,
 // checkpoint-major (p.tiles_per_ckpt per checkpoint); half = which 128 columns of the bottleneck
-// (halves = 2 at width 256, else 1); slice s covers k-tiles [s*n/S, (s+1)*n/S) of the n = d/128
+// (halves = 2 at width 256, else 1); slice s covers k-tiles [s*n/S, (s+1)*n/S) of the n = dpad/128
 // k-tiles of a row (S <= n, so every slice has at least one).
 // kFused (32-row tiles, widths 64 / 128, at most as many tiles as the scratch memory has counters): ONE launch.  Every
 // workgroup leaves its partial results with device-scope stores -- only the register quads that hold rows in use: a
@@ -51,7 +51,7 @@ template <int kBlocks> constexpr int splitk_part_floats() { return kBlocks * 32 
 // not depend on who is last) and finishes the router.  An earlier version of this hand-over read whole 16 KiB blocks,
 // 8 bytes at a time, and lost to the second launch; with the rows in use only it wins at decode sizes (see the host's
 // choice).  Ordering is by completion, as in the latency kernel (device_utils.hpp: stage_store / last_arrival).
-template <int DT, int kBlocks, bool kFused = false>
+template <int DT, int kBlocks, bool kFused = false, bool kRagged = false>
 __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(const PrefillParams p) {
     static_assert(!kFused || kBlocks == 1, "the single-launch form has 32-row tiles");
     typedef __attribute__((address_space(3))) char lds_char;
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
     const int item = blockIdx.x;
     const int th = item / S, slice = item - th * S;
     const int tile = th / halves, half = th - tile * halves;
-    const int ntile = p.d * Storage<DT>::kBytes / kTileBytes;
+    const int ntile = p.dpad * Storage<DT>::kBytes / kTileBytes;
     const int kt0 = slice * ntile / S, nk = (slice + 1) * ntile / S - kt0;
     const int c = tile / p.tiles_per_ckpt;
     const int row0 = (tile - c * p.tiles_per_ckpt) * kRowsM;
@@ -82,6 +82,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
         const int rl = lane >> 4, slot = lane & 15;
         const char* base = p.hidden + (int64_t)c * p.ckpt_stride_bytes + (int64_t)kt0 * kTileBytes;
         const char* gp[kInstrPerProducer];
+        const int row_bytes = p.d * Storage<DT>::kBytes, whole = row_bytes / kTileBytes;   // kRagged: k-tiles from `whole` on reach beyond the rows' end
 #pragma unroll
         for (int i = 0; i < kInstrPerProducer; ++i) {
             const int row = (pw * kInstrPerProducer + i) * 4 + rl;          // row within the tile
@@ -93,10 +94,20 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
         auto issue_next = [&]() {
             if (issued >= nk) return;
             char* dst = ring + (issued % kDmaStages) * kStageBytes;
+            if (kRagged && kt0 + issued >= whole) {
 #pragma unroll
-            for (int i = 0; i < kInstrPerProducer; ++i)
-                __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + (int64_t)issued * kTileBytes),
-                                                 (lds_char*)(dst + (pw * kInstrPerProducer + i) * 1024), 16, 0, kStreamOnce);
+                for (int i = 0; i < kInstrPerProducer; ++i) {
+                    const int row = (pw * kInstrPerProducer + i) * 4 + rl;
+                    const bool inside = (kt0 + issued) * kTileBytes + ((slot ^ (row & 15)) << 4) < row_bytes;
+                    __builtin_amdgcn_global_load_lds((glb_char*)(inside ? gp[i] + (int64_t)issued * kTileBytes : reinterpret_cast<const char*>(g_zeros)),
+                                                     (lds_char*)(dst + (pw * kInstrPerProducer + i) * 1024), 16, 0, 0);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kInstrPerProducer; ++i)
+                    __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + (int64_t)issued * kTileBytes),
+                                                     (lds_char*)(dst + (pw * kInstrPerProducer + i) * 1024), 16, 0, kStreamOnce);
+            }
             ++issued;
         };
         // every ring slot is free at the start: fill them all
@@ -118,11 +129,11 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
         const int r = lane & 31;
         const int a_base = r * kTileBytes;
         const int y16 = ((lane >> 5) ^ (r & 15)) << 4;               // see prefill_dma_kernel.hpp
-        const size_t ckpt_chunks = (size_t)p.d * kBottleneck / Storage<DT>::kElems;
+        const size_t ckpt_chunks = (size_t)p.dpad * kBottleneck / Storage<DT>::kElems;
         const u32x4* bptr = p.packed + ((size_t)c * halves + half) * ckpt_chunks + wave * 64 + lane;
         constexpr int kGroups = Compute<DT>::kMmaGroups, kPlanes = Compute<DT>::kPlanes;
         constexpr int kFrags = kGroups * kPlanes;                    // W1' fragments of one k-tile: 8 either way
-        const size_t plane_chunks = (size_t)p.d * 16;                // fp32 rows: the hi and the mid plane of W1'
+        const size_t plane_chunks = (size_t)p.dpad * 16;                // fp32 rows: the hi and the mid plane of W1'
         const int yf16 = (((lane >> 5) << 1) ^ (r & 15)) << 4;       // fp32 rows: see prefill_dma_kernel.hpp
         auto b_fragment = [&](int kt, int g, int pl) { return bptr[pl * plane_chunks + (size_t)(kt * kGroups + g) * 256]; };
         // W1' fragments of kPre k-tiles in flight: with few k-tiles per workgroup nothing else hides

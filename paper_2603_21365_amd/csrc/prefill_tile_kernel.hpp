@@ -8,7 +8,7 @@
 // 139 here) and set-up time: this form is 1-3 % faster on such batches (measured at d = 2048,
 // 4096 and 8192 on the same box; the 8B-shaped prefill of 8 x 4096 rows is one).  Keeping W1' two
 // k-tiles ahead instead of one, or filling all four ring slots at the start, changes nothing.
-// 16-bit storage types, bottleneck widths 64 / 128, d a multiple of 128.
+// 16-bit storage types, d a multiple of 128 (kRagged: any rows of whole 16-byte chunks, zeros fetched beyond their end).
 #pragma once
 #include <type_traits>
 
@@ -46,7 +46,7 @@ constexpr int tile_lds_bytes(int kHalves) {
 
 // blockIdx.x -> tile as in the other forms: XCD x (workgroup id mod 8) takes the x-th eighth of the
 // checkpoint-major tile list from p.tile_begin on, so that an XCD's L2 holds one W1' at a time.
-template <int DT, int kHalves>
+template <int DT, int kHalves, bool kRagged = false>
 __global__ __launch_bounds__(tile_threads(kHalves), 1) void tide_prefill_tile_kernel(const PrefillParams p) {
     static_assert(DT != kF32, "16-bit storage types only");
     typedef __attribute__((address_space(3))) char lds_char;
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(tile_threads(kHalves), 1) void tide_prefill_tile_ke
     const int per_xcd = (p.total_tiles - p.tile_begin + 7) >> 3;
     const int tile = p.tile_begin + (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if ((int)(blockIdx.x >> 3) >= per_xcd || tile >= p.total_tiles) return;
-    const int ntile = p.d * Storage<DT>::kBytes / kTileBytes;
+    const int ntile = p.dpad * Storage<DT>::kBytes / kTileBytes;
     // Rows are a power-of-two number of bytes apart and all workgroups start together: each tile
     // starts its k loop at a different k-tile and wraps (see prefill_kernel.hpp).
     const int rot = (int)(((unsigned)tile * 5u) % (unsigned)ntile);
@@ -83,6 +83,7 @@ __global__ __launch_bounds__(tile_threads(kHalves), 1) void tide_prefill_tile_ke
         const int rl = lane >> 4, slot = lane & 15;
         const char* base = p.hidden + (int64_t)c * p.ckpt_stride_bytes;
         const char* gp[kInstrPerProducer];
+        const int row_bytes = p.d * Storage<DT>::kBytes, whole = row_bytes / kTileBytes;   // kRagged: k-tiles from `whole` on reach beyond the rows' end
 #pragma unroll
         for (int i = 0; i < kInstrPerProducer; ++i) {
             const int row = (pw * kInstrPerProducer + i) * 4 + rl;          // row within the tile
@@ -95,10 +96,20 @@ __global__ __launch_bounds__(tile_threads(kHalves), 1) void tide_prefill_tile_ke
             if (issued >= ntile) return;
             char* dst = ring + (issued % kDmaStages) * kStageBytes;
             const int kt = kt_of(issued);
+            if (kRagged && kt >= whole) {
 #pragma unroll
-            for (int i = 0; i < kInstrPerProducer; ++i)
-                __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + (int64_t)kt * kTileBytes),
-                                                 (lds_char*)(dst + (pw * kInstrPerProducer + i) * 1024), 16, 0, kStreamOnce);
+                for (int i = 0; i < kInstrPerProducer; ++i) {
+                    const int row = (pw * kInstrPerProducer + i) * 4 + rl;
+                    const bool inside = kt * kTileBytes + ((slot ^ (row & 15)) << 4) < row_bytes;
+                    __builtin_amdgcn_global_load_lds((glb_char*)(inside ? gp[i] + (int64_t)kt * kTileBytes : reinterpret_cast<const char*>(g_zeros)),
+                                                     (lds_char*)(dst + (pw * kInstrPerProducer + i) * 1024), 16, 0, 0);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kInstrPerProducer; ++i)
+                    __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + (int64_t)kt * kTileBytes),
+                                                     (lds_char*)(dst + (pw * kInstrPerProducer + i) * 1024), 16, 0, kStreamOnce);
+            }
             ++issued;
         };
         for (int s = 0; s < kDmaStages - 1; ++s) issue_next();
@@ -124,7 +135,7 @@ __global__ __launch_bounds__(tile_threads(kHalves), 1) void tide_prefill_tile_ke
     const int r = lane & 31;
     const int a_base = r * kTileBytes;
     const int y16 = ((lane >> 5) ^ (r & 15)) << 4;               // see prefill_dma_kernel.hpp
-    const size_t ckpt_chunks = (size_t)p.d * kBottleneck / Storage<DT>::kElems;
+    const size_t ckpt_chunks = (size_t)p.dpad * kBottleneck / Storage<DT>::kElems;
     const u32x4* bptr = p.packed + ((size_t)c * kHalves + half) * ckpt_chunks + cw * 64 + lane;
     // The matrix steps take W1' first and the rows second: the accumulators hold the transposed product,
     // a lane owning one row per block and 16 of the wave's 32 columns (router_epilogue_row).  The b1 / w2

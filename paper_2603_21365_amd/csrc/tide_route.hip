@@ -197,7 +197,8 @@ float threshold_logit(float theta) {
 bool supported_bottleneck(int64_t b) { return b == 64 || b == 128 || b == 256; }
 
 // Hidden sizes.  Multiples of 128 run on the tuned kernels.  Other sizes whose rows are whole 16-byte
-// chunks run, at widths 64 / 128, on the register-ring prefill form with a zero-filled last k-tile and on
+// chunks run, at widths 64 / 128, on the variants of those kernels that fetch zeros beyond the end of a row, under a forced
+// variant or form on the register-ring prefill form with a zero-filled last k-tile, and on
 // the latency kernel with a partial last slice.  Everything else -- rows that are not whole chunks, or
 // width 256 at a hidden size that is not a multiple of 128 -- is first copied into aligned, zero-padded
 // rows (repack_kernel.hpp) and then takes the tuned kernels.
@@ -328,16 +329,16 @@ template <int DT, int kHalves> int launch_wide(unsigned grid, hipStream_t st, co
 
 // The band kernel: `grid` workgroups (a multiple of 8), each a contiguous band of the checkpoint-major list of
 // 32-row blocks; p.tiles_per_ckpt = blocks per checkpoint.
-template <int DT> int launch_band(unsigned grid, hipStream_t st, const PrefillParams& p) {
+template <int DT, bool kRagged> int launch_band(unsigned grid, hipStream_t st, const PrefillParams& p) {
     static bool raised[kMaxDevices] = {};
     int dev = 0;
     TIDE_HIP(hipGetDevice(&dev));
     if (!raised[dev]) {
-        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_prefill_band_kernel<DT>),
+        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_prefill_band_kernel<DT, kRagged>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kBandLdsBytes));
         raised[dev] = true;
     }
-    hipLaunchKernelGGL((tide_prefill_band_kernel<DT>), dim3(grid), dim3(kBandThreads), kBandLdsBytes, st, p);
+    hipLaunchKernelGGL((tide_prefill_band_kernel<DT, kRagged>), dim3(grid), dim3(kBandThreads), kBandLdsBytes, st, p);
     return TIDE_OK;
 }
 
@@ -348,13 +349,13 @@ size_t splitk_part_bytes(int blocks, int64_t tiles, int halves, int64_t S) {
     const size_t items = (size_t)tiles * halves * S;
     return items * ((size_t)blocks * 32 * kBottleneck + (size_t)kDmaConsumers * blocks * 32) * sizeof(float);
 }
-template <int DT, int kBlocks> int launch_splitk(float* part, int64_t tiles, hipStream_t st, PrefillParams& p) {
+template <int DT, int kBlocks, bool kRagged> int launch_splitk(float* part, int64_t tiles, hipStream_t st, PrefillParams& p) {
     static bool raised[kMaxDevices] = {};
     int dev = 0;
     TIDE_HIP(hipGetDevice(&dev));
     constexpr int lds = splitk_lds_bytes<kBlocks>();
     if (!raised[dev]) {
-        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_prefill_splitk_kernel<DT, kBlocks>),
+        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_prefill_splitk_kernel<DT, kBlocks, false, kRagged>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         raised[dev] = true;
     }
@@ -363,7 +364,7 @@ template <int DT, int kBlocks> int launch_splitk(float* part, int64_t tiles, hip
     const size_t z_bytes = items * splitk_part_floats<kBlocks>() * sizeof(float);
     p.zpart = part;
     p.sspart = (float*)((char*)part + z_bytes);
-    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, kBlocks>), dim3((unsigned)items), dim3(kDmaThreads), lds, st, p);
+    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, kBlocks, false, kRagged>), dim3((unsigned)items), dim3(kDmaThreads), lds, st, p);
     if (halves == 2)
         hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, 2>), dim3((unsigned)(tiles * kBlocks)), dim3(2 * kFinishThreads), 0, st, p);
     else
@@ -373,13 +374,13 @@ template <int DT, int kBlocks> int launch_splitk(float* part, int64_t tiles, hip
 
 // The split-k form in one launch (32-row tiles, widths 64 / 128, at most kCounterSlots tiles): the workgroup that
 // completes a tile's count finishes it.
-template <int DT> int launch_splitk_fused(float* part, uint32_t* counters, int64_t tiles, hipStream_t st, PrefillParams& p) {
+template <int DT, bool kRagged> int launch_splitk_fused(float* part, uint32_t* counters, int64_t tiles, hipStream_t st, PrefillParams& p) {
     static_assert(kSplitkMaxSlices == kSplitkMaxS, "the kernel unrolls over the slices");
     const size_t items = (size_t)tiles * p.k_slices;
     p.zpart = part;
     p.sspart = (float*)((char*)part + items * splitk_part_floats<1>() * sizeof(float));
     p.counters = counters;
-    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, 1, true>), dim3((unsigned)items), dim3(kDmaThreads), splitk_lds_bytes<1>(), st, p);
+    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, 1, true, kRagged>), dim3((unsigned)items), dim3(kDmaThreads), splitk_lds_bytes<1>(), st, p);
     return TIDE_OK;
 }
 
@@ -413,33 +414,33 @@ int launch_wide_f32(unsigned grid, hipStream_t st, const PrefillParams& p) {
 }
 
 // The one-tile kernel: a workgroup per 128-row tile from p.tile_begin on.
-template <int DT, int kHalves> int launch_tile(hipStream_t st, const PrefillParams& p) {
+template <int DT, int kHalves, bool kRagged = false> int launch_tile(hipStream_t st, const PrefillParams& p) {
     static bool raised[kMaxDevices] = {};
     int dev = 0;
     TIDE_HIP(hipGetDevice(&dev));
     if (!raised[dev]) {
-        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_prefill_tile_kernel<DT, kHalves>),
+        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_prefill_tile_kernel<DT, kHalves, kRagged>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds_bytes(kHalves)));
         raised[dev] = true;
     }
     const unsigned grid = 8u * (unsigned)((p.total_tiles - p.tile_begin + 7) / 8);
-    hipLaunchKernelGGL((tide_prefill_tile_kernel<DT, kHalves>), dim3(grid), dim3(tile_threads(kHalves)), tile_lds_bytes(kHalves), st, p);
+    hipLaunchKernelGGL((tide_prefill_tile_kernel<DT, kHalves, kRagged>), dim3(grid), dim3(tile_threads(kHalves)), tile_lds_bytes(kHalves), st, p);
     return TIDE_OK;
 }
 
 // The streaming kernels use more LDS than the default per-kernel limit: raise it once.
 // `grid` is the plan's (persistent workgroups, see plan_prefill).
-template <int DT, int M, int CB> int launch_dma(unsigned grid, hipStream_t st, const PrefillParams& p) {
+template <int DT, int M, int CB, bool kRagged = false> int launch_dma(unsigned grid, hipStream_t st, const PrefillParams& p) {
     static bool raised[kMaxDevices] = {};
     int dev = 0;
     TIDE_HIP(hipGetDevice(&dev));
     constexpr int lds = dma_lds_bytes<M>();
     if (!raised[dev]) {
-        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_prefill_dma_kernel<DT, M, CB>),
+        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_prefill_dma_kernel<DT, M, CB, kRagged>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         raised[dev] = true;
     }
-    hipLaunchKernelGGL((tide_prefill_dma_kernel<DT, M, CB>), dim3(grid), dim3(kDmaThreads), lds, st, p);
+    hipLaunchKernelGGL((tide_prefill_dma_kernel<DT, M, CB, kRagged>), dim3(grid), dim3(kDmaThreads), lds, st, p);
     return TIDE_OK;
 }
 
@@ -456,7 +457,7 @@ enum PrefillKernel : int {
     kKernelRing = 7,       // prefill_kernel.hpp
     kKernelBand = 8,       // prefill_band_kernel.hpp: rows_per_tile = 32 (the unit its bands are counted in)
     kKernelSplitKFused = 9,// prefill_splitk_kernel.hpp in one launch: 32-row tiles, the last workgroup of a tile finishes it
-    kKernelSquare = 10     // prefill_square_kernel.hpp (width 256, 16-bit rows: 256-row tiles)
+    kKernelSquare = 10 // prefill_square_kernel.hpp (width 256, 16-bit rows: 256-row tiles)
 };
 struct PlannedLaunch {
     int kernel;            // PrefillKernel
@@ -472,7 +473,7 @@ struct PrefillPlan {
     PlannedLaunch launch[2];
 };
 
-PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, int form_word) {
+PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, int form_word, bool ragged = false, bool split_k = true) {
     PrefillPlan plan;
     const int form = form_word & 0xff, force_rows = (form_word >> 8) & 0xff, force_slices = (form_word >> 16) & 0xff;
     const int64_t eb = (int64_t)elem_bytes(dtype);
@@ -526,7 +527,7 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     //                          (fp32 rows: c_B = 0.65, 0.90, 1.61)
     // Forced (form 5) the cheapest shape is taken whatever the streaming estimate says, and the form
     // word may fix the tile height (bits 8-15) and the slice count (bits 16-23).
-    if (!generic_d && (form == 0 || form == 5 || form == 8)) {
+    if (!generic_d && split_k && (form == 0 || form == 5 || form == 8)) {
         const int64_t ntile = d * eb / kTileBytes;
         const int64_t max_blocks = form == 5 ? (int64_t)kSplitkForcedMaxTiles * 4 : (int64_t)kSplitkMaxTiles * 4;
         double best = 1e30;
@@ -616,7 +617,7 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     // the two launches): 16-bit rows to the streaming kernel with half as many rows per tile, fp32
     // rows to the register-ring kernel.
     const bool wide16 = !ring_form && dtype != TIDE_F32 && !tile256 && (form == 0 || form == 4);
-    const bool wide32 = dtype == TIDE_F32 && !generic_d && !two_halves && (form == 0 || form == 4);
+    const bool wide32 = dtype == TIDE_F32 && !ragged && !generic_d && !two_halves && (form == 0 || form == 4);
     if (wide16 || wide32) {
         const int64_t wrows = two_halves ? kWideRows / 2 : kWideRows;
         const int64_t tpcw = (T + wrows - 1) / wrows, tilesw = C * tpcw;
@@ -731,15 +732,16 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
         p.total_tiles = L.total_tiles;
         p.tile_begin = L.tile_begin;
         p.k_slices = L.k_slices;
-        by_dtype(dtype, [&](auto dt) {
+        auto launch = [&](auto dt, auto ragged_tag) {
             constexpr int DT = decltype(dt)::value;
+            constexpr bool R = decltype(ragged_tag)::value;
             switch (L.kernel) {
             case kKernelSplitK:
-                rc = L.rows_per_tile == 32 ? launch_splitk<DT, 1>(sc.part, L.total_tiles, st, p)
-                   : L.rows_per_tile == 64 ? launch_splitk<DT, 2>(sc.part, L.total_tiles, st, p) : launch_splitk<DT, 4>(sc.part, L.total_tiles, st, p);
+                rc = L.rows_per_tile == 32 ? launch_splitk<DT, 1, R>(sc.part, L.total_tiles, st, p)
+                   : L.rows_per_tile == 64 ? launch_splitk<DT, 2, R>(sc.part, L.total_tiles, st, p) : launch_splitk<DT, 4, R>(sc.part, L.total_tiles, st, p);
                 break;
             case kKernelSplitKFused:
-                rc = launch_splitk_fused<DT>(sc.part, sc.counters, L.total_tiles, st, p);
+                rc = launch_splitk_fused<DT, R>(sc.part, sc.counters, L.total_tiles, st, p);
                 break;
             case kKernelWide:
                 if constexpr (DT != kF32) rc = two_halves ? launch_wide<DT, 2>(L.grid, st, p) : launch_wide<DT, 1>(L.grid, st, p);
@@ -748,36 +750,30 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
                 rc = launch_wide_f32(L.grid, st, p);
                 break;
             case kKernelTile:
-                if constexpr (DT != kF32) rc = two_halves ? launch_tile<DT, 2>(st, p) : launch_tile<DT, 1>(st, p);
+                if constexpr (DT != kF32) rc = two_halves ? launch_tile<DT, 2>(st, p) : launch_tile<DT, 1, R>(st, p);
                 break;
             case kKernelBand:
-                if constexpr (DT != kF32) rc = launch_band<DT>(L.grid, st, p);
+                if constexpr (DT != kF32) rc = launch_band<DT, R>(L.grid, st, p);
                 break;
             case kKernelSquare:
                 if constexpr (DT != kF32) rc = launch_square<DT>(st, p);
                 break;
             case kKernelStream128:
-                rc = launch_dma<DT, 128, 1>(L.grid, st, p);
+                rc = launch_dma<DT, 128, 1, R>(L.grid, st, p);
                 break;
             case kKernelStream64:
-                rc = two_halves ? launch_dma<DT, 64, 2>(L.grid, st, p) : launch_dma<DT, 64, 1>(L.grid, st, p);
+                rc = two_halves ? launch_dma<DT, 64, 2>(L.grid, st, p) : launch_dma<DT, 64, 1, R>(L.grid, st, p);
                 break;
             default:
-                if (ragged) {
-                    if (ntile >= kMaxDepth)
-                        hipLaunchKernelGGL((tide_prefill_kernel<DT, kMaxDepth, true>), dim3(L.grid), dim3(kPrefillThreads), 0, st, p);
-                    else
-                        hipLaunchKernelGGL((tide_prefill_kernel<DT, 1, true>), dim3(L.grid), dim3(kPrefillThreads), 0, st, p);
-                } else {
-                    if (ntile >= kMaxDepth)
-                        hipLaunchKernelGGL((tide_prefill_kernel<DT, kMaxDepth>), dim3(L.grid), dim3(kPrefillThreads), 0, st, p);
-                    else
-                        hipLaunchKernelGGL((tide_prefill_kernel<DT, 1>), dim3(L.grid), dim3(kPrefillThreads), 0, st, p);
-                }
+                if (ntile >= kMaxDepth)
+                    hipLaunchKernelGGL((tide_prefill_kernel<DT, kMaxDepth, R>), dim3(L.grid), dim3(kPrefillThreads), 0, st, p);
+                else
+                    hipLaunchKernelGGL((tide_prefill_kernel<DT, 1, R>), dim3(L.grid), dim3(kPrefillThreads), 0, st, p);
                 break;
             }
             return 0;
-        });
+        };
+        by_dtype(dtype, [&](auto dt) { return ragged ? launch(dt, std::true_type{}) : launch(dt, std::false_type{}); });
         if (rc) return rc;
         TIDE_HIP(hipGetLastError());
     }
@@ -912,7 +908,7 @@ struct CallNeed {
 size_t round256(size_t n) { return (n + 255) & ~size_t(255); }
 
 CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool raw_weights, bool want_exit, unsigned cus, int variant,
-                   int form_word, bool allow_few = true) {
+                   int form_word, bool library, bool allow_few = true) {
     CallNeed n;
     n.state_bytes = round256(kCounterSlots * sizeof(uint32_t)) + (want_exit ? round256((size_t)T * sizeof(uint64_t)) : 0);
     const bool repack = needs_repack(dtype, d, b);
@@ -935,7 +931,15 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
         return n;
     }
     if (raw_weights) n.packed_bytes = round256((size_t)C * tide_packed_router_bytes(dtype, d, b));
-    n.plan = plan_prefill(dtype, C, T, n.d_run, b, cus, form_word);
+    // Rows of whole 16-byte chunks whose length is no multiple of 128: under the automatic settings the plan of the padded
+    // length, on the kernels that read the chunks beyond a row's end as zeros: bf16, d = 1600, C = 12: 53 -> 40 us at T = 4000, 21 -> 17 at 1000;
+    // d = 4104, C = 8, T = 200: 39 -> 15.5; fp32, d = 4000, C = 9, T = 300: 161 -> 28 (before: the register-ring
+    // form, whose loads are selected chunk by chunk).  (The split-k pair only where its partial results do not
+    // have to fit a block that was sized without them.)
+    if (variant == TIDE_VARIANT_AUTO && form_word == 0 && n.d_run % 128 != 0)
+        n.plan = plan_prefill(dtype, C, T, padded_hidden(dtype, d), b, cus, 0, true, library);
+    else
+        n.plan = plan_prefill(dtype, C, T, n.d_run, b, cus, form_word);
     for (int i = 0; i < n.plan.count; ++i) {
         const PlannedLaunch& L = n.plan.launch[i];
         if (L.kernel == kKernelSplitK || L.kernel == kKernelSplitKFused) n.part_bytes = round256(splitk_part_bytes(L.rows_per_tile / 32, L.total_tiles, halves, L.k_slices));
@@ -996,10 +1000,10 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
     rc = resident_cus(&cus);
     if (rc) return rc;
     const bool want_exit = o.exit_layer != nullptr;
-    CallNeed need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form);
+    CallNeed need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, source == kScratchLibrary);
     // a block that holds what the call needs on the other paths is enough
     if (need.few && source != kScratchLibrary && need.total() > (source == kScratchCaller ? block_bytes : kStaticScratchBytes))
-        need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false);
+        need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, source == kScratchLibrary, false);
 
     Scratch sc;
     Workspace* ws = nullptr;        // library workspace, if that is the source
@@ -1240,7 +1244,7 @@ size_t tide_workspace_bytes(int dtype, int64_t C, int64_t T, int64_t d, int64_t 
         (void)hipGetLastError();
     }
     std::lock_guard<std::mutex> lock(g_mu);
-    return call_need(dtype, C, T > 0 ? T : 1, d, b, raw_weights != 0, true, cus, g_variant, g_prefill_form).total();
+    return call_need(dtype, C, T > 0 ? T : 1, d, b, raw_weights != 0, true, cus, g_variant, g_prefill_form, false).total();
 }
 
 int tide_workspace_init(void* workspace, size_t workspace_bytes, void* stream) {

@@ -1,0 +1,80 @@
+"""GPU parity against the fp64 oracle of hidden sizes that are
+no multiple of 128 on every kernel the automatic settings give them."""
+import numpy as np
+import pytest
+
+from paper_2603_21365_amd import synth
+from parity import compare_select, oracle_select, report, routers_to_device, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tr():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2603_21365_amd import tide_route
+    tide_route.load_library()
+    return tide_route
+
+
+def check(tr, C, dtype, T, d, b, *, packed, pad=0):
+    import torch
+    w = synth.Workload(f"bands_{dtype}_C{C}_T{T}_d{d}_b{b}", 89, dtype, d, 4 * C, 4, T, None, b=b)
+    print(f"[gpu-case] {w.name}", flush=True)
+    rt = w.routers()
+    rt.b2[:] = np.linspace(-0.2, 0.2, C) if C > 1 else 0.05
+    hb = w.hidden(row_stride=d + pad)
+    g, W1, b1, w2 = routers_to_device(rt)
+    dev = to_device(hb, dtype)
+    args = (b1, w2, rt.b2, rt.theta, w.layer_ids, 0, w.n_layers)
+    out = []
+    for rep in range(2):
+        if packed:
+            pk = tr.router_pack(tr.DTYPE_CODES[dtype], g, W1)
+            out.append(tr.select_exit_packed(dev, pk, w.eps, *args, d=d))
+        else:
+            out.append(tr.select_exit(dev, g, w.eps, W1, *args))
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(*out)), "two calls differ"
+    ex, z, m = (o.cpu().numpy() for o in out[0])
+    ex_o, z_o, m_o = oracle_select(w, rt, hb, d=d)
+    report(compare_select(w.name, dtype, z, ex, m, z_o, ex_o, m_o, rt.theta, w.layer_ids, 0, w.n_layers))
+
+
+@pytest.mark.parametrize("C,dtype,T,d,b,pad,what", [
+    (1, "bf16", 1100, 2000, 128, 0, "split-k, 16-bit rows"),
+    (4, "f32", 260, 1100, 128, 4, "split-k, fp32 rows: the last two k-tiles are partial and empty; padded strides"),
+    (2, "f16", 40, 8200, 64, 0, "few rows, one 16-byte chunk into a k-tile"),
+    (32, "bf16", 12, 1000, 128, 0, "too many checkpoints for the few-rows kernel: the latency kernel"),
+    (32, "f16", 33, 264, 128, 8, "pieces of the streaming kernel, two chunks in the last k-tile"),
+    (8, "bf16", 1500, 200, 128, 0, "64-row tiles"),
+    (8, "f16", 3001, 1032, 128, 8, "one 128-row tile per CU"),
+    (8, "bf16", 5003, 136, 128, 0, "bands, two k-tiles"),
+    (12, "bf16", 4000, 808, 64, 0, "bands of one checkpoint each"),
+    (3, "f32", 700, 132, 128, 0, "fp32 bands of one block, one chunk in the last k-tile"),
+    (10, "f32", 9000, 140, 128, 4, "fp32 bands in several tiles"),
+    (2, "f32", 9000, 1000, 64, 0, "fp32 bands in pairs of waves")])
+def test_hidden_sizes_that_are_no_multiple_of_128(tr, C, dtype, T, d, b, pad, what):
+    print(f"[gpu-case] {what}", flush=True)
+    check(tr, C, dtype, T, d, b, packed=True, pad=pad)
+    check(tr, C, dtype, T, d, b, packed=False, pad=pad)
+
+
+def test_rows_beside_a_ragged_end_do_not_reach_each_other(tr):
+    """d = 1000 in a buffer whose columns beyond d hold NaN: nothing beyond a row's end is used, on every kernel that
+    fetches zeros there."""
+    import torch
+    for dtype, C, T in (("bf16", 2, 24), ("bf16", 1, 900), ("f16", 8, 3001), ("bf16", 8, 5003), ("f32", 4, 260), ("f32", 3, 1500)):
+        w = synth.Workload(f"bands_nan_{dtype}_T{T}", 97, dtype, 1000, 4 * C, 4, T, None)
+        print(f"[gpu-case] {w.name}", flush=True)
+        rt = w.routers()
+        g, W1, b1, w2 = routers_to_device(rt)
+        pk = tr.router_pack(tr.DTYPE_CODES[dtype], g, W1)
+        h = to_device(w.hidden(), dtype)
+        wide = torch.full((C, T, 1016), float("nan"), dtype=h.dtype, device="cuda")
+        wide[:, :, :1000] = h
+        args = (w.eps, b1, w2, rt.b2, rt.theta, w.layer_ids, 0, w.n_layers)
+        a, b = tr.select_exit_packed(h, pk, *args, d=1000), tr.select_exit_packed(wide, pk, *args, d=1000)
+        torch.cuda.synchronize()
+        assert torch.isfinite(a[1]).all() and all(torch.equal(x, y) for x, y in zip(a, b))
