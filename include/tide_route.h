@@ -302,7 +302,7 @@ int tide_set_prefill_form(int form);
  * checkpoint-major list of tiles of rows_per_tile rows (tiles_per_ckpt per checkpoint, the last one
  * of a checkpoint possibly ragged).  kernel: 1 split-k pair, 2 wide-tile, 3 wide-tile fp32, 4 one-tile,
  * 5 / 6 streaming with 128 / 64 rows, 7 register-ring, 8 band (rows_per_tile = 32: the blocks its
- * bands are counted in, see tide_band_schedule), 9 split-k in one launch, 10 square.  For hidden sizes
+ * bands are counted in, see tide_band_schedule), 9 split-k in one launch, 10 square, 11 band for fp32 rows.  For hidden sizes
  * that are not multiples of 128 this is the plan under a forced variant or form (the register-ring kernel); the automatic
  * settings run the kernels of the plan for the next multiple.  Returns the number of launches (1 or 2) or a
  * negative tide_status_t.  Calls of few rows take the few-rows or the latency kernel

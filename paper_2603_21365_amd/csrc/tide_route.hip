@@ -27,6 +27,7 @@
 #include "prefill_wide_kernel.hpp"
 #include "prefill_band_kernel.hpp"
 #include "prefill_square_kernel.hpp"
+#include "prefill_band32_kernel.hpp"
 #include "mfma_probe_kernel.hpp"
 #include "prefill_wide32_kernel.hpp"
 #include "project_kernel.hpp"
@@ -413,6 +414,20 @@ int launch_wide_f32(unsigned grid, hipStream_t st, const PrefillParams& p) {
     return TIDE_OK;
 }
 
+// The band kernel for fp32 rows: `grid` workgroups (a multiple of 8, at least C), tiles of up to kMaxBlocks blocks of 32 rows.
+template <bool kRagged, int kMaxBlocks> int launch_band_f32(unsigned grid, hipStream_t st, const PrefillParams& p) {
+    static bool raised[kMaxDevices] = {};
+    int dev = 0;
+    TIDE_HIP(hipGetDevice(&dev));
+    if (!raised[dev]) {
+        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_prefill_band_f32_kernel<kRagged, kMaxBlocks>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, band32_lds_bytes<kMaxBlocks>()));
+        raised[dev] = true;
+    }
+    hipLaunchKernelGGL((tide_prefill_band_f32_kernel<kRagged, kMaxBlocks>), dim3(grid), dim3(kWideThreads), band32_lds_bytes<kMaxBlocks>(), st, p);
+    return TIDE_OK;
+}
+
 // The one-tile kernel: a workgroup per 128-row tile from p.tile_begin on.
 template <int DT, int kHalves, bool kRagged = false> int launch_tile(hipStream_t st, const PrefillParams& p) {
     static bool raised[kMaxDevices] = {};
@@ -457,7 +472,8 @@ enum PrefillKernel : int {
     kKernelRing = 7,       // prefill_kernel.hpp
     kKernelBand = 8,       // prefill_band_kernel.hpp: rows_per_tile = 32 (the unit its bands are counted in)
     kKernelSplitKFused = 9,// prefill_splitk_kernel.hpp in one launch: 32-row tiles, the last workgroup of a tile finishes it
-    kKernelSquare = 10 // prefill_square_kernel.hpp (width 256, 16-bit rows: 256-row tiles)
+    kKernelSquare = 10,    // prefill_square_kernel.hpp (width 256, 16-bit rows: 256-row tiles)
+    kKernelBandF32 = 11    // prefill_band32_kernel.hpp: rows_per_tile = 32, as the band kernel
 };
 struct PlannedLaunch {
     int kernel;            // PrefillKernel
@@ -611,6 +627,22 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
         plan.launch[plan.count++] = PlannedLaunch{kKernelBand, 32, (int)U, (int)(C * U), 0, 1, cus};
         return plan;
     }
+    // Band form for fp32 rows: every checkpoint gets cus / C workgroups, each an equal share of its blocks.  Up to four blocks
+    // per workgroup its eight consumer waves share a block in pairs (each half of k): it is the choice from more than two
+    // blocks per workgroup on, where the register-ring kernel's 64-row tiles are more than one per CU; up to six a wave per block.
+    // Measured on 256 CUs (C = 8 where not given; against the forms below, us): d = 4096: 94 against 116 at T = 2300, 101 / 115 at
+    // 2600, 108 / 121 at 3072, 129 / 139 at 4096, 167 / 174 at 4800, 177 / 187 at 5500, but 216 / 219 at 7000 (seven blocks); d = 2560, C = 10, T = 3001: 80 / 99;
+    // d = 1024: 28 / 34 at 2300, 38 / 41 at 4096; d = 8192: 196 / 228 at 2600, 255 / 276 at 4096; C = 32, T = 900, d = 2048: 68 / 79; but 86 / 78
+    // at two blocks (T = 2048) and nothing at d <= 256.  From seven blocks on the wide-tile kernel's
+    // rounds are level.  The ring kernel is
+    // slow on rows that are no whole k-tiles (C = 8, T = 1200, d = 3000: 129 us): those take this form whatever their number.
+    if (dtype == TIDE_F32 && !generic_d && !two_halves && form == 0 && (d >= 512 || ragged) && (int64_t)cus >= C) {
+        const int64_t U = (T + 31) / 32, per_ckpt = (int64_t)cus / C, most = (U + per_ckpt - 1) / per_ckpt;
+        if (ragged || (U > 2 * per_ckpt && most <= 6)) {
+            plan.launch[plan.count++] = PlannedLaunch{kKernelBandF32, 32, (int)U, (int)(C * U), 0, 1, cus};
+            return plan;
+        }
+    }
     // Wide-tile forms: whole rounds of wide tiles (256 rows, or 128 rows at width 256; one per CU and
     // round) go to a wide kernel, what is left of the checkpoint-major row list to a kernel with
     // smaller tiles behind it on the same stream (the arrival words carry the per-token state across
@@ -754,6 +786,12 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
                 break;
             case kKernelBand:
                 if constexpr (DT != kF32) rc = launch_band<DT, R>(L.grid, st, p);
+                break;
+            case kKernelBandF32:
+                if constexpr (DT == kF32) {
+                    const int per_ckpt = (int)L.grid / p.C;
+                    rc = (L.tiles_per_ckpt + per_ckpt - 1) / per_ckpt <= 4 ? launch_band_f32<R, 4>(L.grid, st, p) : launch_band_f32<R, 8>(L.grid, st, p);
+                }
                 break;
             case kKernelSquare:
                 if constexpr (DT != kF32) rc = launch_square<DT>(st, p);
@@ -933,7 +971,7 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
     if (raw_weights) n.packed_bytes = round256((size_t)C * tide_packed_router_bytes(dtype, d, b));
     // Rows of whole 16-byte chunks whose length is no multiple of 128: under the automatic settings the plan of the padded
     // length, on the kernels that read the chunks beyond a row's end as zeros: bf16, d = 1600, C = 12: 53 -> 40 us at T = 4000, 21 -> 17 at 1000;
-    // d = 4104, C = 8, T = 200: 39 -> 15.5; fp32, d = 4000, C = 9, T = 300: 161 -> 28 (before: the register-ring
+    // d = 4104, C = 8, T = 200: 39 -> 15.5; fp32, d = 4000, C = 9, T = 300: 161 -> 28; d = 1608, C = 8, T = 3000: 82 -> 55 (before: the register-ring
     // form, whose loads are selected chunk by chunk).  (The split-k pair only where its partial results do not
     // have to fit a block that was sized without them.)
     if (variant == TIDE_VARIANT_AUTO && form_word == 0 && n.d_run % 128 != 0)

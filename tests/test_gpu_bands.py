@@ -1,4 +1,5 @@
-"""GPU parity against the fp64 oracle of hidden sizes that are
+"""GPU parity of the band kernels' newer branches against the fp64 oracle: fp32 rows in bands (pairs of waves per block up to
+four blocks per workgroup, a wave per block beyond), and hidden sizes that are
 no multiple of 128 on every kernel the automatic settings give them."""
 import numpy as np
 import pytest
@@ -40,6 +41,18 @@ def check(tr, C, dtype, T, d, b, *, packed, pad=0):
     ex, z, m = (o.cpu().numpy() for o in out[0])
     ex_o, z_o, m_o = oracle_select(w, rt, hb, d=d)
     report(compare_select(w.name, dtype, z, ex, m, z_o, ex_o, m_o, rt.theta, w.layer_ids, 0, w.n_layers))
+
+
+@pytest.mark.parametrize("C,T,d,b,what", [
+    (3, 6001, 512, 128, "2 and 3 blocks per workgroup, the last one block of one row"),
+    (7, 4500, 768, 64, "3 and 4 blocks; 4 workgroups without a checkpoint"),
+    (1, 32768, 512, 128, "exactly 4 blocks: the most that pairs of waves take"),
+    (1, 32800, 512, 128, "one block more: 4 and 5 blocks, a wave each"),
+    (10, 4700, 512, 128, "5 and 6 blocks: the largest of its range"),
+    (32, 540, 640, 128, "32 checkpoints, 8 workgroups each, 2 and 3 blocks")])
+def test_fp32_bands(tr, C, T, d, b, what):
+    assert [L["kernel"] for L in tr.prefill_plan(tr.F32, C, T, d, b)] == [11], what
+    check(tr, C, "f32", T, d, b, packed=C % 2 == 1)
 
 
 @pytest.mark.parametrize("C,dtype,T,d,b,pad,what", [
