@@ -320,7 +320,8 @@ int tide_stream_schedule(int rows_per_tile, int64_t b, int64_t k_tiles, int grid
                          int total_tiles, int32_t* out, int max_items);
 
 /* The band kernel's schedule, for tests (host arithmetic, no GPU needed; the very code the kernel
- * runs): the tiles of workgroup `block` of a launch of `grid` workgroups (a multiple of 8) over C
+ * runs where its bands run across checkpoints; a batch whose checkpoints do not divide the workgroups may instead give each
+ * checkpoint equal workgroups of its own): the tiles of workgroup `block` of a launch of `grid` workgroups (a multiple of 8) over C
  * checkpoints of blocks_per_ckpt = ceil(T / 32) blocks of 32 rows each (a tide_prefill_plan launch of
  * kernel 8).  out: HOST int32 [max_items][3] = {checkpoint, first block within the checkpoint,
  * blocks}; a tile has 1 to 9 blocks and lies within one checkpoint.  Returns the number of tiles

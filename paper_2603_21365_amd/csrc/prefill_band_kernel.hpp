@@ -55,12 +55,20 @@ struct BandTile {
 // of C * U blocks (U = ceil(T / 32) per checkpoint) is cut into `grid` contiguous bands of equal length
 // (+-1); workgroup `block` takes band (block % 8) * grid/8 + block / 8, so XCD x (workgroup id mod 8) owns
 // a contiguous eighth of the list and its L2 holds one or two W1' at a time.
+// per_ckpt > 0: the bands do not run across checkpoints -- each checkpoint has per_ckpt workgroups of its own, the C * per_ckpt
+// first ones of the list (see band_per_ckpt).
 struct BandWalk {
     int64_t cur, end;
     int U;
-    __host__ __device__ BandWalk(int block, int grid, int C, int U_) : U(U_) {
+    __host__ __device__ BandWalk(int block, int grid, int C, int U_, int per_ckpt = 0) : U(U_) {
         const int64_t L = (int64_t)(block & 7) * (grid >> 3) + (block >> 3);
         const int64_t B = (int64_t)C * U_;
+        if (per_ckpt > 0) {
+            const int c = (int)L / per_ckpt, j = (int)L - c * per_ckpt;
+            cur = c < C ? (int64_t)c * U_ + (int64_t)j * U_ / per_ckpt : B;
+            end = c < C ? (int64_t)c * U_ + (int64_t)(j + 1) * U_ / per_ckpt : B;
+            return;
+        }
         cur = L * B / grid;
         end = (L + 1) * B / grid;
     }
@@ -74,6 +82,31 @@ struct BandWalk {
     }
     __host__ __device__ void advance() { cur += current().blocks; }
 };
+
+// Workgroups per checkpoint, or 0 for bands across checkpoints: whichever leaves the slowest workgroup less to do.  A tile costs
+// its blocks and, for its pass over W1', about four blocks' worth (16 KiB of W1' per stage against 4 KiB per block), so a band
+// cut by a checkpoint's end costs a tile more than the others -- where the checkpoints do not divide the workgroups, giving each
+// checkpoint workgroups of its own avoids that at the price of up to C - 1 idle ones.  Measured (bf16, us, across / of its
+// own): C = 12, T = 4000, d = 1664 42.4 / 37.2; d = 4096: 76 / 64 at C = 7, T = 5000, 76.7 / 65.6 at C = 10, T = 3700, 86 / 77 at C = 9,
+// T = 5000; fp16 78 / 72.5 at C = 5, T = 8000; C = 9, T = 12000, d = 1024 56.4 / 52.3.  With more tiles per workgroup the others take up the slack:
+// C = 6, T = 16384, d = 3072 119 / 121 (costs 24 and 21), C = 10, T = 16384 level (36 and 33) -- hence a seventh at least; the 36-layer prefill (C = 9,
+// T = 16384) stays across: 18 blocks in two tiles against 19 in three.
+__host__ __device__ inline int band_tiles_cost(int blocks) { return blocks + 4 * ((blocks + kBandMaxBlocks - 1) / kBandMaxBlocks); }
+inline int band_per_ckpt(int64_t C, int64_t U, int64_t grid) {
+    if (C > grid || grid % C == 0) return 0;                                     // (equal shares within checkpoints either way)
+    const int64_t per_ckpt = grid / C, B = C * U;
+    const int own = band_tiles_cost((int)((U + per_ckpt - 1) / per_ckpt));
+    int across = band_tiles_cost((int)((B + grid - 1) / grid));
+    for (int64_t c = 1; c < C; ++c) {                                            // the bands that the checkpoints' ends cut
+        int64_t L = c * U * grid / B;                                            // the band around block c * U
+        while (L * B / grid > c * U) --L;
+        while ((L + 1) * B / grid <= c * U) ++L;
+        const int before = (int)(c * U - L * B / grid), after = (int)((L + 1) * B / grid - c * U);
+        const int cost = (before > 0 ? band_tiles_cost(before) : 0) + band_tiles_cost(after);
+        across = cost > across ? cost : across;
+    }
+    return 7 * own <= 6 * across ? (int)per_ckpt : 0;
+}
 
 // Blocks of row group rg in a tile of n blocks: thirds, the larger ones first.
 __host__ __device__ inline int band_group_first(int n, int rg) { return rg * (n / kBandRowGroups) + (rg < n % kBandRowGroups ? rg : n % kBandRowGroups); }
@@ -97,7 +130,7 @@ __device__ __forceinline__ void band_wait_vmcnt(int n) {
     }
 }
 
-// grid = any multiple of 8 (the host launches one workgroup per CU); p.tiles_per_ckpt = U = ceil(T / 32).
+// grid = any multiple of 8 (the host launches one workgroup per CU); p.tiles_per_ckpt = U = ceil(T / 32); p.k_slices = band_per_ckpt.
 template <int DT, bool kRagged = false>
 __global__ __launch_bounds__(kBandThreads, 1) void tide_prefill_band_kernel(const PrefillParams p) {
     static_assert(DT != kF32, "16-bit storage types only");
@@ -110,7 +143,7 @@ __global__ __launch_bounds__(kBandThreads, 1) void tide_prefill_band_kernel(cons
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nstage = p.dpad * Storage<DT>::kBytes / kWideTileBytes;      // k-tiles of a row
-    BandWalk walk((int)blockIdx.x, (int)gridDim.x, p.C, p.tiles_per_ckpt);
+    BandWalk walk((int)blockIdx.x, (int)gridDim.x, p.C, p.tiles_per_ckpt, p.k_slices);
     if (!walk.valid()) return;                                          // (the whole workgroup, before any barrier)
     // Each workgroup starts its k loop at a different k-tile and wraps (see prefill_kernel.hpp).  The rotation
     // follows the band's position in the list, not the tile's first block: tiles start at multiples of the

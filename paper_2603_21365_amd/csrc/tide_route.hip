@@ -330,7 +330,7 @@ template <int DT, int kHalves> int launch_wide(unsigned grid, hipStream_t st, co
 
 // The band kernel: `grid` workgroups (a multiple of 8), each a contiguous band of the checkpoint-major list of
 // 32-row blocks; p.tiles_per_ckpt = blocks per checkpoint.
-template <int DT, bool kRagged> int launch_band(unsigned grid, hipStream_t st, const PrefillParams& p) {
+template <int DT, bool kRagged> int launch_band(unsigned grid, hipStream_t st, PrefillParams p) {
     static bool raised[kMaxDevices] = {};
     int dev = 0;
     TIDE_HIP(hipGetDevice(&dev));
@@ -339,6 +339,7 @@ template <int DT, bool kRagged> int launch_band(unsigned grid, hipStream_t st, c
                                      hipFuncAttributeMaxDynamicSharedMemorySize, kBandLdsBytes));
         raised[dev] = true;
     }
+    p.k_slices = band_per_ckpt(p.C, p.tiles_per_ckpt, grid);
     hipLaunchKernelGGL((tide_prefill_band_kernel<DT, kRagged>), dim3(grid), dim3(kBandThreads), kBandLdsBytes, st, p);
     return TIDE_OK;
 }

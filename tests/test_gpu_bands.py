@@ -1,5 +1,5 @@
 """GPU parity of the band kernels' newer branches against the fp64 oracle: fp32 rows in bands (pairs of waves per block up to
-four blocks per workgroup, a wave per block beyond), and hidden sizes that are
+four blocks per workgroup, a wave per block beyond), checkpoints that do not divide the workgroups, and hidden sizes that are
 no multiple of 128 on every kernel the automatic settings give them."""
 import numpy as np
 import pytest
@@ -53,6 +53,13 @@ def check(tr, C, dtype, T, d, b, *, packed, pad=0):
 def test_fp32_bands(tr, C, T, d, b, what):
     assert [L["kernel"] for L in tr.prefill_plan(tr.F32, C, T, d, b)] == [11], what
     check(tr, C, "f32", T, d, b, packed=C % 2 == 1)
+
+
+@pytest.mark.parametrize("C,dtype,T,d", [
+    (3, "bf16", 16000, 256), (7, "f16", 5000, 384), (12, "bf16", 4000, 256), (10, "bf16", 3300, 512)])
+def test_checkpoints_that_do_not_divide_the_workgroups(tr, C, dtype, T, d):
+    assert [L["kernel"] for L in tr.prefill_plan(tr.DTYPE_CODES[dtype], C, T, d)] == [8]
+    check(tr, C, dtype, T, d, 128, packed=True)
 
 
 @pytest.mark.parametrize("C,dtype,T,d,b,pad,what", [
