@@ -159,6 +159,21 @@ __device__ __forceinline__ float reduce_scatter16(const float (&x)[16], int lane
     return y + dpp_f32<kDppXor1>(y);
 }
 
+// The same for four values: every lane ends up with the total over its 32 lanes of value 2 * (bit 3 of its lane id) + (bit 2).
+__device__ __forceinline__ float reduce_scatter4(const float (&x)[4], int lane) {
+    float y2[2];
+    bool hi = lane & 8;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y2[i] = (hi ? x[i + 2] : x[i]) + dpp_f32<kDppRor8>(hi ? x[i] : x[i + 2]);
+    hi = lane & 4;
+    float y = (hi ? y2[1] : y2[0]) + dpp_f32<kDppHalfMirror>(hi ? y2[0] : y2[1]);
+    y += dpp_f32<kDppXor2>(y);
+    y += dpp_f32<kDppXor1>(y);
+    float a = y, b = y;
+    asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    return a + b;
+}
+
 // Router epilogue for one consumer wave holding kBlocks 32x32 accumulator blocks (rows
 // 32b..32b+31 of the tile, this wave's 32 columns; matrix-core C layout: lane l has column
 // l%32 and, in register v, row 8*(v/4) + 4*(l/32) + v%4).  Applies the row scale, bias and

@@ -367,10 +367,24 @@ template <int DT, int kBlocks, bool kRagged> int launch_splitk(float* part, int6
     p.zpart = part;
     p.sspart = (float*)((char*)part + z_bytes);
     hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, kBlocks, false, kRagged>), dim3((unsigned)items), dim3(kDmaThreads), lds, st, p);
-    if (halves == 2)
-        hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, 2>), dim3((unsigned)(tiles * kBlocks)), dim3(2 * kFinishThreads), 0, st, p);
-    else
-        hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, 1>), dim3((unsigned)(tiles * kBlocks)), dim3(kFinishThreads), 0, st, p);
+    // 8 rows per workgroup of the second launch while that is at most one and a half workgroups per CU, else 16 (8 / 16 rows, us): 11.5 / 12.7 at
+    // C = 1, T = 1024, 16.9 / 17.4 at C = 8, T = 322 (384 workgroups of 8 rows), 19.8 / 18.8 at C = 1, T = 4096 (512)
+    auto finish = [&](auto halves_tag, auto quads_tag) {
+        constexpr int kH = decltype(halves_tag)::value, kQ = decltype(quads_tag)::value;
+        hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, kH, kQ>), dim3((unsigned)(tiles * kBlocks * (4 / kQ))), dim3(kH * kFinishThreads), 0, st, p);
+    };
+    unsigned cus = 0;
+    const int rc = resident_cus(&cus);
+    if (rc) return rc;
+    const bool fine = 2 * tiles * kBlocks * 4 <= 3 * (int64_t)cus;
+    using std::integral_constant;
+    if (halves == 2) {
+        if (fine) finish(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+        else finish(integral_constant<int, 2>{}, integral_constant<int, 2>{});
+    } else {
+        if (fine) finish(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+        else finish(integral_constant<int, 1>{}, integral_constant<int, 2>{});
+    }
     return TIDE_OK;
 }
 
