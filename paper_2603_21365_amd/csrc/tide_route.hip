@@ -1462,7 +1462,10 @@ int tide_exit_project(const void* hidden, int dtype, int64_t C, int64_t T, int64
     p.d = (int)d;
     p.eps = eps;
     const int64_t row_bytes = d * (int64_t)eb;
-    const bool wave_per_row = row_bytes <= (int64_t)kProjectMaxChunks * 16 * kWave;      // 16 KiB
+    unsigned cus = 0;
+    if ((rc = resident_cus(&cus))) return rc;
+    const bool wave_per_row = row_bytes <= (int64_t)kProjectMaxChunks * 16 * kWave &&       // 16 KiB
+                              (T > 3 * (int64_t)cus || row_bytes < 4096);                   // (project_kernel.hpp has the figures)
     if (row_bytes > (int64_t)kProjectMaxChunks * 16 * kProjectThreads)
         return fail(TIDE_ERR_UNSUPPORTED, "rows of %lld bytes exceed the projection kernel's limit", (long long)row_bytes);
     hipStream_t st = (hipStream_t)stream;
@@ -1475,6 +1478,10 @@ int tide_exit_project(const void* hidden, int dtype, int64_t C, int64_t T, int64
                                dim3(grid), dim3(kProjectThreads), 0, st, p);
         };
         auto pick_chunks = [&](auto wpr, auto gain) {
+            if constexpr (!decltype(wpr)::value) {
+                if (per_thread <= 1) return go(wpr, gain, std::integral_constant<int, 1>{});
+                if (per_thread <= 2) return go(wpr, gain, std::integral_constant<int, 2>{});
+            }
             if (per_thread <= 4) go(wpr, gain, std::integral_constant<int, 4>{});
             else if (per_thread <= 8) go(wpr, gain, std::integral_constant<int, 8>{});
             else go(wpr, gain, std::integral_constant<int, 16>{});
