@@ -10,6 +10,8 @@
 // checkpoint (device-scope counter) reduces them in a fixed order and finishes the router; the last checkpoint to
 // report a token selects its earliest exit.  One launch, no host round trip, deterministic sums.
 #pragma once
+#include <type_traits>
+
 #include "device_utils.hpp"
 
 namespace tide {
@@ -31,7 +33,7 @@ struct DecodeParams {
     int32_t* exit_layer; uint32_t* fire_mask;    // [T], nullable
     uint64_t* arrive;     // [T] arrival words (see report_and_select), zero on entry and on exit
     float* part;          // [C][S][T][halves*128 + 4]: partial pre-activations, then the partial sum of squares
-    uint32_t* counter;    // [C], zero on entry, zero on exit
+    uint32_t* counter;    // 64 words (decode_counter), zero on entry, zero on exit
     CheckpointTable tab;
 };
 
@@ -61,85 +63,122 @@ template <> __device__ __forceinline__ void chunk_to_f32<kBF16>(u32x4 c, float* 
 // The tail of both decode kernels.  Every workgroup of checkpoint c has written its partial
 // pre-activations (and, for column half 0, its partial sum of squares) to p.part; the last one to
 // arrive reduces them in a fixed order, finishes the router and reports on the arrival words.
-template <int kHalves>
-__device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int* flag) {
+// kTB tokens x 32 column quads leave 256 / (32 kTB) threads per pair: each sums a contiguous share of the slices (loads all in
+// flight, surplus ones re-read the last slice), the shares meet in LDS in ascending order.
+// The checkpoints' counters lie 64 bytes apart as far as the block of 64 words goes: 32 workgroups per checkpoint tick at once,
+// and atomics on one line take 14 ns each (all counters in one line: 3.5 us until the last tick at C = 8).
+__device__ __forceinline__ uint32_t* decode_counter(const DecodeParams& p, int c) { return p.counter + ((c & 3) << 4) + (c >> 2); }
+
+template <int kHalves, int kTB>
+__device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int* flag, float* lds) {
     constexpr int part_stride = kHalves * kBottleneck + kPartPad;
+    constexpr int kG = kDecodeThreads / (32 * kTB);      // threads per (token, quad): 8, 4, 2 or 1
     const int tid = threadIdx.x;
     stage_writes_done();
-    if (!last_arrival(p.counter + c, (uint32_t)(p.S * kHalves), flag)) return;
+    if (!last_arrival(decode_counter(p, c), (uint32_t)(p.S * kHalves), flag)) return;
 
-    {
-        const int tl = tid >> 5, q = tid & 31;          // 8 tokens x 32 column quads (per half) per pass
-        f32x4 b1v[kHalves], w2v[kHalves];
+    const int q = tid & 31, tl = (tid >> 5) % kTB, g = (tid >> 5) / kTB;
+    f32x4 b1v[kHalves], w2v[kHalves];
 #pragma unroll
-        for (int hf = 0; hf < kHalves; ++hf) {
-            const int col = hf * kBottleneck + 4 * q;
-            b1v[hf] = f32x4{0, 0, 0, 0};
-            w2v[hf] = f32x4{0, 0, 0, 0};
-            if (col < p.b) {
-                if (p.b1) b1v[hf] = *reinterpret_cast<const f32x4*>(p.b1 + c * p.b + col);
-                w2v[hf] = *reinterpret_cast<const f32x4*>(p.w2 + c * p.b + col);
-            }
+    for (int hf = 0; hf < kHalves; ++hf) {
+        const int col = hf * kBottleneck + 4 * q;
+        b1v[hf] = f32x4{0, 0, 0, 0};
+        w2v[hf] = f32x4{0, 0, 0, 0};
+        if (col < p.b) {
+            if (p.b1) b1v[hf] = *reinterpret_cast<const f32x4*>(p.b1 + c * p.b + col);
+            w2v[hf] = *reinterpret_cast<const f32x4*>(p.w2 + c * p.b + col);
         }
-        const float* pc = p.part + (size_t)c * p.S * p.T * part_stride;
-        for (int t0 = 0; t0 < p.T; t0 += kDecodeTB) {
-            const int t = t0 + tl;
-            const bool valid = t < p.T;
-            f32x4 a[kHalves];
-            float ssum = 0.0f;
-            constexpr int kBatch = 32;                  // partials in flight per thread
+    }
+    const int s_begin = g * p.S / kG, s_end = (g + 1) * p.S / kG;
+    const float* pc = p.part + (size_t)c * p.S * p.T * part_stride;
+    f32x4* shares = reinterpret_cast<f32x4*>(lds);               // [kHalves][kG][kTB][32]
+    float* ss_shares = lds + kHalves * kG * kTB * 128;           // [kG][kTB]
+    for (int t0 = 0; t0 < p.T; t0 += kTB) {
+        const int t = t0 + tl;
+        const bool valid = t < p.T;
+        const int ts = valid ? t : p.T - 1;
+        f32x4 a[kHalves];
+        float ssum = 0.0f;
+#pragma unroll
+        for (int hf = 0; hf < kHalves; ++hf) a[hf] = f32x4{0, 0, 0, 0};
+        // kBatch partials in flight per thread: as few as cover its share (a surplus load is a round trip past every cache too)
+        auto add_slices = [&](auto batch_tag) {
+            constexpr int kBatch = decltype(batch_tag)::value;
+            for (int s0 = s_begin; s0 < s_end; s0 += kBatch) {
+                f32x4 v[kHalves][kBatch];
+#pragma unroll
+                for (int hf = 0; hf < kHalves; ++hf)
+#pragma unroll
+                    for (int u = 0; u < kBatch; ++u)
+                        v[hf][u] = stage_load4(pc + ((size_t)min(s0 + u, s_end - 1) * p.T + ts) * part_stride + hf * kBottleneck + 4 * q);
+                // lane q's slice of the batch
+                const float sv = stage_load(pc + ((size_t)min(s0 + min(q, kBatch - 1), s_end - 1) * p.T + ts) * part_stride + kHalves * kBottleneck);
+#pragma unroll
+                for (int hf = 0; hf < kHalves; ++hf)
+#pragma unroll
+                    for (int u = 0; u < kBatch; ++u) a[hf] += s0 + u < s_end ? v[hf][u] : f32x4{0, 0, 0, 0};
+                ssum += xor_reduce_sum<5>(q < kBatch && s0 + q < s_end ? sv : 0.0f);     // fixed order: deterministic
+            }
+        };
+        const int share = (p.S + kG - 1) / kG;
+        if (share <= 4) add_slices(std::integral_constant<int, 4>{});
+        else if (share <= 8) add_slices(std::integral_constant<int, 8>{});
+        else if (share <= 16 || kHalves == 2) add_slices(std::integral_constant<int, kHalves == 2 ? 8 : 16>{});   // (width 256: two workgroups per CU)
+        else add_slices(std::integral_constant<int, 32>{});
+        if constexpr (kG > 1) {
+#pragma unroll
+            for (int hf = 0; hf < kHalves; ++hf) shares[((hf * kG + g) * kTB + tl) * 32 + q] = a[hf];
+            if (q == 0) ss_shares[g * kTB + tl] = ssum;
+            __syncthreads();
+            ssum = 0.0f;
+#pragma unroll
+            for (int i = 0; i < kG; ++i) ssum += ss_shares[i * kTB + tl];
 #pragma unroll
             for (int hf = 0; hf < kHalves; ++hf) {
                 a[hf] = f32x4{0, 0, 0, 0};
-                for (int s0 = 0; s0 < p.S; s0 += kBatch) {
-                    f32x4 v[kBatch];
 #pragma unroll
-                    for (int u = 0; u < kBatch; ++u) {
-                        v[u] = f32x4{0, 0, 0, 0};
-                        if (valid && s0 + u < p.S)
-                            v[u] = stage_load4(pc + ((size_t)(s0 + u) * p.T + t) * part_stride + hf * kBottleneck + 4 * q);
-                    }
-                    float sv = 0.0f;
-                    if (hf == 0 && valid && s0 + q < p.S)
-                        sv = stage_load(pc + ((size_t)(s0 + q) * p.T + t) * part_stride + kHalves * kBottleneck);
-#pragma unroll
-                    for (int u = 0; u < kBatch; ++u) a[hf] += v[u];
-                    if (hf == 0) ssum += xor_reduce_sum<5>(sv);          // fixed order: deterministic
-                }
-            }
-            const float r = 1.0f / sqrtf(ssum / (float)p.d + p.eps);
-            float term = 0.0f;
-#pragma unroll
-            for (int hf = 0; hf < kHalves; ++hf)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) term += w2v[hf][j] * silu_f32(fmaf(r, a[hf][j], b1v[hf][j]));
-            term = xor_reduce_sum<5>(term);
-            if (valid && q == 0) {
-                const float z = p.tab.b2[c] + term;
-                const int64_t o = (int64_t)c * p.T + t;
-                const bool f = z > p.tab.thr_logit[c];
-                if (p.logits) p.logits[o] = z;
-                if (p.prob) p.prob[o] = sigmoid_f32(z);
-                if (p.fire) p.fire[o] = f ? 1 : 0;
-                if (p.exit_layer)
-                    report_and_select(p.tab, p.C, c, f, p.min_layer, p.no_exit, p.arrive + t, p.exit_layer + t,
-                                      p.fire_mask ? p.fire_mask + t : nullptr);
+                for (int i = 0; i < kG; ++i) a[hf] += shares[((hf * kG + i) * kTB + tl) * 32 + q];
             }
         }
+        const float r = 1.0f / sqrtf(ssum / (float)p.d + p.eps);
+        float term = 0.0f;
+#pragma unroll
+        for (int hf = 0; hf < kHalves; ++hf)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) term += w2v[hf][j] * silu_f32(fmaf(r, a[hf][j], b1v[hf][j]));
+        term = xor_reduce_sum<5>(term);
+        if (valid && q == 0 && g == 0) {
+            const float z = p.tab.b2[c] + term;
+            const int64_t o = (int64_t)c * p.T + t;
+            const bool f = z > p.tab.thr_logit[c];
+            if (p.logits) p.logits[o] = z;
+            if (p.prob) p.prob[o] = sigmoid_f32(z);
+            if (p.fire) p.fire[o] = f ? 1 : 0;
+            if (p.exit_layer)
+                report_and_select(p.tab, p.C, c, f, p.min_layer, p.no_exit, p.arrive + t, p.exit_layer + t,
+                                  p.fire_mask ? p.fire_mask + t : nullptr);
+        }
+        if constexpr (kG > 1) __syncthreads();           // (kG > 1 means T <= kTB: one pass; kept for any T)
     }
-    if (tid == 0) __hip_atomic_store(p.counter + c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) __hip_atomic_store(decode_counter(p, c), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // kHalves = p.halves as a compile-time value (1 or 2): the width-128 kernel carries no code or
-// registers for a second column half.
-template <int DT, int kHalves>
+// registers for a second column half.  kTB = tokens per pass: 1, 2, 4 or 8, the smallest that holds T (8 beyond).
+// What bounds it: 16 MiB of weights on the whole chip (C = 8, d = 4096: 2-3 us), then the hand-over's round trips.  Measured (fp16, C = 8,
+// d = 4096, us per call): 15.3 at any T up to 8 with eight tokens' arithmetic always, the weights queued before the rows (loads return in
+// order, so nothing was staged until the last weight was there), the counters of all checkpoints in one line and one thread per
+// (token, quad) in the finish; now 10.0 / 11.0 / 12.2 / 15.0 at T = 1 / 2 / 4 / 8, width 256 26.7 -> 18 at T = 4.
+template <int DT, int kHalves, int kTB>
 __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const DecodeParams p) {
     constexpr int E = Storage<DT>::kElems;
     constexpr int kChunksPerTok = kDecodeSlice / E;          // 16 or 32 lanes share a token
     constexpr int kLoads = kDecodeSlice / 8;                 // float4 weight loads per thread
-    __shared__ float xs[kDecodeTB][kDecodeSlice];            // gamma-scaled inputs of this slice
-    __shared__ float ss_lds[kDecodeTB];
-    __shared__ float red[4][kDecodeTB][kBottleneck];
+    constexpr int kXLoads = (kTB * kChunksPerTok + kDecodeThreads - 1) / kDecodeThreads;
+    __shared__ __attribute__((aligned(16))) float xs[kTB][kDecodeSlice];   // gamma-scaled inputs of this slice
+    __shared__ float ss_lds[kTB];
+    __shared__ __attribute__((aligned(16))) float red[4][kTB][kBottleneck];
+    __shared__ __attribute__((aligned(16))) float fin[kHalves * kDecodeThreads * 4 + kDecodeThreads / 32];
     __shared__ int flag;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -148,70 +187,91 @@ __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const Decod
     const int nblk = p.C * p.S * kHalves;
     const int per_xcd = (nblk + 7) >> 3;
     const int work = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (work >= nblk) return;
+    if ((int)(blockIdx.x >> 3) >= per_xcd || work >= nblk) return;
     const int c = work / (p.S * kHalves);
     const int rest = work - c * p.S * kHalves;
     const int s = rest / kHalves, half = rest - s * kHalves;
     const int k0 = s * kDecodeSlice;
     constexpr int part_stride = kHalves * kBottleneck + kPartPad;
 
-    // ---- this thread's weights: rows k0 + kk + 8*i, columns 4*jq .. 4*jq+3 of this half ----
+    const char* base = p.hidden + (int64_t)c * p.ckpt_stride_bytes + (int64_t)k0 * Storage<DT>::kBytes;
+    const float* g = p.gamma ? p.gamma + (size_t)c * p.d + k0 : nullptr;
+    // rows first: loads return in order.  Branch-free (a load that does not count goes to a clamped address and its value is
+    // dropped), so that all of them stay in flight together.
+    u32x4 xv[kXLoads];
+    float gv[kXLoads][E];
+    auto load_rows = [&](int t0, int nt) {
+#pragma unroll
+        for (int i = 0; i < kXLoads; ++i) {
+            const int qq = tid + i * kDecodeThreads, t = min(qq / kChunksPerTok, nt - 1), ch = qq % kChunksPerTok;
+            const bool inside = k0 + ch * E < p.d;              // the last slice of a ragged d is partial
+            const int chs = inside ? ch : 0;
+            xv[i] = *reinterpret_cast<const u32x4*>(base + (int64_t)(t0 + t) * p.row_stride_bytes + chs * 16);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const float ge = g ? g[chs * E + e] : 1.0f;
+                gv[i][e] = inside ? ge : 1.0f;
+            }
+            if (!inside) xv[i] = u32x4{0, 0, 0, 0};
+        }
+    };
+    load_rows(0, min(kTB, p.T));
+
+    // ---- this thread's weights: rows k0 + 16*kk + i, columns 4*jq .. 4*jq+3 of this half ----
     const int kk = tid >> 5, jq = tid & 31;
-    // columns beyond the width and rows beyond d read as zeros: branch-free (the load goes to a
-    // clamped address and the value is dropped), so that all loads stay in flight together
+    // columns beyond the width and rows beyond d read as zeros: branch-free, as above
     const bool live = half * kBottleneck + 4 * jq < p.b;
     const float* w = p.W1 + (size_t)c * p.d * p.b + (live ? half * kBottleneck + 4 * jq : 0);
     f32x4 wreg[kLoads];
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
-        const int k = k0 + kk + 8 * i;
-        const bool ok = live && k < p.d;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(w + (size_t)(k < p.d ? k : p.d - 1) * p.b);
-        wreg[i] = ok ? v : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        const int k = k0 + kLoads * kk + i;
+        wreg[i] = *reinterpret_cast<const f32x4*>(w + (size_t)(k < p.d ? k : p.d - 1) * p.b);
     }
 
-    const char* base = p.hidden + (int64_t)c * p.ckpt_stride_bytes + (int64_t)k0 * Storage<DT>::kBytes;
-    const float* g = p.gamma ? p.gamma + (size_t)c * p.d + k0 : nullptr;
-
-    for (int t0 = 0; t0 < p.T; t0 += kDecodeTB) {
-        const int nt = min(kDecodeTB, p.T - t0);
-        // ---- stage x * gamma for up to 8 tokens; partial sums of squares of raw x ----
-        for (int q = tid; q < kDecodeTB * kChunksPerTok; q += kDecodeThreads) {
-            const int t = q / kChunksPerTok, ch = q - t * kChunksPerTok;
-            u32x4 v = {0, 0, 0, 0};
-            const bool inside = k0 + ch * E < p.d;              // the last slice of a ragged d is partial
-            if (t < nt && inside) v = *reinterpret_cast<const u32x4*>(base + (int64_t)(t0 + t) * p.row_stride_bytes + ch * 16);
+    for (int t0 = 0; t0 < p.T; t0 += kTB) {
+        const int nt = min(kTB, p.T - t0);
+        if (t0 > 0) load_rows(t0, nt);
+        // ---- stage x * gamma for up to kTB tokens; partial sums of squares of raw x ----
+#pragma unroll
+        for (int i = 0; i < kXLoads; ++i) {
+            const int qq = tid + i * kDecodeThreads, t = qq / kChunksPerTok, ch = qq % kChunksPerTok;
             float f[E];
-            chunk_to_f32<DT>(v, f);
+            chunk_to_f32<DT>(xv[i], f);
             float sq = 0.0f;
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                sq = fmaf(f[e], f[e], sq);
-                xs[t][ch * E + e] = f[e] * ((g && inside) ? g[ch * E + e] : 1.0f);
+            for (int e = 0; e < E; ++e) sq = fmaf(f[e], f[e], sq);
+            if (t < kTB) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) xs[t][ch * E + e] = f[e] * gv[i][e];
             }
             sq = xor_reduce_sum<(kChunksPerTok == 16 ? 4 : 5)>(sq);
-            if (ch == 0) ss_lds[t] = sq;
+            if (ch == 0 && t < kTB) ss_lds[t] = sq;
         }
         __syncthreads();
 
         // ---- partial products over this thread's 16 k values ----
-        float acc[kDecodeTB][4];
+        float acc[kTB][4];
 #pragma unroll
-        for (int t = 0; t < kDecodeTB; ++t)
+        for (int t = 0; t < kTB; ++t)
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[t][j] = 0.0f;
 #pragma unroll
-        for (int i = 0; i < kLoads; ++i) {
+        for (int i4 = 0; i4 < kLoads / 4; ++i4) {
 #pragma unroll
-            for (int t = 0; t < kDecodeTB; ++t) {
-                const float x = xs[t][kk + 8 * i];
+            for (int t = 0; t < kTB; ++t) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(&xs[t][kLoads * kk + 4 * i4]);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[t][j] = fmaf(x, wreg[i][j], acc[t][j]);
+                for (int i = 0; i < 4; ++i) {
+                    const int k = k0 + kLoads * kk + 4 * i4 + i;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[t][j] = fmaf(x[i], (live && k < p.d) ? wreg[4 * i4 + i][j] : 0.0f, acc[t][j]);
+                }
             }
         }
         // lanes l and l^32 hold the two k phases of a wave; then the four waves meet in LDS
 #pragma unroll
-        for (int t = 0; t < kDecodeTB; ++t)
+        for (int t = 0; t < kTB; ++t)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 float v = acc[t][j] + __shfl_xor(acc[t][j], 32, kWave);
@@ -234,7 +294,7 @@ __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const Decod
         __syncthreads();
     }
 
-    decode_finish<kHalves>(p, c, &flag);
+    decode_finish<kHalves, kTB>(p, c, &flag, fin);
 }
 
 // The same with pre-packed weights (the serving loop's form: gamma already folded in, half the
@@ -250,6 +310,7 @@ __global__ __launch_bounds__(kDecodeThreads) void tide_decode_packed_kernel(cons
     constexpr int kPlanes = Compute<DT>::kPlanes;            // fp32: W1' = hi plane + mid plane
     __shared__ float xs[kDecodeTB][kDecodeSlice];            // raw inputs of this slice (gamma is in the weights)
     __shared__ float ss_lds[kDecodeTB];
+    __shared__ __attribute__((aligned(16))) float fin[kHalves * kDecodeThreads * 4 + kDecodeThreads / 32];
     __shared__ int flag;
 
     const int tid = threadIdx.x, lane = tid & 63, nb = tid >> 6;
@@ -348,7 +409,7 @@ __global__ __launch_bounds__(kDecodeThreads) void tide_decode_packed_kernel(cons
         }
         __syncthreads();
     }
-    decode_finish<kHalves>(p, c, &flag);
+    decode_finish<kHalves, kDecodeTB>(p, c, &flag, fin);
 }
 
 }  // namespace tide

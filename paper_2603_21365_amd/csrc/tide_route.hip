@@ -900,10 +900,17 @@ int launch_decode(const Scratch& sc, const void* hidden, int dtype, int64_t C, i
             hipLaunchKernelGGL((tide_decode_packed_kernel<DT, 2>), dim3(grid), dim3(kDecodeThreads), 0, st, p);
         else if (p.packed)
             hipLaunchKernelGGL((tide_decode_packed_kernel<DT, 1>), dim3(grid), dim3(kDecodeThreads), 0, st, p);
-        else if (p.halves == 2)
-            hipLaunchKernelGGL((tide_decode_kernel<DT, 2>), dim3(grid), dim3(kDecodeThreads), 0, st, p);
-        else
-            hipLaunchKernelGGL((tide_decode_kernel<DT, 1>), dim3(grid), dim3(kDecodeThreads), 0, st, p);
+        else {
+            auto go = [&](auto halves_tag) {
+                constexpr int kH = decltype(halves_tag)::value;
+                if (p.T == 1) hipLaunchKernelGGL((tide_decode_kernel<DT, kH, 1>), dim3(grid), dim3(kDecodeThreads), 0, st, p);
+                else if (p.T == 2) hipLaunchKernelGGL((tide_decode_kernel<DT, kH, 2>), dim3(grid), dim3(kDecodeThreads), 0, st, p);
+                else if (p.T <= 4) hipLaunchKernelGGL((tide_decode_kernel<DT, kH, 4>), dim3(grid), dim3(kDecodeThreads), 0, st, p);
+                else hipLaunchKernelGGL((tide_decode_kernel<DT, kH, 8>), dim3(grid), dim3(kDecodeThreads), 0, st, p);
+            };
+            if (p.halves == 2) go(std::integral_constant<int, 2>{});
+            else go(std::integral_constant<int, 1>{});
+        }
         return 0;
     });
     TIDE_HIP(hipGetLastError());
