@@ -40,7 +40,7 @@ template <int kBlocks> constexpr int splitk_lds_bytes() { return kDmaStages * kB
 // contiguous, and a lane of the second launch reads back the registers of its own position.
 template <int kBlocks> constexpr int splitk_part_floats() { return kBlocks * 32 * kBottleneck; }
 
-// First launch: blockIdx.x = (tile * halves + half) * p.k_slices + slice; tiles of kBlocks*32 rows,
+// First launch: item = (tile * halves + half) * p.k_slices + slice (XCD-contiguous, below); tiles of kBlocks*32 rows,
 // checkpoint-major (p.tiles_per_ckpt per checkpoint); half = which 128 columns of the bottleneck
 // (halves = 2 at width 256, else 1); slice s covers k-tiles [s*n/S, (s+1)*n/S) of the n = dpad/128
 // k-tiles of a row (S <= n, so every slice has at least one).
@@ -67,7 +67,12 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int S = p.k_slices;
     const int halves = (p.b + kBottleneck - 1) / kBottleneck;
-    const int item = blockIdx.x;
+    // XCD x (workgroup id mod 8) takes the x-th eighth of the tile-major list: a tile's partial results come from one XCD, and the
+    // second launch, cut the same way, finds them in that XCD's L2 (dealt out round-robin, the slices of a tile were on eight XCDs;
+    // us per call: 17.0 -> 15.3 at C = 8, T = 322, d = 4096, 16.9 -> 15.5 at C = 1, T = 3000, 18.8 -> 17.2 at 4096; width 256, C = 8, T = 200 18.8 -> 15.5)
+    const int items = p.total_tiles * halves * S, per_xcd = (items + 7) >> 3;
+    const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (item >= items || (int)(blockIdx.x >> 3) >= per_xcd) return;
     const int th = item / S, slice = item - th * S;
     const int tile = th / halves, half = th - tile * halves;
     const int ntile = p.dpad * Storage<DT>::kBytes / kTileBytes;
@@ -328,7 +333,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
     }
 }
 
-// Second launch: one workgroup per 8 kQ rows -- kQ register quads of a 32-row block, blockIdx.x = (tile * kBlocks + block) * 4 / kQ +
+// Second launch: one workgroup per 8 kQ rows -- kQ register quads of a 32-row block, item = (tile * kBlocks + block) * 4 / kQ +
 // group of quads -- with 4 waves per column half; wave w of a half owns its columns 32w..32w+31 as consumer wave w of the first
 // launch did.  Slices are added in ascending order: the result does not depend on timing.  It is a chain of latencies (its start,
 // the partial results from other XCDs' writes, the epilogue, the report), so it is cut finer than the 32-row blocks of the first
@@ -343,7 +348,10 @@ __global__ __launch_bounds__(kFinishThreads * kHalves) void tide_splitk_finish_k
     constexpr int kPartFloats = splitk_part_floats<kBlocks>();
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = wave >> 2, w = wave & 3;
-    const int quad = (blockIdx.x % (4 / kQ)) * kQ, tb = blockIdx.x / (4 / kQ);
+    const int groups = p.total_tiles * kBlocks * (4 / kQ), per_xcd = (groups + 7) >> 3;
+    const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);           // (see the first launch)
+    if (item >= groups || (int)(blockIdx.x >> 3) >= per_xcd) return;
+    const int quad = (item % (4 / kQ)) * kQ, tb = item / (4 / kQ);
     const int tile = tb / kBlocks, blk = tb - tile * kBlocks;
     const int c = tile / p.tiles_per_ckpt;
     const int row0 = (tile - c * p.tiles_per_ckpt) * kRowsM + 32 * blk + 8 * quad;

@@ -366,12 +366,12 @@ template <int DT, int kBlocks, bool kRagged> int launch_splitk(float* part, int6
     const size_t z_bytes = items * splitk_part_floats<kBlocks>() * sizeof(float);
     p.zpart = part;
     p.sspart = (float*)((char*)part + z_bytes);
-    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, kBlocks, false, kRagged>), dim3((unsigned)items), dim3(kDmaThreads), lds, st, p);
+    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, kBlocks, false, kRagged>), dim3(8u * (unsigned)((items + 7) / 8)), dim3(kDmaThreads), lds, st, p);
     // 8 rows per workgroup of the second launch while that is at most one and a half workgroups per CU, else 16 (8 / 16 rows, us): 11.5 / 12.7 at
     // C = 1, T = 1024, 16.9 / 17.4 at C = 8, T = 322 (384 workgroups of 8 rows), 19.8 / 18.8 at C = 1, T = 4096 (512)
     auto finish = [&](auto halves_tag, auto quads_tag) {
         constexpr int kH = decltype(halves_tag)::value, kQ = decltype(quads_tag)::value;
-        hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, kH, kQ>), dim3((unsigned)(tiles * kBlocks * (4 / kQ))), dim3(kH * kFinishThreads), 0, st, p);
+        hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, kH, kQ>), dim3(8u * (unsigned)((tiles * kBlocks * (4 / kQ) + 7) / 8)), dim3(kH * kFinishThreads), 0, st, p);
     };
     unsigned cus = 0;
     const int rc = resident_cus(&cus);
@@ -396,7 +396,7 @@ template <int DT, bool kRagged> int launch_splitk_fused(float* part, uint32_t* c
     p.zpart = part;
     p.sspart = (float*)((char*)part + items * splitk_part_floats<1>() * sizeof(float));
     p.counters = counters;
-    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, 1, true, kRagged>), dim3((unsigned)items), dim3(kDmaThreads), splitk_lds_bytes<1>(), st, p);
+    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, 1, true, kRagged>), dim3(8u * (unsigned)((items + 7) / 8)), dim3(kDmaThreads), splitk_lds_bytes<1>(), st, p);
     return TIDE_OK;
 }
 
