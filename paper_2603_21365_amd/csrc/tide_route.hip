@@ -1065,6 +1065,15 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
     if (need.few && source != kScratchLibrary && need.total() > (source == kScratchCaller ? block_bytes : kStaticScratchBytes))
         need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, source == kScratchLibrary, false);
 
+    // While a call is captured nothing can be allocated: where the library's workspace lacks the partial results of a route that
+    // the caller's blocks are not sized for either, the call takes the route that they would give it.
+    if (source == kScratchLibrary && need.part_bytes > g_ws[dev].part.bytes) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
+        if (cap != hipStreamCaptureStatusNone)
+            need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false, false);
+    }
+
     Scratch sc;
     Workspace* ws = nullptr;        // library workspace, if that is the source
     size_t* clean = nullptr;        // else: the block's count of leading zero-state bytes

@@ -86,3 +86,45 @@ def test_captured_calls_replay_like_eager_calls(tr, case):
             for k in range(n):
                 assert torch.equal(got[k], want[i][k]), f"{case}: replay {rep} of batch {i}, output {k} differs from the eager call"
     print(f"[gpu-case] {case}: 12 replays equal to the eager results", flush=True)
+
+
+@pytest.mark.parametrize("T,d", [(40, 1608), (600, 1608)])     # few rows; rows beyond a multiple of 128, split over k
+def test_capture_after_an_eager_call_that_left_no_partial_results(tr, T, d):
+    """The workspace of a larger streaming call is enough to capture a smaller one, although the smaller one keeps partial
+    results when it may allocate them."""
+    import torch
+    from parity import compare_select, oracle_select, report
+    w = synth.Workload(f"graph_small_T{T}_d{d}", 57, "bf16", d, 4, 4, T, None)      # one checkpoint
+    rt = w.routers()
+    hb = w.hidden()
+    g, W1, b1, w2 = routers_to_device(rt)
+    packed = tr.router_pack(tr.BF16, g, W1)
+    hidden = to_device(hb, "bf16")
+    large = hidden.repeat(1, 16384 // T + 1, 1).contiguous()
+    out = (torch.empty(T, dtype=torch.int32, device="cuda"), torch.empty((w.C, T), dtype=torch.float32, device="cuda"),
+           torch.empty(T, dtype=torch.int32, device="cuda"))
+
+    def call(h, **kw):
+        return tr.select_exit_packed(h, packed, w.eps, b1, w2, rt.b2, rt.theta, w.layer_ids, 0, w.n_layers, d=d, **kw)
+
+    torch.cuda.synchronize()
+    tr.release()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        call(large)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        call(hidden, out=out)
+    for rep in range(3):
+        for o in out:
+            o.fill_(-7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [o.cpu().numpy() for o in out]
+        ex_o, z_o, m_o = oracle_select(w, rt, hb, min_layer=0)
+        report(compare_select(f"{w.name} replay {rep}", "bf16", got[1], got[0], got[2], z_o, ex_o, m_o, rt.theta, w.layer_ids, 0, w.n_layers))
+    with torch.cuda.stream(stream):
+        call(hidden)                    # eager again: may allocate (after the last replay)
+    torch.cuda.synchronize()
+    del graph
