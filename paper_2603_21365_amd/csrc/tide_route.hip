@@ -636,8 +636,13 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     // of 256-row tiles; d = 1024: 23.5 against 26.9 at 4608, 24.6 against 27.4 at 5120; d = 8192: 114 against 131 at 4608, 123
     // against 138 at 5120, 136 against 144 at 6144; the 36-layer batched prefill (C = 9, T = 16384, d = 4096: 18 blocks per
     // CU) 212-219 against 224-226.  At four blocks per CU and below the one-tile kernel is faster (W1' straight from L2).
+    // With few tiles the streaming kernel cuts them into pieces of 32 rows, but only where a row's k-tiles are a
+    // multiple of four (a piece takes four per stage); else the pieces are 64 rows, and the band is faster at every size (bf16, pieces
+    // against band, us): C = 8, T = 765: 16.3 / 11.0 at d = 896, 25.2 / 17.2 at 1920, 31.7 / 21.5 at 2688; C = 8, T = 1000, d = 4480: 47.4 / 32.5;
+    // C = 1, T = 8000: 16.6 / 11.1 at d = 896, 31.6 / 21.8 at 2688; with 32-row pieces 18.1 / 20.9 (d = 2560).
     const int64_t blocks32 = C * ((T + 31) / 32);
-    if (!ring_form && dtype != TIDE_F32 && !two_halves && (form == 7 || (form == 0 && blocks32 > 4 * (int64_t)cus))) {
+    const bool coarse_pieces = rows_per_wg == 128 && 4 * tiles128 <= (int64_t)cus && (d * eb / kTileBytes) % 4 != 0;
+    if (!ring_form && dtype != TIDE_F32 && !two_halves && (form == 7 || (form == 0 && (blocks32 > 4 * (int64_t)cus || coarse_pieces)))) {
         const int64_t U = (T + 31) / 32;
         plan.launch[plan.count++] = PlannedLaunch{kKernelBand, 32, (int)U, (int)(C * U), 0, 1, cus};
         return plan;

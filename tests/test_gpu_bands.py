@@ -62,12 +62,23 @@ def test_checkpoints_that_do_not_divide_the_workgroups(tr, C, dtype, T, d):
     check(tr, C, dtype, T, d, 128, packed=True)
 
 
+@pytest.mark.parametrize("C,dtype,T,d,b", [
+    (9, "bf16", 600, 128, 128), (10, "f16", 161, 384, 64), (16, "bf16", 385, 640, 128), (8, "f16", 1024, 896, 128), (1, "bf16", 8192, 1920, 64)])
+def test_few_rows_of_k_tiles_no_multiple_of_four(tr, C, dtype, T, d, b):
+    """At most a quarter as many 128-row tiles as CUs, k-tiles that do not go four to a stage: the band, most or all of its
+    workgroups with at most one block."""
+    assert [L["kernel"] for L in tr.prefill_plan(tr.DTYPE_CODES[dtype], C, T, d, b)] == [8]
+    check(tr, C, dtype, T, d, b, packed=True)
+    check(tr, C, dtype, T, d, b, packed=False)
+
+
 @pytest.mark.parametrize("C,dtype,T,d,b,pad,what", [
     (1, "bf16", 1100, 2000, 128, 0, "split-k, 16-bit rows"),
     (4, "f32", 260, 1100, 128, 4, "split-k, fp32 rows: the last two k-tiles are partial and empty; padded strides"),
     (2, "f16", 40, 8200, 64, 0, "few rows, one 16-byte chunk into a k-tile"),
     (32, "bf16", 12, 1000, 128, 0, "too many checkpoints for the few-rows kernel: the latency kernel"),
-    (32, "f16", 33, 264, 128, 8, "pieces of the streaming kernel, two chunks in the last k-tile"),
+    (32, "f16", 33, 456, 128, 8, "pieces of the streaming kernel, the last k-tile partial"),
+    (32, "f16", 33, 264, 128, 8, "bands of few rows, the last two k-tiles one chunk and none"),
     (8, "bf16", 1500, 200, 128, 0, "64-row tiles"),
     (8, "f16", 3001, 1032, 128, 8, "one 128-row tile per CU"),
     (8, "bf16", 5003, 136, 128, 0, "bands, two k-tiles"),
