@@ -336,7 +336,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
 // Second launch: one workgroup per 8 kQ rows -- kQ register quads of a 32-row block, item = (tile * kBlocks + block) * 4 / kQ +
 // group of quads -- with 4 waves per column half; wave w of a half owns its columns 32w..32w+31 as consumer wave w of the first
 // launch did.  Slices are added in ascending order: the result does not depend on timing.  It is a chain of latencies (its start,
-// the partial results from other XCDs' writes, the epilogue, the report), so it is cut finer than the 32-row blocks of the first
+// the partial results from this XCD's L2, the epilogue, the report), so it is cut finer than the 32-row blocks of the first
 // launch: an eighth of the loads per lane and a quarter of the SiLUs, which took 0.5-1 us off a call (12.5 -> 11.6 us at C = 1, T = 1024,
 // 14.6 -> 13.6 at 2048, 17.4 -> 16.9 at 3000; width 256, C = 8, T = 200 21.2 -> 18.9).
 template <int kBlocks, int kHalves, int kQ>

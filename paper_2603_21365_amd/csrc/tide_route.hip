@@ -927,7 +927,7 @@ int launch_decode(const Scratch& sc, const void* hidden, int dtype, int64_t C, i
 // d = 4096, C = 1 / 8, fp16: 9.5 / 10.6 us against 10.8 / 13.9 us at T = 1, 13.5 / 15.9 us at T = 8
 // and 40 us at T = 32; fp32 rows: 13.3 / 14.7 us against 11.3 / 14.4 us at T = 1 and 13.6 / 16.4 us at
 // T = 8).  With raw weights that form needs the packing pass first (7.5 us at C = 8), so the latency
-// kernel, which reads W1 as it is, keeps T <= 8 (11-15 us against 17 us); it also keeps, up to
+// kernel, which reads W1 as it is, keeps T <= 8 (10-12.4 us at T = 1-4, against 14 us at T = 40); it also keeps, up to
 // T = 32, what the split-k form does not cover (hidden sizes that are not multiples of 128).  Calls that would pack or have
 // packed weights go to the few-rows kernel instead where use_few_rows says so.
 bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, int variant, int form_word) {
