@@ -302,10 +302,11 @@ int tide_set_prefill_form(int form);
  * checkpoint-major list of tiles of rows_per_tile rows (tiles_per_ckpt per checkpoint, the last one
  * of a checkpoint possibly ragged).  kernel: 1 split-k pair, 2 wide-tile, 3 wide-tile fp32, 4 one-tile,
  * 5 / 6 streaming with 128 / 64 rows, 7 register-ring, 8 band (rows_per_tile = 32: the blocks its
- * bands are counted in, see tide_band_schedule), 9 split-k in one launch, 10 square, 11 band for fp32 rows.  For hidden sizes
- * that are not multiples of 128 this is the plan under a forced variant or form (the register-ring kernel); the automatic
- * settings run the kernels of the plan for the next multiple.  Returns the number of launches (1 or 2) or a
- * negative tide_status_t.  Calls of few rows take the few-rows or the latency kernel
+ * bands are counted in, see tide_band_schedule), 9 split-k in one launch, 10 square, 11 band for fp32 rows.  Hidden sizes
+ * whose rows are copied first (see the conventions) are planned at the padded size.  Other hidden sizes that are not multiples of
+ * 128: with form 0 the kernels that fetch zeros beyond the end of a row, in the plan of a call on the library's workspace (a
+ * call on another block takes no split-k there); under any other form the register-ring kernel.  Returns the number of launches
+ * (1 or 2) or a negative tide_status_t.  Calls of few rows take the few-rows or the latency kernel
  * instead under the automatic settings (see the conventions); this function describes the prefill path only.              */
 int tide_prefill_plan(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int cus, int form, int32_t* out);
 

@@ -529,7 +529,11 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     // Width 256 (two column halves per wave) exists in the streaming form with 64 rows per
     // workgroup only.  With 128 rows the accumulators (256 values per lane) leave room for half a
     // k-tile of W1' in flight, too little to cover the L2 round trip: measured slower.
-    const bool ring_form = generic_d || (!two_halves && (form == 3 || (form == 0 && dtype == TIDE_F32)));
+    // Rows that are no whole k-tiles (ragged), 16 bits, more than one 128-row tile per CU: it also keeps the batches whose checkpoints end in
+    // short tiles, so that the 64-row tiles are two per CU at most (bf16, C = 7, T = 4650, 511 tiles of 64 rows: 60 / 73 us at d = 3080 / 4072 against
+    // 64 / 79 in bands, level at d = 1608); from a third one on bands are faster (C = 9, T = 3600, 513 tiles: 79 / 96 us against 62 / 77).
+    const bool ragged_over = ragged && form == 0 && dtype != TIDE_F32 && !two_halves && tiles128 > (int64_t)cus;
+    const bool ring_form = generic_d || (!two_halves && (form == 3 || (form == 0 && dtype == TIDE_F32))) || (ragged_over && tiles64 <= 2 * (int64_t)cus);
     if (ring_form) rows_per_wg = kRows;
     // Width 256 from more than half as many 128-row tiles as CUs on: the one-tile kernel with eight consumer waves, a
     // workgroup per tile however many rounds that makes -- the rows have the whole ring (three stages of 32 KiB in flight;
@@ -640,9 +644,12 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     // multiple of four (a piece takes four per stage); else the pieces are 64 rows, and the band is faster at every size (bf16, pieces
     // against band, us): C = 8, T = 765: 16.3 / 11.0 at d = 896, 25.2 / 17.2 at 1920, 31.7 / 21.5 at 2688; C = 8, T = 1000, d = 4480: 47.4 / 32.5;
     // C = 1, T = 8000: 16.6 / 11.1 at d = 896, 31.6 / 21.8 at 2688; with 32-row pieces 18.1 / 20.9 (d = 2560).
+    // Rows that are no whole k-tiles take the band from more than one 128-row tile per CU on, also where short last tiles leave that below four
+    // blocks per CU: the wide-tile kernel has no form for them (bf16, d = 1608, against the register-ring form: C = 12, T = 2700: 47 -> 34 us,
+    // C = 31, T = 1040: 46 -> 36; at one 128-row tile per CU the one-tile kernel stays ahead of the band: 28.7 / 32.2 at C = 10, T = 3100).
     const int64_t blocks32 = C * ((T + 31) / 32);
     const bool coarse_pieces = rows_per_wg == 128 && 4 * tiles128 <= (int64_t)cus && (d * eb / kTileBytes) % 4 != 0;
-    if (!ring_form && dtype != TIDE_F32 && !two_halves && (form == 7 || (form == 0 && (blocks32 > 4 * (int64_t)cus || coarse_pieces)))) {
+    if (!ring_form && dtype != TIDE_F32 && !two_halves && (form == 7 || (form == 0 && (blocks32 > 4 * (int64_t)cus || coarse_pieces || ragged_over)))) {
         const int64_t U = (T + 31) / 32;
         plan.launch[plan.count++] = PlannedLaunch{kKernelBand, 32, (int)U, (int)(C * U), 0, 1, cus};
         return plan;
@@ -668,7 +675,8 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     // smaller tiles behind it on the same stream (the arrival words carry the per-token state across
     // the two launches): 16-bit rows to the streaming kernel with half as many rows per tile, fp32
     // rows to the register-ring kernel.
-    const bool wide16 = !ring_form && dtype != TIDE_F32 && !tile256 && (form == 0 || form == 4);
+    // (The wide-tile kernels have no form for rows that are no whole k-tiles.)
+    const bool wide16 = !ring_form && dtype != TIDE_F32 && !ragged && !tile256 && (form == 0 || form == 4);
     const bool wide32 = dtype == TIDE_F32 && !ragged && !generic_d && !two_halves && (form == 0 || form == 4);
     if (wide16 || wide32) {
         const int64_t wrows = two_halves ? kWideRows / 2 : kWideRows;
@@ -739,6 +747,18 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     return plan;
 }
 
+// The launches of a call on rows of d elements (after a repack: of the padded length).
+// Rows of whole 16-byte chunks whose length is no multiple of 128: under the automatic settings the plan of the padded
+// length, on the kernels that read the chunks beyond a row's end as zeros: bf16, d = 1600, C = 12: 53 -> 40 us at T = 4000, 21 -> 17 at 1000;
+// d = 4104, C = 8, T = 200: 39 -> 15.5; fp32, d = 4000, C = 9, T = 300: 161 -> 28; d = 1608, C = 8, T = 3000: 82 -> 55 (before: the register-ring
+// form, whose loads are selected chunk by chunk).  (split_k: the split-k pair only where its partial results do not
+// have to fit a block that was sized without them.)
+PrefillPlan call_plan(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, int variant, int form_word, bool split_k) {
+    if (variant == TIDE_VARIANT_AUTO && form_word == 0 && d % 128 != 0)
+        return plan_prefill(dtype, C, T, padded_hidden(dtype, d), b, cus, 0, true, split_k);
+    return plan_prefill(dtype, C, T, d, b, cus, form_word);
+}
+
 // What the prefill kernels and the few-rows kernel take, all but the tiling.
 PrefillParams prefill_params(const Scratch& sc, const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t d_mean, int64_t b,
                              int64_t ckpt_stride, int64_t row_stride, const void* packed, float eps, const float* b1, const float* w2,
@@ -784,6 +804,8 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
         p.total_tiles = L.total_tiles;
         p.tile_begin = L.tile_begin;
         p.k_slices = L.k_slices;
+        // a kernel that would read such rows wrongly is never launched on them, whatever the plan says
+        auto no_form = [&]() { return fail(TIDE_ERR_UNSUPPORTED, "kernel %d has no form for dtype %d, d = %d", L.kernel, dtype, p.d); };
         auto launch = [&](auto dt, auto ragged_tag) {
             constexpr int DT = decltype(dt)::value;
             constexpr bool R = decltype(ragged_tag)::value;
@@ -796,25 +818,32 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
                 rc = launch_splitk_fused<DT, R>(sc.part, sc.counters, L.total_tiles, st, p);
                 break;
             case kKernelWide:
-                if constexpr (DT != kF32) rc = two_halves ? launch_wide<DT, 2>(L.grid, st, p) : launch_wide<DT, 1>(L.grid, st, p);
+                if constexpr (DT != kF32 && !R) rc = two_halves ? launch_wide<DT, 2>(L.grid, st, p) : launch_wide<DT, 1>(L.grid, st, p);
+                else rc = no_form();
                 break;
             case kKernelWideF32:
-                rc = launch_wide_f32(L.grid, st, p);
+                if constexpr (DT == kF32 && !R) rc = launch_wide_f32(L.grid, st, p);
+                else rc = no_form();
                 break;
             case kKernelTile:
                 if constexpr (DT != kF32) rc = two_halves ? launch_tile<DT, 2>(st, p) : launch_tile<DT, 1, R>(st, p);
+                else rc = no_form();
                 break;
             case kKernelBand:
                 if constexpr (DT != kF32) rc = launch_band<DT, R>(L.grid, st, p);
+                else rc = no_form();
                 break;
             case kKernelBandF32:
                 if constexpr (DT == kF32) {
                     const int per_ckpt = (int)L.grid / p.C;
                     rc = (L.tiles_per_ckpt + per_ckpt - 1) / per_ckpt <= 4 ? launch_band_f32<R, 4>(L.grid, st, p) : launch_band_f32<R, 8>(L.grid, st, p);
+                } else {
+                    rc = no_form();
                 }
                 break;
             case kKernelSquare:
-                if constexpr (DT != kF32) rc = launch_square<DT>(st, p);
+                if constexpr (DT != kF32 && !R) rc = launch_square<DT>(st, p);
+                else rc = no_form();
                 break;
             case kKernelStream128:
                 rc = launch_dma<DT, 128, 1, R>(L.grid, st, p);
@@ -996,15 +1025,7 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
         return n;
     }
     if (raw_weights) n.packed_bytes = round256((size_t)C * tide_packed_router_bytes(dtype, d, b));
-    // Rows of whole 16-byte chunks whose length is no multiple of 128: under the automatic settings the plan of the padded
-    // length, on the kernels that read the chunks beyond a row's end as zeros: bf16, d = 1600, C = 12: 53 -> 40 us at T = 4000, 21 -> 17 at 1000;
-    // d = 4104, C = 8, T = 200: 39 -> 15.5; fp32, d = 4000, C = 9, T = 300: 161 -> 28; d = 1608, C = 8, T = 3000: 82 -> 55 (before: the register-ring
-    // form, whose loads are selected chunk by chunk).  (The split-k pair only where its partial results do not
-    // have to fit a block that was sized without them.)
-    if (variant == TIDE_VARIANT_AUTO && form_word == 0 && n.d_run % 128 != 0)
-        n.plan = plan_prefill(dtype, C, T, padded_hidden(dtype, d), b, cus, 0, true, library);
-    else
-        n.plan = plan_prefill(dtype, C, T, n.d_run, b, cus, form_word);
+    n.plan = call_plan(dtype, C, T, n.d_run, b, cus, variant, form_word, library);
     for (int i = 0; i < n.plan.count; ++i) {
         const PlannedLaunch& L = n.plan.launch[i];
         if (L.kernel == kKernelSplitK || L.kernel == kKernelSplitKFused) n.part_bytes = round256(splitk_part_bytes(L.rows_per_tile / 32, L.total_tiles, halves, L.k_slices));
@@ -1675,7 +1696,7 @@ int tide_prefill_plan(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int
     if (cus < 8 || cus % 8 != 0) return fail(TIDE_ERR_INVALID_ARG, "cus = %d must be a positive multiple of 8", cus);
     if (!valid_form_word(form)) return fail(TIDE_ERR_INVALID_ARG, "prefill form %d: a form in [0, 8], with forms 5 and 8 optionally rows << 8 | slices << 16", form);
     if (!out) return fail(TIDE_ERR_INVALID_ARG, "out must not be NULL");
-    const PrefillPlan plan = plan_prefill(dtype, C, T, d, b, (unsigned)cus, form);
+    const PrefillPlan plan = call_plan(dtype, C, T, d, b, (unsigned)cus, TIDE_VARIANT_AUTO, form, true);
     for (int i = 0; i < plan.count; ++i) {
         const PlannedLaunch& L = plan.launch[i];
         int32_t* o = out + 7 * i;

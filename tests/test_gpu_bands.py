@@ -83,6 +83,10 @@ def test_few_rows_of_k_tiles_no_multiple_of_four(tr, C, dtype, T, d, b):
     (8, "f16", 3001, 1032, 128, 8, "one 128-row tile per CU"),
     (8, "bf16", 5003, 136, 128, 0, "bands, two k-tiles"),
     (12, "bf16", 4000, 808, 64, 0, "bands of one checkpoint each"),
+    (12, "bf16", 2700, 1600, 128, 0, "more than half a round of 256-row tiles, four blocks per CU at most: bands"),
+    (10, "bf16", 3100, 1608, 128, 8, "the same, a 128-row tile per CU at most: the one-tile kernel"),
+    (31, "f16", 1040, 1032, 64, 0, "the same, short last tiles: bands"),
+    (7, "bf16", 4650, 1000, 128, 0, "the same, two 64-row tiles per CU at most: the register-ring kernel"),
     (3, "f32", 700, 132, 128, 0, "fp32 bands of one block, one chunk in the last k-tile"),
     (10, "f32", 9000, 140, 128, 4, "fp32 bands in several tiles"),
     (2, "f32", 9000, 1000, 64, 0, "fp32 bands in pairs of waves")])

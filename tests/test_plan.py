@@ -8,7 +8,8 @@ import pytest
 
 from paper_2603_21365_amd import tide_route as tr
 
-SPLITK, WIDE, WIDE_F32, TILE, STREAM128, STREAM64, RING, BAND, SPLITK_FUSED, SQUARE = 1, 2, 3, 4, 5, 6, 7, 8, 9, 10
+SPLITK, WIDE, WIDE_F32, TILE, STREAM128, STREAM64, RING, BAND, SPLITK_FUSED, SQUARE, BAND_F32 = 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11
+ZERO_FILLS = (SPLITK, SPLITK_FUSED, TILE, STREAM128, STREAM64, RING, BAND, BAND_F32)      # kernels with a form for rows that are no whole k-tiles
 ELEM = {tr.F32: 4, tr.F16: 2, tr.BF16: 2}
 
 
@@ -37,14 +38,14 @@ def check_plan(dtype, C, T, d, b, cus, form):
     assert seen.min() == 1 and seen.max() == 1, what
     assert plan[-1]["total_tiles"] == C * plan[-1]["tiles_per_ckpt"], what   # the last launch runs to the end of the list
     halves = (b + 127) // 128
-    ntile = d * ELEM[dtype] // 256
+    ntile = -(-d // 128) * 128 * ELEM[dtype] // 256
     for i, L in enumerate(plan):
         k, R, wg = L["kernel"], L["rows_per_tile"], L["workgroups"]
         assert wg >= 1, what
         if k == SPLITK_FUSED:
             assert R == 32 and halves == 1 and L["total_tiles"] <= 64 and (form & 0xff) in (0, 8) and ((form & 0xff) == 8 or T <= 16), what
         if k in (SPLITK, SPLITK_FUSED):
-            assert len(plan) == 1 and d % 128 == 0, what
+            assert len(plan) == 1, what
             assert R in (32, 64, 128) and (form >> 8 or R == 32 or T > R // 2), what   # its own choice: never a tile that is mostly padding
             assert L["k_slices"] in (2, 4, 8, ntile) and 2 <= L["k_slices"] <= min(8, ntile), what
             assert wg == L["total_tiles"] * halves * L["k_slices"], what
@@ -71,18 +72,20 @@ def check_plan(dtype, C, T, d, b, cus, form):
                     rem = all_tiles % cus
                     assert 2 * all_tiles > cus and (all_tiles <= cus or rem == 0 or 2 * rem > cus), what
         if k == TILE:
-            assert R == 128 and dtype != tr.F32 and d % 128 == 0, what
+            assert R == 128 and dtype != tr.F32, what
             assert wg == 8 * -(-(L["total_tiles"] - L["tile_begin"]) // 8), what
         if k in (STREAM128, STREAM64):
-            assert R == (128 if k == STREAM128 else 64) and d % 128 == 0, what
+            assert R == (128 if k == STREAM128 else 64), what
             assert wg % 8 == 0 and wg <= cus * (1 if (R == 128 or halves == 2) else 2), what
             assert halves == 1 or k == STREAM64, what
         if k == RING:
             assert R == 64 and halves == 1, what
         if k == BAND:
-            assert len(plan) == 1 and R == 32 and dtype != tr.F32 and halves == 1 and d % 128 == 0 and wg == cus, what
-        if d % 128 != 0:
-            assert k == RING and len(plan) == 1, what
+            assert len(plan) == 1 and R == 32 and dtype != tr.F32 and halves == 1 and wg == cus, what
+        if k == BAND_F32:
+            assert len(plan) == 1 and R == 32 and dtype == tr.F32 and halves == 1 and form == 0 and C <= cus and wg == cus, what
+        if d % 128 != 0:    # forced forms: the register-ring kernel; the automatic choice: kernels that zero-fill beyond the end of a row
+            assert len(plan) == 1 and (k in ZERO_FILLS if form == 0 else k == RING), what
     if len(plan) == 2:
         assert plan[0]["kernel"] in (WIDE, WIDE_F32, SQUARE) and plan[1]["kernel"] not in (WIDE, WIDE_F32, SPLITK, SQUARE), what
     return plan
@@ -203,12 +206,38 @@ def test_the_band_schedule_covers_every_block_once():
     assert sorted(set(counts)) == [2, 3] and counts.count(3) == 8
 
 
-def test_generic_hidden_sizes_take_the_register_ring_kernel():
+def test_generic_hidden_sizes_take_the_register_ring_kernel_when_a_form_is_forced():
     for dtype, d in ((tr.BF16, 200), (tr.F16, 72), (tr.F32, 100), (tr.BF16, 4104), (tr.F32, 708)):
-        for form in range(10):
+        for form in range(1, 10):
             for C, T in ((1, 1), (4, 300), (10, 16384)):
                 plan = check_plan(dtype, C, T, d, 128, 256, form)
                 assert [L["kernel"] for L in plan] == [RING]
+
+
+@pytest.mark.parametrize("dtype,C,T,d", [
+    (tr.BF16, 12, 2700, 1600), (tr.BF16, 10, 3100, 1608), (tr.F16, 10, 3200, 1000), (tr.BF16, 7, 4650, 1608), (tr.F16, 9, 3600, 3080),
+    (tr.BF16, 9, 3600, 136), (tr.F16, 31, 1040, 8200), (tr.BF16, 5, 6500, 40)])
+def test_generic_hidden_sizes_never_reach_a_kernel_without_zero_fill(dtype, C, T, d):
+    """More than half a round of 256-row tiles, at most four 32-row blocks per CU: the wide-tile kernel's range at whole k-tiles."""
+    for b in (64, 128):
+        (L,) = check_plan(dtype, C, T, d, b, 256, 0)
+        assert L["kernel"] == (TILE if C * -(-T // 128) <= 256 else RING if C * -(-T // 64) <= 512 else BAND)
+
+
+def test_generic_hidden_sizes_on_random_shapes():
+    rng = np.random.default_rng(0x4A66)
+    kinds = set()
+    for _ in range(4000):
+        dtype = int(rng.choice([tr.BF16, tr.F16, tr.F32]))
+        C = int(rng.integers(1, 33))
+        T = int(rng.choice([rng.integers(1, 70), rng.integers(1, 3000), 256 * rng.integers(1, 60) + rng.integers(0, 80), rng.integers(1, 40000)]))
+        T = min(T, 600000 // C)
+        d = int(rng.integers(1, 128 * 17)) * 8 % 16384 or 8
+        if d % 128 == 0:
+            d += 8
+        plan = check_plan(dtype, C, T, d, int(rng.choice([64, 128])), int(rng.choice([8, 32, 64, 256, 256, 304])), 0)
+        kinds |= {L["kernel"] for L in plan}
+    assert kinds >= {SPLITK, STREAM128, STREAM64, TILE, BAND, BAND_F32}, kinds
 
 
 def test_the_choices_on_the_named_workloads():
