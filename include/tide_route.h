@@ -50,7 +50,8 @@
  *          busy is refused with TIDE_ERR_WORKSPACE.  tide_release() frees it.  Once it is large
  *          enough a call only enqueues kernels, so it can be captured in a HIP graph; the graph
  *          holds the workspace's addresses, so make one eager call of the largest shape on the
- *          capturing stream first and neither outgrow nor release the workspace while the graph lives;
+ *          capturing stream first and neither outgrow nor release the workspace while the graph lives
+ *          (an eager call leaves room for every smaller T of its type, C, d, b and kind of weights);
  *      (2) the _ws entry points take a caller-owned workspace (tide_workspace_bytes,
  *          tide_workspace_init): nothing is allocated, and calls on different workspaces may run
  *          concurrently on different streams;

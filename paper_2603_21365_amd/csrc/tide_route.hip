@@ -85,8 +85,16 @@ struct Scratch {
 // a workspace of its own.  `last_stream` / `used` remember where its last call was enqueued, `dirty`
 // that a launch failed after an earlier one of the same call had been enqueued (the state words
 // may then be non-zero: the next call clears them first).
+// `sized` remembers for which shapes, and up to which T, the partial results' buffer was sized (see largest_part).
+struct SizedShape {
+    int dtype = 0, raw = 0;
+    int64_t C = 0, d = 0, b = 0, T = 0;
+};
+constexpr int kSizedShapes = 16;
 struct Workspace {
     Buffer counters, arrive, packed, part, rows, batch, compact;
+    SizedShape sized[kSizedShapes];
+    unsigned next_sized = 0;
     hipStream_t last_stream = nullptr;
     bool used = false, dirty = false;
 };
@@ -1035,6 +1043,19 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
     return n;
 }
 
+// The most partial results that any call of these C, d and b with at most T rows per checkpoint keeps under the automatic settings.
+// An eager call on the library's workspace reserves that much, so that no smaller call outgrows the buffer: a captured graph
+// holds its address.  The split-k forms' choice changes with the number of 32-row blocks only; the few-rows kernel has at most two
+// workgroups of 16 rows x 4 bytes per CU; the latency kernel's part grows with T up to 8 or 32.
+size_t largest_part(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool raw_weights, unsigned cus) {
+    size_t most = std::min<size_t>(round256((size_t)(T * C * (b / kFewCols)) * sizeof(float)), (size_t)cus * 2 * kFewRows * sizeof(float));
+    auto at = [&](int64_t t) { most = std::max(most, call_need(dtype, C, t, d, b, raw_weights, false, cus, TIDE_VARIANT_AUTO, 0, true).part_bytes); };
+    at(T);
+    at(std::min<int64_t>(T, kDecodeRawMaxT));
+    for (int64_t t = 32; t < T && C * halves_of(b) * (t / 32) <= 4 * kSplitkMaxTiles; t += 32) at(t);
+    return most;
+}
+
 // Zero-fill for state words (a kernel, not a memset: calls may be captured into HIP graphs).
 __global__ void tide_clear_kernel(u32x4* p, size_t chunks) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < chunks; i += (size_t)gridDim.x * blockDim.x)
@@ -1091,14 +1112,15 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
     if (need.few && source != kScratchLibrary && need.total() > (source == kScratchCaller ? block_bytes : kStaticScratchBytes))
         need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, source == kScratchLibrary, false);
 
-    // While a call is captured nothing can be allocated: where the library's workspace lacks the partial results of a route that
-    // the caller's blocks are not sized for either, the call takes the route that they would give it.
-    if (source == kScratchLibrary && need.part_bytes > g_ws[dev].part.bytes) {
+    auto capturing = [&]() {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
-        if (cap != hipStreamCaptureStatusNone)
-            need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false, false);
-    }
+        return cap != hipStreamCaptureStatusNone;
+    };
+    // While a call is captured nothing can be allocated: where the library's workspace lacks the partial results of a route that
+    // the caller's blocks are not sized for either, the call takes the route that they would give it.
+    if (source == kScratchLibrary && need.part_bytes > g_ws[dev].part.bytes && capturing())
+        need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false, false);
 
     Scratch sc;
     Workspace* ws = nullptr;        // library workspace, if that is the source
@@ -1110,7 +1132,33 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
         if ((rc = reserve(ws->counters, kCounterSlots * sizeof(uint32_t), true))) return rc;
         if (want_exit && (rc = reserve(ws->arrive, (size_t)T * sizeof(uint64_t), true))) return rc;
         if (need.packed_bytes && (rc = reserve(ws->packed, need.packed_bytes, false))) return rc;
-        if (need.part_bytes && (rc = reserve(ws->part, need.part_bytes, false))) return rc;
+        size_t part_bytes = need.part_bytes;
+        SizedShape* shape = nullptr;     // to be remembered once the buffer is there
+        if (g_variant == TIDE_VARIANT_AUTO && g_prefill_form == 0) {
+            bool sized = false;
+            for (SizedShape& s : ws->sized)
+                if (s.C == C && s.d == d && s.b == b && s.dtype == dtype && s.raw == (W1 != nullptr)) {
+                    sized = T <= s.T;
+                    shape = &s;
+                }
+            if (sized) {
+                shape = nullptr;
+            } else if (!capturing()) {
+                if (!shape) shape = &ws->sized[ws->next_sized++ % kSizedShapes];
+                part_bytes = std::max(part_bytes, largest_part(dtype, C, T, d, b, W1 != nullptr, cus));
+            } else {
+                shape = nullptr;
+            }
+        }
+        rc = part_bytes ? reserve(ws->part, part_bytes, false) : TIDE_OK;
+        if (rc && part_bytes > need.part_bytes) {       // no room for more than this call needs
+            (void)hipGetLastError();
+            for (SizedShape& s : ws->sized) s = SizedShape{};
+            shape = nullptr;
+            rc = need.part_bytes ? reserve(ws->part, need.part_bytes, false) : TIDE_OK;
+        }
+        if (rc) return rc;
+        if (shape) *shape = SizedShape{dtype, W1 != nullptr, C, d, b, T};
         if (need.rows_bytes && (rc = reserve(ws->rows, need.rows_bytes, false))) return rc;
         if (ws->dirty) {            // an earlier call broke off between two launches: its state words may be set
             if ((rc = launch_clear(ws->counters.ptr, ws->counters.bytes, st))) return rc;
@@ -1760,6 +1808,7 @@ int tide_release(void) {
         b->ptr = nullptr;
         b->bytes = 0;
     }
+    for (SizedShape& s : ws->sized) s = SizedShape{};
     ws->used = false;
     ws->dirty = false;
     return TIDE_OK;

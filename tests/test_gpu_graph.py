@@ -128,3 +128,55 @@ def test_capture_after_an_eager_call_that_left_no_partial_results(tr, T, d):
         call(hidden)                    # eager again: may allocate (after the last replay)
     torch.cuda.synchronize()
     del graph
+
+
+@pytest.mark.parametrize("dtype,C,d,b,raw,T_graph,T_later", [
+    ("bf16", 4, 768, 128, False, 48, (96, 300, 5, 1000)),      # few rows where larger calls stream: no partial results there
+    ("bf16", 4, 1608, 128, False, 300, (48, 600, 2000)),       # a ragged hidden size, split over k
+    ("f16", 8, 4096, 128, False, 8, (16, 48, 64, 500)),        # few rows, then the split-k pair
+    ("f32", 3, 1000, 64, False, 20, (32, 33, 150)),
+    ("bf16", 2, 1024, 256, False, 30, (70, 800)),
+    ("f16", 4, 2048, 128, True, 4, (8, 40, 300))])
+def test_a_captured_call_survives_later_calls_that_are_no_larger_than_the_first(tr, dtype, C, d, b, raw, T_graph, T_later):
+    """One eager call of the largest T sizes the workspace for every smaller one of the shape: neither the captured call nor the
+    eager ones behind it allocate, so the addresses in the graph stay the workspace's."""
+    import torch
+    w = synth.Workload(f"graph_later_{dtype}_d{d}", 59, dtype, d, 4 * C, 4, 4000, None, b=b)
+    rt = w.routers()
+    rt.b2[:] = np.linspace(-0.2, 0.2, C)
+    g, W1, b1, w2 = routers_to_device(rt)
+    packed = None if raw else tr.router_pack(tr.DTYPE_CODES[dtype], g, W1)
+    hidden = to_device(w.hidden(), dtype)
+
+    def call(T, **kw):
+        h = hidden[:, :T]
+        if raw:
+            return tr.select_exit(h, g, w.eps, W1, b1, w2, rt.b2, rt.theta, w.layer_ids, 0, w.n_layers, **kw)
+        return tr.select_exit_packed(h, packed, w.eps, b1, w2, rt.b2, rt.theta, w.layer_ids, 0, w.n_layers, d=d, **kw)
+
+    out = (torch.empty(T_graph, dtype=torch.int32, device="cuda"), torch.empty((C, T_graph), dtype=torch.float32, device="cuda"),
+           torch.empty(T_graph, dtype=torch.int32, device="cuda"))
+    torch.cuda.synchronize()
+    tr.release()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        call(w.T)
+    torch.cuda.synchronize()
+    allocations = tr.workspace_allocations()
+    with torch.cuda.stream(stream):
+        want = [o.clone() for o in call(T_graph)]
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        call(T_graph, out=out)
+    for T in T_later:
+        with torch.cuda.stream(stream):
+            call(T)
+        torch.cuda.synchronize()
+        assert tr.workspace_allocations() == allocations, f"T = {T} outgrew the workspace of T = {w.T}"
+        for o in out:
+            o.fill_(-7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b_) for a, b_ in zip(out, want)), f"replay after T = {T}"
+    del graph
