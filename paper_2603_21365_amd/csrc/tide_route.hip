@@ -1023,12 +1023,12 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
         const size_t S = (size_t)((d + kDecodeSlice - 1) / kDecodeSlice);
         n.part_bytes = round256((size_t)C * S * (size_t)T * (size_t)(halves * kBottleneck + kPartPad) * sizeof(float));
     }
-    // (the other paths' needs are counted all the same: what a caller has to bring does not depend on this choice)
+    // (the other paths' needs are counted all the same for a caller's block: what a caller has to bring does not depend on this choice)
     n.few = allow_few && !(raw_weights && n.decode) && variant == TIDE_VARIANT_AUTO && form_word == 0 && use_few_rows(dtype, C, T, n.d_run, b, cus);
     const size_t few_bytes = n.few ? round256((size_t)T * (size_t)C * (size_t)(b / kFewCols) * sizeof(float)) : 0;
     if (n.decode) {
         n.leaves_data = true;
-        n.part_bytes = std::max(n.part_bytes, few_bytes);
+        n.part_bytes = n.few && library ? few_bytes : std::max(n.part_bytes, few_bytes);
         if (n.few) n.decode = false;
         return n;
     }
@@ -1039,7 +1039,7 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
         if (L.kernel == kKernelSplitK || L.kernel == kKernelSplitKFused) n.part_bytes = round256(splitk_part_bytes(L.rows_per_tile / 32, L.total_tiles, halves, L.k_slices));
     }
     n.leaves_data = n.packed_bytes + n.part_bytes + n.rows_bytes > 0;
-    n.part_bytes = std::max(n.part_bytes, few_bytes);
+    n.part_bytes = n.few && library ? few_bytes : std::max(n.part_bytes, few_bytes);
     return n;
 }
 

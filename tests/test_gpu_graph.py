@@ -180,3 +180,41 @@ def test_a_captured_call_survives_later_calls_that_are_no_larger_than_the_first(
         torch.cuda.synchronize()
         assert all(torch.equal(a, b_) for a, b_ in zip(out, want)), f"replay after T = {T}"
     del graph
+
+def test_few_rows_are_captured_on_what_a_few_rows_call_left(tr):
+    """d = 4096 with the partial results of a d = 768 call of the few-rows kernel in the workspace: enough for that kernel, too
+    little for the split-k form of the same call."""
+    import torch
+    def call_of(d, T):
+        w = synth.Workload(f"graph_few_d{d}", 61, "f16", d, 16, 4, T, None)
+        rt = w.routers()
+        g, W1, b1, w2 = routers_to_device(rt)
+        packed, h = tr.router_pack(tr.F16, g, W1), to_device(w.hidden(), "f16")
+        out = (torch.empty(T, dtype=torch.int32, device="cuda"), torch.empty((w.C, T), dtype=torch.float32, device="cuda"),
+               torch.empty(T, dtype=torch.int32, device="cuda"))
+        torch.cuda.synchronize()
+        return lambda: tr.select_exit_packed(h, packed, w.eps, b1, w2, rt.b2, rt.theta, w.layer_ids, 0, w.n_layers, d=d, out=out)
+    small, large = call_of(768, 48), call_of(4096, 8)
+    tr.release()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        small()
+    torch.cuda.synchronize()
+    allocations = tr.workspace_allocations()
+    with torch.cuda.graph(graph, stream=stream):
+        out = large()
+    assert tr.workspace_allocations() == allocations
+    got = []
+    for rep in range(3):
+        for o in out:
+            o.fill_(-7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got.append([o.clone() for o in out])
+    del graph
+    with torch.cuda.stream(stream):
+        large()
+    torch.cuda.synchronize()
+    for g_ in got:
+        assert all(torch.equal(a, b) for a, b in zip(g_, out))
