@@ -1024,7 +1024,11 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
         n.part_bytes = round256((size_t)C * S * (size_t)T * (size_t)(halves * kBottleneck + kPartPad) * sizeof(float));
     }
     // (the other paths' needs are counted all the same for a caller's block: what a caller has to bring does not depend on this choice)
-    n.few = allow_few && !(raw_weights && n.decode) && variant == TIDE_VARIANT_AUTO && form_word == 0 && use_few_rows(dtype, C, T, n.d_run, b, cus);
+    // fp32 rows that the latency kernel takes stay with it on packed weights too: it multiplies the whole fp32 value of a row by both terms of
+    // the weight, the few-rows kernel the row's two leading bf16 terms (error against 64 bits at T = 32, d = 1000: 2.6e-6 against 4.7e-6).
+    // 16-bit rows are exact in either.
+    n.few = allow_few && !(n.decode && (raw_weights || dtype == TIDE_F32)) && variant == TIDE_VARIANT_AUTO && form_word == 0 &&
+            use_few_rows(dtype, C, T, n.d_run, b, cus);
     const size_t few_bytes = n.few ? round256((size_t)T * (size_t)C * (size_t)(b / kFewCols) * sizeof(float)) : 0;
     if (n.decode) {
         n.leaves_data = true;

@@ -62,6 +62,28 @@ def test_every_output_without_exit_selection(tr, T, d):
     assert np.array_equal(fire.cpu().numpy()[away], f_o[away])
 
 
+@pytest.mark.parametrize("C,T,d,b", [(1, 8, 128, 128), (8, 1, 128, 64), (8, 32, 1000, 128), (4, 32, 4104, 64), (2, 9, 1608, 128)])
+def test_fp32_rows_keep_all_their_bits_where_the_latency_kernel_does(tr, C, T, d, b):
+    """fp32 rows, up to 32 per checkpoint, d = 128 or no multiple of 128, packed weights that the packed form holds exactly (16 bits
+    of fraction at most): what is left is fp32 summation.  A pre-activation is a sum of about unit size, in error by the rounding
+    of its d products and sums, at most 2 sqrt(d) * 2^-24 of it (the roundings are independent), and the logit, a sum of b terms
+    of |w2| = 1 / sqrt(b) with slopes of SiLU up to 1.1, by at most the same relative to its own unit size.  Rows cut to two
+    bf16 terms (2^-17 of a value) show 3e-6 and more of the norm."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(1000 * T + d)
+    r = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    h, W1, w2, b1 = r(C, T, d), torch.round(r(C, d, b) / d ** 0.5 * 2 ** 14) / 2 ** 14, r(C, b) / b ** 0.5, 0.1 * r(C, b)
+    print(f"[gpu-case] fp32 bits C={C} T={T} d={d} b={b}", flush=True)
+    ids = [4 * c + 3 for c in range(C)]
+    z = tr.select_exit_packed(h, tr.router_pack(tr.F32, None, W1), 1e-6, b1, w2, [0.0] * C, [0.5] * C, ids, 0, 4 * C, d=d)[1].cpu().double()
+    hd, Wd, bd, wd = (x.cpu().double() for x in (h, W1, b1, w2))
+    x = hd / torch.sqrt((hd * hd).mean(-1, keepdim=True) + 1e-6)
+    pre = torch.stack([x[c] @ Wd[c] for c in range(C)]) + bd[:, None]
+    z_o = (pre * torch.sigmoid(pre) * wd[:, None]).sum(-1)
+    err = ((z - z_o).norm() / z_o.norm()).item()
+    assert err < min(2 * d ** 0.5 * 2.0 ** -24, 1.5e-6), err
+
+
 def test_non_finite_rows_stay_by_themselves(tr):
     """A row with an infinity or a NaN has a NaN logit and fires nothing; the rows beside it in its tile, and the zeros that
     stand in beyond the end of a row (d = 1544), are not touched by it."""
