@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -312,13 +313,18 @@ int launch_pack(int dtype, int64_t C, int64_t d, int64_t b, const float* gamma, 
     return TIDE_OK;
 }
 
-// CUs of the current device, rounded down to a multiple of 8 (one slice of the tile list per XCD).
+// CUs of the current device, rounded down to a multiple of 8 (one slice of the tile list per XCD).  Called with and without g_mu held.
 int resident_cus(unsigned* out) {
-    static int cus[kMaxDevices] = {};
+    static std::atomic<int> cus[kMaxDevices];                // 0: not asked for yet
     int dev = 0;
     TIDE_HIP(hipGetDevice(&dev));
-    if (!cus[dev]) TIDE_HIP(hipDeviceGetAttribute(&cus[dev], hipDeviceAttributeMultiprocessorCount, dev));
-    *out = (unsigned)(cus[dev] > 8 ? cus[dev] & ~7 : 8);
+    const bool known = dev >= 0 && dev < kMaxDevices;        // (an entry point without a workspace runs on any device)
+    int n = known ? cus[dev].load(std::memory_order_relaxed) : 0;
+    if (!n) {
+        TIDE_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
+        if (known) cus[dev].store(n, std::memory_order_relaxed);
+    }
+    *out = (unsigned)(n > 8 ? n & ~7 : 8);
     return TIDE_OK;
 }
 
@@ -1556,10 +1562,12 @@ int tide_exit_project(const void* hidden, int dtype, int64_t C, int64_t T, int64
     p.d = (int)d;
     p.eps = eps;
     const int64_t row_bytes = d * (int64_t)eb;
-    unsigned cus = 0;
-    if ((rc = resident_cus(&cus))) return rc;
-    const bool wave_per_row = row_bytes <= (int64_t)kProjectMaxChunks * 16 * kWave &&       // 16 KiB
-                              (T > 3 * (int64_t)cus || row_bytes < 4096);                   // (project_kernel.hpp has the figures)
+    bool wave_per_row = row_bytes <= (int64_t)kProjectMaxChunks * 16 * kWave;        // 16 KiB
+    if (wave_per_row && row_bytes >= 4096) {                                          // (project_kernel.hpp has the figures)
+        unsigned cus = 0;
+        if ((rc = resident_cus(&cus))) return rc;
+        wave_per_row = T > 3 * (int64_t)cus;
+    }
     if (row_bytes > (int64_t)kProjectMaxChunks * 16 * kProjectThreads)
         return fail(TIDE_ERR_UNSUPPORTED, "rows of %lld bytes exceed the projection kernel's limit", (long long)row_bytes);
     hipStream_t st = (hipStream_t)stream;

@@ -1,7 +1,8 @@
 """Host code under AddressSanitizer and UndefinedBehaviorSanitizer (CPU only; GPU code is never
 instrumented): the C oracle runs its pins once as a sanitizer build, and the host side of
 libtide_route -- argument checks, the prefill plan, the persistent kernels' tile schedule, the
-workspace arithmetic -- runs the plan and boundary tests as a sanitizer build of the same sources."""
+workspace arithmetic -- runs the plan and boundary tests as a sanitizer build of the same sources, and what it
+looks up without its lock (the device's number of CUs) is called from several threads at once."""
 import os
 import shutil
 import subprocess
@@ -94,3 +95,63 @@ def test_host_side_of_the_library_under_sanitizers(tmp_path):
     run = _pytest([os.path.join(ROOT, "tests", "test_plan.py"), os.path.join(ROOT, "tests", "test_abi.py")], env, 900)
     assert _clean(run, tmp_path), run.stdout[-3000:] + run.stderr[-3000:] + _reports(tmp_path)[-3000:]
     assert " passed" in run.stdout
+
+
+_THREADS = r"""
+#include <dlfcn.h>
+#include <atomic>
+#include <cstdint>
+#include <cstdio>
+#include <thread>
+#include <vector>
+static thread_local int g_dev = 0;                       // in place of the HIP runtime: a device per thread, no GPU
+extern "C" int hipGetDevice(int* d) { *d = g_dev; return 0; }
+extern "C" int hipDeviceGetAttribute(int* v, int, int) { *v = 304; return 0; }
+int main(int, char** argv) {
+    void* lib = dlopen(argv[1], RTLD_NOW);
+    if (!lib) { puts(dlerror()); return 3; }
+    auto need = (size_t(*)(int, int64_t, int64_t, int64_t, int64_t, int))dlsym(lib, "tide_workspace_bytes");
+    for (int first : {3, 40}) {                          // one device's entry; devices beyond the table
+        std::atomic<int> ready{0};
+        std::vector<size_t> got(8);
+        std::vector<std::thread> threads;
+        for (int i = 0; i < 8; ++i)
+            threads.emplace_back([&, i] {
+                g_dev = first;
+                ready.fetch_add(1, std::memory_order_relaxed);
+                while (ready.load(std::memory_order_relaxed) < 8) std::this_thread::yield();
+                got[i] = need(2, 8, 100, 4096, 128, 0);
+            });
+        for (auto& t : threads) t.join();
+        for (size_t g : got)
+            if (g != got[0] || g == 0) { printf("%zu\n", g); return 4; }
+    }
+    puts("same answer");
+}
+"""
+
+
+def test_first_calls_from_several_threads(tmp_path):
+    """The number of CUs is cached per device and read without the library's lock (by the exit projection, which needs no
+    workspace and runs on any device index, and by tide_workspace_bytes): no race on it, no index beyond the cache."""
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    clang = "/opt/rocm/lib/llvm/bin/clang++"
+    runtime = _tool_file(clang, "libclang_rt.tsan-x86_64.so") if os.path.exists(hipcc) and os.path.exists(clang) else None
+    if runtime is None:
+        pytest.skip("hipcc or clang's ThreadSanitizer runtime is not installed")
+    from paper_2603_21365_amd.build import CSRC, HIPCC_FLAGS, INCLUDE
+    lib, driver, source = (str(tmp_path / n) for n in ("libtide_route_tsan.so", "threads", "threads.cpp"))
+    with open(source, "w") as f:
+        f.write(_THREADS)
+    host_san = []
+    for f in ("-fsanitize=thread", "-fsanitize=bounds", "-fno-sanitize-recover=bounds"):
+        host_san += ["-Xarch_host", f]                               # host pass only
+    builds = ([hipcc, *[f for f in HIPCC_FLAGS if f != "-O3"], "-O1", "-g", *host_san, "-shared-libsan", "-I", INCLUDE, "-o", lib, os.path.join(CSRC, "tide_route.hip")],
+              [clang, "-std=c++17", "-O1", "-g", "-fsanitize=thread", "-shared-libsan", "-rdynamic", "-o", driver, source, "-ldl", "-pthread"])
+    for cmd in builds:
+        build = subprocess.run(cmd, capture_output=True, text=True, timeout=900)
+        assert build.returncode == 0, build.stderr[-3000:]
+    run = subprocess.run([driver, lib], capture_output=True, text=True, timeout=300,
+                         env=dict(os.environ, LD_LIBRARY_PATH=os.path.dirname(runtime) + ":" + os.environ.get("LD_LIBRARY_PATH", "")))
+    text = run.stdout + run.stderr
+    assert run.returncode == 0 and "ThreadSanitizer" not in text and "same answer" in text, text[-3000:]
