@@ -60,8 +60,8 @@ template <int DT, bool kGain> __device__ __forceinline__ u32x4 scale_round_chunk
 }
 
 // kWavePerRow: 4 rows per workgroup (one per wave), else 1 row per workgroup.  kChunks = 16-byte
-// chunks of the row held per thread (the host picks the smallest of 4, 8, 16 that covers it).
-template <int DT, bool kWavePerRow, bool kGain, int kChunks>
+// chunks of the row held per thread (the host picks the smallest of 1 and 2 (a workgroup per row), 4, 8, 16 that covers it).
+template <int DT, bool kWavePerRow, bool kGain, int kChunks, bool kAhead>
 __global__ __launch_bounds__(kProjectThreads) void tide_project_kernel(const ProjectParams p) {
     __shared__ float part[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -83,11 +83,13 @@ __global__ __launch_bounds__(kProjectThreads) void tide_project_kernel(const Pro
     // Every thread's share of the row sits in registers between the read and the write.  Chunk
     // indices past the row's end are clamped for the load (in bounds, branch-free) and zeroed.
     u32x4 v[kChunks];
-    // A workgroup per row: the gain is on its way with the row (loaded where it is used, behind the bounds check of its chunk, every
-    // chunk waits for an L2 round trip of its own).  A wave per row: many rows per CU cover that, and the registers it takes
-    // cost more (T = 4096, d = 4096, bf16: 12.8 -> 16 us).
+    // kAhead: the gain is on its way with the row (loaded where it is used, behind the bounds check of its chunk, every chunk waits
+    // for an L2 round trip of its own).  A wave per row: many rows per CU cover that, and the registers it takes cost more
+    // (T = 4096, d = 4096, bf16: 12.8 -> 16 us).  A workgroup per row: up to four chunks per thread always; eight and more (rows above 16 KiB)
+    // while the rows are at most one per CU, and where they are so many that memory is the bound, but not between, where the registers cost
+    // workgroups that would overlap (bf16, d = 16384, gain ahead / not, us: 4.3 / 5.1 at T = 1, 6.2 / 6.8 at 256, 12.0 / 9.1 at 700, 17.2 / 15.4 at 1150,
+    // 21.3 / 23.8 at 1500; fp32, d = 8192: 4.5 / 4.8, 5.7 / 6.0, 11.2 / 8.5, 16.7 / 13.2, 20.8 / 16.5, at T = 2600 32.4 / 33.5; d = 16384 4.3 / 6.3 at T = 1).
     constexpr int kG = Storage<DT>::kElems / 4;
-    constexpr bool kAhead = kGain && !kWavePerRow && kChunks * kG <= 16;
     f32x4 g[kAhead ? kChunks : 1][kG];
     auto load_gain = [&](int j, f32x4 (&dst)[kG]) {
 #pragma unroll

@@ -1563,10 +1563,12 @@ int tide_exit_project(const void* hidden, int dtype, int64_t C, int64_t T, int64
     p.eps = eps;
     const int64_t row_bytes = d * (int64_t)eb;
     bool wave_per_row = row_bytes <= (int64_t)kProjectMaxChunks * 16 * kWave;        // 16 KiB
-    if (wave_per_row && row_bytes >= 4096) {                                          // (project_kernel.hpp has the figures)
+    bool gain_ahead = true;
+    if (row_bytes >= 4096) {                                                          // (project_kernel.hpp has the figures of both choices)
         unsigned cus = 0;
         if ((rc = resident_cus(&cus))) return rc;
-        wave_per_row = T > 3 * (int64_t)cus;
+        gain_ahead = wave_per_row || T <= (int64_t)cus || T > (eb == 2 ? 5 : 8) * (int64_t)cus;
+        wave_per_row = wave_per_row && T > 3 * (int64_t)cus;
     }
     if (row_bytes > (int64_t)kProjectMaxChunks * 16 * kProjectThreads)
         return fail(TIDE_ERR_UNSUPPORTED, "rows of %lld bytes exceed the projection kernel's limit", (long long)row_bytes);
@@ -1576,8 +1578,14 @@ int tide_exit_project(const void* hidden, int dtype, int64_t C, int64_t T, int64
     by_dtype(dtype, [&](auto dt) {
         constexpr int DT = decltype(dt)::value;
         auto go = [&](auto wpr, auto gain, auto chunks) {
-            hipLaunchKernelGGL((tide_project_kernel<DT, decltype(wpr)::value, decltype(gain)::value, decltype(chunks)::value>),
-                               dim3(grid), dim3(kProjectThreads), 0, st, p);
+            constexpr bool kWpr = decltype(wpr)::value, kGain = decltype(gain)::value, kAhead = kGain && !kWpr;
+            constexpr int kChunks = decltype(chunks)::value;
+            if constexpr (kAhead && kChunks > 4)
+                if (!gain_ahead) {
+                    hipLaunchKernelGGL((tide_project_kernel<DT, kWpr, kGain, kChunks, false>), dim3(grid), dim3(kProjectThreads), 0, st, p);
+                    return;
+                }
+            hipLaunchKernelGGL((tide_project_kernel<DT, kWpr, kGain, kChunks, kAhead>), dim3(grid), dim3(kProjectThreads), 0, st, p);
         };
         auto pick_chunks = [&](auto wpr, auto gain) {
             if constexpr (!decltype(wpr)::value) {

@@ -1,5 +1,5 @@
 """GPU: the exit projection with a workgroup per row (at most three rows per CU, rows of 4 KiB and more) and with a wave per
-row, on both sides of either line, against the fp64 oracle."""
+row, on both sides of either line, and with the gain loaded ahead or not (rows above 16 KiB), against the fp64 oracle."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype,d,T,gain", [
     ("bf16", 2048, 768, True), ("bf16", 2048, 769, True), ("f16", 2040, 300, True), ("f16", 2056, 300, False),
-    ("f32", 1024, 768, True), ("f32", 1024, 770, True), ("bf16", 4104, 40, True), ("bf16", 8192, 31, True), ("f32", 4096, 800, False)])
+    ("f32", 1024, 768, True), ("f32", 1024, 770, True), ("bf16", 4104, 40, True), ("bf16", 8192, 31, True), ("f32", 4096, 800, False),
+    ("bf16", 8200, 256, True), ("bf16", 8200, 257, True), ("f16", 16384, 600, True), ("f32", 4100, 600, True), ("f32", 16384, 300, True)])
 def test_rows_per_workgroup(dtype, d, T, gain):
     import torch
     from paper_2603_21365_amd import tide_route as tr
