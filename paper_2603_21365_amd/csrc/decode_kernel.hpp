@@ -101,30 +101,52 @@ __device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int*
         float ssum = 0.0f;
 #pragma unroll
         for (int hf = 0; hf < kHalves; ++hf) a[hf] = f32x4{0, 0, 0, 0};
-        // kBatch partials in flight per thread: as few as cover its share (a surplus load is a round trip past every cache too)
-        auto add_slices = [&](auto batch_tag) {
+        // kBatch partials in flight per thread, from slice s0 on.  kExact: slices beyond the last are not loaded, else the last one is
+        // loaded again (branch-free).
+        auto add_batch = [&](int s0, auto batch_tag, auto exact_tag) {
             constexpr int kBatch = decltype(batch_tag)::value;
-            for (int s0 = s_begin; s0 < s_end; s0 += kBatch) {
-                f32x4 v[kHalves][kBatch];
+            constexpr bool kExact = decltype(exact_tag)::value;
+            f32x4 v[kHalves][kBatch];
 #pragma unroll
-                for (int hf = 0; hf < kHalves; ++hf)
+            for (int hf = 0; hf < kHalves; ++hf)
 #pragma unroll
-                    for (int u = 0; u < kBatch; ++u)
-                        v[hf][u] = stage_load4(pc + ((size_t)min(s0 + u, s_end - 1) * p.T + ts) * part_stride + hf * kBottleneck + 4 * q);
-                // lane q's slice of the batch
-                const float sv = stage_load(pc + ((size_t)min(s0 + min(q, kBatch - 1), s_end - 1) * p.T + ts) * part_stride + kHalves * kBottleneck);
+                for (int u = 0; u < kBatch; ++u) {
+                    const float* at = pc + ((size_t)(kExact ? s0 + u : min(s0 + u, s_end - 1)) * p.T + ts) * part_stride + hf * kBottleneck + 4 * q;
+                    if constexpr (kExact) v[hf][u] = f32x4{0, 0, 0, 0};
+                    if (!kExact || s0 + u < s_end) v[hf][u] = stage_load4(at);
+                }
+            // lane q's slice of the batch
+            const float sv = stage_load(pc + ((size_t)min(s0 + min(q, kBatch - 1), s_end - 1) * p.T + ts) * part_stride + kHalves * kBottleneck);
 #pragma unroll
-                for (int hf = 0; hf < kHalves; ++hf)
+            for (int hf = 0; hf < kHalves; ++hf)
 #pragma unroll
-                    for (int u = 0; u < kBatch; ++u) a[hf] += s0 + u < s_end ? v[hf][u] : f32x4{0, 0, 0, 0};
-                ssum += xor_reduce_sum<5>(q < kBatch && s0 + q < s_end ? sv : 0.0f);     // fixed order: deterministic
-            }
+                for (int u = 0; u < kBatch; ++u) a[hf] += s0 + u < s_end ? v[hf][u] : f32x4{0, 0, 0, 0};
+            ssum += xor_reduce_sum<5>(q < kBatch && s0 + q < s_end ? sv : 0.0f);     // fixed order: deterministic
         };
-        const int share = (p.S + kG - 1) / kG;
-        if (share <= 4) add_slices(std::integral_constant<int, 4>{});
-        else if (share <= 8) add_slices(std::integral_constant<int, 8>{});
-        else if (share <= 16 || kHalves == 2) add_slices(std::integral_constant<int, kHalves == 2 ? 8 : 16>{});   // (width 256: two workgroups per CU)
-        else add_slices(std::integral_constant<int, 32>{});
+        using std::integral_constant;
+        if constexpr (kG == 1) {
+            // Eight tokens per pass: a thread has all slices of its token.  As few loads as cover them, batch after batch, and none for a token
+            // that does not exist: a surplus load is a round trip past every cache too (us, all of 32 slices loaded against this: 57 / 47 at C = 12, T = 25,
+            // d = 4296, 34 slices; 15.0 / 14.1 at C = 16, T = 5, 19 slices).  (Width 256: two workgroups per CU, so smaller batches.)
+            constexpr int kMost = kHalves == 2 ? 8 : 32;
+            for (int s0 = s_begin; valid && s0 < s_end;) {
+                const int left = s_end - s0;
+                if (kMost == 32 && left > 16) { add_batch(s0, integral_constant<int, kMost>{}, std::true_type{}); s0 += 32; }
+                else if (kMost == 32 && left > 8) { add_batch(s0, integral_constant<int, kMost / 2>{}, std::false_type{}); s0 += 16; }
+                else if (left > 4) { add_batch(s0, integral_constant<int, 8>{}, std::false_type{}); s0 += 8; }
+                else { add_batch(s0, integral_constant<int, 4>{}, std::false_type{}); s0 += 4; }
+            }
+        } else {
+            // fewer tokens: as small a batch as covers the thread's share
+            auto add_slices = [&](auto batch_tag) {
+                for (int s0 = s_begin; s0 < s_end; s0 += decltype(batch_tag)::value) add_batch(s0, batch_tag, std::false_type{});
+            };
+            const int share = (p.S + kG - 1) / kG;
+            if (share <= 4) add_slices(integral_constant<int, 4>{});
+            else if (share <= 8) add_slices(integral_constant<int, 8>{});
+            else if (share <= 16 || kHalves == 2) add_slices(integral_constant<int, kHalves == 2 ? 8 : 16>{});
+            else add_slices(integral_constant<int, 32>{});
+        }
         if constexpr (kG > 1) {
 #pragma unroll
             for (int hf = 0; hf < kHalves; ++hf) shares[((hf * kG + g) * kTB + tl) * 32 + q] = a[hf];

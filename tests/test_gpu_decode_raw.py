@@ -1,5 +1,5 @@
 """GPU parity of the raw-weight latency kernel at the edges of its token counts (1, 2, 4 and 8 tokens per pass, several passes),
-its slices (one, fewer than a finishing thread's batch, more than 32) and its widths, against the fp64 oracle."""
+its slices (one, fewer than a finishing thread's batch, more than 32, every size of the last batch) and its widths, against the fp64 oracle."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("C,dtype,T,d,b", [
     (8, "f16", 1, 4096, 128), (8, "bf16", 2, 2048, 64), (5, "f32", 3, 4096, 128), (8, "f16", 4, 8192, 256), (32, "bf16", 5, 1024, 128),
     (3, "f32", 8, 16384, 64), (2, "bf16", 1, 16384, 256), (1, "f16", 9, 72, 128), (4, "f32", 32, 1004, 128), (7, "bf16", 17, 4104, 64),
-    (2, "f32", 4, 12, 128), (6, "f16", 7, 128, 256)])
+    (2, "f32", 4, 12, 128), (6, "f16", 7, 128, 256),
+    (16, "bf16", 5, 2344, 128), (4, "f16", 25, 4296, 64), (2, "f32", 6, 5320, 128), (3, "bf16", 8, 648, 128), (2, "f16", 5, 1024, 256)])
 def test_raw_weights_few_rows(C, dtype, T, d, b):
     import torch
     from paper_2603_21365_amd import tide_route as tr
