@@ -970,7 +970,9 @@ int launch_decode(const Scratch& sc, const void* hidden, int dtype, int64_t C, i
 // d = 4096, C = 1 / 8, fp16: 9.5 / 10.6 us against 10.8 / 13.9 us at T = 1, 13.5 / 15.9 us at T = 8
 // and 40 us at T = 32; fp32 rows: 13.3 / 14.7 us against 11.3 / 14.4 us at T = 1 and 13.6 / 16.4 us at
 // T = 8).  With raw weights that form needs the packing pass first (7.5 us at C = 8), so the latency
-// kernel, which reads W1 as it is, keeps T <= 8 (10-12.4 us at T = 1-4, against 14 us at T = 40); it also keeps, up to
+// kernel, which reads W1 as it is, keeps T <= 8 (fp16, C = 8, d = 4096: 9.1 / 10.7 / 12.2 / 13.2 us at T = 1 / 4 / 5 / 8, against the packing pass and
+// the few-rows kernel's 13.0 at T = 12: level at the line, but the latency kernel multiplies the fp32 weights, not their 16-bit
+// rounding, so a call does not lose those bits below it); it also keeps, up to
 // T = 32, what the split-k form does not cover (hidden sizes that are not multiples of 128).  Calls that would pack or have
 // packed weights go to the few-rows kernel instead where use_few_rows says so.
 bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, int variant, int form_word) {
@@ -983,10 +985,17 @@ bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, i
 }
 
 // The few-rows kernel (a workgroup per 16 rows and 16 columns, all of k) or the paths above?  It is the faster one as long
-// as its workgroups fit the chip once, whatever the hidden size (256 CUs, packed weights, against the split-k forms, us:
-// C = 8, d = 4096: 8.7 -> 6.3 at T = 1, 9.5 -> 7.3 at 16, 11.3 -> 8.5 at 48, 11.3 -> 9.2 at 64 = 256 workgroups; d = 16384, T = 32:
-// 18.3 -> 17.2) and, with rows of up to 8 KiB, up to one and a half workgroups per CU (two are resident): 11.8 -> 11.4 at
+// as its workgroups fit the chip once (256 CUs, packed weights, against the split-k forms, us:
+// C = 8, d = 4096: 8.7 -> 6.3 at T = 1, 9.5 -> 7.3 at 16, 11.3 -> 8.5 at 48, 11.3 -> 9.2 at 64 = 256 workgroups; fp32 rows, d = 5120, C = 8, T = 64:
+// 15.7 -> 15.1) and, with rows of up to 8 KiB, up to one and a half workgroups per CU (two are resident): 11.8 -> 11.4 at
 // T = 96, 11.6 -> 11.4 at C = 1, T = 768, level from there on; longer rows lose there (d = 8192, C = 10, T = 96: 15.8 -> 18.1).
+// Rows above 20 KiB pass through one workgroup's LDS for longer than split-k takes unless the rows of a tile or the workgroups are few:
+//   up to 8 rows always (fp32, d = 8192, C = 8: 17.0 -> 16.1; bf16, d = 16384, C = 1 / 8: 12.5 -> 12.3, 14.6 / 14.8);
+//   9 to 16 rows meet the one-launch split-k form at widths 64 / 128 (bf16 at T = 12 / 16: d = 12288 11.8 -> 11.4, but 11.7 / 12.5, d = 16384 13.2 / 13.9, 13.2 / 15.4;
+//   fp32: d = 6144 14.8 -> 13.0, 14.7 -> 14.1; d = 8192 17.2 -> 16.1, but 17.1 / 17.4 and 17.8 / 18.9 at C = 8), not at 256 (fp32, d = 8192, C = 8: 21.1 -> 20.6);
+//   more rows: at 24 KiB up to three quarters of the CUs (fp32, C = 4: 16.7 -> 16.6 at T = 96, but 16.8 / 17.2 at 128; width 256 half: 17.4 -> 17.0 at C = 2, T = 64,
+//   but 17.9 / 18.1 at 128), at 28 KiB a quarter (17.1 -> 16.8 at C = 1, T = 128, but 18.0 / 18.4 at C = 4, T = 96), at 32 KiB three sixteenths (18.1 -> 17.6 at C = 2,
+//   T = 32, but 18.2 / 18.9 at 64 and 19.5 / 21.4 at C = 8).
 // Rows of 64 KiB (fp32, d = 16384) are level at best.  Every workgroup of a row tile ticks the tile's counter (14 ns each): from 256 of
 // them on that costs what the kernel gains (C = 32, width 128: 12.2 -> 12.6; C = 20: 10.2 -> 9.1).
 // Hidden sizes that are no multiple of 128 go to the register-ring kernel otherwise (18.9 -> 9.3 us at C = 8, T = 100, d = 1600):
@@ -994,9 +1003,13 @@ bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, i
 bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus) {
     const int64_t tiles = (T + kFewRows - 1) / kFewRows, nbk = b / kFewCols, row_bytes = d * (int64_t)elem_bytes(dtype);
     if (tiles > kFewMaxTiles || C * nbk >= 256 || row_bytes > 32768) return false;
-    const int64_t W = C * tiles * nbk;
-    if (d % 128 != 0) return W <= 2 * (int64_t)cus;
-    return W <= (int64_t)cus || (row_bytes <= 8192 && 2 * W <= 3 * (int64_t)cus);
+    const int64_t W = C * tiles * nbk, n = (int64_t)cus;
+    if (d % 128 != 0) return W <= 2 * n;
+    if (row_bytes <= 20480) return W <= n || (row_bytes <= 8192 && 2 * W <= 3 * n);
+    if (T <= 8 || (T <= kFewRows && b == 256)) return W <= n;
+    if (T <= kFewRows) return W <= n && (dtype == TIDE_F32 ? T <= 12 || row_bytes <= 24576 : T <= 12 && row_bytes <= 24576);
+    if (row_bytes <= 24576) return b == 256 ? 2 * W <= n : 4 * W <= 3 * n;
+    return row_bytes <= 28672 ? 4 * W <= n : 16 * W <= 3 * n;
 }
 
 // ---- What a router call needs of scratch memory, and which path it takes: host arithmetic only.

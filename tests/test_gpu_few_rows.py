@@ -24,7 +24,8 @@ def tr():
     (1, "f16", 1, 4096, 128), (8, "bf16", 17, 4096, 128), (3, "f32", 16, 768, 128), (8, "f32", 5, 4096, 128),
     (5, "bf16", 33, 1608, 128), (2, "f16", 15, 72, 64), (7, "bf16", 40, 2056, 64), (3, "f32", 20, 100, 128),
     (4, "bf16", 9, 4096, 256), (15, "f16", 7, 1024, 256), (31, "f16", 3, 256, 128), (1, "bf16", 1024, 256, 64),
-    (1, "f16", 1009, 384, 64), (3, "bf16", 8, 16384, 128), (2, "bf16", 50, 1001, 128), (2, "f16", 30, 200, 256)])
+    (1, "f16", 1009, 384, 64), (3, "bf16", 8, 16384, 128), (2, "bf16", 50, 1001, 128), (2, "f16", 30, 200, 256),
+    (2, "f32", 8, 8192, 128), (2, "f32", 9, 8192, 256), (1, "bf16", 24, 16384, 128), (2, "f16", 12, 12288, 64)])
 def test_few_rows(tr, C, dtype, T, d, b):
     import torch
     w = synth.Workload(f"few_{dtype}_C{C}_T{T}_d{d}_b{b}", 71, dtype, d, 4 * C, 4, T, None, b=b)
