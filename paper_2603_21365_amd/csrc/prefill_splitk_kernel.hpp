@@ -71,8 +71,8 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
     // second launch, cut the same way, finds them in that XCD's L2 (dealt out round-robin, the slices of a tile were on eight XCDs;
     // us per call: 17.0 -> 15.3 at C = 8, T = 322, d = 4096, 16.9 -> 15.5 at C = 1, T = 3000, 18.8 -> 17.2 at 4096; width 256, C = 8, T = 200 18.8 -> 15.5)
     const int items = p.total_tiles * halves * S, per_xcd = (items + 7) >> 3;
-    const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (item >= items || (int)(blockIdx.x >> 3) >= per_xcd) return;
+    const int item = kFused ? (int)blockIdx.x : (int)((blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
+    if (item >= items || (!kFused && (int)(blockIdx.x >> 3) >= per_xcd)) return;
     const int th = item / S, slice = item - th * S;
     const int tile = th / halves, half = th - tile * halves;
     const int ntile = p.dpad * Storage<DT>::kBytes / kTileBytes;
