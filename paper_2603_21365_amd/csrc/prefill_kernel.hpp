@@ -51,6 +51,7 @@ struct PrefillParams {
     uint64_t* arrive;          // [T] arrival words (see report_and_select), zero on entry and on exit
     // split-k form only (prefill_splitk_kernel.hpp)
     int k_slices;              // workgroups that share a tile's k range
+    int deal_out;              // the pair: its workgroups in launch order, slice s on XCD s mod 8 (else a tile's slices on one XCD)
     float* zpart;              // [total_tiles][k_slices][rows per tile * 128] partial accumulators
     float* sspart;             // [total_tiles][k_slices][4 waves][rows per tile] partial sums of squares
     uint32_t* counters;        // single-launch split-k form: one arrival counter per tile (state words: zero between calls)

@@ -40,7 +40,7 @@ template <int kBlocks> constexpr int splitk_lds_bytes() { return kDmaStages * kB
 // contiguous, and a lane of the second launch reads back the registers of its own position.
 template <int kBlocks> constexpr int splitk_part_floats() { return kBlocks * 32 * kBottleneck; }
 
-// First launch: item = (tile * halves + half) * p.k_slices + slice (XCD-contiguous, below); tiles of kBlocks*32 rows,
+// First launch: item = (tile * halves + half) * p.k_slices + slice (XCD-contiguous or dealt out, below); tiles of kBlocks*32 rows,
 // checkpoint-major (p.tiles_per_ckpt per checkpoint); half = which 128 columns of the bottleneck
 // (halves = 2 at width 256, else 1); slice s covers k-tiles [s*n/S, (s+1)*n/S) of the n = dpad/128
 // k-tiles of a row (S <= n, so every slice has at least one).
@@ -69,10 +69,13 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
     const int halves = (p.b + kBottleneck - 1) / kBottleneck;
     // XCD x (workgroup id mod 8) takes the x-th eighth of the tile-major list: a tile's partial results come from one XCD, and the
     // second launch, cut the same way, finds them in that XCD's L2 (dealt out round-robin, the slices of a tile were on eight XCDs;
-    // us per call: 17.0 -> 15.3 at C = 8, T = 322, d = 4096, 16.9 -> 15.5 at C = 1, T = 3000, 18.8 -> 17.2 at 4096; width 256, C = 8, T = 200 18.8 -> 15.5)
+    // us per call: 17.0 -> 15.3 at C = 8, T = 322, d = 4096, 16.9 -> 15.5 at C = 1, T = 3000, 18.8 -> 17.2 at 4096; width 256, C = 8, T = 200 18.8 -> 15.5).
+    // Every XCD then reads the whole W1' of its tiles: few tiles of long rows are dealt out instead (p.deal_out, see deals_out in tide_route.hip),
+    // and so is the one-launch form, which hands over past every cache (C = 4, T = 16, bf16: 13.0 -> 12.3 at d = 12288, 15.5 -> 13.7 at 16384).
     const int items = p.total_tiles * halves * S, per_xcd = (items + 7) >> 3;
-    const int item = kFused ? (int)blockIdx.x : (int)((blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
-    if (item >= items || (!kFused && (int)(blockIdx.x >> 3) >= per_xcd)) return;
+    const bool dealt = kFused || p.deal_out;
+    const int item = dealt ? (int)blockIdx.x : (int)((blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
+    if (item >= items || (!dealt && (int)(blockIdx.x >> 3) >= per_xcd)) return;
     const int th = item / S, slice = item - th * S;
     const int tile = th / halves, half = th - tile * halves;
     const int ntile = p.dpad * Storage<DT>::kBytes / kTileBytes;
@@ -349,8 +352,8 @@ __global__ __launch_bounds__(kFinishThreads * kHalves) void tide_splitk_finish_k
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = wave >> 2, w = wave & 3;
     const int groups = p.total_tiles * kBlocks * (4 / kQ), per_xcd = (groups + 7) >> 3;
-    const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);           // (see the first launch)
-    if (item >= groups || (int)(blockIdx.x >> 3) >= per_xcd) return;
+    const int item = p.deal_out ? (int)blockIdx.x : (int)((blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));           // (see the first launch)
+    if (item >= groups || (!p.deal_out && (int)(blockIdx.x >> 3) >= per_xcd)) return;
     const int quad = (item % (4 / kQ)) * kQ, tb = item / (4 / kQ);
     const int tile = tb / kBlocks, blk = tb - tile * kBlocks;
     const int c = tile / p.tiles_per_ckpt;

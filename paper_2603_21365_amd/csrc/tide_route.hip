@@ -996,15 +996,18 @@ bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, i
 //   more rows: at 24 KiB up to three quarters of the CUs (fp32, C = 4: 16.7 -> 16.6 at T = 96, but 16.8 / 17.2 at 128; width 256 half: 17.4 -> 17.0 at C = 2, T = 64,
 //   but 17.9 / 18.1 at 128), at 28 KiB a quarter (17.1 -> 16.8 at C = 1, T = 128, but 18.0 / 18.4 at C = 4, T = 96), at 32 KiB three sixteenths (18.1 -> 17.6 at C = 2,
 //   T = 32, but 18.2 / 18.9 at 64 and 19.5 / 21.4 at C = 8).
+// Weights that this call packed come from memory, and 40 workgroups ask for them more slowly than split-k's 256: one or two checkpoints' of 4 MiB
+// and more go to the pair (fp32, d = 8192, C = 1, T = 40: 22.2 / 24.1 us; bf16, width 256: 16.5 / 17.3).
 // Rows of 64 KiB (fp32, d = 16384) are level at best.  Every workgroup of a row tile ticks the tile's counter (14 ns each): from 256 of
 // them on that costs what the kernel gains (C = 32, width 128: 12.2 -> 12.6; C = 20: 10.2 -> 9.1).
 // Hidden sizes that are no multiple of 128 go to the register-ring kernel otherwise (18.9 -> 9.3 us at C = 8, T = 100, d = 1600):
 // there up to two workgroups per CU.
-bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus) {
+bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool raw_weights, unsigned cus) {
     const int64_t tiles = (T + kFewRows - 1) / kFewRows, nbk = b / kFewCols, row_bytes = d * (int64_t)elem_bytes(dtype);
     if (tiles > kFewMaxTiles || C * nbk >= 256 || row_bytes > 32768) return false;
     const int64_t W = C * tiles * nbk, n = (int64_t)cus;
     if (d % 128 != 0) return W <= 2 * n;
+    if (raw_weights && d >= 8192 && C * b <= 256 && T > kFewRows && d * b * (int64_t)elem_bytes(dtype) >= 4 << 20) return false;
     if (row_bytes <= 20480) return W <= n || (row_bytes <= 8192 && 2 * W <= 3 * n);
     if (T <= 8 || (T <= kFewRows && b == 256)) return W <= n;
     if (T <= kFewRows) return W <= n && (dtype == TIDE_F32 ? T <= 12 || row_bytes <= 24576 : T <= 12 && row_bytes <= 24576);
@@ -1047,7 +1050,7 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
     // the weight, the few-rows kernel the row's two leading bf16 terms (error against 64 bits at T = 32, d = 1000: 2.6e-6 against 4.7e-6).
     // 16-bit rows are exact in either.
     n.few = allow_few && !(n.decode && (raw_weights || dtype == TIDE_F32)) && variant == TIDE_VARIANT_AUTO && form_word == 0 &&
-            use_few_rows(dtype, C, T, n.d_run, b, cus);
+            use_few_rows(dtype, C, T, n.d_run, b, raw_weights, cus);
     const size_t few_bytes = n.few ? round256((size_t)T * (size_t)C * (size_t)(b / kFewCols) * sizeof(float)) : 0;
     if (n.decode) {
         n.leaves_data = true;
@@ -1077,6 +1080,19 @@ size_t largest_part(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool 
     at(std::min<int64_t>(T, kDecodeRawMaxT));
     for (int64_t t = 32; t < T && C * halves_of(b) * (t / 32) <= 4 * kSplitkMaxTiles; t += 32) at(t);
     return most;
+}
+
+// The split-k pair: the slices of a tile dealt out over the XCDs instead of kept on one?  Kept together, every XCD reads the whole W1' of
+// its tiles; dealt out, an eighth of it, but the second launch finds the partial results in other XCDs' L2s.  The first is the dearer one where
+// the W1' of a checkpoint fills an XCD's 4 MiB L2 and the tiles are few, more so where this call packed the weights, which then come from
+// memory.  Measured (us, dealt out / together; R = 32-row blocks x column halves of the call): raw weights, C = 1, 4 MiB and more: fp32, d = 8192 21.1 / 24.6
+// at T = 200, 23.9 / 26.2 at 1000 (R = 32), bf16, d = 16384 19.9 / 23.3 at T = 100; packed, width 256, C = 1: bf16, d = 16384 16.2 / 18.4 at T = 200 (R = 14), d = 8192 13.4 / 14.1
+// at T = 455 (30), but 18.0 / 16.4 at 1000 (64); from 8 MiB on with more checkpoints too: bf16, d = 16384, width 256, C = 4 22.1 / 23.5 at T = 200 (56), but 40.3 / 35.4
+// at 455 (120).  With 2 MiB and less the first is the faster one throughout (C = 8, T = 322, d = 4096: 17.0 / 15.3).
+bool deals_out(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool raw_weights) {
+    const int64_t w1 = (int64_t)tide_packed_router_bytes(dtype, d, b), R = C * ((T + 31) / 32) * halves_of(b);
+    if (w1 >= 8 << 20 && R <= 56) return true;
+    return w1 >= 4 << 20 && C == 1 && R <= (raw_weights ? 32 : 30);
 }
 
 // Zero-fill for state words (a kernel, not a memset: calls may be captured into HIP graphs).
@@ -1259,8 +1275,10 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
             packed = sc.packed;
         }
         auto params = [&]() {
-            return prefill_params(sc, hidden, dtype, C, T, need.d_run, d, b, ckpt_stride, row_stride, packed, eps, b1, w2, tab, min_layer,
-                                  no_exit, o);
+            PrefillParams p = prefill_params(sc, hidden, dtype, C, T, need.d_run, d, b, ckpt_stride, row_stride, packed, eps, b1, w2, tab, min_layer,
+                                             no_exit, o);
+            p.deal_out = deals_out(dtype, C, T, d, b, W1 != nullptr);
+            return p;
         };
         if (!rc)
             rc = need.few ? launch_few_rows(sc, params(), dtype, st) : launch_prefill(sc, need.plan, params(), dtype, st);

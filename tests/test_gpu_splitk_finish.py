@@ -1,5 +1,6 @@
 """GPU parity of the split-k pair's second launch at the edges of its row groups (8 or 16 rows per workgroup), against the fp64
-oracle: row counts one below, at and one above a group's and a block's end, both group sizes, both widths of workgroup."""
+oracle: row counts one below, at and one above a group's and a block's end, both group sizes, both widths of workgroup, and with the
+slices of a tile on one XCD or (few tiles of 4 MiB and more of weights) dealt out over them."""
 import numpy as np
 import pytest
 
@@ -11,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("C,dtype,T,d,b,rows,slices", [
     (1, "bf16", 7, 512, 128, 32, 2), (2, "f16", 9, 512, 128, 32, 4), (1, "f32", 33, 512, 128, 64, 8), (3, "bf16", 41, 1408, 256, 64, 8),
-    (1, "f16", 1025, 512, 64, 128, 4), (1, "bf16", 3079, 512, 128, 64, 2), (1, "f32", 4095, 256, 128, 32, 2), (2, "bf16", 1801, 512, 256, 32, 2)])
+    (1, "f16", 1025, 512, 64, 128, 4), (1, "bf16", 3079, 512, 128, 64, 2), (1, "f32", 4095, 256, 128, 32, 2), (2, "bf16", 1801, 512, 256, 32, 2),
+    (1, "bf16", 455, 16384, 256, 32, 8), (1, "f32", 70, 8192, 128, 64, 4), (2, "f32", 33, 16384, 256, 32, 8)])
 def test_row_groups_of_the_second_launch(C, dtype, T, d, b, rows, slices):
     import torch
     from paper_2603_21365_amd import tide_route as tr
