@@ -321,14 +321,18 @@ int tide_prefill_plan(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int
 int tide_stream_schedule(int rows_per_tile, int64_t b, int64_t k_tiles, int grid, int block, int tile_begin,
                          int total_tiles, int32_t* out, int max_items);
 
-/* The band kernel's schedule, for tests (host arithmetic, no GPU needed; the very code the kernel
- * runs where its bands run across checkpoints; a batch whose checkpoints do not divide the workgroups may instead give each
- * checkpoint equal workgroups of its own): the tiles of workgroup `block` of a launch of `grid` workgroups (a multiple of 8) over C
+/* The band kernel's schedule, for tests (host arithmetic, no GPU needed; the very code the launch and the kernel
+ * run, which gives each checkpoint equal workgroups of its own where bands across checkpoints would leave the slowest workgroup
+ * clearly more): the tiles of workgroup `block` of a launch of `grid` workgroups (a multiple of 8) over C
  * checkpoints of blocks_per_ckpt = ceil(T / 32) blocks of 32 rows each (a tide_prefill_plan launch of
  * kernel 8).  out: HOST int32 [max_items][3] = {checkpoint, first block within the checkpoint,
  * blocks}; a tile has 1 to 9 blocks and lies within one checkpoint.  Returns the number of tiles
  * (only the first max_items are written) or a negative tide_status_t.                          */
 int tide_band_schedule(int64_t C, int64_t blocks_per_ckpt, int grid, int block, int32_t* out, int max_items);
+
+/* The same for the band kernel for fp32 rows (kernel 11; grid at least C): every checkpoint has grid / C workgroups, a tile
+ * 1 to 4 blocks where no workgroup's share is larger, else 1 to 8.                             */
+int tide_band_f32_schedule(int64_t C, int64_t blocks_per_ckpt, int grid, int block, int32_t* out, int max_items);
 
 /* Free the current device's workspace (synchronises that device).                       */
 int tide_release(void);

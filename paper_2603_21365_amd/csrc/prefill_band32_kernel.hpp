@@ -40,6 +40,12 @@ struct Band32Walk {
     __host__ __device__ void advance() { cur += current().blocks; }
 };
 
+// Blocks per tile at most: 4, with two waves to a block, while every workgroup's share is that much at most, else 8.
+inline int band32_max_blocks(int C, int U, int grid) {
+    const int per_ckpt = grid / C;
+    return (U + per_ckpt - 1) / per_ckpt <= 4 ? 4 : 8;
+}
+
 template <int kMaxBlocks> constexpr int band32_stages() { return kMaxBlocks == 4 ? 4 : 3; }
 template <int kMaxBlocks> constexpr int band32_lds_bytes() {
     // rings, then per-wave 1/rms (8 blocks) or the exchange area of the two k halves (4 blocks)

@@ -849,8 +849,7 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
                 break;
             case kKernelBandF32:
                 if constexpr (DT == kF32) {
-                    const int per_ckpt = (int)L.grid / p.C;
-                    rc = (L.tiles_per_ckpt + per_ckpt - 1) / per_ckpt <= 4 ? launch_band_f32<R, 4>(L.grid, st, p) : launch_band_f32<R, 8>(L.grid, st, p);
+                    rc = band32_max_blocks(p.C, L.tiles_per_ckpt, (int)L.grid) == 4 ? launch_band_f32<R, 4>(L.grid, st, p) : launch_band_f32<R, 8>(L.grid, st, p);
                 } else {
                     rc = no_form();
                 }
@@ -1294,7 +1293,7 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
 
 extern "C" {
 
-int tide_version(void) { return 111; }
+int tide_version(void) { return 112; }
 
 const char* tide_last_error(void) { return g_err; }
 
@@ -1831,11 +1830,29 @@ int tide_band_schedule(int64_t C, int64_t blocks_per_ckpt, int grid, int block, 
     if (grid < 8 || grid % 8 != 0 || block < 0 || block >= grid) return fail(TIDE_ERR_INVALID_ARG, "grid = %d (a multiple of 8), block = %d", grid, block);
     if (!out || max_items < 0) return fail(TIDE_ERR_INVALID_ARG, "out / max_items");
     int n = 0;
-    for (BandWalk w(block, grid, (int)C, (int)blocks_per_ckpt); w.valid(); w.advance()) {
+    for (BandWalk w(block, grid, (int)C, (int)blocks_per_ckpt, band_per_ckpt(C, blocks_per_ckpt, grid)); w.valid(); w.advance()) {
         const BandTile t = w.current();
         if (n < max_items) { out[3 * n] = t.c; out[3 * n + 1] = t.block0; out[3 * n + 2] = t.blocks; }
         ++n;
     }
+    return n;
+}
+
+int tide_band_f32_schedule(int64_t C, int64_t blocks_per_ckpt, int grid, int block, int32_t* out, int max_items) {
+    if (C < 1 || C > TIDE_MAX_CHECKPOINTS || blocks_per_ckpt < 1 || C * blocks_per_ckpt > (int64_t)1 << 30)
+        return fail(TIDE_ERR_INVALID_ARG, "C = %lld, blocks_per_ckpt = %lld out of range", (long long)C, (long long)blocks_per_ckpt);
+    if (grid < C || grid % 8 != 0 || block < 0 || block >= grid) return fail(TIDE_ERR_INVALID_ARG, "grid = %d (a multiple of 8, at least C), block = %d", grid, block);
+    if (!out || max_items < 0) return fail(TIDE_ERR_INVALID_ARG, "out / max_items");
+    int n = 0;
+    auto emit = [&](auto walk) {
+        for (; walk.valid(); walk.advance()) {
+            const BandTile t = walk.current();
+            if (n < max_items) { out[3 * n] = t.c; out[3 * n + 1] = t.block0; out[3 * n + 2] = t.blocks; }
+            ++n;
+        }
+    };
+    if (band32_max_blocks((int)C, (int)blocks_per_ckpt, grid) == 4) emit(Band32Walk<4>(block, grid, (int)C, (int)blocks_per_ckpt));
+    else emit(Band32Walk<8>(block, grid, (int)C, (int)blocks_per_ckpt));
     return n;
 }
 

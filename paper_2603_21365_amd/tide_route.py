@@ -25,7 +25,7 @@ DTYPE_CODES = {"f32": F32, "f16": F16, "bf16": BF16}
 EXPORTS = (
     "tide_version", "tide_last_error", "tide_router_eval", "tide_select_exit",
     "tide_packed_router_bytes", "tide_router_pack", "tide_router_eval_packed",
-    "tide_select_exit_packed", "tide_exit_project", "tide_batch_exit", "tide_cosine_labels", "tide_batch_compact", "tide_set_variant", "tide_set_prefill_form", "tide_prefill_plan", "tide_stream_schedule", "tide_band_schedule", "tide_release",
+    "tide_select_exit_packed", "tide_exit_project", "tide_batch_exit", "tide_cosine_labels", "tide_batch_compact", "tide_set_variant", "tide_set_prefill_form", "tide_prefill_plan", "tide_stream_schedule", "tide_band_schedule", "tide_band_f32_schedule", "tide_release",
     "tide_workspace_bytes", "tide_workspace_init", "tide_workspace_forget", "tide_router_eval_ws", "tide_select_exit_ws",
     "tide_select_exit_packed_noalloc", "tide_noalloc_scratch_bytes", "tide_workspace_allocations", "tide_mfma_probe",
 )
@@ -80,6 +80,7 @@ def load_library() -> ctypes.CDLL:
     lib.tide_prefill_plan.argtypes = [ci, i64, i64, i64, i64, ci, ci, vp]
     lib.tide_stream_schedule.argtypes = [ci, i64, i64, ci, ci, ci, ci, vp, ci]
     lib.tide_band_schedule.argtypes = [i64, i64, ci, ci, vp, ci]
+    lib.tide_band_f32_schedule.argtypes = lib.tide_band_schedule.argtypes
     lib.tide_mfma_probe.argtypes = [ci, ci, ci, ci, vp]
     lib.tide_mfma_probe.restype = ci
     for name in ("tide_router_eval", "tide_router_eval_packed", "tide_select_exit", "tide_select_exit_packed",
@@ -164,17 +165,26 @@ def set_prefill_form(form: int) -> int:
     return prev
 
 
-def band_schedule(C: int, blocks_per_ckpt: int, grid: int, block: int) -> list:
-    """Tiles (checkpoint, first 32-row block, blocks) of one workgroup of a band-kernel launch (host arithmetic)."""
+def _band_tiles(fn, C, blocks_per_ckpt, grid, block):
     cap = 64
     while True:
         out = (ctypes.c_int32 * (3 * cap))()
-        n = load_library().tide_band_schedule(int(C), int(blocks_per_ckpt), int(grid), int(block), out, cap)
+        n = fn(int(C), int(blocks_per_ckpt), int(grid), int(block), out, cap)
         if n < 0:
             _check(n)
         if n <= cap:
             return [tuple(out[3 * i:3 * i + 3]) for i in range(n)]
         cap = n
+
+
+def band_schedule(C: int, blocks_per_ckpt: int, grid: int, block: int) -> list:
+    """Tiles (checkpoint, first 32-row block, blocks) of one workgroup of a band-kernel launch (host arithmetic)."""
+    return _band_tiles(load_library().tide_band_schedule, C, blocks_per_ckpt, grid, block)
+
+
+def band_f32_schedule(C: int, blocks_per_ckpt: int, grid: int, block: int) -> list:
+    """The same for the band kernel for fp32 rows."""
+    return _band_tiles(load_library().tide_band_f32_schedule, C, blocks_per_ckpt, grid, block)
 
 
 def mfma_probe(waves_per_cu: int = 4, iters: int = 512, launches: int = 20, zero_operands: bool = False) -> dict:

@@ -158,40 +158,50 @@ def test_the_persistent_schedule_covers_every_tile_once():
     assert checked > 60
 
 
-def check_band_schedule(C, U, grid):
-    """Every 32-row block of every checkpoint lies in exactly one tile of exactly one workgroup; a tile has 1 to 9
-    blocks of one checkpoint; the workgroups' shares differ by at most one block; XCD x (workgroup id mod 8) owns
-    a contiguous eighth of the list."""
+def check_band_schedule(schedule, C, U, grid, most):
+    """Every 32-row block of every checkpoint lies in exactly one tile of exactly one workgroup; a tile has 1 to `most`
+    blocks of one checkpoint; XCD x (workgroup id mod 8) owns a contiguous eighth of the list.  The workgroups' shares differ by
+    at most one block -- of the whole list (bands across checkpoints), or within every checkpoint, which then has grid / C
+    workgroups of its own.  Returns whether each checkpoint has its own."""
     seen = np.zeros((C, U), np.uint8)
     share = []
     first = {}
+    ckpts = {}
     for block in range(grid):
-        tiles = tr.band_schedule(C, U, grid, block)
+        tiles = schedule(C, U, grid, block)
         n = 0
         pos = None
         for c, b0, nb in tiles:
-            assert 0 <= c < C and 1 <= nb <= 9 and 0 <= b0 and b0 + nb <= U, (C, U, grid, block, tiles)
+            assert 0 <= c < C and 1 <= nb <= most and 0 <= b0 and b0 + nb <= U, (C, U, grid, block, tiles)
             assert pos is None or pos == c * U + b0, "a workgroup's tiles are contiguous in the checkpoint-major list"
             pos = c * U + b0 + nb
             seen[c, b0:b0 + nb] += 1
             n += nb
-        # as few tiles as cover each piece of the band: a piece of L blocks within one checkpoint takes ceil(L / 9)
+        # as few tiles as cover each piece of the band: a piece of L blocks within one checkpoint takes ceil(L / most)
         pieces = {}
         for c, b0, nb in tiles:
             pieces.setdefault(c, []).append(nb)
         for c, sizes in pieces.items():
-            assert len(sizes) == -(-sum(sizes) // 9) and max(sizes) - min(sizes) <= 1, (C, U, grid, block, tiles)
+            assert len(sizes) == -(-sum(sizes) // most) and max(sizes) - min(sizes) <= 1, (C, U, grid, block, tiles)
         share.append(n)
         if tiles:
             first[block] = tiles[0][0] * U + tiles[0][1]
+            ckpts[block] = set(pieces)
     assert seen.min() == 1 and seen.max() == 1, (C, U, grid)
-    assert max(share) - min(share) <= 1, (C, U, grid, share)
+    own = max(share) - min(share) > 1
+    if own:
+        per = grid // C
+        for c in range(C):
+            mine = [share[block] for block in ckpts if ckpts[block] == {c}]
+            mine += [0] * (per - len(mine))                      # (fewer blocks than workgroups: some of them idle)
+            assert len(mine) == per and max(mine) - min(mine) <= 1 and sum(mine) == U, (C, U, grid, c, mine)
     for x in range(8):                      # XCD x: workgroups x, x + 8, ... take ascending, adjacent bands
         starts = [first[b] for b in range(x, grid, 8) if b in first]
         assert starts == sorted(starts)
         if x and starts:
             prev = [first[b] for b in range(x - 1, grid, 8) if b in first]
             assert not prev or max(prev) < min(starts)
+    return own
 
 
 def test_the_band_schedule_covers_every_block_once():
@@ -199,11 +209,27 @@ def test_the_band_schedule_covers_every_block_once():
     cases = [(9, 512, 256), (10, 512, 256), (8, 128, 256), (1, 1, 8), (1, 7, 256), (3, 1000, 304), (32, 17, 64), (2, 5000, 8)]
     for _ in range(200):
         cases.append((int(rng.integers(1, 33)), int(rng.choice([rng.integers(1, 40), rng.integers(1, 2000)])), int(rng.choice([8, 64, 256, 304]))))
-    for C, U, grid in cases:
-        check_band_schedule(C, U, grid)
+    owns = [check_band_schedule(tr.band_schedule, C, U, grid, 9) for C, U, grid in cases]
+    assert 5 <= sum(owns) <= len(owns) - 50
     # the 36-layer batched prefill on 256 CUs: 18 blocks per workgroup, two tiles of 9 unless a checkpoint ends inside the band
     counts = [len(tr.band_schedule(9, 512, 256, block)) for block in range(256)]
     assert sorted(set(counts)) == [2, 3] and counts.count(3) == 8
+    # C = 12, T = 4000 and C = 7, T = 5000: a band that a checkpoint's end cuts would take a tile more, so each checkpoint has its own workgroups
+    assert check_band_schedule(tr.band_schedule, 12, 125, 256, 9) and check_band_schedule(tr.band_schedule, 7, 157, 256, 9)
+    # more blocks per workgroup (C = 6, T = 16384) and checkpoints that divide the workgroups: across
+    assert not check_band_schedule(tr.band_schedule, 6, 512, 256, 9) and not check_band_schedule(tr.band_schedule, 8, 160, 256, 9)
+
+
+def test_the_fp32_band_schedule_covers_every_block_once():
+    rng = np.random.default_rng(13)
+    cases = [(10, 94, 256), (3, 188, 256), (7, 141, 256), (1, 1024, 256), (1, 1025, 256), (32, 17, 256), (32, 3, 32), (8, 1, 8), (1, 4000, 8)]
+    for _ in range(200):
+        grid = int(rng.choice([32, 64, 256, 304]))
+        cases.append((int(rng.integers(1, 33)), int(rng.choice([rng.integers(1, 40), rng.integers(1, 1500)])), grid))
+    for C, U, grid in cases:
+        check_band_schedule(tr.band_f32_schedule, C, U, grid, 4 if -(-U // (grid // C)) <= 4 else 8)
+    with pytest.raises(tr.TideError):
+        tr.band_f32_schedule(9, 10, 8, 0)                        # a workgroup per checkpoint at least
 
 
 def test_generic_hidden_sizes_take_the_register_ring_kernel_when_a_form_is_forced():
