@@ -840,7 +840,7 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
                 else rc = no_form();
                 break;
             case kKernelTile:
-                if constexpr (DT != kF32) rc = two_halves ? launch_tile<DT, 2>(st, p) : launch_tile<DT, 1, R>(st, p);
+                if constexpr (DT != kF32) rc = !two_halves ? launch_tile<DT, 1, R>(st, p) : R ? no_form() : launch_tile<DT, 2>(st, p);
                 else rc = no_form();
                 break;
             case kKernelBand:
@@ -858,11 +858,15 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
                 if constexpr (DT != kF32 && !R) rc = launch_square<DT>(st, p);
                 else rc = no_form();
                 break;
+            // (fp32 rows that are no whole k-tiles always have another plan: band, split-k or register ring)
             case kKernelStream128:
-                rc = launch_dma<DT, 128, 1, R>(L.grid, st, p);
+                if constexpr (DT != kF32 || !R) rc = launch_dma<DT, 128, 1, R>(L.grid, st, p);
+                else rc = no_form();
                 break;
             case kKernelStream64:
-                rc = two_halves ? launch_dma<DT, 64, 2>(L.grid, st, p) : launch_dma<DT, 64, 1, R>(L.grid, st, p);
+                if (two_halves) rc = R ? no_form() : launch_dma<DT, 64, 2>(L.grid, st, p);
+                else if constexpr (DT != kF32 || !R) rc = launch_dma<DT, 64, 1, R>(L.grid, st, p);
+                else rc = no_form();
                 break;
             default:
                 if (ntile >= kMaxDepth)

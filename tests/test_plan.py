@@ -86,6 +86,7 @@ def check_plan(dtype, C, T, d, b, cus, form):
             assert len(plan) == 1 and R == 32 and dtype == tr.F32 and halves == 1 and form == 0 and C <= cus and wg == cus, what
         if d % 128 != 0:    # forced forms: the register-ring kernel; the automatic choice: kernels that zero-fill beyond the end of a row
             assert len(plan) == 1 and (k in ZERO_FILLS if form == 0 else k == RING), what
+            assert not (dtype == tr.F32 and k in (STREAM128, STREAM64)), what              # that form is built for 16-bit rows only
     if len(plan) == 2:
         assert plan[0]["kernel"] in (WIDE, WIDE_F32, SQUARE) and plan[1]["kernel"] not in (WIDE, WIDE_F32, SPLITK, SQUARE), what
     return plan
