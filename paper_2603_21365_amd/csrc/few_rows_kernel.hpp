@@ -51,7 +51,10 @@ template <> __device__ __forceinline__ f32x4 mma_k32<kF16>(u32x4 a, u32x4 b, f32
 // p.zpart: [16 * tiles_per_ckpt][C][b / 16] floats; p.counters: kFewMaxTiles words, zero on entry and on exit.
 // blockIdx.x -> (checkpoint, row tile, column block), XCD x taking the x-th eighth of that list: a checkpoint's rows and
 // weights stay in one or two L2s.
-template <int DT>
+// kFull (fp32 rows): the whole fp32 value of a row times both terms of the weight, as the latency kernel multiplies them, for the calls
+// that are its otherwise.  x = hi + mid + lo, three bf16 terms with 8 bits each; of the six products lo * w_mid is left out (2^-26 of x * w).  The
+// small ones have an accumulator of their own: they do not lose bits against the large sum, and the chain of dependent steps stays short.
+template <int DT, bool kFull = false>
 __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const PrefillParams p) {
     typedef __attribute__((address_space(3))) char lds_char;
     typedef __attribute__((address_space(1))) const char glb_char;
@@ -59,6 +62,7 @@ __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const Pre
     constexpr int kLd = DT == kF32 ? 2 : 1;                      // 16-byte chunks per 8 elements of a row
     constexpr int kU = few_groups<DT>();
     static_assert(kU * 32 * kE == kFewChunks * 16, "a wave's turn is kFewChunks chunks of a row");
+    static_assert(!kFull || DT == kF32, "16-bit rows are exact in one term");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ __attribute__((aligned(16))) f32x4 part[kFewWaves][kWave];
     __shared__ float ssq_part[kFewWaves][kFewRows];
@@ -94,6 +98,7 @@ __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const Pre
     f32x4 b1v = *reinterpret_cast<const f32x4*>((p.b1 ? p.b1 : p.w2) + col);
 
     f32x4 acc = f32x4{0, 0, 0, 0};
+    [[maybe_unused]] f32x4 small = f32x4{0, 0, 0, 0};            // kFull
     float ssq = 0.0f;
     const int turns = (ng + kFewWaves * kU - 1) / (kFewWaves * kU);
     const int rl = lane / kFewChunks, slot = lane % kFewChunks;  // transfer: row within it, chunk slot
@@ -135,8 +140,18 @@ __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const Pre
 #pragma unroll
                 for (int e = 0; e < 8; ++e) { h8[e] = hi[e]; m8[e] = mid[e]; }
                 const u32x4 ah = __builtin_bit_cast(u32x4, h8), am = __builtin_bit_cast(u32x4, m8);
-                acc = mma_k32<kBF16>(w[u][0], am, acc);          // small terms first (mma_k16_split)
-                acc = mma_k32<kBF16>(w[u][1], ah, acc);
+                if constexpr (kFull) {
+                    bf16x8 l8;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) l8[e] = static_cast<__bf16>((x[e] - static_cast<float>(hi[e])) - static_cast<float>(mid[e]));   // exact differences
+                    small = mma_k32<kBF16>(w[u][0], __builtin_bit_cast(u32x4, l8), small);
+                    small = mma_k32<kBF16>(w[u][1], am, small);
+                    small = mma_k32<kBF16>(w[u][0], am, small);
+                    small = mma_k32<kBF16>(w[u][1], ah, small);
+                } else {
+                    acc = mma_k32<kBF16>(w[u][0], am, acc);      // small terms first (mma_k16_split)
+                    acc = mma_k32<kBF16>(w[u][1], ah, acc);
+                }
                 acc = mma_k32<kBF16>(w[u][0], ah, acc);
                 ssq = chunk_sumsq<kF32>(x1, chunk_sumsq<kF32>(x0, ssq));
             } else {
@@ -150,6 +165,7 @@ __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const Pre
     }
 
     // ---- the eight waves' shares of k meet in LDS; wave 0 finishes
+    if constexpr (kFull) acc += small;
     part[wave][lane] = acc;
     ssq += __shfl_xor(ssq, 16, kWave);
     ssq += __shfl_xor(ssq, 32, kWave);

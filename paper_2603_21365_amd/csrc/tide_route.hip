@@ -884,27 +884,28 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
     return TIDE_OK;
 }
 
-// The few-rows kernel: a workgroup per 16 rows and 16 columns of the bottleneck.
-template <int DT> int launch_few(unsigned grid, hipStream_t st, const PrefillParams& p) {
+// The few-rows kernel: a workgroup per 16 rows and 16 columns of the bottleneck.  full: fp32 rows with all their bits.
+template <int DT, bool kFull = false> int launch_few(unsigned grid, hipStream_t st, const PrefillParams& p) {
     static bool raised[kMaxDevices] = {};
     int dev = 0;
     TIDE_HIP(hipGetDevice(&dev));
     if (!raised[dev]) {
-        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_few_rows_kernel<DT>),
+        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_few_rows_kernel<DT, kFull>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, few_lds_bytes(kFewRows)));
         raised[dev] = true;
     }
-    hipLaunchKernelGGL((tide_few_rows_kernel<DT>), dim3(grid), dim3(kFewThreads), few_lds_bytes(std::min(p.T, kFewRows)), st, p);
+    hipLaunchKernelGGL((tide_few_rows_kernel<DT, kFull>), dim3(grid), dim3(kFewThreads), few_lds_bytes(std::min(p.T, kFewRows)), st, p);
     return TIDE_OK;
 }
-int launch_few_rows(const Scratch& sc, PrefillParams p, int dtype, hipStream_t st) {
+int launch_few_rows(const Scratch& sc, PrefillParams p, int dtype, bool full, hipStream_t st) {
     p.tiles_per_ckpt = (p.T + kFewRows - 1) / kFewRows;
     p.total_tiles = p.C * p.tiles_per_ckpt;
     p.k_slices = p.b / kFewCols;
     p.zpart = sc.part;
     p.counters = sc.counters;
     const unsigned grid = 8u * (unsigned)((p.total_tiles * p.k_slices + 7) / 8);
-    const int rc = by_dtype(dtype, [&](auto dt) { return launch_few<decltype(dt)::value>(grid, st, p); });
+    const int rc = dtype == TIDE_F32 && full ? launch_few<kF32, true>(grid, st, p)
+                                             : by_dtype(dtype, [&](auto dt) { return launch_few<decltype(dt)::value>(grid, st, p); });
     if (rc) return rc;
     TIDE_HIP(hipGetLastError());
     return TIDE_OK;
@@ -1021,7 +1022,8 @@ bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool ra
 // ---- What a router call needs of scratch memory, and which path it takes: host arithmetic only.
 struct CallNeed {
     bool decode = false;            // the latency kernel takes the call, else the prefill path with `plan`
-    bool few = false;               // the few-rows kernel takes the call
+    bool few = false;               // the few-rows kernel takes the call, ...
+    bool few_full = false;          // ... fp32 rows with all their bits
     PrefillPlan plan;
     size_t state_bytes = 0;         // counters + arrival words, a multiple of 256
     size_t packed_bytes = 0;        // a multiple of 256
@@ -1049,11 +1051,11 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
         n.part_bytes = round256((size_t)C * S * (size_t)T * (size_t)(halves * kBottleneck + kPartPad) * sizeof(float));
     }
     // (the other paths' needs are counted all the same for a caller's block: what a caller has to bring does not depend on this choice)
-    // fp32 rows that the latency kernel takes stay with it on packed weights too: it multiplies the whole fp32 value of a row by both terms of
-    // the weight, the few-rows kernel the row's two leading bf16 terms (error against 64 bits at T = 32, d = 1000: 2.6e-6 against 4.7e-6).
-    // 16-bit rows are exact in either.
-    n.few = allow_few && !(n.decode && (raw_weights || dtype == TIDE_F32)) && variant == TIDE_VARIANT_AUTO && form_word == 0 &&
+    n.few = allow_few && !(raw_weights && n.decode) && variant == TIDE_VARIANT_AUTO && form_word == 0 &&
             use_few_rows(dtype, C, T, n.d_run, b, raw_weights, cus);
+    // fp32 rows that are the latency kernel's otherwise: it multiplies the whole fp32 value of a row by both terms of the weight, the other kernels
+    // for packed weights the row's two leading bf16 terms (error against 64 bits at T = 32, d = 1000: 2.6e-6 / 4.7e-6).  16-bit rows are exact in any.
+    n.few_full = n.few && n.decode;
     const size_t few_bytes = n.few ? round256((size_t)T * (size_t)C * (size_t)(b / kFewCols) * sizeof(float)) : 0;
     if (n.decode) {
         n.leaves_data = true;
@@ -1284,7 +1286,7 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
             return p;
         };
         if (!rc)
-            rc = need.few ? launch_few_rows(sc, params(), dtype, st) : launch_prefill(sc, need.plan, params(), dtype, st);
+            rc = need.few ? launch_few_rows(sc, params(), dtype, need.few_full, st) : launch_prefill(sc, need.plan, params(), dtype, st);
     }
     if (rc) {                       // a launch failed, possibly after an earlier one of this call was enqueued
         if (ws) ws->dirty = true;
