@@ -989,7 +989,7 @@ bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, i
 }
 
 // The few-rows kernel (a workgroup per 16 rows and 16 columns, all of k) or the paths above?  It is the faster one as long
-// as its workgroups fit the chip once (256 CUs, packed weights, against the split-k forms, us:
+// as its workgroups fit the chip once and the checkpoints are not too many (256 CUs, packed weights, against the split-k forms, us:
 // C = 8, d = 4096: 8.7 -> 6.3 at T = 1, 9.5 -> 7.3 at 16, 11.3 -> 8.5 at 48, 11.3 -> 9.2 at 64 = 256 workgroups; fp32 rows, d = 5120, C = 8, T = 64:
 // 15.7 -> 15.1) and, with rows of up to 8 KiB, up to one and a half workgroups per CU (two are resident): 11.8 -> 11.4 at
 // T = 96, 11.6 -> 11.4 at C = 1, T = 768, level from there on; longer rows lose there (d = 8192, C = 10, T = 96: 15.8 -> 18.1).
@@ -1002,17 +1002,24 @@ bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, i
 //   T = 32, but 18.2 / 18.9 at 64 and 19.5 / 21.4 at C = 8).
 // Weights that this call packed come from memory, and 40 workgroups ask for them more slowly than split-k's 256: one or two checkpoints' of 4 MiB
 // and more go to the pair (fp32, d = 8192, C = 1, T = 40: 22.2 / 24.1 us; bf16, width 256: 16.5 / 17.3).
-// Rows of 64 KiB (fp32, d = 16384) are level at best.  Every workgroup of a row tile ticks the tile's counter (14 ns each): from 256 of
-// them on that costs what the kernel gains (C = 32, width 128: 12.2 -> 12.6; C = 20: 10.2 -> 9.1).
+// Rows of 64 KiB (fp32, d = 16384) are level at best.  Every workgroup of a row tile ticks the tile's counter (14 ns each), which from 128 ticks on costs what
+// the kernel gains against the 128-column split-k forms (width 256, where those take twice the workgroups, does not meet that line: 1.03-1.6 times
+// up to 240 ticks).  17 to 24 checkpoints at width 128: up to 16 rows still for 4 rows or rows of 4 KiB (f16, C = 24: 1.2 times at d = 768, T = 1, 1.05 at T = 4, d = 5120,
+// but bf16, C = 20: 8.6 / 9.1 us at T = 8, 9.4 / 10.1 at 16, d = 2560); more rows for fp32 or rows of 8 KiB (f16, C = 24: 1.12 times at d = 5120, T = 32, but bf16 9.3 / 10.3 us at
+// d = 1024, 11.2 / 12.0 at 2560).  More checkpoints: 9.9 / 11.4 at C = 28, T = 16, d = 2560, 9.3 / 10.4 at T = 8.  Beyond one workgroup per CU rows of up to
+// 2 KiB meet it from 112 ticks on (C = 16, T = 33, d = 1024: 9.2 / 9.6; d = 2560 11.6 / 10.8).
 // Hidden sizes that are no multiple of 128 go to the register-ring kernel otherwise (18.9 -> 9.3 us at C = 8, T = 100, d = 1600):
 // there up to two workgroups per CU.
 bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool raw_weights, unsigned cus) {
     const int64_t tiles = (T + kFewRows - 1) / kFewRows, nbk = b / kFewCols, row_bytes = d * (int64_t)elem_bytes(dtype);
     if (tiles > kFewMaxTiles || C * nbk >= 256 || row_bytes > 32768) return false;
     const int64_t W = C * tiles * nbk, n = (int64_t)cus;
-    if (d % 128 != 0) return W <= 2 * n;
+    const bool few_ticks = C * nbk <= 112 || row_bytes > 2048;
+    if (d % 128 != 0) return W <= (few_ticks ? 2 * n : n);
     if (raw_weights && d >= 8192 && C * b <= 256 && T > kFewRows && d * b * (int64_t)elem_bytes(dtype) >= 4 << 20) return false;
-    if (row_bytes <= 20480) return W <= n || (row_bytes <= 8192 && 2 * W <= 3 * n);
+    if (b <= 128 && C * nbk >= 200) return false;
+    if (b <= 128 && C * nbk > 128 && !(T <= kFewRows ? T <= 4 || row_bytes <= 4096 : dtype == TIDE_F32 || row_bytes >= 8192)) return false;
+    if (row_bytes <= 20480) return W <= n || (row_bytes <= 8192 && few_ticks && 2 * W <= 3 * n);
     if (T <= 8 || (T <= kFewRows && b == 256)) return W <= n;
     if (T <= kFewRows) return W <= n && (dtype == TIDE_F32 ? T <= 12 || row_bytes <= 24576 : T <= 12 && row_bytes <= 24576);
     if (row_bytes <= 24576) return b == 256 ? 2 * W <= n : 4 * W <= 3 * n;
