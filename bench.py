@@ -13,7 +13,7 @@ pass is inside the timed region).  Prints ONE JSON line.
              step), algorithmic bytes / HIP-event time per launch, against 8 TB/s
   cpu_baseline  the fp64 oracle on the same workload on this machine's host cores
   decode     config-2 latency (fp16, T=1 and T=8), us per call: warm (back to back) and cold
-  sweep      configs[4]: d x dtype at T=16384, C=10 on packed weights
+  sweep      d x dtype at T=16384, C=10 on packed weights
 
 Every timed loop is cut into windows by HIP events; a window that takes more than 1.5 times
 the median window is listed as a stall (the device idling between two launches: not kernel
@@ -83,11 +83,11 @@ def main() -> int:
     ap.add_argument("--no-decode", action="store_true")
     ap.add_argument("--no-extras", action="store_true",
                     help="skip the steps around the path (exit projection, calibration labels, other bottleneck widths)")
-    ap.add_argument("--no-sweep", action="store_true", help="skip the hidden-size x dtype sweep (configs[4])")
+    ap.add_argument("--no-sweep", action="store_true", help="skip the hidden-size x dtype sweep")
     ap.add_argument("--no-settle", action="store_true", help="skip the untimed settling phase (short profiler runs)")
     ap.add_argument("--pmc-shapes", action="store_true",
-                    help="only launch four shapes ten times each, untimed, for rocprofv3 --pmc runs: configs[1] (one-tile kernel), "
-                         "configs[3] (band kernel), width 256 at C=8, T=4096, d=4096 (one-tile kernel, eight consumer waves) and at "
+                    help="only launch four shapes ten times each, untimed, for rocprofv3 --pmc runs: C=8, T=4096, d=4096 (one-tile kernel), "
+                         "C=9, T=16384, d=4096 (band kernel), width 256 at C=8, T=4096, d=4096 (one-tile kernel, eight consumer waves) and at "
                          "T=8192 (square kernel)")
     ap.add_argument("--mfma-rate", action="store_true",
                     help="only measure the sustained rate of the prefill kernels' matrix instruction (random and all-zero operands, "
@@ -305,7 +305,7 @@ def main() -> int:
         "scaling": "weak", "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
         "paper_context": "end-to-end model figures on one A100, bf16 (Table 3): DeepSeek R1 Distill 8B prefill latency -7.2 %, "
                          "throughput +6.6 % at batch 1; Qwen3 8B throughput +8.1 % at batch 8 -- not kernel figures, hence vs_baseline null",
-        "config": {"workload": "configs[1]: 8B-shaped prefill, bf16, d=4096, 32 layers, checkpoints every 4 (C=8), "
+        "config": {"workload": "8B-shaped prefill, bf16, d=4096, 32 layers, checkpoints every 4 (C=8), "
                                "T=4096 tokens, ~30% firing per checkpoint", "C": C, "T": T, "d": d,
                    "entry_point": "tide_select_exit (raw fp32 router weights; gain fold + packing inside the step)",
                    "input_buffers_rotated": args.buffers,
@@ -381,7 +381,7 @@ def main() -> int:
             del hbs, cb, pkb, Wb, out_t
         result["bottleneck_widths"] = {"workload": f"Table 2 pairs with b != 128: bf16, C={C}, T={T} (or the T a key names), packed weights", **widths}
 
-        # ---- configs[3]: the 36-layer batched prefill (C=9, T=8x2048)
+        # ---- the 36-layer batched prefill (C=9, T=8x2048)
         w3 = synth.config3()
         gen3 = torch.Generator(device="cuda").manual_seed(0x71DE + 3)
         hb3 = [torch.randn((w3.C, w3.T, d), generator=gen3, device="cuda").to(torch.bfloat16) for _ in range(2)]
@@ -395,14 +395,14 @@ def main() -> int:
         r3 = timed(lambda i: c3[i & 1](), n_x, 5)
         by3 = w3.C * w3.T * d * esz + w3.C * d * 128 * esz + w3.T * 8 + w3.C * w3.T * 4
         plan3 = tr.prefill_plan(tr.BF16, w3.C, w3.T, d, 128, cus=torch.cuda.get_device_properties(0).multi_processor_count & ~7)
-        result["large_batch"] = {"workload": "configs[3]: bf16, d=4096, 36 layers, C=9, T=16384 (8 x 2048), packed weights",
+        result["large_batch"] = {"workload": "bf16, d=4096, 36 layers, C=9, T=16384 (8 x 2048), packed weights",
                                  "launches": [{k: L[k] for k in ("kernel", "rows_per_tile", "total_tiles", "tile_begin", "workgroups")} for L in plan3],
                                  "us_per_call": round(r3["clean"] * 1e6, 2), "us_per_call_median_window": round(r3["median"] * 1e6, 2),
                                  "tokens_per_s": round(w3.T / r3["clean"], 1),
                                  "algorithmic_bytes": by3, **hbm(by3, r3["clean"])}
         del hb3, c3
 
-    # ---- configs[4]: hidden size x storage type at T = 16384, C = 10, packed weights.  fp32 rows reach the
+    # ---- hidden size x storage type at T = 16384, C = 10, packed weights.  fp32 rows reach the
     # matrix cores as two bf16 terms per value and three bf16 products per pair, so the matrix-core work
     # issued is 3 x 2 d 128 flops per row on the bf16 units; the fp32 MFMA peak is quoted for context only.
     if not args.no_sweep:
@@ -435,7 +435,7 @@ def main() -> int:
                 sweep[f"d{dd}_{name}"] = point
                 del hs, c4, pk4
             del W4
-        result["sweep"] = {"workload": f"configs[4]: T={Ts}, C={Cs}, b=128, packed weights, random rows, 48 back-to-back calls on "
+        result["sweep"] = {"workload": f"T={Ts}, C={Cs}, b=128, packed weights, random rows, 48 back-to-back calls on "
                                        "rotating inputs; d=8192 is the 80-layer point", **sweep}
 
     # ---- decode latency (config 2): fp16, T = 1 and 8.  Router weights are static at inference, so the
@@ -518,7 +518,7 @@ def main() -> int:
                                            "us_replay_plus_sync_median": round(lat_g[500] * 1e6, 2),
                                            "note": "the packed call captured as a graph (one kernel)"}}
         del evict_src, evict_dst
-        result["decode"] = {"workload": "configs[2]: fp16, d=4096, C=8, back-to-back calls on one stream "
+        result["decode"] = {"workload": "fp16, d=4096, C=8, back-to-back calls on one stream "
                                         "(us_per_call), one call then a stream synchronisation (us_call_plus_sync), and "
                                         "one call after the caches were flushed (cold)", **dec}
 

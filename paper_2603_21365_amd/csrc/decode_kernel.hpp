@@ -188,9 +188,9 @@ __device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int*
 // kHalves = p.halves as a compile-time value (1 or 2): the width-128 kernel carries no code or
 // registers for a second column half.  kTB = tokens per pass: 1, 2, 4 or 8, the smallest that holds T (8 beyond).
 // What bounds it: 16 MiB of weights on the whole chip (C = 8, d = 4096: 2-3 us), then the hand-over's round trips.  Measured (fp16, C = 8,
-// d = 4096, us per call): 15.3 at any T up to 8 with eight tokens' arithmetic always, the weights queued before the rows (loads return in
+// d = 4096, us per call back to back, weights in the caches): 13.7 / 13.7 / 13.8 / 15.1 at T = 1 / 2 / 4 / 8 with eight tokens' arithmetic always, the weights queued before the rows (loads return in
 // order, so nothing was staged until the last weight was there), the counters of all checkpoints in one line and one thread per
-// (token, quad) in the finish; now 10.0 / 11.0 / 12.2 / 15.0 at T = 1 / 2 / 4 / 8, width 256 26.7 -> 18 at T = 4.
+// (token, quad) in the finish; now 9.0 / 9.5 / 10.6 / 13.1, width 256 24.8 -> 16.1 at T = 4.
 template <int DT, int kHalves, int kTB>
 __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const DecodeParams p) {
     constexpr int E = Storage<DT>::kElems;

@@ -13,7 +13,7 @@
 // the matrix cores' operand layout a load touches 64 bytes of each of 16 rows, 2 us more at 16 rows of d = 4096.
 // Measured (C = 8, d = 4096, packed weights, us per call back to back; before = split-k in one launch up to 16 rows,
 // the pair beyond): 8.7 -> 6.4 at T = 1, 8.8 -> 6.9 at 8, 9.6 -> 7.4 at 16, 11.5 -> 8.6 at 48; width 256, T = 8: 12.7 -> 8.8;
-// fp32 rows, T = 4: 12.4 -> 9.4; d = 768, T = 4: 10.0 -> 6.3; d = 1600 (no multiple of 128), C = 12, T = 48: 18.8 -> 9.9.
+// fp32 rows, T = 4: 12.4 -> 9.4; d = 768, T = 4: 10.0 -> 6.3; d = 1600 (no multiple of 128), C = 12, T = 48: 18.4 -> 8.8.  kFull against the latency kernel: 34.6 -> 9.0 at C = 4, T = 32, d = 1608, 12.2 -> 8.0 at C = 8, T = 4.
 // Every storage type, every width, every hidden size whose rows are whole 16-byte chunks.
 #pragma once
 #include <type_traits>

@@ -671,9 +671,9 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     // Band form for fp32 rows: every checkpoint gets cus / C workgroups, each an equal share of its blocks.  Up to four blocks
     // per workgroup its eight consumer waves share a block in pairs (each half of k): it is the choice from more than two
     // blocks per workgroup on, where the register-ring kernel's 64-row tiles are more than one per CU; up to six a wave per block.
-    // Measured on 256 CUs (C = 8 where not given; against the forms below, us): d = 4096: 94 against 116 at T = 2300, 101 / 115 at
-    // 2600, 108 / 121 at 3072, 129 / 139 at 4096, 167 / 174 at 4800, 177 / 187 at 5500, but 216 / 219 at 7000 (seven blocks); d = 2560, C = 10, T = 3001: 80 / 99;
-    // d = 1024: 28 / 34 at 2300, 38 / 41 at 4096; d = 8192: 196 / 228 at 2600, 255 / 276 at 4096; C = 32, T = 900, d = 2048: 68 / 79; but 86 / 78
+    // Measured on 256 CUs (C = 8 where not given; against the forms below, us): d = 4096: 94 against 111 at T = 2300, 90 / 111 at
+    // 2600, 97 / 113 at 3072, 122 / 132 at 4096, 162 / 171 at 4800, 177 / 187 at 5500, but 216 / 219 at 7000 (seven blocks); d = 2560, C = 10, T = 3001: 79 / 87;
+    // d = 1024: 27 / 33 at 2300, 36 / 38 at 4096; d = 8192: 196 / 228 at 2600, 255 / 276 at 4096; C = 32, T = 900, d = 2048: 59 / 70; but 86 / 78
     // at two blocks (T = 2048) and nothing at d <= 256.  From seven blocks on the wide-tile kernel's
     // rounds are level.  The ring kernel is
     // slow on rows that are no whole k-tiles (C = 8, T = 1200, d = 3000: 129 us): those take this form whatever their number.
@@ -763,8 +763,8 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
 
 // The launches of a call on rows of d elements (after a repack: of the padded length).
 // Rows of whole 16-byte chunks whose length is no multiple of 128: under the automatic settings the plan of the padded
-// length, on the kernels that read the chunks beyond a row's end as zeros: bf16, d = 1600, C = 12: 53 -> 40 us at T = 4000, 21 -> 17 at 1000;
-// d = 4104, C = 8, T = 200: 39 -> 15.5; fp32, d = 4000, C = 9, T = 300: 161 -> 28; d = 1608, C = 8, T = 3000: 82 -> 55 (before: the register-ring
+// length, on the kernels that read the chunks beyond a row's end as zeros: bf16, d = 1600, C = 12: 50 -> 33 us at T = 4000, 20 -> 16 at 1000;
+// d = 4104, C = 8, T = 200: 38 -> 12.5; fp32, d = 4000, C = 9, T = 300: 161 -> 28; bf16, d = 1608, C = 8, T = 3000: 31 -> 26 (before: the register-ring
 // form, whose loads are selected chunk by chunk).  (split_k: the split-k pair only where its partial results do not
 // have to fit a block that was sized without them.)
 PrefillPlan call_plan(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, int variant, int form_word, bool split_k) {
