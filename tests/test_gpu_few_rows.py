@@ -85,15 +85,16 @@ def test_fp32_rows_keep_all_their_bits_where_the_latency_kernel_does(tr, C, T, d
     assert err < min(2 * d ** 0.5 * 2.0 ** -24, 1.5e-6), err
 
 
-def test_non_finite_rows_stay_by_themselves(tr):
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_non_finite_rows_stay_by_themselves(tr, dtype):
     """A row with an infinity or a NaN has a NaN logit and fires nothing; the rows beside it in its tile, and the zeros that
     stand in beyond the end of a row (d = 1544), are not touched by it."""
     import torch
-    w = synth.Workload("few_nonfinite", 79, "bf16", 1544, 12, 4, 21, None)
+    w = synth.Workload("few_nonfinite", 79, dtype, 1544, 12, 4, 21, None)
     rt = w.routers()
     g, W1, b1, w2 = routers_to_device(rt)
-    pk = tr.router_pack(tr.BF16, g, W1)
-    h = to_device(w.hidden(), "bf16")
+    pk = tr.router_pack(tr.DTYPE_CODES[dtype], g, W1)
+    h = to_device(w.hidden(), dtype)
     args = (w.eps, b1, w2, rt.b2, rt.theta, w.layer_ids, 0, w.n_layers)
     ex0, z0, m0 = tr.select_exit_packed(h, pk, *args, d=w.d)
     bad = h.clone()
