@@ -13,7 +13,8 @@
 // the matrix cores' operand layout a load touches 64 bytes of each of 16 rows, 2 us more at 16 rows of d = 4096.
 // Measured (C = 8, d = 4096, packed weights, us per call back to back; before = split-k in one launch up to 16 rows,
 // the pair beyond): 8.7 -> 6.4 at T = 1, 8.8 -> 6.9 at 8, 9.6 -> 7.4 at 16, 11.5 -> 8.6 at 48; width 256, T = 8: 12.7 -> 8.8;
-// fp32 rows, T = 4: 12.4 -> 9.4; d = 768, T = 4: 10.0 -> 6.3; d = 1600 (no multiple of 128), C = 12, T = 48: 18.4 -> 8.8.  kFull against the latency kernel: 34.6 -> 9.0 at C = 4, T = 32, d = 1608, 12.2 -> 8.0 at C = 8, T = 4.
+// fp32 rows, T = 4: 12.4 -> 9.4; d = 768, T = 4: 10.0 -> 6.3; d = 1600 (no multiple of 128), C = 12, T = 48: 18.4 -> 8.8.  kFull against the latency kernel: 34.6 -> 8.6 at C = 4, T = 32, d = 1608, 12.2 -> 7.5
+// at C = 8, T = 4, 13.2 -> 9.9 at C = 1, T = 1, d = 4104 (terms rounded to the nearest instead: 9.0, 8.0 and 11.8).
 // Every storage type, every width, every hidden size whose rows are whole 16-byte chunks.
 #pragma once
 #include <type_traits>
@@ -52,8 +53,9 @@ template <> __device__ __forceinline__ f32x4 mma_k32<kF16>(u32x4 a, u32x4 b, f32
 // blockIdx.x -> (checkpoint, row tile, column block), XCD x taking the x-th eighth of that list: a checkpoint's rows and
 // weights stay in one or two L2s.
 // kFull (fp32 rows): the whole fp32 value of a row times both terms of the weight, as the latency kernel multiplies them, for the calls
-// that are its otherwise.  x = hi + mid + lo, three bf16 terms with 8 bits each; of the six products lo * w_mid is left out (2^-26 of x * w).  The
-// small ones have an accumulator of their own: they do not lose bits against the large sum, and the chain of dependent steps stays short.
+// that are its otherwise.  x = hi + mid + lo, each the upper 16 bits of what the one before leaves: exact (24 bits in three times 8), and fewer vector
+// instructions, which bound this form, than rounding to the nearest.  The five small products of the six have an accumulator
+// of their own and do not lose bits against the large sum.
 template <int DT, bool kFull = false>
 __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const PrefillParams p) {
     typedef __attribute__((address_space(3))) char lds_char;
@@ -131,28 +133,37 @@ __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const Pre
             if constexpr (DT == kF32) {
                 const u32x4 x0 = *reinterpret_cast<const u32x4*>(a_lds + ((ax ^ (8 * u)) << 4));
                 const u32x4 x1 = *reinterpret_cast<const u32x4*>(a_lds + ((ax ^ (8 * u) ^ 1) << 4));
-                float x[8];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) { x[e] = __uint_as_float(x0[e]); x[4 + e] = __uint_as_float(x1[e]); }
-                __bf16 hi[8], mid[8];
-                split_bf16(x, 8, hi, mid);
-                bf16x8 h8, m8;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { h8[e] = hi[e]; m8[e] = mid[e]; }
-                const u32x4 ah = __builtin_bit_cast(u32x4, h8), am = __builtin_bit_cast(u32x4, m8);
                 if constexpr (kFull) {
-                    bf16x8 l8;
+                    u32x4 ah, am, al;                            // pairs of terms: the upper halves of two values
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) l8[e] = static_cast<__bf16>((x[e] - static_cast<float>(hi[e])) - static_cast<float>(mid[e]));   // exact differences
-                    small = mma_k32<kBF16>(w[u][0], __builtin_bit_cast(u32x4, l8), small);
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t a = e < 2 ? x0[2 * e] : x1[2 * e - 4], b = e < 2 ? x0[2 * e + 1] : x1[2 * e - 3];
+                        const float ra = __uint_as_float(a) - __uint_as_float(a & 0xffff0000u), rb = __uint_as_float(b) - __uint_as_float(b & 0xffff0000u);
+                        const float la = ra - __uint_as_float(__float_as_uint(ra) & 0xffff0000u), lb = rb - __uint_as_float(__float_as_uint(rb) & 0xffff0000u);
+                        ah[e] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+                        am[e] = __builtin_amdgcn_perm(__float_as_uint(rb), __float_as_uint(ra), 0x07060302u);
+                        al[e] = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
+                    }
+                    small = mma_k32<kBF16>(w[u][1], al, small);
+                    small = mma_k32<kBF16>(w[u][0], al, small);
                     small = mma_k32<kBF16>(w[u][1], am, small);
                     small = mma_k32<kBF16>(w[u][0], am, small);
                     small = mma_k32<kBF16>(w[u][1], ah, small);
+                    acc = mma_k32<kBF16>(w[u][0], ah, acc);
                 } else {
+                    float x[8];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { x[e] = __uint_as_float(x0[e]); x[4 + e] = __uint_as_float(x1[e]); }
+                    __bf16 hi[8], mid[8];
+                    split_bf16(x, 8, hi, mid);
+                    bf16x8 h8, m8;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) { h8[e] = hi[e]; m8[e] = mid[e]; }
+                    const u32x4 ah = __builtin_bit_cast(u32x4, h8), am = __builtin_bit_cast(u32x4, m8);
                     acc = mma_k32<kBF16>(w[u][0], am, acc);      // small terms first (mma_k16_split)
                     acc = mma_k32<kBF16>(w[u][1], ah, acc);
+                    acc = mma_k32<kBF16>(w[u][0], ah, acc);
                 }
-                acc = mma_k32<kBF16>(w[u][0], ah, acc);
                 ssq = chunk_sumsq<kF32>(x1, chunk_sumsq<kF32>(x0, ssq));
             } else {
                 const u32x4 a = *reinterpret_cast<const u32x4*>(a_lds + ((ax ^ (4 * u)) << 4));
