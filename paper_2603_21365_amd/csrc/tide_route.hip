@@ -1081,16 +1081,16 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
     return n;
 }
 
-// The most partial results that any call of these C, d and b with at most T rows per checkpoint keeps under the automatic settings.
-// An eager call on the library's workspace reserves that much, so that no smaller call outgrows the buffer: a captured graph
-// holds its address.  The split-k forms' choice changes with the number of 32-row blocks only; the few-rows kernel has at most two
-// workgroups of 16 rows x 4 bytes per CU; the latency kernel's part grows with T up to 8 or 32.
-size_t largest_part(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool raw_weights, unsigned cus) {
-    size_t most = std::min<size_t>(round256((size_t)(T * C * (b / kFewCols)) * sizeof(float)), (size_t)cus * 2 * kFewRows * sizeof(float));
+// The most partial results that any call of these C, d and b with more than `from` and at most `to` rows per checkpoint keeps under the automatic
+// settings (both multiples of 32).  An eager call on the library's workspace reserves that much for every row count up to its own, so that no
+// smaller call outgrows the buffer: a captured graph holds its address.  The split-k forms' choice changes with the number of
+// 32-row blocks only; the few-rows kernel has at most two workgroups of 16 rows x 4 bytes per CU; the latency kernel's part grows with
+// T up to 8 or 32.
+size_t largest_part(int dtype, int64_t C, int64_t from, int64_t to, int64_t d, int64_t b, bool raw_weights, unsigned cus) {
+    size_t most = std::min<size_t>(round256((size_t)(to * C * (b / kFewCols)) * sizeof(float)), (size_t)cus * 2 * kFewRows * sizeof(float));
     auto at = [&](int64_t t) { most = std::max(most, call_need(dtype, C, t, d, b, raw_weights, false, cus, TIDE_VARIANT_AUTO, 0, true).part_bytes); };
-    at(T);
-    at(std::min<int64_t>(T, kDecodeRawMaxT));
-    for (int64_t t = 32; t < T && C * halves_of(b) * (t / 32) <= 4 * kSplitkMaxTiles; t += 32) at(t);
+    if (from == 0) at(kDecodeRawMaxT);
+    for (int64_t t = from + 32; t <= to && C * halves_of(b) * (t / 32) <= 4 * kSplitkMaxTiles; t += 32) at(t);
     return most;
 }
 
@@ -1186,17 +1186,14 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
         size_t part_bytes = need.part_bytes;
         SizedShape* shape = nullptr;     // to be remembered once the buffer is there
         if (g_variant == TIDE_VARIANT_AUTO && g_prefill_form == 0) {
-            bool sized = false;
             for (SizedShape& s : ws->sized)
-                if (s.C == C && s.d == d && s.b == b && s.dtype == dtype && s.raw == (W1 != nullptr)) {
-                    sized = T <= s.T;
-                    shape = &s;
-                }
-            if (sized) {
+                if (s.C == C && s.d == d && s.b == b && s.dtype == dtype && s.raw == (W1 != nullptr)) shape = &s;
+            if (shape && T <= shape->T) {
                 shape = nullptr;
             } else if (!capturing()) {
+                const int64_t from = shape ? shape->T : 0;
                 if (!shape) shape = &ws->sized[ws->next_sized++ % kSizedShapes];
-                part_bytes = std::max(part_bytes, largest_part(dtype, C, T, d, b, W1 != nullptr, cus));
+                part_bytes = std::max(part_bytes, largest_part(dtype, C, from, (T + 31) / 32 * 32, d, b, W1 != nullptr, cus));
             } else {
                 shape = nullptr;
             }
@@ -1209,7 +1206,7 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
             rc = need.part_bytes ? reserve(ws->part, need.part_bytes, false) : TIDE_OK;
         }
         if (rc) return rc;
-        if (shape) *shape = SizedShape{dtype, W1 != nullptr, C, d, b, T};
+        if (shape) *shape = SizedShape{dtype, W1 != nullptr, C, d, b, (T + 31) / 32 * 32};
         if (need.rows_bytes && (rc = reserve(ws->rows, need.rows_bytes, false))) return rc;
         if (ws->dirty) {            // an earlier call broke off between two launches: its state words may be set
             if ((rc = launch_clear(ws->counters.ptr, ws->counters.bytes, st))) return rc;
