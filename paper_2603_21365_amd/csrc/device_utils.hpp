@@ -130,6 +130,17 @@ constexpr int kDppXor2 = 0x4E;        // quad_perm [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141; // lane i <-> 7-i within 8: flips bit 2 (and the bits below)
 constexpr int kDppRor8 = 0x128;       // rotate a row by 8 = lane i <-> i^8
 
+// v of this lane plus v of lane ^ 8, ^ 16 or ^ 32: one or three vector instructions (a shuffle by address is seven and an LDS round trip).
+// The 16- and 32-lane row swaps, given the same value twice, leave the even rows' values in one register and the odd rows' in the other.
+template <int kXor> __device__ __forceinline__ float add_xor(float v) {
+    static_assert(kXor == 8 || kXor == 16 || kXor == 32, "within a row of 16, between rows, between halves");
+    if constexpr (kXor == 8) return v + dpp_f32<kDppRor8>(v);
+    float a = v, b = v;
+    if constexpr (kXor == 16) asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    else asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    return a + b;
+}
+
 // Sum each of 16 per-lane values over the 32 lanes that share lane>>5, leaving every lane
 // with ONE finished total (a reduce-scatter: 8+4+2+1+1 exchanges instead of 16 x 5).
 // The total a lane ends up with is that of index v = bits (4,3,2,1) of its lane id; lanes
@@ -324,6 +335,20 @@ __device__ __forceinline__ bool last_arrival(uint32_t* counter, uint32_t expecte
     return *flag_lds != 0;
 }
 
+// Kernel arguments fetched together: the compiler loads each where it is first used, and every 64-byte line of the argument block
+// touched for the first time is a round trip of some 500 cycles, one after the other at the start of a small call.
+#define TIDE_FETCH_ARGS8(a, b, c, d, e, f, g, h) asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g), "s"(h))
+#define TIDE_FETCH_ARGS16(a, b, c, d, e, f, g, h, i, j, k, l, m, n, o, q)                                                                   \
+    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g), "s"(h), "s"(i), "s"(j), "s"(k), "s"(l), "s"(m), "s"(n), "s"(o), "s"(q))
+
+// Division of a workgroup's index by a launch constant: the compiler's own sequence is some thirty dependent instructions, and at the
+// start of a small call nothing runs beside them.  Exact for x * d < 2^32.
+struct FastDiv {
+    uint32_t d, m;        // divisor; floor(2^32 / d) + 1, 0 for d = 1
+    static FastDiv of(uint32_t d) { return FastDiv{d, d <= 1 ? 0u : (uint32_t)((1ull << 32) / d) + 1u}; }
+    __device__ __forceinline__ int operator()(int x) const { return m ? (int)__umulhi((uint32_t)x, m) : x; }
+};
+
 // Per-checkpoint scalars that travel by value in the kernel argument block.
 struct CheckpointTable {
     float b2[32];
@@ -341,6 +366,11 @@ struct CheckpointTable {
 __device__ __forceinline__ void report_and_select(const CheckpointTable& tab, int C, int c, bool fire, int32_t min_layer,
                                                   int32_t no_exit, uint64_t* arrive_word, int32_t* exit_out,
                                                   uint32_t* mask_out) {
+    if (C == 1) {                                   // nobody else reports on this token: no round trip to its word
+        *exit_out = fire && tab.layer_id[0] >= min_layer ? tab.layer_id[0] : no_exit;
+        if (mask_out) *mask_out = fire ? 1u : 0u;
+        return;
+    }
     const uint64_t mine = (1ull << 32) | ((uint64_t)(fire ? 1u : 0u) << c);
     const uint64_t old = __hip_atomic_fetch_add(arrive_word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((uint32_t)(old >> 32) != (uint32_t)C - 1) return;

@@ -51,6 +51,8 @@ struct PrefillParams {
     uint64_t* arrive;          // [T] arrival words (see report_and_select), zero on entry and on exit
     // split-k form only (prefill_splitk_kernel.hpp)
     int k_slices;              // workgroups that share a tile's k range
+    FastDiv by_slices, by_tiles;   // by k_slices and tiles_per_ckpt (the pair)
+    int ring_stages;           // k-tiles of rows that the split-k kernel's ring holds
     int deal_out;              // the pair: its workgroups in launch order, slice s on XCD s mod 8 (else a tile's slices on one XCD)
     float* zpart;              // [total_tiles][k_slices][rows per tile * 128] partial accumulators
     float* sspart;             // [total_tiles][k_slices][4 waves][rows per tile] partial sums of squares
@@ -60,15 +62,19 @@ struct PrefillParams {
 
 // One router result: logit z of (checkpoint c, token t) -> the optional outputs, and its report on
 // the token's arrival word (Eq. (2)'s sigmoid and threshold; Fig. 1 step 3's earliest exit).
-__device__ __forceinline__ void emit_router_result(const PrefillParams& p, int c, int t, float z) {
+// thr: the checkpoint's threshold logit, p.tab.thr_logit[c], which a latency-bound caller fetches ahead.
+__device__ __forceinline__ void emit_router_result(const PrefillParams& p, int c, int t, float z, float thr) {
     const int64_t o = (int64_t)c * p.T + t;
-    const bool f = z > p.tab.thr_logit[c];
+    const bool f = z > thr;
     if (p.logits) p.logits[o] = z;
     if (p.prob) p.prob[o] = sigmoid_f32(z);
     if (p.fire) p.fire[o] = f ? 1 : 0;
     if (p.exit_layer)
         report_and_select(p.tab, p.C, c, f, p.min_layer, p.no_exit, p.arrive + t, p.exit_layer + t,
                           p.fire_mask ? p.fire_mask + t : nullptr);
+}
+__device__ __forceinline__ void emit_router_result(const PrefillParams& p, int c, int t, float z) {
+    emit_router_result(p, c, t, z, p.tab.thr_logit[c]);
 }
 
 constexpr int kPrefillThreads = 256;

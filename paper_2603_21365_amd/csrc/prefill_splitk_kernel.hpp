@@ -34,11 +34,27 @@ namespace tide {
 constexpr int kFinishThreads = 256;
 constexpr int kSplitkMaxS = 8;           // most workgroups that share a tile's k range (the single-launch form unrolls over them)
 
-template <int kBlocks> constexpr int splitk_lds_bytes() { return kDmaStages * kBlocks * 32 * kTileBytes; }   // the ring
+template <int kBlocks> constexpr int splitk_lds_bytes(int stages) { return stages * kBlocks * 32 * kTileBytes; }   // the ring
 // floats a workgroup leaves in p.zpart: kBlocks*32 rows x 128 columns, in the order
 // [consumer wave][block][register quad][lane][4] -- every store instruction of a wave is 1 KiB
 // contiguous, and a lane of the second launch reads back the registers of its own position.
 template <int kBlocks> constexpr int splitk_part_floats() { return kBlocks * 32 * kBottleneck; }
+
+// What bounds the pair (C = 1, T = 3000, bf16, d = 4096: 14.4 us as it was, of which the second launch 4.4): a CU takes 22-28 bytes a
+// cycle from beyond its own caches, rows and W1' alike, so bytes per CU set the pace of the first launch; rows and matrix steps have to overlap
+// for that, and a wave alone on its SIMD takes some eight cycles for every dependent instruction.  Hence
+//   - two consumer waves per SIMD, each one half of every k-tile; the two of a column block exchange halves of their accumulators at the end;
+//   - up to eight k-tiles in the ring, four in flight (a producer that asks for all eight at once is held up 3.3 us in doing so and hands
+//     the first one over at 3.5 us instead of 1.5);
+//   - in both launches the kernel arguments in one round trip, divisions by multiplication, and in the second one 32-bit offsets, no load
+//     under a condition and vector-ALU exchanges.
+// us per call, before / after: 14.7 / 13.5 at C = 1, T = 3000; 14.0 / 13.5 at C = 8, T = 322; 10.5 / 9.3 at C = 1, T = 1000; fp32, C = 1, T = 3000 24.8 / 23.3;
+// width 256, C = 8, T = 200 14.3 / 13.4.  (Rotating the k order of a slice from tile to tile: 0.3 us slower; channels are hashed.)
+// The one-launch form keeps one wave per SIMD and four k-tiles.
+constexpr int splitk_kwaves(bool fused) { return fused ? 1 : 2; }
+constexpr int splitk_producers(bool fused) { return fused ? kDmaProducers : 4; }
+constexpr int splitk_threads(bool fused) { return (splitk_kwaves(fused) * kDmaConsumers + splitk_producers(fused)) * kWave; }   // 384 / 768
+constexpr int kSplitkMaxStages = 8;     // k-tiles of rows in flight at most
 
 // First launch: item = (tile * halves + half) * p.k_slices + slice (XCD-contiguous or dealt out, below); tiles of kBlocks*32 rows,
 // checkpoint-major (p.tiles_per_ckpt per checkpoint); half = which 128 columns of the bottleneck
@@ -52,20 +68,23 @@ template <int kBlocks> constexpr int splitk_part_floats() { return kBlocks * 32 
 // 8 bytes at a time, and lost to the second launch; with the rows in use only it wins at decode sizes (see the host's
 // choice).  Ordering is by completion, as in the latency kernel (device_utils.hpp: stage_store / last_arrival).
 template <int DT, int kBlocks, bool kFused = false, bool kRagged = false>
-__global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(const PrefillParams p) {
+__global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk_kernel(const PrefillParams p) {
     static_assert(!kFused || kBlocks == 1, "the single-launch form has 32-row tiles");
     typedef __attribute__((address_space(3))) char lds_char;
     typedef __attribute__((address_space(1))) const char glb_char;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int kRowsM = kBlocks * 32;
     constexpr int kStageBytes = kRowsM * kTileBytes;
-    constexpr int kInstrPerProducer = kRowsM / 4 / kDmaProducers;   // one transfer = 4 rows x 256 B
-    constexpr int kPre = (DT == kF32 && kBlocks == 4) ? 1 : 2;     // k-tiles of W1' a consumer keeps in flight (registers permitting)
+    constexpr int kInstrPerProducer = kRowsM / 4 / splitk_producers(kFused);   // one transfer = 4 rows x 256 B
+    constexpr int kKW = splitk_kwaves(kFused), kConsumers = kKW * kDmaConsumers;
+    constexpr int kPre = kBlocks == 4 ? 1 : 2;                     // k-tiles of W1' a consumer keeps in flight (registers permitting)
     constexpr int kPartFloats = splitk_part_floats<kBlocks>();
     char* ring = smem;
+    TIDE_FETCH_ARGS16(p.total_tiles, p.tiles_per_ckpt, p.by_tiles.m, p.by_slices.m, p.deal_out, p.k_slices, p.ring_stages, p.T, p.d, p.dpad, p.b,
+                      p.hidden, p.ckpt_stride_bytes, p.row_stride_bytes, p.packed, p.zpart);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int S = p.k_slices;
+    const int S = p.k_slices, stages = p.ring_stages;
     const int halves = (p.b + kBottleneck - 1) / kBottleneck;
     // XCD x (workgroup id mod 8) takes the x-th eighth of the tile-major list: a tile's partial results come from one XCD, and the
     // second launch, cut the same way, finds them in that XCD's L2 (dealt out round-robin, the slices of a tile were on eight XCDs;
@@ -76,17 +95,18 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
     const bool dealt = kFused || p.deal_out;
     const int item = dealt ? (int)blockIdx.x : (int)((blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
     if (item >= items || (!dealt && (int)(blockIdx.x >> 3) >= per_xcd)) return;
-    const int th = item / S, slice = item - th * S;
-    const int tile = th / halves, half = th - tile * halves;
+    const int th = p.by_slices(item), slice = item - th * S;
+    const int tile = halves == 2 ? th >> 1 : th, half = th - tile * halves;
     const int ntile = p.dpad * Storage<DT>::kBytes / kTileBytes;
-    const int kt0 = slice * ntile / S, nk = (slice + 1) * ntile / S - kt0;
-    const int c = tile / p.tiles_per_ckpt;
+    const int kt0 = p.by_slices(slice * ntile), nk = p.by_slices((slice + 1) * ntile) - kt0;
+    const int c = p.by_tiles(tile);
     const int row0 = (tile - c * p.tiles_per_ckpt) * kRowsM;
-    float* zmine = p.zpart + (size_t)item * kPartFloats + (size_t)(wave * kBlocks) * 1024 + lane * 4;
+    const int cb = wave & 3;                                       // a consumer's column block
+    float* zmine = p.zpart + (size_t)item * kPartFloats + (size_t)(cb * kBlocks) * 1024 + lane * 4;
 
-    if (wave >= kDmaConsumers) {
+    if (wave >= kConsumers) {
         // ------------------------------------------------------------------ producers
-        const int pw = wave - kDmaConsumers;
+        const int pw = wave - kConsumers;
         const int rl = lane >> 4, slot = lane & 15;
         const char* base = p.hidden + (int64_t)c * p.ckpt_stride_bytes + (int64_t)kt0 * kTileBytes;
         const char* gp[kInstrPerProducer];
@@ -98,10 +118,11 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
             r = r < p.T ? r : p.T - 1;                                      // ragged tail: re-read the last row
             gp[i] = base + (int64_t)r * p.row_stride_bytes + ((slot ^ (row & 15)) << 4);
         }
-        int issued = 0;
+        int issued = 0, slot_in = 0;
         auto issue_next = [&]() {
             if (issued >= nk) return;
-            char* dst = ring + (issued % kDmaStages) * kStageBytes;
+            char* dst = ring + slot_in * kStageBytes;
+            slot_in = slot_in + 1 == stages ? 0 : slot_in + 1;
             if (kRagged && kt0 + issued >= whole) {
 #pragma unroll
                 for (int i = 0; i < kInstrPerProducer; ++i) {
@@ -118,32 +139,46 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
             }
             ++issued;
         };
-        // every ring slot is free at the start: fill them all
+        // Four stages in flight.  (More at the start hold the wave up in issuing them, and the first one is handed over late.)
         for (int s = 0; s < kDmaStages; ++s) issue_next();
         for (int k = 0; k < nk; ++k) {
             // stage k has landed once only the transfers of the younger stages are outstanding
             // (every stage is kInstrPerProducer transfers; loads complete in issue order)
             const int younger = issued - k - 1;
-            if (younger >= 3) __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * kInstrPerProducer));
-            else if (younger == 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kInstrPerProducer));
-            else if (younger == 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kInstrPerProducer));
-            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            static_assert((kSplitkMaxStages - 1) * kInstrPerProducer < 64, "the wave's load counter");
+            switch (younger) {
+            case 0: __builtin_amdgcn_s_waitcnt(vmcnt_imm(0)); break;
+            case 1: __builtin_amdgcn_s_waitcnt(vmcnt_imm(kInstrPerProducer)); break;
+            case 2: __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kInstrPerProducer)); break;
+            case 3: __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * kInstrPerProducer)); break;
+            case 4: __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * kInstrPerProducer)); break;
+            case 5: __builtin_amdgcn_s_waitcnt(vmcnt_imm(5 * kInstrPerProducer)); break;
+            case 6: __builtin_amdgcn_s_waitcnt(vmcnt_imm(6 * kInstrPerProducer)); break;
+            default: __builtin_amdgcn_s_waitcnt(vmcnt_imm(7 * kInstrPerProducer)); break;
+            }
+            const bool fresh = issued < stages;    // a slot that no stage has used yet: no need to wait for the consumers
+            if (fresh) issue_next();
             ring_barrier();                        // stage k handed over; the consumers are done with stage k-1
-            if (k > 0) issue_next();               // ... whose slot takes stage k+3
+            if (!fresh && k > 0) issue_next();     // ... whose slot takes the next one
+        }
+        if constexpr (kKW == 2) {                  // the two barriers of the consumers' exchange
+            ring_barrier();
+            ring_barrier();
         }
     } else {
         // ------------------------------------------------------------------ consumers
-        const int wave_u = __builtin_amdgcn_readfirstlane(wave);     // uniform: branches on it are scalar
+        const int wave_u = __builtin_amdgcn_readfirstlane(cb);       // uniform: branches on it are scalar
+        const int kh = kKW == 2 ? __builtin_amdgcn_readfirstlane(wave >> 2) : 0;   // this wave's half of every k-tile
         const int r = lane & 31;
         const int a_base = r * kTileBytes;
-        const int y16 = ((lane >> 5) ^ (r & 15)) << 4;               // see prefill_dma_kernel.hpp
+        const int y16 = (((lane >> 5) ^ (r & 15)) << 4) ^ (kh << 7);   // see prefill_dma_kernel.hpp; a half k-tile is 128 bytes of a row
         const size_t ckpt_chunks = (size_t)p.dpad * kBottleneck / Storage<DT>::kElems;
-        const u32x4* bptr = p.packed + ((size_t)c * halves + half) * ckpt_chunks + wave * 64 + lane;
-        constexpr int kGroups = Compute<DT>::kMmaGroups, kPlanes = Compute<DT>::kPlanes;
-        constexpr int kFrags = kGroups * kPlanes;                    // W1' fragments of one k-tile: 8 either way
+        constexpr int kGroups = Compute<DT>::kMmaGroups / kKW, kPlanes = Compute<DT>::kPlanes;   // 16-k groups of a k-tile that this wave takes
+        constexpr int kFrags = kGroups * kPlanes;                    // their W1' fragments
+        const u32x4* bptr = p.packed + ((size_t)c * halves + half) * ckpt_chunks + (size_t)(kh * kGroups) * 256 + cb * 64 + lane;
         const size_t plane_chunks = (size_t)p.dpad * 16;                // fp32 rows: the hi and the mid plane of W1'
-        const int yf16 = (((lane >> 5) << 1) ^ (r & 15)) << 4;       // fp32 rows: see prefill_dma_kernel.hpp
-        auto b_fragment = [&](int kt, int g, int pl) { return bptr[pl * plane_chunks + (size_t)(kt * kGroups + g) * 256]; };
+        const int yf16 = ((((lane >> 5) << 1) ^ (r & 15)) << 4) ^ (kh << 7);       // fp32 rows: see prefill_dma_kernel.hpp
+        auto b_fragment = [&](int kt, int g, int pl) { return bptr[pl * plane_chunks + (size_t)(kt * Compute<DT>::kMmaGroups + g) * 256]; };
         // W1' fragments of kPre k-tiles in flight: with few k-tiles per workgroup nothing else hides
         // the L2 round trip.  Slot j holds k-tile k with k % kPre == j.
         u32x4 breg[kPre][kFrags];                                    // [g * kPlanes + plane]
@@ -166,7 +201,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
         // are issued (a wave is alone on its SIMD, so nothing else would cover the LDS round trip, and
         // the fewer blocks a tile has the fewer matrix steps there are per group to cover it with).
         // Not at 128 rows: with two k-tiles of W1' in registers there are none left for it.
-        constexpr int kAhead = kBlocks >= 4 ? 0 : kBlocks == 2 ? 2 : 4;
+        constexpr int kAhead = kBlocks >= 4 ? (kKW == 2 ? 1 : 0) : kBlocks == 2 ? 2 : 4;
         auto read_a = [&](const char* st, int g, u32x4* dst) {
 #pragma unroll
             for (int b = 0; b < kBlocks; ++b)
@@ -200,7 +235,7 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
 #pragma unroll
                     for (int b = 0; b < kBlocks; ++b) acc[b] = mma_k16_split(ah[b], am[b], bf[2 * g], bf[2 * g + 1], acc[b]);
 #pragma unroll
-                    for (int b = 0; b < kBlocks; ++b) ssq[b] += g == wave_u ? sq[b] : 0.0f;   // this wave's share of the sums of squares
+                    for (int b = 0; b < kBlocks; ++b) ssq[b] += kh * kGroups + g == wave_u ? sq[b] : 0.0f;   // this wave's share of the sums of squares
                 } else {
                     if (g == 0) {
 #pragma unroll
@@ -221,19 +256,24 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
                 }
             }
         };
-        int k = 0;
+        int k = 0, slot_out = 0;
+        auto next_stage = [&]() {
+            const char* st = ring + slot_out * kStageBytes + a_base;
+            slot_out = slot_out + 1 == stages ? 0 : slot_out + 1;
+            return st;
+        };
         for (; k + 2 * kPre <= nk; k += kPre) {    // steady state: every k-tile refills its slot
 #pragma unroll
             for (int j = 0; j < kPre; ++j) {
                 ring_barrier();
-                k_tile(ring + ((k + j) % kDmaStages) * kStageBytes + a_base, breg[j], kt0 + k + j + kPre, std::true_type{});
+                k_tile(next_stage(), breg[j], kt0 + k + j + kPre, std::true_type{});
             }
         }
 #pragma unroll
         for (int j = 0; j < 2 * kPre - 1; ++j) {   // fewer than 2 kPre k-tiles left (k is a multiple of kPre)
             if (k + j < nk) {
                 ring_barrier();
-                const char* st = ring + ((k + j) % kDmaStages) * kStageBytes + a_base;
+                const char* st = next_stage();
                 if (k + j + kPre < nk) k_tile(st, breg[j % kPre], kt0 + k + j + kPre, std::true_type{});
                 else k_tile(st, breg[j % kPre], 0, std::false_type{});
             }
@@ -252,11 +292,39 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
                     if (q < quads) stage_store4(zmine + q * 256, f32x4{acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]});
                 if (lane < 32) stage_store(p.sspart + ((size_t)item * kDmaConsumers + wave) * kRowsM + lane, s2);
             } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<f32x4*>(zmine + (b * 4 + q) * 256) = f32x4{acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]};
-                if (lane < 32) p.sspart[((size_t)item * kDmaConsumers + wave) * kRowsM + 32 * b + lane] = s2;
+                ssq[b] = s2;
             }
+        }
+        if constexpr (!kFused) {
+            // The two waves of a column block exchange halves of their accumulators through the ring's memory (one block: its
+            // register quads 0, 1 / 2, 3; else the lower and the upper blocks); each adds and stores the half it keeps.
+            constexpr int kMoved = 2 * kBlocks;                      // register quads that change hands: half of 4 kBlocks
+            f32x4* ex = reinterpret_cast<f32x4*>(smem);              // [wave][kMoved][lane]
+            float* ex_ss = reinterpret_cast<float*>(smem + kConsumers * kMoved * 1024);   // [wave][kBlocks][32]
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            ring_barrier();                                          // every wave is done with the ring
+            auto quad = [&](int q) { return f32x4{acc[q >> 2][(q & 3) * 4], acc[q >> 2][(q & 3) * 4 + 1], acc[q >> 2][(q & 3) * 4 + 2], acc[q >> 2][(q & 3) * 4 + 3]}; };
+#pragma unroll
+            for (int j = 0; j < kMoved; ++j) {
+                const f32x4 lo = quad(j), hi = quad(kMoved + j);
+                ex[(wave * kMoved + j) * kWave + lane] = kh ? lo : hi;
+            }
+#pragma unroll
+            for (int b = 0; b < kBlocks; ++b)
+                if (lane < 32) ex_ss[(wave * kBlocks + b) * 32 + lane] = ssq[b];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            ring_barrier();
+            const int other = wave ^ 4;
+#pragma unroll
+            for (int j = 0; j < kMoved; ++j) {
+                const f32x4 lo = quad(j), hi = quad(kMoved + j);
+                const f32x4 sum = (kh ? hi : lo) + ex[(other * kMoved + j) * kWave + lane];
+                *reinterpret_cast<f32x4*>(zmine + (kh * kMoved + j) * 256) = sum;
+            }
+#pragma unroll
+            for (int b = 0; b < kBlocks; ++b)
+                if (lane < 32 && (kBlocks == 1 ? 0 : b / (kBlocks / 2)) == kh)
+                    p.sspart[((size_t)item * kDmaConsumers + cb) * kRowsM + 32 * b + lane] = ssq[b] + ex_ss[(other * kBlocks + b) * 32 + lane];
         }
     }
     if constexpr (kFused) {
@@ -342,52 +410,57 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_splitk_kernel(con
 // the partial results from this XCD's L2, the epilogue, the report), so it is cut finer than the 32-row blocks of the first
 // launch: an eighth of the loads per lane and a quarter of the SiLUs, which took 0.5-1 us off a call (12.5 -> 11.6 us at C = 1, T = 1024,
 // 14.6 -> 13.6 at 2048, 17.4 -> 16.9 at 3000; width 256, C = 8, T = 200 21.2 -> 18.9).
-template <int kBlocks, int kHalves, int kQ>
+template <int kBlocks, int kHalves, int kQ, int kS>
 __global__ __launch_bounds__(kFinishThreads * kHalves) void tide_splitk_finish_kernel(const PrefillParams p) {
     constexpr int kRows8 = 8 * kQ;
     __shared__ float z_part[4 * kHalves][kRows8];
     __shared__ float ss_part[4][kRows8];
-    constexpr int kRowsM = kBlocks * 32;
-    constexpr int kPartFloats = splitk_part_floats<kBlocks>();
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int half = wave >> 2, w = wave & 3;
-    const int groups = p.total_tiles * kBlocks * (4 / kQ), per_xcd = (groups + 7) >> 3;
-    const int item = p.deal_out ? (int)blockIdx.x : (int)((blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));           // (see the first launch)
-    if (item >= groups || (!p.deal_out && (int)(blockIdx.x >> 3) >= per_xcd)) return;
-    const int quad = (item % (4 / kQ)) * kQ, tb = item / (4 / kQ);
-    const int tile = tb / kBlocks, blk = tb - tile * kBlocks;
-    const int c = tile / p.tiles_per_ckpt;
-    const int row0 = (tile - c * p.tiles_per_ckpt) * kRowsM + 32 * blk + 8 * quad;
-    if (row0 >= p.T) return;                       // padding rows only
-    const int S = p.k_slices;                      // at most kSplitkMaxS
+    constexpr uint32_t kRowsM = kBlocks * 32;
+    constexpr uint32_t kPartBytes = splitk_part_floats<kBlocks>() * sizeof(float);
+    TIDE_FETCH_ARGS16(p.total_tiles, p.tiles_per_ckpt, p.by_tiles.m, p.deal_out, p.k_slices, p.T, p.b, p.b1, p.w2, p.zpart, p.sspart, p.eps, p.C,
+                      p.logits, p.exit_layer, p.arrive);
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = wave >> 2, w = wave & 3;
+    const uint32_t groups = (uint32_t)p.total_tiles * kBlocks * (4 / kQ), per_xcd = (groups + 7) >> 3;
+    const uint32_t item = p.deal_out ? blockIdx.x : (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);           // (see the first launch)
+    if (item >= groups || (!p.deal_out && (blockIdx.x >> 3) >= per_xcd)) return;
+    const uint32_t quad = (item % (4 / kQ)) * kQ, tb = item / (4 / kQ);
+    const uint32_t tile = tb / kBlocks, blk = tb - tile * kBlocks;
+    const uint32_t c = p.by_tiles((int)tile);
+    const uint32_t row0 = (tile - c * p.tiles_per_ckpt) * kRowsM + 32 * blk + 8 * quad;
+    if (row0 >= (uint32_t)p.T) return;             // padding rows only
+    const float b2c = p.tab.b2[c], thr = p.tab.thr_logit[c];
+    const uint32_t S = p.k_slices;                 // at most kS
     // partial accumulators: rows 8 q + 4 (lane / 32) + (0..3) of the block per quad, one column per lane; all slices' loads in
-    // flight (a surplus load re-reads the last slice)
-    const float* zp = p.zpart + (size_t)(tile * kHalves + half) * S * kPartFloats + (size_t)(w * kBlocks + blk) * 1024 + quad * 256 + lane * 4;
-    f32x4 v[kSplitkMaxS][kQ];
+    // flight (a surplus load re-reads the last slice).  Offsets into the partial results have 32 bits: they are 512 MiB at most.
+    const char* zp = reinterpret_cast<const char*>(p.zpart) + ((tile * kHalves + half) * S * kPartBytes + (w * kBlocks + blk) * 4096 + quad * 1024);
+    f32x4 v[kS][kQ];
 #pragma unroll
-    for (int j = 0; j < kSplitkMaxS; ++j)
+    for (uint32_t j = 0; j < kS; ++j) {
 #pragma unroll
-        for (int q = 0; q < kQ; ++q) v[j][q] = *reinterpret_cast<const f32x4*>(zp + (size_t)(j < S ? j : S - 1) * kPartFloats + q * 256);
-    // partial sums of squares (those of column half 0; every half computed the same ones): thread (row, slice, wave of the first launch)
-    float ss[kQ];
-    if (kHalves == 1 || half == 0) {
-        const int j = tid >> 3, sl = j >> 2;
-        const float* sp = p.sspart + ((size_t)(tile * kHalves * S + (sl < S ? sl : S - 1)) * kDmaConsumers + (j & 3)) * kRowsM + 32 * blk + 8 * quad + (tid & 7);
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) ss[q] = sp[8 * q];
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) ss[q] = sl < S ? ss[q] : 0.0f;
+        for (int q = 0; q < kQ; ++q) v[j][q] = *reinterpret_cast<const f32x4*>(zp + (uint32_t)(q * 1024 + lane * 16));
+        if (j + 1 < kS) zp += j + 1 < S ? kPartBytes : 0;
     }
-    // this lane's column of the second layer (columns at and beyond the bottleneck width are zero padding: their w2 is zero)
-    const int col = kBottleneck * half + 32 * w + (lane & 31);
-    const float b1c = (p.b1 && col < p.b) ? p.b1[c * p.b + col] : 0.0f;
-    const float w2c = col < p.b ? p.w2[c * p.b + col] : 0.0f;
-    if (kHalves == 1 || half == 0) {
+    // partial sums of squares (those of column half 0; every half computed the same ones): thread (row, slice, column block of the first launch)
+    const bool squares = kHalves == 1 || half == 0;
+    const uint32_t sl = tid >> 5;
+    float ss[kQ];
+    if (squares) {
+        const char* sp = reinterpret_cast<const char*>(p.sspart) +
+                         ((tile * kHalves * S + (sl < S ? sl : S - 1)) * kDmaConsumers + ((tid >> 3) & 3)) * (kRowsM * 4) + (32 * blk + 8 * quad + (tid & 7)) * 4;
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) ss[q] = *reinterpret_cast<const float*>(sp + 32 * q);
+    }
+    // this lane's column of the second layer (columns at and beyond the bottleneck width are zero padding: their w2 is zero), branch-free
+    const uint32_t col = kBottleneck * half + 32 * w + (lane & 31), at = c * p.b + (col < (uint32_t)p.b ? col : 0);
+    float b1c = (p.b1 ? p.b1 : p.w2)[at], w2c = p.w2[at];
+    if (!p.b1) b1c = 0.0f;
+    if (col >= (uint32_t)p.b) w2c = 0.0f;
+    if (squares) {
 #pragma unroll
         for (int q = 0; q < kQ; ++q) {
-#pragma unroll
-            for (int x = 8; x <= 32; x *= 2) ss[q] += __shfl_xor(ss[q], x, kWave);
-            if (lane < 8) ss_part[w][8 * q + lane] = ss[q];
+            const float t = add_xor<32>(add_xor<16>(add_xor<8>(sl < S ? ss[q] : 0.0f)));
+            if (lane < 8) ss_part[w][8 * q + lane] = t;
         }
     }
     f32x4 sum[kQ];
@@ -395,7 +468,7 @@ __global__ __launch_bounds__(kFinishThreads * kHalves) void tide_splitk_finish_k
     for (int q = 0; q < kQ; ++q) {
         sum[q] = v[0][q];
 #pragma unroll
-        for (int j = 1; j < kSplitkMaxS; ++j) sum[q] += j < S ? v[j][q] : f32x4{0, 0, 0, 0};
+        for (uint32_t j = 1; j < kS; ++j) sum[q] += j < S ? v[j][q] : f32x4{0, 0, 0, 0};
     }
     __syncthreads();
     const int h = lane >> 5;
@@ -417,7 +490,7 @@ __global__ __launch_bounds__(kFinishThreads * kHalves) void tide_splitk_finish_k
         if (t < p.T) {
             float zsum = (z_part[0][tid] + z_part[1][tid]) + (z_part[2][tid] + z_part[3][tid]);
             if constexpr (kHalves == 2) zsum += (z_part[4][tid] + z_part[5][tid]) + (z_part[6][tid] + z_part[7][tid]);
-            emit_router_result(p, c, t, p.tab.b2[c] + zsum);
+            emit_router_result(p, c, t, b2c + zsum, thr);
         }
     }
 }

@@ -61,6 +61,7 @@ constexpr int kDecodeRawMaxT = 8;          // raw weights where the split-k pref
 constexpr int kDecodeMaxT = 64;
 static_assert(kFewMaxTiles <= (int)kCounterSlots, "the few-rows kernel: a counter per row tile");
 constexpr int kSplitkMaxSlices = 8;        // workgroups that share a tile's k range in the split-k prefill form
+constexpr int kSplitkRingBytes = 128 * 1024;   // most LDS for its ring
 constexpr int kSplitkMaxTiles = 128;       // most 128-row tiles' worth of rows (x column halves) the split-k form is considered for ...
 constexpr int kSplitkForcedMaxTiles = 1024;   // ... and when it is forced (tide_set_prefill_form(5)): bounds the partial results at 512 MiB
 
@@ -369,27 +370,32 @@ template <int DT, int kBlocks, bool kRagged> int launch_splitk(float* part, int6
     static bool raised[kMaxDevices] = {};
     int dev = 0;
     TIDE_HIP(hipGetDevice(&dev));
-    constexpr int lds = splitk_lds_bytes<kBlocks>();
+    constexpr int kMostStages = std::min(kSplitkMaxStages, kSplitkRingBytes / splitk_lds_bytes<kBlocks>(1));
     if (!raised[dev]) {
         TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_prefill_splitk_kernel<DT, kBlocks, false, kRagged>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, splitk_lds_bytes<kBlocks>(kMostStages)));
         raised[dev] = true;
     }
     const int halves = halves_of(p.b);
     const size_t items = (size_t)tiles * halves * p.k_slices;
     const size_t z_bytes = items * splitk_part_floats<kBlocks>() * sizeof(float);
+    unsigned cus = 0;
+    const int rc = resident_cus(&cus);
+    if (rc) return rc;
+    // as many k-tiles as a workgroup has, while the workgroups that share a CU have room for them (at least four)
+    const int ntile = p.dpad * Storage<DT>::kBytes / kTileBytes, nk = (ntile + p.k_slices - 1) / p.k_slices, per_cu = (int)((items + cus - 1) / cus);
+    p.ring_stages = std::min({kMostStages, std::max(nk, 4), std::max(4, kMostStages / per_cu)});
+    const int lds = splitk_lds_bytes<kBlocks>(p.ring_stages);
     p.zpart = part;
     p.sspart = (float*)((char*)part + z_bytes);
-    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, kBlocks, false, kRagged>), dim3(8u * (unsigned)((items + 7) / 8)), dim3(kDmaThreads), lds, st, p);
+    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, kBlocks, false, kRagged>), dim3(8u * (unsigned)((items + 7) / 8)), dim3(splitk_threads(false)), lds, st, p);
     // 8 rows per workgroup of the second launch while that is at most one and a half workgroups per CU, else 16 (8 / 16 rows, us): 11.5 / 12.7 at
     // C = 1, T = 1024, 16.9 / 17.4 at C = 8, T = 322 (384 workgroups of 8 rows), 19.8 / 18.8 at C = 1, T = 4096 (512)
     auto finish = [&](auto halves_tag, auto quads_tag) {
         constexpr int kH = decltype(halves_tag)::value, kQ = decltype(quads_tag)::value;
-        hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, kH, kQ>), dim3(8u * (unsigned)((tiles * kBlocks * (4 / kQ) + 7) / 8)), dim3(kH * kFinishThreads), 0, st, p);
+        if (p.k_slices <= 4) hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, kH, kQ, 4>), dim3(8u * (unsigned)((tiles * kBlocks * (4 / kQ) + 7) / 8)), dim3(kH * kFinishThreads), 0, st, p);
+        else hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, kH, kQ, kSplitkMaxS>), dim3(8u * (unsigned)((tiles * kBlocks * (4 / kQ) + 7) / 8)), dim3(kH * kFinishThreads), 0, st, p);
     };
-    unsigned cus = 0;
-    const int rc = resident_cus(&cus);
-    if (rc) return rc;
     const bool fine = 2 * tiles * kBlocks * 4 <= 3 * (int64_t)cus;
     using std::integral_constant;
     if (halves == 2) {
@@ -410,7 +416,8 @@ template <int DT, bool kRagged> int launch_splitk_fused(float* part, uint32_t* c
     p.zpart = part;
     p.sspart = (float*)((char*)part + items * splitk_part_floats<1>() * sizeof(float));
     p.counters = counters;
-    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, 1, true, kRagged>), dim3(8u * (unsigned)((items + 7) / 8)), dim3(kDmaThreads), splitk_lds_bytes<1>(), st, p);
+    p.ring_stages = kDmaStages;
+    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, 1, true, kRagged>), dim3(8u * (unsigned)((items + 7) / 8)), dim3(splitk_threads(true)), splitk_lds_bytes<1>(kDmaStages), st, p);
     return TIDE_OK;
 }
 
@@ -818,6 +825,8 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
         p.total_tiles = L.total_tiles;
         p.tile_begin = L.tile_begin;
         p.k_slices = L.k_slices;
+        p.by_slices = FastDiv::of((uint32_t)L.k_slices);
+        p.by_tiles = FastDiv::of((uint32_t)L.tiles_per_ckpt);
         // a kernel that would read such rows wrongly is never launched on them, whatever the plan says
         auto no_form = [&]() { return fail(TIDE_ERR_UNSUPPORTED, "kernel %d has no form for dtype %d, d = %d", L.kernel, dtype, p.d); };
         auto launch = [&](auto dt, auto ragged_tag) {
