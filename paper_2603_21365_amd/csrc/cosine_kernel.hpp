@@ -14,6 +14,7 @@ struct CosineParams {
     const char* final_hidden;
     int64_t final_row_stride_bytes;
     int C, T, d;
+    int group_bits;    // a token's checkpoints go to 1 << group_bits units, unit g takes checkpoints g, g + (1 << group_bits), ...
     float tau;
     float* sim;        // [C][T] or null
     uint8_t* label;    // [C][T] or null
@@ -48,13 +49,24 @@ template <> __device__ __forceinline__ void chunk_dot<kBF16>(u32x4 a, u32x4 b, f
 }
 #undef TIDE_CHUNK_DOT_ASM
 
-// kChunks = 16-byte chunks of a row held per thread (the host picks the smallest of 4, 8, 16
-// that covers the row: three rows' worth of registers decide the occupancy).
+// kChunks = 16-byte chunks of a row held per thread (the host picks the smallest instantiation that covers the row: three rows'
+// worth of registers decide the occupancy, and a surplus chunk is a load all the same).  A token's checkpoints are dealt out to
+// 1 << group_bits units (waves of one workgroup, or workgroups of one XCD).
 template <int DT, bool kWavePerRow, int kChunks>
 __global__ __launch_bounds__(kCosineThreads) void tide_cosine_kernel(const CosineParams p) {
     __shared__ float part[2][4][2];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int t = kWavePerRow ? blockIdx.x * 4 + wave : blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: a row's base is, too
+    const int step = 1 << p.group_bits;
+    int t, c0;
+    if (kWavePerRow) {
+        const int unit = blockIdx.x * 4 + wave;
+        t = unit >> p.group_bits;
+        c0 = unit & (step - 1);
+    } else {
+        const int u = blockIdx.x >> 3;                              // workgroup ids 8 apart share an XCD, whose L2 has the last layer's row
+        t = ((u >> p.group_bits) << 3) | (blockIdx.x & 7);
+        c0 = u & (step - 1);
+    }
     const bool live = t < p.T;
     const int tt = live ? t : p.T - 1;             // dead waves shadow the last token and store nothing
     const int nchunk = p.d * Storage<DT>::kBytes / 16;
@@ -62,8 +74,8 @@ __global__ __launch_bounds__(kCosineThreads) void tide_cosine_kernel(const Cosin
     const int first = kWavePerRow ? lane : tid;
 
     auto reduce2 = [&](float& a, float& b, int slot) {
-        a = xor_reduce_sum<6>(a);
-        b = xor_reduce_sum<6>(b);
+        a = wave_sum(a);
+        b = wave_sum(b);
         if (!kWavePerRow) {
             if (lane == 0) { part[slot][wave][0] = a; part[slot][wave][1] = b; }
             __syncthreads();
@@ -71,36 +83,38 @@ __global__ __launch_bounds__(kCosineThreads) void tide_cosine_kernel(const Cosin
             b = (part[slot][0][1] + part[slot][1][1]) + (part[slot][2][1] + part[slot][3][1]);
         }
     };
+    // The next checkpoint's row is requested before this one's is reduced, so that a wave
+    // always has a row in flight.
+    uint32_t at[kChunks];                          // byte offsets of the thread's chunks, clamped: in bounds and branch-free
+#pragma unroll
+    for (int j = 0; j < kChunks; ++j) at[j] = 16u * (uint32_t)min(first + j * stride, nchunk - 1);
+    auto fetch = [&](int c, u32x4 (&x)[kChunks]) {
+        const char* row = p.hidden + (int64_t)c * p.ckpt_stride_bytes + (int64_t)tt * p.row_stride_bytes;
+#pragma unroll
+        for (int j = 0; j < kChunks; ++j) {
+            const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(row + at[j]));
+            x[j] = first + j * stride < nchunk ? v : u32x4{0, 0, 0, 0};
+        }
+    };
 
-    const u32x4* fin = reinterpret_cast<const u32x4*>(p.final_hidden + (int64_t)tt * p.final_row_stride_bytes);
-    u32x4 y[kChunks];
+    const char* fin = p.final_hidden + (int64_t)tt * p.final_row_stride_bytes;
+    u32x4 y[kChunks], xa[kChunks], xb[kChunks];
     float nl = 0.0f, unused = 0.0f;
 #pragma unroll
     for (int j = 0; j < kChunks; ++j) {
-        const int q = first + j * stride;
-        const u32x4 v = fin[min(q, nchunk - 1)];     // clamped: in bounds and branch-free
-        y[j] = q < nchunk ? v : u32x4{0, 0, 0, 0};
+        const u32x4 v = *reinterpret_cast<const u32x4*>(fin + at[j]);
+        y[j] = first + j * stride < nchunk ? v : u32x4{0, 0, 0, 0};
     }
+    fetch(c0, xa);
 #pragma unroll
     for (int j = 0; j < kChunks; ++j) nl = chunk_sumsq<DT>(y[j], nl);
     reduce2(nl, unused, 0);
 
-    // The next checkpoint's row is requested before this one's is reduced, so that a wave
-    // always has a row in flight.
-    auto fetch = [&](int c, u32x4 (&x)[kChunks]) {
-        const u32x4* row = reinterpret_cast<const u32x4*>(p.hidden + (int64_t)c * p.ckpt_stride_bytes + (int64_t)tt * p.row_stride_bytes);
-#pragma unroll
-        for (int j = 0; j < kChunks; ++j) {
-            const int q = first + j * stride;
-            const u32x4 v = __builtin_nontemporal_load(row + min(q, nchunk - 1));
-            x[j] = q < nchunk ? v : u32x4{0, 0, 0, 0};
-        }
-    };
-    auto finish = [&](int c, const u32x4 (&x)[kChunks]) {
+    auto finish = [&](int c, const u32x4 (&x)[kChunks], int slot) {
         float dot = 0.0f, nk = 0.0f;
 #pragma unroll
         for (int j = 0; j < kChunks; ++j) chunk_dot<DT>(x[j], y[j], dot, nk);
-        reduce2(dot, nk, (c & 1) ? 0 : 1);         // alternate the LDS slot so one barrier per checkpoint suffices
+        reduce2(dot, nk, slot);                    // alternate the LDS slot so one barrier per checkpoint suffices
         const float s = dot / (sqrtf(nk) * sqrtf(nl));
         if (live && (kWavePerRow ? lane == 0 : tid == 0)) {
             const int64_t o = (int64_t)c * p.T + t;
@@ -108,14 +122,12 @@ __global__ __launch_bounds__(kCosineThreads) void tide_cosine_kernel(const Cosin
             if (p.label) p.label[o] = s > p.tau ? 1 : 0;
         }
     };
-    u32x4 xa[kChunks], xb[kChunks];
-    fetch(0, xa);
-    for (int c = 0; c < p.C; c += 2) {
-        if (c + 1 < p.C) fetch(c + 1, xb);
-        finish(c, xa);
-        if (c + 1 < p.C) {
-            if (c + 2 < p.C) fetch(c + 2, xa);
-            finish(c + 1, xb);
+    for (int c = c0; c < p.C; c += 2 * step) {
+        if (c + step < p.C) fetch(c + step, xb);
+        finish(c, xa, 1);
+        if (c + step < p.C) {
+            if (c + 2 * step < p.C) fetch(c + 2 * step, xa);
+            finish(c + step, xb, 0);
         }
     }
 }

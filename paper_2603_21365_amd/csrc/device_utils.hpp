@@ -141,6 +141,14 @@ template <int kXor> __device__ __forceinline__ float add_xor(float v) {
     return a + b;
 }
 
+// xor_reduce_sum<6> without its six LDS round trips: the same pairs are added in the same order, so the bits are the same.
+__device__ __forceinline__ float wave_sum(float v) {
+    v += dpp_f32<kDppXor1>(v);
+    v += dpp_f32<kDppXor2>(v);
+    v += dpp_f32<kDppHalfMirror>(v);               // quads hold equal values by now: 7 - i is as good as i ^ 4
+    return add_xor<32>(add_xor<16>(add_xor<8>(v)));
+}
+
 // Sum each of 16 per-lane values over the 32 lanes that share lane>>5, leaving every lane
 // with ONE finished total (a reduce-scatter: 8+4+2+1+1 exchanges instead of 16 x 5).
 // The total a lane ends up with is that of index v = bits (4,3,2,1) of its lane id; lanes

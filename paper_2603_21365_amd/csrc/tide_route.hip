@@ -1721,7 +1721,24 @@ int tide_cosine_labels(const void* hidden, int dtype, int64_t C, int64_t T, int6
     p.sim = sim;
     p.label = label;
     const bool wave_per_row = row_bytes <= (int64_t)kCosineMaxChunks * 16 * kWave;
-    const unsigned grid = wave_per_row ? (unsigned)((T + 3) / 4) : (unsigned)T;
+    // Units per token (1, 2 or 4) that its checkpoints are dealt out to: more of them are more waves in flight and a shorter chain per wave, but
+    // each reads the last layer's row.  While one wave per token leaves the chip empty more units win whatever they read: four (us, 1 / 2 / 4 units,
+    // kernels back to back in a graph) bf16, C = 8, d = 768 7.7 / 5.0 / 3.8 at T = 340, 9.0 / 6.2 / 5.4 at 1360; d = 4096 14.3 / 8.9 / 7.3 and
+    // 14.9 / 10.5 / 9.6 at 600, then two: 16.3 / 13.1 / 13.8 at 1000, 19.2 / 17.3 / 17.4 at 1360; short rows two up to 2600: 9.3 / 7.3 / 7.6 at 2200 (d = 768).
+    // Once one unit's waves are a full round of the chip (and not two) they win: d = 4096, T = 1700, C = 5 14.9 / 16.2 / 15.2, d = 1024, C = 4,
+    // T = 3600 7.6 / 7.8 / 7.9.  Longer rows in many waves balance better in four: d = 4096 28.8 / 28.5 / 26.6 at 2200, 65.8 / 60.9 / 59.2 at 5440, d = 8192
+    // 126 / 120 / 118, fp32 d = 2560 97 / 90 / 90.  A workgroup per row (rows above 16 KiB): two for few or
+    // many, fp32, d = 8192, C = 9 23.0 / 20.8 at T = 350, 61 / 57 at 1100, C = 5 163 / 157 / 177 at 5440; one between, d = 5120 24.9 / 27.9 at 758.
+    // (Four chunks per thread before, and eight for five or six: bf16, C = 5, d = 5120 80 -> 50 at T = 5440; C = 8, d = 4096, T = 1360 20.0 -> 17.3.)
+    const int64_t row_chunks = row_bytes / 16;
+    if (!wave_per_row) p.group_bits = C > 1 && (T <= 400 || T > 1000) ? 1 : 0;
+    else if (C < 4) p.group_bits = C > 1 && T <= 1500 ? 1 : 0;
+    else if (T <= (row_chunks <= 320 ? 1000 : 700)) p.group_bits = 2;
+    else if (T <= 1500) p.group_bits = 1;
+    else if (row_chunks <= 256) p.group_bits = T <= 2600 ? 1 : 0;
+    else p.group_bits = T <= 1900 ? 0 : 2;
+    const int64_t units = T << p.group_bits;
+    const unsigned grid = wave_per_row ? (unsigned)((units + 3) / 4) : (unsigned)(((T + 7) / 8 * 8) << p.group_bits);
     const int64_t per_thread = (row_bytes / 16 + (wave_per_row ? kWave : kCosineThreads) - 1) / (wave_per_row ? kWave : kCosineThreads);
     hipStream_t st = (hipStream_t)stream;
     by_dtype(dtype, [&](auto dt) {
@@ -1731,8 +1748,14 @@ int tide_cosine_labels(const void* hidden, int dtype, int64_t C, int64_t T, int6
                                dim3(kCosineThreads), 0, st, p);
         };
         auto pick = [&](auto wpr) {
-            if (per_thread <= 4) go(wpr, std::integral_constant<int, 4>{});
+            if (per_thread <= 2) go(wpr, std::integral_constant<int, 2>{});
+            else if (per_thread <= 3) go(wpr, std::integral_constant<int, 3>{});
+            else if (per_thread <= 4) go(wpr, std::integral_constant<int, 4>{});
+            else if (per_thread <= 5) go(wpr, std::integral_constant<int, 5>{});
+            else if (per_thread <= 6) go(wpr, std::integral_constant<int, 6>{});
             else if (per_thread <= 8) go(wpr, std::integral_constant<int, 8>{});
+            else if (per_thread <= 10) go(wpr, std::integral_constant<int, 10>{});
+            else if (per_thread <= 12) go(wpr, std::integral_constant<int, 12>{});
             else go(wpr, std::integral_constant<int, 16>{});
         };
         if (wave_per_row) pick(std::true_type{});
