@@ -525,7 +525,15 @@ struct PrefillPlan {
     PlannedLaunch launch[2];
 };
 
-PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, int form_word, bool ragged = false, bool split_k = true) {
+// The split-k pair's cost (see plan_prefill), us: for 16-bit and fp32 rows, tiles of 32, 64 and 128 rows.
+struct PairCost { double launch, chain, row, slice; };
+constexpr PairCost kPairCost[2][3] = {{{4.7, 0.59, 0.0063, 0.0087}, {4.8, 0.77, 0.0111, 0.0070}, {5.9, 1.07, 0.0119, 0.0059}},
+                                      {{5.3, 0.58, 0.0101, 0.0103}, {6.1, 0.84, 0.0098, 0.0081}, {7.0, 1.47, 0.0095, 0.0070}}};
+int64_t splitk_max_blocks(int dtype, int halves) { return (int64_t)kSplitkMaxTiles * (halves == 1 ? 4 : dtype == TIDE_F32 ? 10 : 6); }
+constexpr double kPairLaunches = 8.3;      // two launches from a host that issues them back to back
+
+PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, int form_word, bool ragged = false, bool split_k = true,
+                         size_t most_part = SIZE_MAX) {
     PrefillPlan plan;
     const int form = form_word & 0xff, force_rows = (form_word >> 8) & 0xff, force_slices = (form_word >> 16) & 0xff;
     const int64_t eb = (int64_t)elem_bytes(dtype);
@@ -573,19 +581,24 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     // dependent chain of k-tiles, longer per k-tile the taller the tile), on how many workgroups that
     // makes (beyond one per CU they run in rounds) and on the volume of partial results (16 KiB per
     // workgroup and 32-row block), so the choice compares cost estimates, in microseconds, fitted to
-    // measurements on a 256-CU device (d = 1024 ... 8192, 32 ... 8192 rows, widths 128 and 256), with
+    // measurements on a 256-CU device (d = 768 ... 8192, 100 ... 16384 rows, C = 1, 6 and 8; within 4-5 % rms), with
     // n = k-tiles of a row, B = 32-row blocks per tile, S = slices, R = 32-row blocks of the whole call
     // (x 2 at width 256), W = workgroups:
-    //   streaming, few tiles:  5.7 + 0.48 n + 0.07 (n / 32) (tiles of 128 rows)   (width 256: 7.0 + 1.17 n; fp32 rows,
-    //                          register-ring form: 8.5 + 0.75 n)
-    //   split-k pair:          a_B + c_B ceil(n / S) ceil(W / CUs) + (0.011 n / 32 + 0.009 S) R
-    //                          with (a_B, c_B) = (8.5, 0.50), (8.9, 0.60), (9.6, 0.92) for B = 1, 2, 4
-    //                          (fp32 rows: c_B = 0.65, 0.90, 1.61)
+    //   streaming, few tiles:  5.1 + 0.45 n + 0.089 (n / 32) (tiles of 128 rows); fp32 rows, register-ring form:
+    //                          5.5 + 0.84 n + 0.026 (n / 32) (tiles of 128 rows); width 256: 3.4 + 1.4 n, fp32 rows
+    //                          2.5 + 1.87 n per round of 64-row tiles
+    //   split-k pair:          launch + chain ceil(n / S) ceil(W / CUs) + (row n / 32 + slice S) R   (kPairCost, by type and B),
+    //                          and no less than the host takes to issue two launches (where they are two)
+    // The pair has to be 8 % cheaper, twice what the estimates are good for.  What that moved (us, before / after):
+    // bf16, C = 1: d = 5120, T = 5000 24.5 / 21.1, d = 2048, T = 3000 12.7 / 9.9, d = 4096, T = 5000 20.8 / 18.4; C = 8, d = 8192, T = 700 36.3 / 31.4;
+    // fp32, C = 6: d = 5120, T = 700 47.9 / 41.3, d = 768, T = 700 16.6 / 14.2; fp32, width 256, C = 6: d = 1024, T = 600 31.8 / 17.9, d = 4096 121 / 70 at
+    // T = 1000 and 125 / 110 at 1500 (the streaming form's 64-row tiles leave CUs idle there, and past one round it takes two: five times
+    // as many blocks as otherwise are the pair's to compare).
     // Forced (form 5) the cheapest shape is taken whatever the streaming estimate says, and the form
     // word may fix the tile height (bits 8-15) and the slice count (bits 16-23).
     if (!generic_d && split_k && (form == 0 || form == 5 || form == 8)) {
         const int64_t ntile = d * eb / kTileBytes;
-        const int64_t max_blocks = form == 5 ? (int64_t)kSplitkForcedMaxTiles * 4 : (int64_t)kSplitkMaxTiles * 4;
+        const int64_t max_blocks = form == 5 ? (int64_t)kSplitkForcedMaxTiles * 4 : splitk_max_blocks(dtype, halves);
         double best = 1e30;
         int best_rows = 0;
         int64_t best_S = 0;
@@ -593,25 +606,25 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
             if (form == 8 && rows != 32) continue;                                         // the single-launch form has 32-row tiles
             if (force_rows ? rows != force_rows : (rows > 32 && 2 * T <= rows)) continue;   // never a tile that is mostly padding
             const int64_t tiles = C * ((T + rows - 1) / rows);
-            const double B = rows / 32, R = (double)(tiles * halves) * B;
-            const double launch_cost = rows == 32 ? 8.5 : rows == 64 ? 8.9 : 9.6;
-            const double row_cost = 0.011 * (double)ntile / 32.0;                 // reading a 32-row block's rows: by their length
-            const double chain_cost = dtype == TIDE_F32 ? (rows == 32 ? 0.65 : rows == 64 ? 0.90 : 1.61)     // three matrix steps per value
-                                                        : (rows == 32 ? 0.50 : rows == 64 ? 0.60 : 0.92);
+            const double R = (double)(tiles * halves * (rows / 32)), lines = (double)ntile / 32.0;
+            const PairCost& cost = kPairCost[dtype == TIDE_F32][rows / 64];
+            const bool one_launch = form != 5 && rows == 32 && halves == 1 && tiles <= (int64_t)kCounterSlots && T <= 16;     // see `fused` below
+            const double least = one_launch ? 0.0 : kPairLaunches;
             if (tiles * halves * (rows / 32) > max_blocks) continue;
             for (int64_t s = kSplitkMaxSlices; s >= 2; s /= 2) {
                 const int64_t S = std::min<int64_t>(ntile, s);
                 if (S < 2 || (force_slices && s != force_slices)) continue;
+                if (splitk_part_bytes(rows / 32, (int)tiles, halves, (int)S) > most_part) continue;
                 const int64_t W = tiles * halves * S;
-                const double t = launch_cost + chain_cost * (double)((ntile + S - 1) / S) * (double)((W + cus - 1) / cus) +
-                                 (row_cost + 0.009 * (double)S) * R;
+                const double t = std::max(least, cost.launch + cost.chain * (double)((ntile + S - 1) / S) * (double)((W + cus - 1) / cus) +
+                                                         (cost.row * lines + cost.slice * (double)S) * R);
                 if (t < best) { best = t; best_rows = rows; best_S = S; }
             }
         }
-        const double t_stream = dtype == TIDE_F32 ? 8.5 + 0.75 * (double)ntile     // the register-ring form
-                              : halves == 1 ? 5.7 + 0.48 * (double)ntile + 0.07 * ((double)ntile / 32.0) * (double)tiles128
-                                            : 7.0 + 1.17 * (double)ntile;
-        if (best_rows && (form == 5 || form == 8 || best + 0.3 < t_stream)) {
+        const double t_stream = halves == 2 ? (dtype == TIDE_F32 ? (2.5 + 1.87 * (double)ntile) * (double)((tiles64 + cus - 1) / cus) : 3.4 + 1.4 * (double)ntile)
+                              : dtype == TIDE_F32 ? 5.5 + 0.84 * (double)ntile + 0.026 * ((double)ntile / 32.0) * (double)tiles128     // the register-ring form
+                                                  : 5.1 + 0.45 * (double)ntile + 0.089 * ((double)ntile / 32.0) * (double)tiles128;
+        if (best_rows && (form == 5 || form == 8 || best < 0.92 * t_stream)) {
             const int64_t tpc = (T + best_rows - 1) / best_rows, tiles = C * tpc;
             // One launch instead of two where the kernel has it (32-row tiles, one column half, a counter per tile) and
             // where it is faster: the finishing workgroup reads the partial results past every cache, so it wins while
@@ -774,10 +787,11 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
 // d = 4104, C = 8, T = 200: 38 -> 12.5; fp32, d = 4000, C = 9, T = 300: 161 -> 28; bf16, d = 1608, C = 8, T = 3000: 31 -> 26 (before: the register-ring
 // form, whose loads are selected chunk by chunk).  (split_k: the split-k pair only where its partial results do not
 // have to fit a block that was sized without them.)
-PrefillPlan call_plan(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, int variant, int form_word, bool split_k) {
+PrefillPlan call_plan(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, int variant, int form_word, bool split_k,
+                      size_t most_part = SIZE_MAX) {
     if (variant == TIDE_VARIANT_AUTO && form_word == 0 && d % 128 != 0)
-        return plan_prefill(dtype, C, T, padded_hidden(dtype, d), b, cus, 0, true, split_k);
-    return plan_prefill(dtype, C, T, d, b, cus, form_word);
+        return plan_prefill(dtype, C, T, padded_hidden(dtype, d), b, cus, 0, true, split_k, most_part);
+    return plan_prefill(dtype, C, T, d, b, cus, form_word, false, true, most_part);
 }
 
 // What the prefill kernels and the few-rows kernel take, all but the tiling.
@@ -997,42 +1011,45 @@ bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, i
     return !packed_given && T <= kDecodeRawMaxT;
 }
 
-// The few-rows kernel (a workgroup per 16 rows and 16 columns, all of k) or the paths above?  It is the faster one as long
-// as its workgroups fit the chip once and the checkpoints are not too many (256 CUs, packed weights, against the split-k forms, us:
-// C = 8, d = 4096: 8.7 -> 6.3 at T = 1, 9.5 -> 7.3 at 16, 11.3 -> 8.5 at 48, 11.3 -> 9.2 at 64 = 256 workgroups; fp32 rows, d = 5120, C = 8, T = 64:
-// 15.7 -> 15.1) and, with rows of up to 8 KiB, up to one and a half workgroups per CU (two are resident): 11.8 -> 11.4 at
-// T = 96, 11.6 -> 11.4 at C = 1, T = 768, level from there on; longer rows lose there (d = 8192, C = 10, T = 96: 15.8 -> 18.1).
-// Rows above 20 KiB pass through one workgroup's LDS for longer than split-k takes unless the rows of a tile or the workgroups are few:
-//   up to 8 rows always (fp32, d = 8192, C = 8: 17.0 -> 16.1; bf16, d = 16384, C = 1 / 8: 12.5 -> 12.3, 14.6 / 14.8);
+// The few-rows kernel (a workgroup per 16 rows and 16 columns, all of k) or the paths above?  Its one launch beats the split-k pair's two
+// (8.3 us from a host that issues them back to back, whatever the kernels take, and 2-3 us more where the exit projection follows) until a workgroup
+// has to walk long rows or the workgroups are more than the CUs; the lines lie where the few-rows kernel takes 9 us (256 CUs, packed weights, bf16
+// unless said, few rows / pair, us, at a share w of the CUs):
+//   rows up to 4 KiB:   C = 8, d = 1024: 7.0 / 9.1 at w = 0.75, 7.5 / 8.3 at 1, 8.8 / 7.8 at 1.5; d = 2048 7.5 / 8.7, 8.8 / 8.5; fp32, d = 1024 7.9 / 8.4,
+//                       9.3 / 7.8; with the exit projection, C = 5, d = 2048, 11.5 / 13.4 at 1.1; d = 1448, C = 8: 8.9 / 7.3 at 1.5, 9.8 / 7.5 at 2 -- 1.5;
+//   up to 6 KiB:        d = 2560: 8.3 / 8.4 at 0.75, 8.9 / 8.2 at 1, 10.7 / 7.9 at 1.5; d = 3072 with the projection 12.4 / 13.5 at 0.94 -- 1;
+//   up to 8 KiB:        d = 4096: 8.3 / 8.9 at 0.66, 8.6 / 8.2 at 0.75, 9.4 / 8.4 at 1, 11.5 / 8.8 at 1.5; fp32, d = 2048 9.1 / 9.1, 9.8 / 9.1 at 1, 12.5 / 9.6; width 64
+//                       with the projection 12.9 / 14.1 at 0.875; width 256, C = 2: 9.0 / 8.6 at 0.5, 10.3 / 9.4 at 1 -- seven eighths;
+//   longer:             d = 5120: 9.1 / 8.2 at 0.28, 9.4 / 8.8 at 0.5, 10.9 / 9.1 at 1; fp32, d = 2560 9.7 / 9.4 at 0.28, d = 5120 13.6 / 12.3, 15.5 / 13.2 at 1 -- never.
+// Up to 16 rows per checkpoint the other path is the one-launch split-k form or, at width 256, a pair that is mostly padding, and the lines are:
+// rows up to 20 KiB whenever the workgroups fit the chip (C = 8, d = 4096: 8.7 -> 6.3 at T = 1, 9.5 -> 7.3 at 16);
+//   longer ones: up to 8 rows always (fp32, d = 8192, C = 8: 17.0 -> 16.1; bf16, d = 16384, C = 1 / 8: 12.5 -> 12.3, 14.6 / 14.8);
 //   9 to 16 rows meet the one-launch split-k form at widths 64 / 128 (bf16 at T = 12 / 16: d = 12288 11.8 -> 11.4, but 11.7 / 12.5, d = 16384 13.2 / 13.9, 13.2 / 15.4;
-//   fp32: d = 6144 14.8 -> 13.0, 14.7 -> 14.1; d = 8192 17.2 -> 16.1, but 17.1 / 17.4 and 17.8 / 18.9 at C = 8), not at 256 (fp32, d = 8192, C = 8: 21.1 -> 20.6);
-//   more rows: at 24 KiB up to three quarters of the CUs (fp32, C = 4: 16.7 -> 16.6 at T = 96, but 16.8 / 17.2 at 128; width 256 half: 17.4 -> 17.0 at C = 2, T = 64,
-//   but 17.9 / 18.1 at 128), at 28 KiB a quarter (17.1 -> 16.8 at C = 1, T = 128, but 18.0 / 18.4 at C = 4, T = 96), at 32 KiB three sixteenths (18.1 -> 17.6 at C = 2,
-//   T = 32, but 18.2 / 18.9 at 64 and 19.5 / 21.4 at C = 8).
-// Weights that this call packed come from memory, and 40 workgroups ask for them more slowly than split-k's 256: one or two checkpoints' of 4 MiB
-// and more go to the pair (fp32, d = 8192, C = 1, T = 40: 22.2 / 24.1 us; bf16, width 256: 16.5 / 17.3).
+//   fp32: d = 6144 14.8 -> 13.0, 14.7 -> 14.1; d = 8192 17.2 -> 16.1, but 17.1 / 17.4 and 17.8 / 18.9 at C = 8), not at 256 (fp32, d = 8192, C = 8: 21.1 -> 20.6).
 // Rows of 64 KiB (fp32, d = 16384) are level at best.  Every workgroup of a row tile ticks the tile's counter (14 ns each), which from 128 ticks on costs what
 // the kernel gains against the 128-column split-k forms (width 256, where those take twice the workgroups, does not meet that line: 1.03-1.6 times
 // up to 240 ticks).  17 to 24 checkpoints at width 128: up to 16 rows still for 4 rows or rows of 4 KiB (f16, C = 24: 1.2 times at d = 768, T = 1, 1.05 at T = 4, d = 5120,
 // but bf16, C = 20: 8.6 / 9.1 us at T = 8, 9.4 / 10.1 at 16, d = 2560); more rows for fp32 or rows of 8 KiB (f16, C = 24: 1.12 times at d = 5120, T = 32, but bf16 9.3 / 10.3 us at
 // d = 1024, 11.2 / 12.0 at 2560).  More checkpoints: 9.9 / 11.4 at C = 28, T = 16, d = 2560, 9.3 / 10.4 at T = 8.  Beyond one workgroup per CU rows of up to
-// 2 KiB meet it from 112 ticks on (C = 16, T = 33, d = 1024: 9.2 / 9.6; d = 2560 11.6 / 10.8).
-// Hidden sizes that are no multiple of 128 go to the register-ring kernel otherwise (18.9 -> 9.3 us at C = 8, T = 100, d = 1600):
-// there up to two workgroups per CU.
-bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool raw_weights, unsigned cus) {
+// 2 KiB meet it from 112 ticks on (C = 16, T = 33, d = 1024: 9.2 / 9.6).
+// Hidden sizes that are no multiple of 128 have no split-k form on the calls that would be the latency kernel's (d = 1600 at T <= 32: 25-50 us against 6-9) and
+// none in a block that was sized without it (`pair` false; the register-ring kernel, 18.9 -> 9.3 us at C = 8, T = 100, d = 1600): there up to
+// two workgroups per CU; with the pair they follow the lines above (d = 2904, C = 8: 8.3 / 8.7 at T = 48, 10.7 / 8.2 at 96; d = 4304 14.2 / 9.3).
+bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, bool pair) {
     const int64_t tiles = (T + kFewRows - 1) / kFewRows, nbk = b / kFewCols, row_bytes = d * (int64_t)elem_bytes(dtype);
     if (tiles > kFewMaxTiles || C * nbk >= 256 || row_bytes > 32768) return false;
     const int64_t W = C * tiles * nbk, n = (int64_t)cus;
     const bool few_ticks = C * nbk <= 112 || row_bytes > 2048;
-    if (d % 128 != 0) return W <= (few_ticks ? 2 * n : n);
-    if (raw_weights && d >= 8192 && C * b <= 256 && T > kFewRows && d * b * (int64_t)elem_bytes(dtype) >= 4 << 20) return false;
+    if (d % 128 != 0 && (!pair || C * nbk > 128)) return W <= (few_ticks ? 2 * n : n);
     if (b <= 128 && C * nbk >= 200) return false;
     if (b <= 128 && C * nbk > 128 && !(T <= kFewRows ? T <= 4 || row_bytes <= 4096 : dtype == TIDE_F32 || row_bytes >= 8192)) return false;
-    if (row_bytes <= 20480) return W <= n || (row_bytes <= 8192 && few_ticks && 2 * W <= 3 * n);
-    if (T <= 8 || (T <= kFewRows && b == 256)) return W <= n;
-    if (T <= kFewRows) return W <= n && (dtype == TIDE_F32 ? T <= 12 || row_bytes <= 24576 : T <= 12 && row_bytes <= 24576);
-    if (row_bytes <= 24576) return b == 256 ? 2 * W <= n : 4 * W <= 3 * n;
-    return row_bytes <= 28672 ? 4 * W <= n : 16 * W <= 3 * n;
+    if (T > kFewRows) {
+        if (row_bytes > 8192) return false;
+        if (row_bytes > 6144) return 8 * W <= 7 * n;
+        return W <= n || (row_bytes <= 4096 && few_ticks && 2 * W <= 3 * n);
+    }
+    if (row_bytes <= 20480 || T <= 8 || b == 256) return W <= n;
+    return W <= n && (dtype == TIDE_F32 ? T <= 12 || row_bytes <= 24576 : T <= 12 && row_bytes <= 24576);
 }
 
 // ---- What a router call needs of scratch memory, and which path it takes: host arithmetic only.
@@ -1053,7 +1070,7 @@ struct CallNeed {
 size_t round256(size_t n) { return (n + 255) & ~size_t(255); }
 
 CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool raw_weights, bool want_exit, unsigned cus, int variant,
-                   int form_word, bool library, bool allow_few = true) {
+                   int form_word, bool library, bool allow_few = true, size_t most_part = SIZE_MAX) {
     CallNeed n;
     n.state_bytes = round256(kCounterSlots * sizeof(uint32_t)) + (want_exit ? round256((size_t)T * sizeof(uint64_t)) : 0);
     const bool repack = needs_repack(dtype, d, b);
@@ -1068,7 +1085,7 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
     }
     // (the other paths' needs are counted all the same for a caller's block: what a caller has to bring does not depend on this choice)
     n.few = allow_few && !(raw_weights && n.decode) && variant == TIDE_VARIANT_AUTO && form_word == 0 &&
-            use_few_rows(dtype, C, T, n.d_run, b, raw_weights, cus);
+            use_few_rows(dtype, C, T, n.d_run, b, cus, library && !n.decode);
     // fp32 rows that are the latency kernel's otherwise: it multiplies the whole fp32 value of a row by both terms of the weight, the other kernels
     // for packed weights the row's two leading bf16 terms (error against 64 bits at T = 32, d = 1000: 2.6e-6 / 4.7e-6).  16-bit rows are exact in any.
     n.few_full = n.few && n.decode;
@@ -1080,7 +1097,7 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
         return n;
     }
     if (raw_weights) n.packed_bytes = round256((size_t)C * tide_packed_router_bytes(dtype, d, b));
-    n.plan = call_plan(dtype, C, T, n.d_run, b, cus, variant, form_word, library);
+    n.plan = call_plan(dtype, C, T, n.d_run, b, cus, variant, form_word, library, most_part);
     for (int i = 0; i < n.plan.count; ++i) {
         const PlannedLaunch& L = n.plan.launch[i];
         if (L.kernel == kKernelSplitK || L.kernel == kKernelSplitKFused) n.part_bytes = round256(splitk_part_bytes(L.rows_per_tile / 32, L.total_tiles, halves, L.k_slices));
@@ -1099,7 +1116,7 @@ size_t largest_part(int dtype, int64_t C, int64_t from, int64_t to, int64_t d, i
     size_t most = std::min<size_t>(round256((size_t)(to * C * (b / kFewCols)) * sizeof(float)), (size_t)cus * 2 * kFewRows * sizeof(float));
     auto at = [&](int64_t t) { most = std::max(most, call_need(dtype, C, t, d, b, raw_weights, false, cus, TIDE_VARIANT_AUTO, 0, true).part_bytes); };
     if (from == 0) at(kDecodeRawMaxT);
-    for (int64_t t = from + 32; t <= to && C * halves_of(b) * (t / 32) <= 4 * kSplitkMaxTiles; t += 32) at(t);
+    for (int64_t t = from + 32; t <= to && C * halves_of(b) * (t / 32) <= splitk_max_blocks(dtype, halves_of(b)); t += 32) at(t);
     return most;
 }
 
@@ -1171,6 +1188,10 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
     // a block that holds what the call needs on the other paths is enough
     if (need.few && source != kScratchLibrary && need.total() > (source == kScratchCaller ? block_bytes : kStaticScratchBytes))
         need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, source == kScratchLibrary, false);
+    // the fixed array: a pair with fewer partial results, or none, rather than no call
+    if (source == kScratchStatic && g_prefill_form == 0 && need.total() > kStaticScratchBytes && need.total() - need.part_bytes <= kStaticScratchBytes)
+        need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false, false,
+                         kStaticScratchBytes - (need.total() - need.part_bytes));
 
     auto capturing = [&]() {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
