@@ -230,37 +230,24 @@ __global__ __launch_bounds__(kWideThreads, 1) void tide_prefill_band_f32_kernel(
             continue;
         }
         const int c = t.c, row0 = (t.block0 + wb) * 32;
-        f32x16 acc[4];
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x16{0};
-        float ssq = 0.0f;
-        for (int k = 0; k < nstage; ++k) {
-            ring_barrier();
-            const char* sa = a_ring + (stage % kStages) * kABytes + a_row;
-            const char* sb = b_ring + (stage % kStages) * kWide32BBytes + lane * 16;
-#pragma unroll
-            for (int gi = 0; gi < (kPair ? 1 : 2); ++gi) {
-                const int g = kPair ? kg_u : gi;
-                const u32x4 c0 = *reinterpret_cast<const u32x4*>(sa + (((4 * g + 2 * h) ^ a_swz) << 4));
-                const u32x4 c1 = *reinterpret_cast<const u32x4*>(sa + (((4 * g + 2 * h + 1) ^ a_swz) << 4));
-                float x[8] = {__uint_as_float(c0.x), __uint_as_float(c0.y), __uint_as_float(c0.z), __uint_as_float(c0.w),
-                              __uint_as_float(c1.x), __uint_as_float(c1.y), __uint_as_float(c1.z), __uint_as_float(c1.w)};
-                __bf16 hi[8], mid[8];
-                split_bf16(x, 8, hi, mid);
-                bf16x8 h8, m8;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { h8[e] = hi[e]; m8[e] = mid[e]; }
-                const u32x4 ah = __builtin_bit_cast(u32x4, h8), am = __builtin_bit_cast(u32x4, m8);
-                ssq = chunk_sumsq<kF32>(c1, chunk_sumsq<kF32>(c0, ssq));
-#pragma unroll
-                for (int nb = 0; nb < 4; ++nb) {
-                    const u32x4 bh = *reinterpret_cast<const u32x4*>(sb + (g * 4 + nb) * 1024);
-                    const u32x4 bm = *reinterpret_cast<const u32x4*>(sb + kWide32PlaneBytes + (g * 4 + nb) * 1024);
-                    acc[nb] = mma_k16_split(ah, am, bh, bm, acc[nb]);
-                }
-            }
+        Wide32Steps steps;
+        steps.clear();
+        auto read = [&](int g, auto multiply_tag) {
+            steps.template advance<decltype(multiply_tag)::value>(a_ring + (stage % kStages) * kABytes + a_row, b_ring + (stage % kStages) * kWide32BBytes + lane * 16, g, h, a_swz);
+        };
+        ring_barrier();
+        read(kPair ? kg_u : 0, std::false_type{});
+        if constexpr (!kPair) read(1, std::true_type{});
+        ++stage;
+        for (int k = 1; k < nstage; ++k) {
+            wide32_hand_over();
+            read(kPair ? kg_u : 0, std::true_type{});
+            if constexpr (!kPair) read(1, std::true_type{});
             ++stage;
         }
+        steps.finish();
+        f32x16 (&acc)[4] = steps.acc;
+        const float ssq = steps.ssq;
         float xs[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) xs[v] = 0.0f;

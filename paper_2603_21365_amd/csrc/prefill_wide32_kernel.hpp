@@ -15,6 +15,8 @@
 // after the k loop at all.
 // Bottleneck widths 64 / 128, d a multiple of 128.
 #pragma once
+#include <type_traits>
+
 #include "device_utils.hpp"
 #include "prefill_dma_kernel.hpp"
 #include "prefill_wide_kernel.hpp"
@@ -26,6 +28,69 @@ constexpr int kWide32ABytes = kWideRows * kWideTileBytes;                 // 32 
 constexpr int kWide32PlaneBytes = (kWideTileBytes / 4 / 16) * 4096;       // one plane of W1' per stage: 2 groups x 4 KiB
 constexpr int kWide32BBytes = 2 * kWide32PlaneBytes;                      // 16 KiB
 constexpr int kWide32LdsBytes = kWide32Stages * (kWide32ABytes + kWide32BBytes) + kWideConsumers * 32 * (int)sizeof(float);
+
+// What a consumer wave has in registers: its 32 rows' 128 accumulators and the fragments of ONE step of 16 values of k, which is read while
+// the step before it is multiplied, each fragment into the registers of the one just used.  The waves leave a barrier together: with a step's reads
+// and conversions in front of its own products the matrix cores idle while all eight waves wait for LDS (fp32, d = 2560, C = 10, T = 3001 on the band
+// kernel: 88.3 -> 79.5 us; C = 8, T = 4096, d = 4096: 128 -> 123).  The products of a value and the sums are the same, in the same order.
+struct Wide32Steps {
+    f32x16 acc[4];
+    u32x4 ah, am, bh[4], bm[4];
+    float ssq;
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x16{0};
+        ssq = 0.0f;
+    }
+    // Reads step g of the stage at sa (this lane's row) and sb (this lane's chunk of W1'); kMultiply: and multiplies what was read before.
+    template <bool kMultiply> __device__ __forceinline__ void advance(const char* sa, const char* sb, int g, int h, int a_swz) {
+        const u32x4 c0 = *reinterpret_cast<const u32x4*>(sa + (((4 * g + 2 * h) ^ a_swz) << 4));
+        const u32x4 c1 = *reinterpret_cast<const u32x4*>(sa + (((4 * g + 2 * h + 1) ^ a_swz) << 4));
+        if constexpr (kMultiply) {                               // small terms first, as in mma_k16_split
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) acc[nb] = mma_k16<kBF16>(am, bh[nb], acc[nb]);
+        }
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+            if constexpr (kMultiply) acc[nb] = mma_k16<kBF16>(ah, bm[nb], acc[nb]);
+            bm[nb] = *reinterpret_cast<const u32x4*>(sb + kWide32PlaneBytes + (g * 4 + nb) * 1024);
+        }
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+            if constexpr (kMultiply) acc[nb] = mma_k16<kBF16>(ah, bh[nb], acc[nb]);
+            bh[nb] = *reinterpret_cast<const u32x4*>(sb + (g * 4 + nb) * 1024);
+        }
+        if constexpr (kMultiply) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);             // the two row reads, then as written
+            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);                             // (the split waits for the row reads)
+        }
+        float x[8] = {__uint_as_float(c0.x), __uint_as_float(c0.y), __uint_as_float(c0.z), __uint_as_float(c0.w),
+                      __uint_as_float(c1.x), __uint_as_float(c1.y), __uint_as_float(c1.z), __uint_as_float(c1.w)};
+        __bf16 hi[8], mid[8];
+        split_bf16(x, 8, hi, mid);
+        bf16x8 h8, m8;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { h8[e] = hi[e]; m8[e] = mid[e]; }
+        ah = __builtin_bit_cast(u32x4, h8);
+        am = __builtin_bit_cast(u32x4, m8);
+        ssq = chunk_sumsq<kF32>(c1, chunk_sumsq<kF32>(c0, ssq));
+    }
+    __device__ __forceinline__ void finish() {
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) acc[nb] = mma_k16_split(ah, am, bh[nb], bm[nb], acc[nb]);
+    }
+};
+// A consumer's hand-over: what it has read is in its registers before the producers may write there again.
+__device__ __forceinline__ void wide32_hand_over() {
+    __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));      // lgkmcnt(0) and nothing else
+    ring_barrier();
+}
 
 // p.total_tiles counts tiles of 256 rows: the first p.total_tiles of the checkpoint-major list (the host hands
 // the rest of the batch, if any, to the register-ring kernel); the last round may be partly filled, and a
@@ -162,36 +227,25 @@ __global__ __launch_bounds__(kWideThreads, 1) void tide_prefill_wide_f32_kernel(
         const int tile = tile_of(it);
         const int c = tile / p.tiles_per_ckpt;
         const int row0 = (tile - c * p.tiles_per_ckpt) * kWideRows + 32 * wave;
-        f32x16 acc[4];
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x16{0};
-        float ssq = 0.0f;
-        for (int k = 0; k < nstage; ++k) {
-            ring_barrier();
-            const char* sa = a_ring + (stage % kWide32Stages) * kWide32ABytes + a_row;
-            const char* sb = b_ring + (stage % kWide32Stages) * kWide32BBytes + lane * 16;
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                const u32x4 c0 = *reinterpret_cast<const u32x4*>(sa + (((4 * g + 2 * h) ^ a_swz) << 4));
-                const u32x4 c1 = *reinterpret_cast<const u32x4*>(sa + (((4 * g + 2 * h + 1) ^ a_swz) << 4));
-                float x[8] = {__uint_as_float(c0.x), __uint_as_float(c0.y), __uint_as_float(c0.z), __uint_as_float(c0.w),
-                              __uint_as_float(c1.x), __uint_as_float(c1.y), __uint_as_float(c1.z), __uint_as_float(c1.w)};
-                __bf16 hi[8], mid[8];
-                split_bf16(x, 8, hi, mid);
-                bf16x8 h8, m8;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { h8[e] = hi[e]; m8[e] = mid[e]; }
-                const u32x4 ah = __builtin_bit_cast(u32x4, h8), am = __builtin_bit_cast(u32x4, m8);
-                ssq = chunk_sumsq<kF32>(c1, chunk_sumsq<kF32>(c0, ssq));
-#pragma unroll
-                for (int nb = 0; nb < 4; ++nb) {
-                    const u32x4 bh = *reinterpret_cast<const u32x4*>(sb + (g * 4 + nb) * 1024);
-                    const u32x4 bm = *reinterpret_cast<const u32x4*>(sb + kWide32PlaneBytes + (g * 4 + nb) * 1024);
-                    acc[nb] = mma_k16_split(ah, am, bh, bm, acc[nb]);
-                }
-            }
+        Wide32Steps steps;
+        steps.clear();
+        auto read = [&](int g, auto multiply_tag) {
+            steps.template advance<decltype(multiply_tag)::value>(a_ring + (stage % kWide32Stages) * kWide32ABytes + a_row,
+                                                                  b_ring + (stage % kWide32Stages) * kWide32BBytes + lane * 16, g, h, a_swz);
+        };
+        ring_barrier();
+        read(0, std::false_type{});
+        read(1, std::true_type{});
+        ++stage;
+        for (int k = 1; k < nstage; ++k) {
+            wide32_hand_over();
+            read(0, std::true_type{});
+            read(1, std::true_type{});
             ++stage;
         }
+        steps.finish();
+        const f32x16 (&acc)[4] = steps.acc;
+        const float ssq = steps.ssq;
 
         // ---- epilogue, all within the wave: lanes l and l^32 hold the two halves of row l%32's sum of squares
         const float s2 = ssq + __shfl_xor(ssq, 32, kWave);
