@@ -374,11 +374,6 @@ struct CheckpointTable {
 __device__ __forceinline__ void report_and_select(const CheckpointTable& tab, int C, int c, bool fire, int32_t min_layer,
                                                   int32_t no_exit, uint64_t* arrive_word, int32_t* exit_out,
                                                   uint32_t* mask_out) {
-    if (C == 1) {                                   // nobody else reports on this token: no round trip to its word
-        *exit_out = fire && tab.layer_id[0] >= min_layer ? tab.layer_id[0] : no_exit;
-        if (mask_out) *mask_out = fire ? 1u : 0u;
-        return;
-    }
     const uint64_t mine = (1ull << 32) | ((uint64_t)(fire ? 1u : 0u) << c);
     const uint64_t old = __hip_atomic_fetch_add(arrive_word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((uint32_t)(old >> 32) != (uint32_t)C - 1) return;
