@@ -179,9 +179,11 @@ __global__ __launch_bounds__(kWideThreads, 1) void tide_prefill_band_f32_kernel(
                     for (int i = 0; i < 2 * kN; ++i)
                         __builtin_amdgcn_global_load_lds((glb_char*)((int)koff + cx[i] < p.d * 4 ? gp[i] + koff : zeros), (lds_char*)(dst + i * 2048), 16, 0, 0);
                 } else {
+                    row_transfers<kRagged>(p.shared_lines, [&](auto policy) {
 #pragma unroll
-                    for (int i = 0; i < 2 * kN; ++i)
-                        __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + koff), (lds_char*)(dst + i * 2048), 16, 0, kStreamOnce);
+                        for (int i = 0; i < 2 * kN; ++i)
+                            __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + koff), (lds_char*)(dst + i * 2048), 16, 0, decltype(policy)::value);
+                    });
                 }
                 ++issued;
                 push(2 * kN);

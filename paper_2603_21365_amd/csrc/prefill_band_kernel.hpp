@@ -261,9 +261,11 @@ __global__ __launch_bounds__(kBandThreads, 1) void tide_prefill_band_kernel(cons
                         __builtin_amdgcn_global_load_lds((glb_char*)(inside ? gp[i] + koff : reinterpret_cast<const char*>(g_zeros)), (lds_char*)(dst + i * 2048), 16, 0, 0);
                     }
                 } else {
+                    row_transfers<kRagged>(p.shared_lines, [&](auto policy) {
 #pragma unroll
-                    for (int i = 0; i < 2 * kN; ++i)
-                        __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + koff), (lds_char*)(dst + i * 2048), 16, 0, kStreamOnce);
+                        for (int i = 0; i < 2 * kN; ++i)
+                            __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + koff), (lds_char*)(dst + i * 2048), 16, 0, decltype(policy)::value);
+                    });
                 }
                 ++issued;
                 if (hand) end_of_consumed_tile();

@@ -39,6 +39,16 @@ constexpr int kDmaThreads = (kDmaConsumers + kDmaProducers) * kWave;   // 384
 constexpr int kDmaStages = 4;
 constexpr int kStreamOnce = 2;   // cache-policy bits of the transfer: "nt" -- every hidden byte is read exactly once
 
+// Rows that are no whole k-tiles and do not start on 128-byte lines either (p.shared_lines): a k-tile's segment of a row ends inside a line
+// that the next k-tile begins with, and "nt" lets the L2 drop that line in between, to be read from memory twice.  They are transferred under the
+// default policy (bf16: C = 8, T = 5433, d = 4536 112 -> 98 us, C = 5, T = 12146, d = 4024 138 -> 114, C = 10, T = 4962, d = 1040 33.6 -> 29.9; fp32, C = 7,
+// T = 10505, d = 808 82 -> 77); rows on whole lines stay faster with "nt" (C = 12, T = 4000, d = 1600: 34.9 against 35.6).
+// `transfers` issues a stage's transfers with the policy it is given: the branch is one per stage.
+template <bool kRagged, typename F> __device__ __forceinline__ void row_transfers(bool shared_lines, F transfers) {
+    if (kRagged && shared_lines) transfers(std::integral_constant<int, 0>{});
+    else transfers(std::integral_constant<int, kStreamOnce>{});
+}
+
 template <int kRowsM> constexpr int dma_lds_bytes() {
     // ring + per-wave row sums of squares + per-wave logit partials + per-row inverse RMS
     return kDmaStages * kRowsM * kTileBytes + (2 * kDmaConsumers + 1) * kRowsM * (int)sizeof(float);
@@ -180,9 +190,11 @@ __global__ __launch_bounds__(kDmaThreads, 1) void tide_prefill_dma_kernel(const 
                                                                                                         : reinterpret_cast<const char*>(g_zeros)),
                                                      (lds_char*)(dst + doff[i]), 16, 0, 0);
             } else {
+                row_transfers<kRagged>(p.shared_lines, [&](auto policy) {
 #pragma unroll
-                for (int i = 0; i < kInstrPerProducer; ++i)
-                    __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + (int64_t)ks * f_stage_bytes), (lds_char*)(dst + doff[i]), 16, 0, kStreamOnce);
+                    for (int i = 0; i < kInstrPerProducer; ++i)
+                        __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + (int64_t)ks * f_stage_bytes), (lds_char*)(dst + doff[i]), 16, 0, decltype(policy)::value);
+                });
             }
             ++issued;
             if (++f_k == f_stages) {

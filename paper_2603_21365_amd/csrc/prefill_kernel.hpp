@@ -53,6 +53,7 @@ struct PrefillParams {
     int k_slices;              // workgroups that share a tile's k range
     FastDiv by_slices, by_tiles;   // by k_slices and tiles_per_ckpt (the pair)
     int ring_stages;           // k-tiles of rows that the split-k kernel's ring holds
+    int shared_lines;          // rows that are no whole k-tiles: they do not all start on a 128-byte line (see row_transfers)
     int deal_out;              // the pair: its workgroups in launch order, slice s on XCD s mod 8 (else a tile's slices on one XCD)
     float* zpart;              // [total_tiles][k_slices][rows per tile * 128] partial accumulators
     float* sspart;             // [total_tiles][k_slices][4 waves][rows per tile] partial sums of squares
@@ -146,12 +147,13 @@ __global__ __launch_bounds__(kPrefillThreads, 2) void tide_prefill_kernel(const 
     auto load_a = [&](int j, int kt) {
         const int off = kt * kTileBytes + cc * 16;            // this thread's chunk within the row
         if constexpr (kRagged) {
-            // branch-free: a chunk past the end of the row is fetched from the row's start and zeroed
+            // branch-free: a chunk past the end of the row is fetched from the row's start and zeroed.  (Not "nt": these k-tiles share lines, see
+            // row_transfers; bf16, C = 7, T = 4650: 36.0 -> 33.0 us at d = 1608, 61.0 -> 58.5 at 3080, on whole lines, d = 1600, 32.8 -> 32.1.)
             const bool inside = off < row_bytes;
             const int safe = inside ? off : 0;
 #pragma unroll
             for (int i = 0; i < kChunksPerThread; ++i) {
-                const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(gptr[i] + safe));
+                const u32x4 v = *reinterpret_cast<const u32x4*>(gptr[i] + safe);
                 areg[j][i] = inside ? v : u32x4{0, 0, 0, 0};
             }
         } else {

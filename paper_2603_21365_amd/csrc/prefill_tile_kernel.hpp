@@ -105,10 +105,12 @@ __global__ __launch_bounds__(tile_threads(kHalves), 1) void tide_prefill_tile_ke
                                                      (lds_char*)(dst + (pw * kInstrPerProducer + i) * 1024), 16, 0, 0);
                 }
             } else {
+                row_transfers<kRagged>(p.shared_lines, [&](auto policy) {
 #pragma unroll
-                for (int i = 0; i < kInstrPerProducer; ++i)
-                    __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + (int64_t)kt * kTileBytes),
-                                                     (lds_char*)(dst + (pw * kInstrPerProducer + i) * 1024), 16, 0, kStreamOnce);
+                    for (int i = 0; i < kInstrPerProducer; ++i)
+                        __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + (int64_t)kt * kTileBytes),
+                                                         (lds_char*)(dst + (pw * kInstrPerProducer + i) * 1024), 16, 0, decltype(policy)::value);
+                });
             }
             ++issued;
         };

@@ -804,6 +804,7 @@ PrefillParams prefill_params(const Scratch& sc, const void* hidden, int dtype, i
     p.hidden = (const char*)hidden;
     p.ckpt_stride_bytes = ckpt_stride * (int64_t)eb;
     p.row_stride_bytes = row_stride * (int64_t)eb;
+    p.shared_lines = (((uintptr_t)hidden | (uintptr_t)(T > 1 ? p.row_stride_bytes : 0) | (uintptr_t)(C > 1 ? p.ckpt_stride_bytes : 0)) & 127) != 0;
     p.packed = (const u32x4*)packed;
     p.b1 = b1;
     p.w2 = w2;
@@ -887,6 +888,9 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
                 else rc = no_form();
                 break;
             case kKernelStream64:
+                // (rows above 7 KiB: "nt" is as fast or faster here, us default / nt, C = 4, T = 3232 and C = 10, T = 1300: 16.2 / 18.0 and 16.3 / 18.3 at d = 1752,
+                // 21.3 / 23.9 and 22.0 / 24.3 at 2600, but 33.3 / 32.9 and 34.6 / 33.2 at 3848, 38.5 / 37.3 and 40.0 / 37.6 at 4568)
+                if (p.d * (int)elem_bytes(dtype) > 7168) p.shared_lines = 0;
                 if (two_halves) rc = R ? no_form() : launch_dma<DT, 64, 2>(L.grid, st, p);
                 else if constexpr (DT != kF32 || !R) rc = launch_dma<DT, 64, 1, R>(L.grid, st, p);
                 else rc = no_form();
