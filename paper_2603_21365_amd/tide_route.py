@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 import numpy as np
 import torch
@@ -125,6 +126,24 @@ def _f32dev(t, shape, name):
 def _host(a, C, np_dtype):
     a = np.ascontiguousarray(np.broadcast_to(np.asarray(a, dtype=np_dtype), (C,)))
     return a, a.ctypes.data_as(ctypes.c_void_p)
+
+
+_PLAIN = frozenset((int, float))
+_PACK = {np.float32: "%df", np.int32: "%di"}
+
+
+def _host_once(a, C, np_dtype):
+    """_host for the arguments of one call: Python numbers, C of them or one for all, are packed without numpy's conversions (three
+    arguments: 22.8 -> 14.9 us of host time per select_exit_packed).  Anything else, and what struct refuses, goes the other way."""
+    try:
+        if type(a) in _PLAIN:
+            a = (a,) * C
+        if (type(a) is list or type(a) is tuple) and len(a) == C and _PLAIN.issuperset(map(type, a)):
+            packed = struct.pack(_PACK[np_dtype] % C, *a)
+            return packed, packed                  # a bytes object is passed by its address
+    except (struct.error, OverflowError):
+        pass
+    return _host(a, C, np_dtype)
 
 
 def _stream() -> int:
@@ -280,15 +299,15 @@ def router_eval_packed(hidden, packed, eps, b1, w2, b2, threshold, *, d, want_pr
     return prob, fire, logit
 
 
-def _select_common(hidden, d, b1, w2, b2, threshold, layer_ids, want_logits, want_mask, out):
+def _select_common(hidden, d, b1, w2, b2, threshold, layer_ids, want_logits, want_mask, out, host=_host_once):
     (C, T, width), (cs, rs, _) = _rows(hidden, 3)
     if width < d:
         raise ValueError("hidden rows are shorter than d")
     b = int(w2.shape[-1])
     _f32dev(b1, (C, b), "b1"), _f32dev(w2, (C, b), "w2")
-    b2h, b2p = _host(b2, C, np.float32)
-    thh, thp = _host(threshold, C, np.float32)
-    idh, idp = _host(layer_ids, C, np.int32)
+    b2h, b2p = host(b2, C, np.float32)
+    thh, thp = host(threshold, C, np.float32)
+    idh, idp = host(layer_ids, C, np.int32)
     dev = hidden.device
     if out is None:
         exit_layer = torch.empty(T, dtype=torch.int32, device=dev)
@@ -511,7 +530,7 @@ def prepare_select_exit(hidden, gamma, eps, W1, b1, w2, b2, threshold, layer_ids
     """select_exit with its arguments frozen; the stream is torch's current stream at preparation."""
     d = int(W1.shape[1])
     C, T, cs, rs, b2p, thp, idp, exit_layer, logits, mask, keep = _select_common(
-        hidden, d, b1, w2, b2, threshold, layer_ids, want_logits, want_mask, out)
+        hidden, d, b1, w2, b2, threshold, layer_ids, want_logits, want_mask, out, _host)
     _f32dev(W1, (C, d, keep[3]), "W1"), _f32dev(gamma, (C, d), "gamma")
     fn = load_library().tide_select_exit
     vals = (_ptr(hidden), _dtype_code(hidden), C, T, d, keep[3], cs, rs, _ptr(gamma), float(eps), _ptr(W1), _ptr(b1), _ptr(w2),
@@ -523,7 +542,7 @@ def prepare_select_exit(hidden, gamma, eps, W1, b1, w2, b2, threshold, layer_ids
 def prepare_select_exit_packed(hidden, packed, eps, b1, w2, b2, threshold, layer_ids, min_layer, no_exit_layer, *,
                                d, want_logits=True, want_mask=True, out=None) -> PreparedCall:
     C, T, cs, rs, b2p, thp, idp, exit_layer, logits, mask, keep = _select_common(
-        hidden, int(d), b1, w2, b2, threshold, layer_ids, want_logits, want_mask, out)
+        hidden, int(d), b1, w2, b2, threshold, layer_ids, want_logits, want_mask, out, _host)
     fn = load_library().tide_select_exit_packed
     vals = (_ptr(hidden), _dtype_code(hidden), C, T, int(d), keep[3], cs, rs, _ptr(packed), float(eps), _ptr(b1), _ptr(w2),
             b2p.value, thp.value, idp.value, int(min_layer), int(no_exit_layer), _ptr(exit_layer), _ptr(logits),
