@@ -1039,13 +1039,17 @@ bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, i
 // Hidden sizes that are no multiple of 128 have no split-k form on the calls that would be the latency kernel's (d = 1600 at T <= 32: 25-50 us against 6-9) and
 // none in a block that was sized without it (`pair` false; the register-ring kernel, 18.9 -> 9.3 us at C = 8, T = 100, d = 1600): there up to
 // two workgroups per CU; with the pair they follow the lines above (d = 2904, C = 8: 8.3 / 8.7 at T = 48, 10.7 / 8.2 at 96; d = 4304 14.2 / 9.3).
-bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, bool pair) {
+// kFewWide: a captured call whose pair would have to allocate takes the kernel wherever it is at all reasonable.
+enum FewRule { kFewNever, kFewByRule, kFewWide };
+bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, bool pair, FewRule rule) {
+    if (rule == kFewNever) return false;
     const int64_t tiles = (T + kFewRows - 1) / kFewRows, nbk = b / kFewCols, row_bytes = d * (int64_t)elem_bytes(dtype);
     if (tiles > kFewMaxTiles || C * nbk >= 256 || row_bytes > 32768) return false;
     const int64_t W = C * tiles * nbk, n = (int64_t)cus;
     const bool few_ticks = C * nbk <= 112 || row_bytes > 2048;
     if (d % 128 != 0 && (!pair || C * nbk > 128)) return W <= (few_ticks ? 2 * n : n);
     if (b <= 128 && C * nbk >= 200) return false;
+    if (rule == kFewWide) return W <= (few_ticks ? 2 * n : n);
     if (b <= 128 && C * nbk > 128 && !(T <= kFewRows ? T <= 4 || row_bytes <= 4096 : dtype == TIDE_F32 || row_bytes >= 8192)) return false;
     if (T > kFewRows) {
         if (row_bytes > 8192) return false;
@@ -1074,7 +1078,7 @@ struct CallNeed {
 size_t round256(size_t n) { return (n + 255) & ~size_t(255); }
 
 CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool raw_weights, bool want_exit, unsigned cus, int variant,
-                   int form_word, bool library, bool allow_few = true, size_t most_part = SIZE_MAX) {
+                   int form_word, bool library, FewRule few_rule = kFewByRule, size_t most_part = SIZE_MAX) {
     CallNeed n;
     n.state_bytes = round256(kCounterSlots * sizeof(uint32_t)) + (want_exit ? round256((size_t)T * sizeof(uint64_t)) : 0);
     const bool repack = needs_repack(dtype, d, b);
@@ -1088,8 +1092,8 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
         n.part_bytes = round256((size_t)C * S * (size_t)T * (size_t)(halves * kBottleneck + kPartPad) * sizeof(float));
     }
     // (the other paths' needs are counted all the same for a caller's block: what a caller has to bring does not depend on this choice)
-    n.few = allow_few && !(raw_weights && n.decode) && variant == TIDE_VARIANT_AUTO && form_word == 0 &&
-            use_few_rows(dtype, C, T, n.d_run, b, cus, library && !n.decode);
+    n.few = !(raw_weights && n.decode) && variant == TIDE_VARIANT_AUTO && form_word == 0 &&
+            use_few_rows(dtype, C, T, n.d_run, b, cus, library && !n.decode, few_rule);
     // fp32 rows that are the latency kernel's otherwise: it multiplies the whole fp32 value of a row by both terms of the weight, the other kernels
     // for packed weights the row's two leading bf16 terms (error against 64 bits at T = 32, d = 1000: 2.6e-6 / 4.7e-6).  16-bit rows are exact in any.
     n.few_full = n.few && n.decode;
@@ -1119,7 +1123,10 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
 size_t largest_part(int dtype, int64_t C, int64_t from, int64_t to, int64_t d, int64_t b, bool raw_weights, unsigned cus) {
     size_t most = std::min<size_t>(round256((size_t)(to * C * (b / kFewCols)) * sizeof(float)), (size_t)cus * 2 * kFewRows * sizeof(float));
     auto at = [&](int64_t t) { most = std::max(most, call_need(dtype, C, t, d, b, raw_weights, false, cus, TIDE_VARIANT_AUTO, 0, true).part_bytes); };
-    if (from == 0) at(kDecodeRawMaxT);
+    if (from == 0) {
+        at(kDecodeRawMaxT);
+        at(kFewRows);                 // up to 16 rows the split-k form is one launch, with a line of its own to the streaming forms
+    }
     for (int64_t t = from + 32; t <= to && C * halves_of(b) * (t / 32) <= splitk_max_blocks(dtype, halves_of(b)); t += 32) at(t);
     return most;
 }
@@ -1191,10 +1198,10 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
     CallNeed need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, source == kScratchLibrary);
     // a block that holds what the call needs on the other paths is enough
     if (need.few && source != kScratchLibrary && need.total() > (source == kScratchCaller ? block_bytes : kStaticScratchBytes))
-        need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, source == kScratchLibrary, false);
+        need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, source == kScratchLibrary, kFewNever);
     // the fixed array: a pair with fewer partial results, or none, rather than no call
     if (source == kScratchStatic && g_prefill_form == 0 && need.total() > kStaticScratchBytes && need.total() - need.part_bytes <= kStaticScratchBytes)
-        need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false, false,
+        need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false, kFewNever,
                          kStaticScratchBytes - (need.total() - need.part_bytes));
 
     auto capturing = [&]() {
@@ -1202,10 +1209,15 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
         if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
         return cap != hipStreamCaptureStatusNone;
     };
-    // While a call is captured nothing can be allocated: where the library's workspace lacks the partial results of a route that
-    // the caller's blocks are not sized for either, the call takes the route that they would give it.
-    if (source == kScratchLibrary && need.part_bytes > g_ws[dev].part.bytes && capturing())
-        need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false, false);
+    // While a call is captured nothing can be allocated: where the library's workspace lacks the partial results of a route, the call takes the
+    // few-rows kernel if that is near its range and has room, else the route that a caller's block would give it, with a pair that fits or none.
+    if (source == kScratchLibrary && need.part_bytes > g_ws[dev].part.bytes && capturing()) {
+        const size_t room = g_ws[dev].part.bytes;
+        const CallNeed wide = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, true, kFewWide);
+        need = wide.few && wide.part_bytes <= room
+                   ? wide
+                   : call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false, kFewNever, g_prefill_form == 0 ? room : SIZE_MAX);
+    }
 
     Scratch sc;
     Workspace* ws = nullptr;        // library workspace, if that is the source

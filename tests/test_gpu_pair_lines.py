@@ -73,3 +73,36 @@ def test_the_fixed_scratch_array(dtype, C, T, d, b):
     torch.cuda.synchronize()
     ex_o, z_o, m_o = oracle_select(w, rt, hb)
     report(compare_select(w.name, dtype, z.cpu().numpy(), ex.cpu().numpy(), m.cpu().numpy(), z_o, ex_o, m_o, rt.theta, w.layer_ids, 0, w.n_layers))
+
+
+@pytest.mark.parametrize("dtype,C,T,d,b", [("f16", 8, 96, 4096, 128), ("bf16", 1, 3000, 2048, 128), ("f32", 6, 600, 768, 256), ("bf16", 8, 96, 2904, 128),
+                                           ("f32", 8, 64, 5120, 128)])
+def test_captured_without_an_eager_call(dtype, C, T, d, b):
+    """A graph of a call that the pair would take, captured while the library's workspace holds no partial results of that size: it takes a route that needs no more."""
+    import torch
+    from paper_2603_21365_amd import tide_route as tr
+    w0, rt0, _, h0, (g0, W0, b10, w20) = inputs("bf16", 2, 3100, 256, 128)
+    w, rt, hb, h, (g, W1, b1, w2) = inputs(dtype, C, T, d, b)
+    pk0, pk = tr.router_pack(tr.BF16, g0, W0), tr.router_pack(tr.DTYPE_CODES[dtype], g, W1)
+    out = (torch.empty(T, dtype=torch.int32, device="cuda"), torch.empty((C, T), dtype=torch.float32, device="cuda"), torch.empty(T, dtype=torch.int32, device="cuda"))
+    call = lambda **kw: tr.select_exit_packed(h, pk, w.eps, b1, w2, rt.b2, rt.theta, w.layer_ids, 0, w.n_layers, d=d, **kw)
+    torch.cuda.synchronize()
+    tr.release()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):                   # arrival words for T tokens, room for few partial results
+        tr.select_exit_packed(h0, pk0, w0.eps, b10, w20, rt0.b2, rt0.theta, w0.layer_ids, 0, w0.n_layers, d=256)
+        tr.select_exit_packed(h0[:, :40], pk0, w0.eps, b10, w20, rt0.b2, rt0.theta, w0.layer_ids, 0, w0.n_layers, d=256)
+    torch.cuda.synchronize()
+    allocations = tr.workspace_allocations()
+    with torch.cuda.graph(graph, stream=stream):
+        call(out=out)
+    assert tr.workspace_allocations() == allocations
+    ex_o, z_o, m_o = oracle_select(w, rt, hb)
+    for rep in range(3):
+        for o in out:
+            o.fill_(-7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        report(compare_select(f"{w.name}_{rep}", dtype, out[1].cpu().numpy(), out[0].cpu().numpy(), out[2].cpu().numpy(), z_o, ex_o, m_o, rt.theta, w.layer_ids, 0, w.n_layers))
+    del graph
