@@ -7,8 +7,9 @@
 // each half of every stage's k: a wave alone on its SIMD hides neither its conversions nor its LDS reads behind its matrix steps,
 // and the two waves' accumulators meet once per tile, in LDS.  What bounds it: three matrix steps per value and the W1' every wave
 // reads from LDS (64 of the 112 KiB that cross LDS per 16 KiB of rows); 4.2 TB/s at four blocks against 4.5 at eight.
-// Measured (us, against the forms it replaces): d = 2560, C = 10, T = 3001 87 -> 79 (one wave per block instead of two: 84); d = 4096, C = 8: 111 -> 94 at
-// T = 2300, 132 -> 122 at 4096.
+// Measured (us, against the forms it replaces, before its fragments were read a step ahead, see Wide32Steps): d = 2560, C = 10, T = 3001 87 -> 79 (one wave
+// per block instead of two: 84); d = 4096, C = 8: 111 -> 94 at T = 2300, 132 -> 122 at 4096.  A ring of rows of six or seven stages (the exchange area in its
+// slots) was no faster, with the read-ahead or without (76.0 / 77.4): the memory's latency is covered.
 // kRagged as in prefill_band_kernel.hpp.  Bottleneck widths 64 / 128.
 #pragma once
 #include <type_traits>
