@@ -311,6 +311,14 @@ int tide_set_prefill_form(int form);
  * instead under the automatic settings (see the conventions); this function describes the prefill path only.              */
 int tide_prefill_plan(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int cus, int form, int32_t* out);
 
+/* The route a select_exit call of this shape takes on a device with `cus` compute units (a positive multiple of 8) under the current
+ * variant / prefill-form settings, for tests: host arithmetic only, no GPU needed.  block_bytes: size of the caller-owned workspace
+ * (TIDE_NOALLOC_SCRATCH_BYTES: the no-allocation call), 0 for an eager call on the library's workspace; raw_weights as for tide_workspace_bytes.
+ * out: HOST int64 [4] = {kernel, rows_per_tile, k_slices, bytes of scratch memory used}, kernel as in tide_prefill_plan (the first
+ * launch's), 12 for the few-rows kernel or 0 for the latency kernel.  Returns TIDE_OK, or TIDE_ERR_WORKSPACE where such a call would be refused
+ * for the size of its workspace.                                                                */
+int tide_call_route(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int raw_weights, int cus, size_t block_bytes, int64_t* out);
+
 /* The persistent streaming kernels' schedule, for tests (host arithmetic, no GPU needed; the very
  * code the kernels run): the work items of workgroup `block` of a launch of `grid` workgroups over
  * tiles tile_begin .. total_tiles-1 (as in a tide_prefill_plan launch of kernel 5 or 6);

@@ -1070,6 +1070,7 @@ struct CallNeed {
     size_t state_bytes = 0;         // counters + arrival words, a multiple of 256
     size_t packed_bytes = 0;        // a multiple of 256
     size_t part_bytes = 0;          // a multiple of 256
+    size_t few_bytes = 0;           // ... of which the few-rows kernel uses so much, if it takes the call; a multiple of 256
     size_t rows_bytes = 0;          // generic fallback: the re-aligned copy of the hidden rows; a multiple of 256
     int64_t d_run = 0;              // the row length the kernels run on: d, or d padded to a multiple of 128 with rows_bytes
     size_t total() const { return state_bytes + packed_bytes + part_bytes + rows_bytes; }
@@ -1098,10 +1099,10 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
     // fp32 rows that are the latency kernel's otherwise: it multiplies the whole fp32 value of a row by both terms of the weight, the other kernels
     // for packed weights the row's two leading bf16 terms (error against 64 bits at T = 32, d = 1000: 2.6e-6 / 4.7e-6).  16-bit rows are exact in any.
     n.few_full = n.few && n.decode;
-    const size_t few_bytes = n.few ? round256((size_t)T * (size_t)C * (size_t)(b / kFewCols) * sizeof(float)) : 0;
+    n.few_bytes = n.few ? round256((size_t)T * (size_t)C * (size_t)(b / kFewCols) * sizeof(float)) : 0;
     if (n.decode) {
         n.leaves_data = true;
-        n.part_bytes = n.few && library ? few_bytes : std::max(n.part_bytes, few_bytes);
+        n.part_bytes = n.few && library ? n.few_bytes : std::max(n.part_bytes, n.few_bytes);
         if (n.few) n.decode = false;
         return n;
     }
@@ -1112,8 +1113,28 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
         if (L.kernel == kKernelSplitK || L.kernel == kKernelSplitKFused) n.part_bytes = round256(splitk_part_bytes(L.rows_per_tile / 32, L.total_tiles, halves, L.k_slices));
     }
     n.leaves_data = n.packed_bytes + n.part_bytes + n.rows_bytes > 0;
-    n.part_bytes = n.few && library ? few_bytes : std::max(n.part_bytes, few_bytes);
+    n.part_bytes = n.few && library ? n.few_bytes : std::max(n.part_bytes, n.few_bytes);
     return n;
+}
+
+// The route of a call on a block of `room` bytes (a caller's workspace, the fixed array): the one without a limit where that fits; else the few-rows
+// kernel where that does, whatever the paths behind it would need; else those paths with a split-k pair whose partial results fit, or none.  Only
+// what a call cannot do without is left to be refused: state, weights packed or rows copied by the call, the latency kernel's part, a forced form's.
+CallNeed block_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool raw_weights, bool want_exit, unsigned cus, int variant, int form_word,
+                    size_t room) {
+    auto need = [&](FewRule rule, size_t most_part) {
+        return call_need(dtype, C, T, d, b, raw_weights, want_exit, cus, variant, form_word, false, rule, most_part);
+    };
+    CallNeed n = need(kFewByRule, SIZE_MAX);
+    const size_t fixed = n.total() - n.part_bytes;
+    if (n.total() <= room) return n;
+    const size_t most_part = form_word == 0 && fixed <= room ? room - fixed : SIZE_MAX;
+    if (n.few && fixed + n.few_bytes <= room) {
+        n = need(kFewByRule, most_part);
+        n.part_bytes = n.few_bytes;
+        return n;
+    }
+    return need(kFewNever, most_part);
 }
 
 // The most partial results that any call of these C, d and b with more than `from` and at most `to` rows per checkpoint keeps under the automatic
@@ -1179,6 +1200,7 @@ BlockRecord* find_block(void* ptr) {
 
 // Where a call's scratch memory comes from.
 enum ScratchSource { kScratchLibrary, kScratchCaller, kScratchStatic };
+constexpr int kRouteFewRows = 12;      // tide_call_route's number for the few-rows kernel, behind those of PrefillKernel (0: the latency kernel)
 
 // Shared body of the compute entry points.  Exactly one of (W1) / (packed) is given.  Everything that
 // can fail for lack of memory or for a misused workspace happens before the first kernel is enqueued.
@@ -1196,14 +1218,10 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
     rc = resident_cus(&cus);
     if (rc) return rc;
     const bool want_exit = o.exit_layer != nullptr;
-    CallNeed need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, source == kScratchLibrary);
-    // a block that holds what the call needs on the other paths is enough
-    if (need.few && source != kScratchLibrary && need.total() > (source == kScratchCaller ? block_bytes : kStaticScratchBytes))
-        need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, source == kScratchLibrary, kFewNever);
-    // the fixed array: a pair with fewer partial results, or none, rather than no call
-    if (source == kScratchStatic && g_prefill_form == 0 && need.total() > kStaticScratchBytes && need.total() - need.part_bytes <= kStaticScratchBytes)
-        need = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false, kFewNever,
-                         kStaticScratchBytes - (need.total() - need.part_bytes));
+    CallNeed need = source == kScratchLibrary
+                        ? call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, true)
+                        : block_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form,
+                                     source == kScratchCaller ? block_bytes : kStaticScratchBytes);
 
     auto capturing = [&]() {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -1485,6 +1503,26 @@ size_t tide_workspace_bytes(int dtype, int64_t C, int64_t T, int64_t d, int64_t 
     }
     std::lock_guard<std::mutex> lock(g_mu);
     return call_need(dtype, C, T > 0 ? T : 1, d, b, raw_weights != 0, true, cus, g_variant, g_prefill_form, false).total();
+}
+
+int tide_call_route(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int raw_weights, int cus, size_t block_bytes, int64_t* out) {
+    g_err[0] = 0;
+    if (dtype != TIDE_F32 && dtype != TIDE_F16 && dtype != TIDE_BF16) return fail(TIDE_ERR_INVALID_ARG, "dtype %d is not a tide_dtype_t", dtype);
+    if (C < 1 || C > TIDE_MAX_CHECKPOINTS || T < 1 || C * T > (int64_t)1 << 30) return fail(TIDE_ERR_INVALID_ARG, "C = %lld, T = %lld out of range", (long long)C, (long long)T);
+    if (!supported_hidden(dtype, d) || !supported_bottleneck(b)) return fail(TIDE_ERR_UNSUPPORTED, "d = %lld, b = %lld unsupported", (long long)d, (long long)b);
+    if (cus < 8 || cus % 8 != 0) return fail(TIDE_ERR_INVALID_ARG, "cus = %d must be a positive multiple of 8", cus);
+    if (!out) return fail(TIDE_ERR_INVALID_ARG, "out must not be NULL");
+    std::lock_guard<std::mutex> lock(g_mu);
+    const bool library = block_bytes == 0;
+    const CallNeed n = library ? call_need(dtype, C, T, d, b, raw_weights != 0, true, (unsigned)cus, g_variant, g_prefill_form, true)
+                               : block_need(dtype, C, T, d, b, raw_weights != 0, true, (unsigned)cus, g_variant, g_prefill_form, block_bytes);
+    if (!library && n.total() > block_bytes) return fail(TIDE_ERR_WORKSPACE, "this call needs %zu bytes of workspace, %zu given", n.total(), block_bytes);
+    const PlannedLaunch none{kRouteFewRows, kFewRows, 0, 0, 0, 1, 0}, &L = n.few || n.decode ? none : n.plan.launch[0];
+    out[0] = n.decode ? 0 : L.kernel;
+    out[1] = n.decode ? 0 : L.rows_per_tile;
+    out[2] = L.k_slices;
+    out[3] = (int64_t)n.total();
+    return TIDE_OK;
 }
 
 int tide_workspace_init(void* workspace, size_t workspace_bytes, void* stream) {

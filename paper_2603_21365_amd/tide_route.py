@@ -26,7 +26,7 @@ DTYPE_CODES = {"f32": F32, "f16": F16, "bf16": BF16}
 EXPORTS = (
     "tide_version", "tide_last_error", "tide_router_eval", "tide_select_exit",
     "tide_packed_router_bytes", "tide_router_pack", "tide_router_eval_packed",
-    "tide_select_exit_packed", "tide_exit_project", "tide_batch_exit", "tide_cosine_labels", "tide_batch_compact", "tide_set_variant", "tide_set_prefill_form", "tide_prefill_plan", "tide_stream_schedule", "tide_band_schedule", "tide_band_f32_schedule", "tide_release",
+    "tide_select_exit_packed", "tide_exit_project", "tide_batch_exit", "tide_cosine_labels", "tide_batch_compact", "tide_set_variant", "tide_set_prefill_form", "tide_prefill_plan", "tide_stream_schedule", "tide_band_schedule", "tide_band_f32_schedule", "tide_call_route", "tide_release",
     "tide_workspace_bytes", "tide_workspace_init", "tide_workspace_forget", "tide_router_eval_ws", "tide_select_exit_ws",
     "tide_select_exit_packed_noalloc", "tide_noalloc_scratch_bytes", "tide_workspace_allocations", "tide_mfma_probe",
 )
@@ -82,6 +82,7 @@ def load_library() -> ctypes.CDLL:
     lib.tide_stream_schedule.argtypes = [ci, i64, i64, ci, ci, ci, ci, vp, ci]
     lib.tide_band_schedule.argtypes = [i64, i64, ci, ci, vp, ci]
     lib.tide_band_f32_schedule.argtypes = lib.tide_band_schedule.argtypes
+    lib.tide_call_route.argtypes = [ci, i64, i64, i64, i64, ci, ci, sz, vp]
     lib.tide_mfma_probe.argtypes = [ci, ci, ci, ci, vp]
     lib.tide_mfma_probe.restype = ci
     for name in ("tide_router_eval", "tide_router_eval_packed", "tide_select_exit", "tide_select_exit_packed",
@@ -223,6 +224,17 @@ def prefill_plan(dtype: int, C: int, T: int, d: int, b: int = BOTTLENECK, *, cus
     if n < 0:
         _check(n)
     return [dict(zip(PLAN_FIELDS, out[7 * i:7 * i + 7])) for i in range(n)]
+
+
+ROUTE_LATENCY, ROUTE_FEW_ROWS = 0, 12
+ROUTE_FIELDS = ("kernel", "rows_per_tile", "k_slices", "scratch_bytes")
+
+
+def call_route(dtype: int, C: int, T: int, d: int, b: int = BOTTLENECK, *, raw_weights: bool = False, cus: int = 256, block_bytes: int = 0) -> dict:
+    """The route of a select_exit call (host arithmetic only; no GPU needed) in a block of block_bytes, 0 for the library's workspace."""
+    out = (ctypes.c_int64 * len(ROUTE_FIELDS))()
+    _check(load_library().tide_call_route(int(dtype), int(C), int(T), int(d), int(b), 1 if raw_weights else 0, int(cus), int(block_bytes), out))
+    return dict(zip(ROUTE_FIELDS, out))
 
 
 def stream_schedule(rows_per_tile: int, b: int, k_tiles: int, grid: int, block: int, tile_begin: int, total_tiles: int) -> list:
