@@ -314,8 +314,9 @@ int tide_prefill_plan(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int
 /* The route a select_exit call of this shape takes on a device with `cus` compute units (a positive multiple of 8) under the current
  * variant / prefill-form settings, for tests: host arithmetic only, no GPU needed.  block_bytes: size of the caller-owned workspace
  * (TIDE_NOALLOC_SCRATCH_BYTES: the no-allocation call), 0 for an eager call on the library's workspace; raw_weights as for tide_workspace_bytes.
- * out: HOST int64 [4] = {kernel, rows_per_tile, k_slices, bytes of scratch memory used}, kernel as in tide_prefill_plan (the first
- * launch's), 12 for the few-rows kernel or 0 for the latency kernel.  Returns TIDE_OK, or TIDE_ERR_WORKSPACE where such a call would be refused
+ * out: HOST int64 [5] = {kernel, rows_per_tile, k_slices, bytes of scratch memory used, bytes at the start of the block that hold zeros
+ * afterwards if they did before (0 for the library's workspace)}, kernel as in tide_prefill_plan (the first launch's), 12 for the few-rows
+ * kernel or 0 for the latency kernel.  Returns TIDE_OK, or TIDE_ERR_WORKSPACE where such a call would be refused
  * for the size of its workspace.                                                                */
 int tide_call_route(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int raw_weights, int cus, size_t block_bytes, int64_t* out);
 

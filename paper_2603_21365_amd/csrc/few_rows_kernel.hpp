@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const Pre
                 thr[k] = p.tab.thr_logit[cc];
                 lid[k] = p.tab.layer_id[cc];
             }
-            // the block is left as it was found: zeros, like state words (see the host's leaves_data)
+            // the block is left as it was found: zeros, like state words (see the host's part_stays)
 #pragma unroll
             for (int k = 0; k < kBatch; ++k) {
                 const int cc = cb0 + 4 * k + q;

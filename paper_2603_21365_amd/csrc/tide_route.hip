@@ -113,10 +113,13 @@ int g_prefill_form = 0;   // a form word (see valid_form_word): 0 auto; 1 / 2: s
 // point are single blocks laid out per call: state words first, data behind them.  A call with more
 // state words than an earlier one would find that call's data where it needs zeros, so the library
 // keeps, per block, how many leading bytes are known to hold zero state (`clean`): the whole block
-// after tide_workspace_init, at most the call's state bytes after a call that wrote data.
+// after tide_workspace_init, what lies before a call's data after a call that wrote some.  `settled`: the leading bytes that hold
+// zeros or a split-k form's partial results.  Those depend on the block's size and on estimates, so a program cannot know of them: a later call that
+// keeps its state there clears it, whereas other data (packed weights, copied rows, the latency kernel's part) asks for another tide_workspace_init.
 struct BlockRecord {
     void* ptr = nullptr;
-    size_t bytes = 0, clean = 0;
+    size_t bytes = 0, clean = 0, settled = 0;
+    size_t state = 0;               // the most state that a call since tide_workspace_init has kept
     uint64_t stamp = 0;             // for replacing the least recently used record
 };
 constexpr int kMaxBlockRecords = 64;
@@ -533,7 +536,7 @@ int64_t splitk_max_blocks(int dtype, int halves) { return (int64_t)kSplitkMaxTil
 constexpr double kPairLaunches = 8.3;      // two launches from a host that issues them back to back
 
 PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, int form_word, bool ragged = false, bool split_k = true,
-                         size_t most_part = SIZE_MAX) {
+                         size_t most_part = SIZE_MAX, bool behind_few = false) {
     PrefillPlan plan;
     const int form = form_word & 0xff, force_rows = (form_word >> 8) & 0xff, force_slices = (form_word >> 16) & 0xff;
     const int64_t eb = (int64_t)elem_bytes(dtype);
@@ -599,6 +602,9 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     if (!generic_d && split_k && (form == 0 || form == 5 || form == 8)) {
         const int64_t ntile = d * eb / kTileBytes;
         const int64_t max_blocks = form == 5 ? (int64_t)kSplitkForcedMaxTiles * 4 : splitk_max_blocks(dtype, halves);
+        // A call of up to 16 rows that the few-rows kernel takes never runs this plan, but a caller's block is asked for its partial results and counts
+        // as written by them (see call_need): there the line between the two forms is one of the interface, and stays where it is (these estimates).
+        const bool asked = behind_few && T <= 16 && halves == 1;
         double best = 1e30;
         int best_rows = 0;
         int64_t best_S = 0;
@@ -616,15 +622,17 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
                 if (S < 2 || (force_slices && s != force_slices)) continue;
                 if (splitk_part_bytes(rows / 32, (int)tiles, halves, (int)S) > most_part) continue;
                 const int64_t W = tiles * halves * S;
-                const double t = std::max(least, cost.launch + cost.chain * (double)((ntile + S - 1) / S) * (double)((W + cus - 1) / cus) +
-                                                         (cost.row * lines + cost.slice * (double)S) * R);
+                const double rounds = (double)((ntile + S - 1) / S) * (double)((W + cus - 1) / cus);
+                const double t = asked ? 8.8 + (dtype == TIDE_F32 ? 0.65 : 0.50) * rounds + (0.011 * lines + 0.009 * (double)S) * R
+                                       : std::max(least, cost.launch + cost.chain * rounds + (cost.row * lines + cost.slice * (double)S) * R);
                 if (t < best) { best = t; best_rows = rows; best_S = S; }
             }
         }
         const double t_stream = halves == 2 ? (dtype == TIDE_F32 ? (2.5 + 1.87 * (double)ntile) * (double)((tiles64 + cus - 1) / cus) : 3.4 + 1.4 * (double)ntile)
                               : dtype == TIDE_F32 ? 5.5 + 0.84 * (double)ntile + 0.026 * ((double)ntile / 32.0) * (double)tiles128     // the register-ring form
                                                   : 5.1 + 0.45 * (double)ntile + 0.089 * ((double)ntile / 32.0) * (double)tiles128;
-        if (best_rows && (form == 5 || form == 8 || best < 0.92 * t_stream)) {
+        const double t_asked = dtype == TIDE_F32 ? 8.5 + 0.75 * (double)ntile : 5.7 + 0.48 * (double)ntile + 0.07 * ((double)ntile / 32.0) * (double)tiles128;
+        if (best_rows && (form == 5 || form == 8 || best < (asked ? t_asked : 0.92 * t_stream))) {
             const int64_t tpc = (T + best_rows - 1) / best_rows, tiles = C * tpc;
             // One launch instead of two where the kernel has it (32-row tiles, one column half, a counter per tile) and
             // where it is faster: the finishing workgroup reads the partial results past every cache, so it wins while
@@ -788,10 +796,10 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
 // form, whose loads are selected chunk by chunk).  (split_k: the split-k pair only where its partial results do not
 // have to fit a block that was sized without them.)
 PrefillPlan call_plan(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, int variant, int form_word, bool split_k,
-                      size_t most_part = SIZE_MAX) {
+                      size_t most_part = SIZE_MAX, bool behind_few = false) {
     if (variant == TIDE_VARIANT_AUTO && form_word == 0 && d % 128 != 0)
-        return plan_prefill(dtype, C, T, padded_hidden(dtype, d), b, cus, 0, true, split_k, most_part);
-    return plan_prefill(dtype, C, T, d, b, cus, form_word, false, true, most_part);
+        return plan_prefill(dtype, C, T, padded_hidden(dtype, d), b, cus, 0, true, split_k, most_part, behind_few);
+    return plan_prefill(dtype, C, T, d, b, cus, form_word, false, true, most_part, behind_few);
 }
 
 // What the prefill kernels and the few-rows kernel take, all but the tiling.
@@ -1074,8 +1082,14 @@ struct CallNeed {
     size_t rows_bytes = 0;          // generic fallback: the re-aligned copy of the hidden rows; a multiple of 256
     int64_t d_run = 0;              // the row length the kernels run on: d, or d padded to a multiple of 128 with rows_bytes
     size_t total() const { return state_bytes + packed_bytes + part_bytes + rows_bytes; }
-    bool leaves_data = false;       // whether a block counts as written behind the state words afterwards: as on the paths without
-                                    // the few-rows kernel, which itself leaves zeros where it wrote
+    bool part_last = false;         // a split-k form's partial results: they lie at the end of a block, behind the state of as many calls as it has room for
+    bool part_stays = false;        // whether part counts as written behind the state words afterwards (the few-rows kernel leaves zeros where it wrote)
+    size_t part_offset(size_t room) const { return part_last ? (room - part_bytes) & ~size_t(255) : state_bytes + packed_bytes; }
+    size_t rows_offset() const { return total() - rows_bytes - (part_last ? part_bytes : 0); }
+    size_t data_begin(size_t room) const {      // the first byte of a block of `room` bytes that may not be zero afterwards
+        if (packed_bytes || rows_bytes) return state_bytes;
+        return part_stays ? part_offset(room) : SIZE_MAX;
+    }
 };
 size_t round256(size_t n) { return (n + 255) & ~size_t(255); }
 
@@ -1101,18 +1115,19 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
     n.few_full = n.few && n.decode;
     n.few_bytes = n.few ? round256((size_t)T * (size_t)C * (size_t)(b / kFewCols) * sizeof(float)) : 0;
     if (n.decode) {
-        n.leaves_data = true;
+        n.part_stays = true;
         n.part_bytes = n.few && library ? n.few_bytes : std::max(n.part_bytes, n.few_bytes);
         if (n.few) n.decode = false;
         return n;
     }
     if (raw_weights) n.packed_bytes = round256((size_t)C * tide_packed_router_bytes(dtype, d, b));
-    n.plan = call_plan(dtype, C, T, n.d_run, b, cus, variant, form_word, library, most_part);
-    for (int i = 0; i < n.plan.count; ++i) {
-        const PlannedLaunch& L = n.plan.launch[i];
-        if (L.kernel == kKernelSplitK || L.kernel == kKernelSplitKFused) n.part_bytes = round256(splitk_part_bytes(L.rows_per_tile / 32, L.total_tiles, halves, L.k_slices));
+    n.plan = call_plan(dtype, C, T, n.d_run, b, cus, variant, form_word, library, most_part, n.few);
+    if (const PlannedLaunch& L = n.plan.launch[0]; L.kernel == kKernelSplitK || L.kernel == kKernelSplitKFused) {      // (always the only launch)
+        n.part_bytes = round256(splitk_part_bytes(L.rows_per_tile / 32, L.total_tiles, halves, L.k_slices));
+        n.part_last = !n.few;
+        // a few-rows call of up to 16 rows counts as what it always has counted as, the one-launch form behind it
+        n.part_stays = !n.few || L.kernel == kKernelSplitKFused;
     }
-    n.leaves_data = n.packed_bytes + n.part_bytes + n.rows_bytes > 0;
     n.part_bytes = n.few && library ? n.few_bytes : std::max(n.part_bytes, n.few_bytes);
     return n;
 }
@@ -1180,15 +1195,15 @@ int launch_clear(void* ptr, size_t bytes, hipStream_t st) {      // ptr 16-byte 
     return TIDE_OK;
 }
 
-// One block (a caller's workspace or the static array) laid out for a call: state first, data behind.
-Scratch carve(void* block, const CallNeed& n, bool want_exit) {
+// One block of `room` bytes (a caller's workspace or the static array) laid out for a call: state first, data behind, a split-k form's at the end.
+Scratch carve(void* block, size_t room, const CallNeed& n, bool want_exit) {
     Scratch sc;
     char* base = (char*)block;
     sc.counters = (uint32_t*)base;
     sc.arrive = want_exit ? (uint64_t*)(base + round256(kCounterSlots * sizeof(uint32_t))) : nullptr;
     sc.packed = n.packed_bytes ? base + n.state_bytes : nullptr;
-    sc.part = n.part_bytes ? (float*)(base + n.state_bytes + n.packed_bytes) : nullptr;
-    sc.rows = n.rows_bytes ? base + n.state_bytes + n.packed_bytes + n.part_bytes : nullptr;
+    sc.part = n.part_bytes ? (float*)(base + n.part_offset(room)) : nullptr;
+    sc.rows = n.rows_bytes ? base + n.rows_offset() : nullptr;
     return sc;
 }
 
@@ -1218,10 +1233,10 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
     rc = resident_cus(&cus);
     if (rc) return rc;
     const bool want_exit = o.exit_layer != nullptr;
+    const size_t room = source == kScratchCaller ? block_bytes : kStaticScratchBytes;      // of a block that is not the library's workspace
     CallNeed need = source == kScratchLibrary
                         ? call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, true)
-                        : block_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form,
-                                     source == kScratchCaller ? block_bytes : kStaticScratchBytes);
+                        : block_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, room);
 
     auto capturing = [&]() {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -1231,16 +1246,17 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
     // While a call is captured nothing can be allocated: where the library's workspace lacks the partial results of a route, the call takes the
     // few-rows kernel if that is near its range and has room, else the route that a caller's block would give it, with a pair that fits or none.
     if (source == kScratchLibrary && need.part_bytes > g_ws[dev].part.bytes && capturing()) {
-        const size_t room = g_ws[dev].part.bytes;
+        const size_t part_room = g_ws[dev].part.bytes;
         const CallNeed wide = call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, true, kFewWide);
-        need = wide.few && wide.part_bytes <= room
+        need = wide.few && wide.part_bytes <= part_room
                    ? wide
-                   : call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false, kFewNever, g_prefill_form == 0 ? room : SIZE_MAX);
+                   : call_need(dtype, C, T, d, b, W1 != nullptr, want_exit, cus, g_variant, g_prefill_form, false, kFewNever, g_prefill_form == 0 ? part_room : SIZE_MAX);
     }
 
     Scratch sc;
     Workspace* ws = nullptr;        // library workspace, if that is the source
     size_t* clean = nullptr;        // else: the block's count of leading zero-state bytes
+    BlockRecord* rec = nullptr;     // ... and a caller's block's record
     if (source == kScratchLibrary) {
         ws = &g_ws[dev];
         rc = claim_workspace(*ws, st);
@@ -1284,18 +1300,23 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
         sc.part = (float*)ws->part.ptr;
         sc.rows = ws->rows.ptr;
     } else if (source == kScratchCaller) {
-        BlockRecord* rec = find_block(block);
+        rec = find_block(block);
         if (!rec) return fail(TIDE_ERR_WORKSPACE, "unknown workspace %p: call tide_workspace_init on it first", block);
         if (block_bytes > rec->bytes)
             return fail(TIDE_ERR_WORKSPACE, "workspace_bytes %zu exceeds the %zu bytes tide_workspace_init was given", block_bytes, rec->bytes);
         if (need.total() > block_bytes)
             return fail(TIDE_ERR_WORKSPACE, "this call needs %zu bytes of workspace (tide_workspace_bytes), %zu given", need.total(), block_bytes);
-        if (need.state_bytes > rec->clean)
+        if (need.state_bytes > rec->settled)
             return fail(TIDE_ERR_WORKSPACE, "this call keeps %zu bytes of state at the start of the workspace, where an earlier call of "
                         "another shape left data (or a launch failed): call tide_workspace_init again first", need.state_bytes);
+        if (need.state_bytes > rec->clean) {         // an earlier call's partial results lie where this one keeps state: clear it
+            if ((rc = launch_clear(block, need.state_bytes, st))) return rc;
+            rec->clean = need.state_bytes;
+        }
         rec->stamp = ++g_block_clock;
+        rec->state = std::max(rec->state, need.state_bytes);
         clean = &rec->clean;
-        sc = carve(block, need, want_exit);
+        sc = carve(block, room, need, want_exit);
     } else {
         StaticScratch& ss = g_static[dev];
         if (!ss.ptr) {              // once per device, with that device current
@@ -1312,10 +1333,13 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
             ss.clean = need.state_bytes;
         }
         clean = &ss.clean;
-        sc = carve(ss.ptr, need, want_exit);
+        sc = carve(ss.ptr, room, need, want_exit);
     }
-    // the data regions of this call overwrite whatever zero state lay behind its own state words
-    if (clean && need.leaves_data && *clean > need.state_bytes) *clean = need.state_bytes;
+    // the data regions of this call overwrite whatever zero state lay there
+    const size_t data = need.data_begin(room);
+    const bool split_k_only = need.part_last && !need.packed_bytes && !need.rows_bytes;
+    if (clean) *clean = std::min(*clean, data);
+    if (rec && !split_k_only) rec->settled = std::min(rec->settled, data);
 
     if (need.decode) {
         rc = launch_decode(sc, hidden, dtype, C, T, d, b, ckpt_stride, row_stride, gamma, W1, packed, eps, b1, w2, tab,
@@ -1357,9 +1381,14 @@ int run(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t 
         if (!rc)
             rc = need.few ? launch_few_rows(sc, params(), dtype, need.few_full, st) : launch_prefill(sc, need.plan, params(), dtype, st);
     }
+    if (!rc && rec && split_k_only && data < rec->state) {      // over the state of an earlier call, which may be captured and replayed: zeros again
+        rc = launch_clear((char*)block + data, rec->state - data, st);
+        if (rec->clean == data) rec->clean = rec->state;
+    }
     if (rc) {                       // a launch failed, possibly after an earlier one of this call was enqueued
         if (ws) ws->dirty = true;
         if (clean) *clean = 0;
+        if (rec) rec->settled = 0;
     }
     return rc;
 }
@@ -1522,6 +1551,7 @@ int tide_call_route(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int r
     out[1] = n.decode ? 0 : L.rows_per_tile;
     out[2] = L.k_slices;
     out[3] = (int64_t)n.total();
+    out[4] = library ? 0 : (int64_t)std::min(n.data_begin(block_bytes), block_bytes);
     return TIDE_OK;
 }
 
@@ -1543,7 +1573,8 @@ int tide_workspace_init(void* workspace, size_t workspace_bytes, void* stream) {
     }
     rec->ptr = workspace;
     rec->bytes = bytes;
-    rec->clean = bytes;
+    rec->clean = rec->settled = bytes;
+    rec->state = 0;
     rec->stamp = ++g_block_clock;
     return TIDE_OK;
 }

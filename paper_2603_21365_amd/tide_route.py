@@ -227,7 +227,7 @@ def prefill_plan(dtype: int, C: int, T: int, d: int, b: int = BOTTLENECK, *, cus
 
 
 ROUTE_LATENCY, ROUTE_FEW_ROWS = 0, 12
-ROUTE_FIELDS = ("kernel", "rows_per_tile", "k_slices", "scratch_bytes")
+ROUTE_FIELDS = ("kernel", "rows_per_tile", "k_slices", "scratch_bytes", "zeros_kept")
 
 
 def call_route(dtype: int, C: int, T: int, d: int, b: int = BOTTLENECK, *, raw_weights: bool = False, cus: int = 256, block_bytes: int = 0) -> dict:

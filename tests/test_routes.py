@@ -42,7 +42,8 @@ def test_any_block_that_holds_what_the_call_cannot_do_without():
         shape = (dtype, C, T, d, b)
         full, free = tr.workspace_bytes(*shape, raw_weights=raw), tr.call_route(*shape, raw_weights=raw, block_bytes=1 << 40)
         assert free["scratch_bytes"] == full
-        assert tr.call_route(*shape, raw_weights=raw, block_bytes=full) == free
+        fits = tr.call_route(*shape, raw_weights=raw, block_bytes=full)
+        assert all(fits[k] == free[k] for k in ("kernel", "rows_per_tile", "k_slices", "scratch_bytes"))
         least = state_bytes(T) + (C * tr.packed_router_bytes(dtype, d, b) if raw else 0)
         if d * (4 if dtype == tr.F32 else 2) % 16 or (b == 256 and d % 128):
             least += -(-C * T * -(-d // 128) * 128 * (4 if dtype == tr.F32 else 2) // 256) * 256
@@ -60,8 +61,18 @@ def test_a_small_block_gives_the_few_rows_kernel_what_it_uses():
     least = state_bytes(48) + 48 * 8 * 8 * 4
     assert tr.workspace_bytes(*shape) > 64 * least
     assert tr.call_route(*shape)["kernel"] == tr.ROUTE_FEW_ROWS
-    assert tr.call_route(*shape, block_bytes=least) == {"kernel": tr.ROUTE_FEW_ROWS, "rows_per_tile": 16, "k_slices": 1, "scratch_bytes": least}
+    assert tr.call_route(*shape, block_bytes=least) == {"kernel": tr.ROUTE_FEW_ROWS, "rows_per_tile": 16, "k_slices": 1, "scratch_bytes": least, "zeros_kept": least}
     assert tr.call_route(*shape, block_bytes=least - 256)["kernel"] not in (SPLITK, FUSED, tr.ROUTE_FEW_ROWS)
+
+
+@pytest.mark.parametrize("dtype,C,T,d,b", [(tr.BF16, 1, 3000, 2048, 128), (tr.BF16, 8, 48, 4096, 128), (tr.F32, 6, 600, 1024, 256), (tr.F16, 8, 700, 1024, 64),
+                                           (tr.BF16, 8, 4096, 768, 128), (tr.BF16, 28, 8, 2560, 128)])
+def test_a_call_leaves_the_state_of_larger_ones_alone(dtype, C, T, d, b):
+    """In a block with room for both: partial results lie at its end, and the few-rows kernel leaves zeros where it wrote."""
+    block = (16 << 20) + 512
+    route = tr.call_route(dtype, C, T, d, b, block_bytes=block)
+    assert route["zeros_kept"] > state_bytes(16384)
+    assert route["zeros_kept"] == (block - (route["scratch_bytes"] - state_bytes(T)) if route["kernel"] in (SPLITK, FUSED) else block)
 
 
 def test_a_forced_form_is_refused_below_its_need():
