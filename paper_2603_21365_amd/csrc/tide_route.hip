@@ -532,6 +532,9 @@ struct PrefillPlan {
 struct PairCost { double launch, chain, row, slice; };
 constexpr PairCost kPairCost[2][3] = {{{4.7, 0.59, 0.0063, 0.0087}, {4.8, 0.77, 0.0111, 0.0070}, {5.9, 1.07, 0.0119, 0.0059}},
                                       {{5.3, 0.58, 0.0101, 0.0103}, {6.1, 0.84, 0.0098, 0.0081}, {7.0, 1.47, 0.0095, 0.0070}}};
+// The one-launch form's (up to 16 rows per checkpoint, widths 64 / 128): within 4 % rms of C = 1 ... 32, n = 2 ... 64 k-tiles, two, four and eight slices.
+// Up to 8 rows; 0.8 more beyond, as much as the streaming form's.
+constexpr PairCost kOneLaunchCost[2] = {{5.8, 0.41, 0.057, 0.0099}, {5.9, 0.59, 0.033, 0.0121}};
 int64_t splitk_max_blocks(int dtype, int halves) { return (int64_t)kSplitkMaxTiles * (halves == 1 ? 4 : dtype == TIDE_F32 ? 10 : 6); }
 constexpr double kPairLaunches = 8.3;      // two launches from a host that issues them back to back
 
@@ -592,7 +595,9 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     //                          2.5 + 1.87 n per round of 64-row tiles
     //   split-k pair:          launch + chain ceil(n / S) ceil(W / CUs) + (row n / 32 + slice S) R   (kPairCost, by type and B),
     //                          and no less than the host takes to issue two launches (where they are two)
-    // The pair has to be 8 % cheaper, twice what the estimates are good for.  What that moved (us, before / after):
+    // The pair has to be 8 % cheaper, twice what the estimates are good for; the one launch just cheaper (kOneLaunchCost; bf16, streaming / one launch:
+    // C = 28: 7.4 / 7.3 us at d = 512, 8.4 / 7.7 at 768, 9.2 / 7.8 at 1024, T = 8; two slices or four where eight would share a CU's
+    // time: C = 28, T = 8, d = 2560 10.6 / 10.1 at eight / four).  What the pair's line moved (us, before / after):
     // bf16, C = 1: d = 5120, T = 5000 24.5 / 21.1, d = 2048, T = 3000 12.7 / 9.9, d = 4096, T = 5000 20.8 / 18.4; C = 8, d = 8192, T = 700 36.3 / 31.4;
     // fp32, C = 6: d = 5120, T = 700 47.9 / 41.3, d = 768, T = 700 16.6 / 14.2; fp32, width 256, C = 6: d = 1024, T = 600 31.8 / 17.9, d = 4096 121 / 70 at
     // T = 1000 and 125 / 110 at 1500 (the streaming form's 64-row tiles leave CUs idle there, and past one round it takes two: five times
@@ -613,8 +618,8 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
             if (force_rows ? rows != force_rows : (rows > 32 && 2 * T <= rows)) continue;   // never a tile that is mostly padding
             const int64_t tiles = C * ((T + rows - 1) / rows);
             const double R = (double)(tiles * halves * (rows / 32)), lines = (double)ntile / 32.0;
-            const PairCost& cost = kPairCost[dtype == TIDE_F32][rows / 64];
-            const bool one_launch = form != 5 && rows == 32 && halves == 1 && tiles <= (int64_t)kCounterSlots && T <= 16;     // see `fused` below
+            const bool one_launch = form != 5 && rows == 32 && halves == 1 && tiles <= (int64_t)kCounterSlots && (form == 8 || T <= 16);
+            const PairCost& cost = one_launch ? kOneLaunchCost[dtype == TIDE_F32] : kPairCost[dtype == TIDE_F32][rows / 64];
             const double least = one_launch ? 0.0 : kPairLaunches;
             if (tiles * halves * (rows / 32) > max_blocks) continue;
             for (int64_t s = kSplitkMaxSlices; s >= 2; s /= 2) {
@@ -632,7 +637,7 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
                               : dtype == TIDE_F32 ? 5.5 + 0.84 * (double)ntile + 0.026 * ((double)ntile / 32.0) * (double)tiles128     // the register-ring form
                                                   : 5.1 + 0.45 * (double)ntile + 0.089 * ((double)ntile / 32.0) * (double)tiles128;
         const double t_asked = dtype == TIDE_F32 ? 8.5 + 0.75 * (double)ntile : 5.7 + 0.48 * (double)ntile + 0.07 * ((double)ntile / 32.0) * (double)tiles128;
-        if (best_rows && (form == 5 || form == 8 || best < (asked ? t_asked : 0.92 * t_stream))) {
+        if (best_rows && (form == 5 || form == 8 || best < (asked ? t_asked : T <= 16 && halves == 1 ? t_stream : 0.92 * t_stream))) {
             const int64_t tpc = (T + best_rows - 1) / best_rows, tiles = C * tpc;
             // One launch instead of two where the kernel has it (32-row tiles, one column half, a counter per tile) and
             // where it is faster: the finishing workgroup reads the partial results past every cache, so it wins while
