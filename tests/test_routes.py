@@ -88,7 +88,7 @@ def test_a_forced_form_is_refused_below_its_need():
 
 # up to 16 rows of more checkpoints than the few-rows kernel takes: (dtype, T, d) -> kernel and slices at C = 28
 @pytest.mark.parametrize("dtype,T,d,kernel,slices", [(tr.BF16, 8, 512, 5, 1), (tr.BF16, 16, 512, 5, 1), (tr.BF16, 8, 768, FUSED, 2), (tr.BF16, 16, 1024, FUSED, 4),
-                                                     (tr.F16, 1, 2560, FUSED, 4), (tr.BF16, 16, 2560, FUSED, 4), (tr.BF16, 8, 4096, FUSED, 8), (tr.F32, 8, 1024, FUSED, 8)])
+                                                     (tr.F16, 1, 2560, FUSED, 4), (tr.BF16, 16, 2560, FUSED, 4), (tr.BF16, 8, 4096, FUSED, 8), (tr.F32, 8, 1024, FUSED, 4)])
 def test_few_rows_of_many_checkpoints(dtype, T, d, kernel, slices):
     for C in (28, 32):
         route = tr.call_route(dtype, C, T, d)
