@@ -1037,8 +1037,9 @@ bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, i
 //   up to 6 KiB:        d = 2560: 8.3 / 8.4 at 0.75, 8.9 / 8.2 at 1, 10.7 / 7.9 at 1.5; d = 3072 with the projection 12.4 / 13.5 at 0.94 -- 1;
 //   up to 8 KiB:        d = 4096: 8.3 / 8.9 at 0.66, 8.6 / 8.2 at 0.75, 9.4 / 8.4 at 1, 11.5 / 8.8 at 1.5; fp32, d = 2048 9.1 / 9.1, 9.8 / 9.1 at 1, 12.5 / 9.6; width 64
 //                       with the projection 12.9 / 14.1 at 0.875; width 256, C = 2: 9.0 / 8.6 at 0.5, 10.3 / 9.4 at 1 -- seven eighths;
-//   longer:             d = 5120: 8.4 / 9.0 at 0.16, 9.1 / 8.2 at 0.28, 9.4 / 8.8 at 0.5, 10.9 / 9.1 at 1; fp32, d = 2560 9.7 / 9.4 at 0.28, d = 5120 13.6 / 12.3, 15.5 / 13.2 at 1 -- a fifth
-//                       up to 10 KiB, else never.
+//   up to 12 KiB:       16 bits: d = 5120 8.4 / 9.0 at 0.16, 8.8 / 8.3 at 0.22, 9.4 / 8.8 at 0.5; d = 6144 8.6 / 9.3 at 0.125, 8.9 / 9.2 at 0.19, 9.2 / 8.9 at 0.25 (width 64:
+//                       8.9 / 9.7) -- a fifth; fp32: d = 2560 9.3 / 9.7 at 0.19, 9.7 / 9.8 at 0.25, 9.8 / 9.4 at 0.31; d = 3072 9.3 / 10.2 at 0.125, 9.8 / 10.3 at 0.28 -- three tenths;
+//   longer:             d = 8192 10.0 / 10.4 and 9.5 / 8.8 (one checkpoint) at 0.06-0.125, 10.7 / 10.4 at 0.19; fp32, d = 4096 11.0 / 11.3, 10.5 / 10.3, 11.4 / 11.3 -- never.
 // Up to 16 rows per checkpoint the other path is the one-launch split-k form or, at width 256, a pair that is mostly padding, and the lines are:
 // rows up to 20 KiB whenever the workgroups fit the chip (C = 8, d = 4096: 8.7 -> 6.3 at T = 1, 9.5 -> 7.3 at 16);
 //   longer ones: up to 8 rows always (fp32, d = 8192, C = 8: 17.0 -> 16.1; bf16, d = 16384, C = 1 / 8: 12.5 -> 12.3, 14.6 / 14.8);
@@ -1066,7 +1067,7 @@ bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigne
     if (rule == kFewWide) return W <= (few_ticks ? 2 * n : n);
     if (b <= 128 && C * nbk > 128 && !(T <= kFewRows ? T <= 4 || row_bytes <= 4096 : dtype == TIDE_F32 || row_bytes >= 8192)) return false;
     if (T > kFewRows) {
-        if (row_bytes > 8192) return row_bytes <= 10240 && 5 * W <= n;
+        if (row_bytes > 8192) return row_bytes <= 12288 && (dtype == TIDE_F32 ? 10 * W <= 3 * n : b == 64 && row_bytes > 10240 ? 4 * W <= n : 5 * W <= n);
         if (row_bytes > 6144) return 8 * W <= 7 * n;
         return W <= n || (row_bytes <= 4096 && few_ticks && 2 * W <= 3 * n);
     }

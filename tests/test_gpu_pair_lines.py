@@ -27,6 +27,7 @@ FEW += [("bf16", 1, T, 2560, 128) for T in (512, 513)] + [("bf16", 1, T, 4096, 1
 FEW += [("bf16", 2, T, 4096, 256) for T in (112, 113)] + [("f16", 8, T, 5120, 128) for T in (16, 17)] + [("f32", 3, T, 2560, 64) for T in (16, 17)]
 FEW += [("bf16", 1, T, 8192, 128) for T in (16, 17, 33)] + [("bf16", 8, T, 2904, 128) for T in (32, 33, 64, 65)] + [("f32", 6, T, 1448, 128) for T in (32, 33, 80, 81)]
 FEW += [("f16", 20, 40, 1000, 128), ("bf16", 8, 97, 1448, 128)] + [("bf16", 1, T, 5120, 128) for T in (96, 97)]
+FEW += [("bf16", 3, T, 6144, 128) for T in (32, 33)] + [("f32", 2, T, 3072, 128) for T in (64, 65)] + [("bf16", 8, T, 6144, 64) for T in (32, 33)]
 # pair | streaming forms, width 256 with fp32 rows beyond a 64-row tile per CU
 PAIR = [("bf16", 1, 3000, 2048, 128), ("f16", 1, 5000, 4096, 128), ("f32", 6, 700, 768, 128), ("f32", 6, 600, 768, 256), ("f32", 5, 1000, 1024, 256),
         ("f32", 5, 3400, 512, 256), ("f32", 7, 1676, 2560, 256), ("f16", 6, 1500, 8192, 256), ("bf16", 7, 722, 8192, 128)]
