@@ -1850,6 +1850,7 @@ int tide_cosine_labels(const void* hidden, int dtype, int64_t C, int64_t T, int6
     else if (T <= 1500) p.group_bits = 1;
     else if (row_chunks <= 256) p.group_bits = T <= 2600 ? 1 : 0;
     else p.group_bits = T <= 1900 ? 0 : 2;
+    if (T >= (int64_t)1 << 22) p.group_bits = 0;      // a launch has fewer than 2^32 threads: as many tokens as with one unit each
     const int64_t units = T << p.group_bits;
     const unsigned grid = wave_per_row ? (unsigned)((units + 3) / 4) : (unsigned)(((T + 7) / 8 * 8) << p.group_bits);
     const int64_t per_thread = (row_bytes / 16 + (wave_per_row ? kWave : kCosineThreads) - 1) / (wave_per_row ? kWave : kCosineThreads);

@@ -33,3 +33,25 @@ def test_labels_where_the_kernel_changes_shape(dtype, d, C, T):
     assert np.abs(sim.cpu().numpy() - sim_o).max() <= bound
     clear = np.abs(sim_o - tau) > bound
     np.testing.assert_array_equal(lab.cpu().numpy()[clear], lab_o[clear])
+
+
+def test_more_tokens_than_a_launch_has_threads_for_four_units():
+    """17 million rows of just over 4 KiB: four waves per token would be 2^32 threads.  One buffer serves as both rows (the last layer's one token
+    ahead) and, without a stride between them, as all checkpoints'; the rows are one row and its negative by turns of seven, so the similarity is 1 or -1."""
+    import torch
+    from paper_2603_21365_amd import tide_route as tr
+    C, T, d = 4, (1 << 24) + 5, 2056
+    if torch.cuda.get_device_properties(0).total_memory < 100 << 30:
+        pytest.skip("69 GB of rows")
+    print(f"[gpu-case] labels C={C} T={T} d={d}", flush=True)
+    sign = (torch.arange(T + 1, device="cuda") % 7 < 3).to(torch.bfloat16) * 2 - 1
+    row = torch.randn(d, generator=torch.Generator(device="cuda").manual_seed(5), device="cuda").to(torch.bfloat16)
+    buf = torch.empty((T + 1, d), dtype=torch.bfloat16, device="cuda")
+    torch.mul(sign[:, None], row[None, :], out=buf)
+    hidden = buf.as_strided((C, T, d), (0, d, 1))
+    sim, label = tr.cosine_labels(hidden, buf[1:], 0.5)
+    torch.cuda.synchronize()
+    want = sign[:-1].float() * sign[1:].float()
+    assert (sim - want).abs().max().item() < 1e-5 and torch.equal(label.bool(), (want > 0).expand(C, T))
+    del buf, hidden
+    torch.cuda.empty_cache()
