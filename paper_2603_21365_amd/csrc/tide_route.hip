@@ -1805,6 +1805,39 @@ int tide_batch_compact(const int32_t* exit_layer, int64_t T, int32_t layer, int3
     return TIDE_OK;
 }
 
+namespace {
+// Cosine labels: units per token (1 << the result: 1, 2 or 4) that its checkpoints are dealt out to.  More of them are more waves in flight and a shorter
+// chain per wave, but each reads the last layer's row.  The lines are tokens on 256 CUs, which is waves per CU at one unit (longer rows take more
+// registers, so fewer waves are resident: 32 per CU up to three chunks per lane, 28 at four, 24 / 20 / 16 / 12 / 8 at 5 / 6 / 8 / 10 / more).  Measured (us,
+// one / two / four units, kernels back to back in a graph, bf16, C = 8 where not given; C = 4, 10, 16, 32 alike within the noise unless said):
+int label_unit_bits(bool wave_per_row, int64_t row_chunks, int64_t C, int64_t T, unsigned cus) {
+    if (C == 1 || T >= (int64_t)1 << 22) return 0;     // a launch has fewer than 2^32 threads: as many tokens as with one unit each
+    const int64_t t = T * 256 / (int64_t)cus;
+    // A workgroup per row (above 16 KiB; fp32, d = 5120, C = 9): 14.7 / 10.4 at 200, 18.0 / 16.6 at 420, 23.9 / 27.0 at 700, 32.0 / 32.6 at 980, 52.4 / 47.5 at 1500.
+    if (!wave_per_row) return t <= 500 || t > 1000 ? 1 : 0;
+    int bits;
+    if (row_chunks <= 192)
+        // d = 768: 8.1 / 5.2 / 4.0 at 500, 8.7 / 5.9 / 5.2 at 1300, 9.0 / 6.5 / 6.1 at 1850, 9.3 / 7.4 / 8.2 at 2300, 9.8 / 8.9 / 9.4 at 3000, 10.7 / 9.9 at 3500, 13.0 / 14.5 at 5000;
+        // d = 1024, C = 16: 16.5 / 12.1 / 13.9 at 1850; C = 8 10.2 / 10.0 at 2600, 10.6 / 10.7 at 3000, 12.1 / 12.6 at 3500; d = 1536 14.9 / 13.2 at 2600, 15.6 / 15.4 at 3000.
+        bits = t <= (row_chunks <= 96 ? 1800 : 1000) ? 2 : t <= 3200 ? 1 : 0;
+    else if (row_chunks <= 256)
+        // d = 2048: 12.0 / 7.6 / 5.4 at 500, 12.8 / 8.3 / 7.7 at 900, 14.2 / 11.3 / 11.9 at 1550, 16.3 / 16.0 / 15.8 at 2400, 17.0 / 18.2 / 16.9 at 2600, 18.5 / 19.7 / 19.9 at 3000.
+        bits = t <= 1000 ? 2 : t <= 2500 ? 1 : 0;
+    else if (row_chunks <= 384)
+        // d = 2560: 13.3 / 9.3 / 8.8 at 900, 14.9 / 10.9 / 11.7 at 1300, 15.6 / 13.2 / 13.2 at 1550, 16.3 / 15.5 / 15.3 at 1850, 18.1 / 18.9 / 17.4 at 2200, 20.4 / 22.7 / 20.8 at 2700
+        // (C = 4 12.4 / 13.3 / 12.3, C = 16 35.9 / 40.6 / 38.3), 27.2 / 27.7 / 26.0 at 3500, 42.0 / 39.9 / 38.1 at 5440; d = 3072 18.7 / 19.2 / 19.7 at 2000, 40.4 / 37.5 / 36.9 at
+        // 4200, 51.8 / 47.1 / 48.7 at 5440.
+        bits = t <= (row_chunks <= 320 ? 1000 : 700) ? 2 : t <= (row_chunks <= 320 ? 2000 : 1500) ? 1 : t <= 2000 || (C >= 8 && t > 2400 && t <= 3200) ? 0
+               : row_chunks > 320 && t > 4800 ? 1 : 2;
+    else
+        // d = 4096: 14.7 / 9.4 / 8.1 at 500, 15.8 / 11.9 / 12.6 at 900, 19.0 / 16.8 / 16.8 at 1300, 20.2 / 22.1 / 20.8 at 1550, 20.8 / 23.0 / 21.0 at 1700 (C = 5 14.9 / 16.2 / 15.4,
+        // C = 16 36.2 / 40.9 / 37.8), 28.9 / 28.3 / 26.6 at 2200; d = 8192 37.6 / 39.6 / 38.5 at 1550, 62.2 / 53.2 / 49.9 at 2200.
+        bits = t <= 700 ? 2 : t <= 1500 ? 1 : t <= 1900 ? 0 : 2;
+    // Two or three checkpoints: two units at most, and one where many waves would only be the better balanced (d = 4096, C = 3: 17.2 / 17.5 at 3000).
+    return C >= 4 ? bits : bits == 2 && t > 1500 && row_chunks > 256 ? 0 : std::min(bits, 1);
+}
+}  // namespace
+
 int tide_cosine_labels(const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t ckpt_stride,
                        int64_t row_stride, const void* final_hidden, int64_t final_row_stride, float tau, float* sim,
                        uint8_t* label, void* stream) {
@@ -1834,26 +1867,13 @@ int tide_cosine_labels(const void* hidden, int dtype, int64_t C, int64_t T, int6
     p.sim = sim;
     p.label = label;
     const bool wave_per_row = row_bytes <= (int64_t)kCosineMaxChunks * 16 * kWave;
-    // Units per token (1, 2 or 4) that its checkpoints are dealt out to: more of them are more waves in flight and a shorter chain per wave, but
-    // each reads the last layer's row.  While one wave per token leaves the chip empty more units win whatever they read: four (us, 1 / 2 / 4 units,
-    // kernels back to back in a graph) bf16, C = 8, d = 768 7.7 / 5.0 / 3.8 at T = 340, 9.0 / 6.2 / 5.4 at 1360; d = 4096 14.3 / 8.9 / 7.3 and
-    // 14.9 / 10.5 / 9.6 at 600, then two: 16.3 / 13.1 / 13.8 at 1000, 19.2 / 17.3 / 17.4 at 1360; short rows two up to 2600: 9.3 / 7.3 / 7.6 at 2200 (d = 768).
-    // Once one unit's waves are a full round of the chip (and not two) they win: d = 4096, T = 1700, C = 5 14.9 / 16.2 / 15.2, d = 1024, C = 4,
-    // T = 3600 7.6 / 7.8 / 7.9.  Longer rows in many waves balance better in four: d = 4096 28.8 / 28.5 / 26.6 at 2200, 65.8 / 60.9 / 59.2 at 5440, d = 8192
-    // 126 / 120 / 118, fp32 d = 2560 97 / 90 / 90.  A workgroup per row (rows above 16 KiB): two for few or
-    // many, fp32, d = 8192, C = 9 23.0 / 20.8 at T = 350, 61 / 57 at 1100, C = 5 163 / 157 / 177 at 5440; one between, d = 5120 24.9 / 27.9 at 758.
-    // (Four chunks per thread before, and eight for five or six: bf16, C = 5, d = 5120 80 -> 50 at T = 5440; C = 8, d = 4096, T = 1360 20.0 -> 17.3.)
     const int64_t row_chunks = row_bytes / 16;
-    if (!wave_per_row) p.group_bits = C > 1 && (T <= 400 || T > 1000) ? 1 : 0;
-    else if (C < 4) p.group_bits = C > 1 && T <= 1500 ? 1 : 0;
-    else if (T <= (row_chunks <= 320 ? 1000 : 700)) p.group_bits = 2;
-    else if (T <= 1500) p.group_bits = 1;
-    else if (row_chunks <= 256) p.group_bits = T <= 2600 ? 1 : 0;
-    else p.group_bits = T <= 1900 ? 0 : 2;
-    if (T >= (int64_t)1 << 22) p.group_bits = 0;      // a launch has fewer than 2^32 threads: as many tokens as with one unit each
+    unsigned cus = 0;
+    if ((rc = resident_cus(&cus))) return rc;
+    p.group_bits = label_unit_bits(wave_per_row, row_chunks, C, T, cus);
     const int64_t units = T << p.group_bits;
     const unsigned grid = wave_per_row ? (unsigned)((units + 3) / 4) : (unsigned)(((T + 7) / 8 * 8) << p.group_bits);
-    const int64_t per_thread = (row_bytes / 16 + (wave_per_row ? kWave : kCosineThreads) - 1) / (wave_per_row ? kWave : kCosineThreads);
+    const int64_t per_thread = (row_chunks + (wave_per_row ? kWave : kCosineThreads) - 1) / (wave_per_row ? kWave : kCosineThreads);
     hipStream_t st = (hipStream_t)stream;
     by_dtype(dtype, [&](auto dt) {
         constexpr int DT = decltype(dt)::value;

@@ -15,6 +15,9 @@ SHAPES += [("f16", 2552, 9, 70), ("f32", 512, 4, 33), ("f32", 1276, 6, 41), ("f3
 SHAPES += [("bf16", 768, 7, T) for T in (999, 1001, 1501, 2599, 2602)] + [("f16", 2560, 6, T) for T in (1000, 1003)]
 SHAPES += [("bf16", 3072, 5, T) for T in (700, 701, 1500, 1503, 1899, 1901)] + [("f16", 1024, C, T) for C in (1, 2, 3) for T in (50, 1500, 1505)] + [("f32", 8192, C, 11) for C in (1, 2, 3)]
 
+SHAPES += [("bf16", 768, 8, T) for T in (1800, 1801, 3200, 3201)] + [("f16", 1536, 4, T) for T in (3200, 3203)] + [("bf16", 2048, 5, T) for T in (2500, 2501)]
+SHAPES += [("bf16", 2560, C, T) for C in (4, 9) for T in (2000, 2001, 2401, 3201)] + [("f16", 3072, 4, T) for T in (2001, 4801)] + [("bf16", 4096, 3, 1901), ("f32", 4104, 3, 501)]
+
 
 @pytest.mark.parametrize("dtype,d,C,T", SHAPES)
 def test_labels_where_the_kernel_changes_shape(dtype, d, C, T):
