@@ -54,7 +54,7 @@ template <int kBlocks> constexpr int splitk_part_floats() { return kBlocks * 32 
 constexpr int splitk_kwaves(bool fused) { return fused ? 1 : 2; }
 constexpr int splitk_producers(bool fused) { return fused ? kDmaProducers : 4; }
 constexpr int splitk_threads(bool fused) { return (splitk_kwaves(fused) * kDmaConsumers + splitk_producers(fused)) * kWave; }   // 384 / 768
-constexpr int kSplitkMaxStages = 8;     // k-tiles of rows in flight at most
+constexpr int kSplitkMaxStages = 8;     // k-tiles of rows in the ring at most (of which four in flight)
 
 // First launch: item = (tile * halves + half) * p.k_slices + slice (XCD-contiguous or dealt out, below); tiles of kBlocks*32 rows,
 // checkpoint-major (p.tiles_per_ckpt per checkpoint); half = which 128 columns of the bottleneck
@@ -146,18 +146,13 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
         for (int k = 0; k < nk; ++k) {
             // stage k has landed once only the transfers of the younger stages are outstanding
             // (every stage is kInstrPerProducer transfers; loads complete in issue order)
+            // -- at most three: four are requested at the start and one more per stage handed over
             const int younger = issued - k - 1;
-            static_assert((kSplitkMaxStages - 1) * kInstrPerProducer < 64, "the wave's load counter");
-            switch (younger) {
-            case 0: __builtin_amdgcn_s_waitcnt(vmcnt_imm(0)); break;
-            case 1: __builtin_amdgcn_s_waitcnt(vmcnt_imm(kInstrPerProducer)); break;
-            case 2: __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kInstrPerProducer)); break;
-            case 3: __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * kInstrPerProducer)); break;
-            case 4: __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * kInstrPerProducer)); break;
-            case 5: __builtin_amdgcn_s_waitcnt(vmcnt_imm(5 * kInstrPerProducer)); break;
-            case 6: __builtin_amdgcn_s_waitcnt(vmcnt_imm(6 * kInstrPerProducer)); break;
-            default: __builtin_amdgcn_s_waitcnt(vmcnt_imm(7 * kInstrPerProducer)); break;
-            }
+            static_assert((kDmaStages - 1) * kInstrPerProducer < 64, "the wave's load counter");
+            if (younger >= 3) __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * kInstrPerProducer));
+            else if (younger == 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kInstrPerProducer));
+            else if (younger == 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kInstrPerProducer));
+            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             const bool fresh = issued < stages;    // a slot that no stage has used yet: no need to wait for the consumers
             if (fresh) issue_next();
             ring_barrier();                        // stage k handed over; the consumers are done with stage k-1
@@ -199,11 +194,10 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
             acc[b] = f32x16{0};
             ssq[b] = 0.0f;
         }
-        // 16-bit rows: the A fragments of a group are read from LDS kAhead groups before its matrix steps
-        // are issued (a wave is alone on its SIMD, so nothing else would cover the LDS round trip, and
-        // the fewer blocks a tile has the fewer matrix steps there are per group to cover it with).
-        // Not at 128 rows: with two k-tiles of W1' in registers there are none left for it.
-        constexpr int kAhead = kBlocks >= 4 ? (kKW == 2 ? 1 : 0) : kBlocks == 2 ? 2 : 4;
+        // 16-bit rows: the A fragments of a group are read from LDS kAhead groups before its matrix steps are issued: the two consumer waves of
+        // a SIMD (the one-launch form: the only one) leave the barrier together, so nothing else covers the LDS round trip, and the fewer blocks
+        // a tile has the fewer matrix steps there are per group to cover it with.  128 rows have registers for one group.
+        constexpr int kAhead = kBlocks >= 4 ? 1 : kBlocks == 2 ? 2 : 4;
         auto read_a = [&](const char* st, int g, u32x4* dst) {
 #pragma unroll
             for (int b = 0; b < kBlocks; ++b)
@@ -325,7 +319,7 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
             }
 #pragma unroll
             for (int b = 0; b < kBlocks; ++b)
-                if (lane < 32 && (kBlocks == 1 ? 0 : b / (kBlocks / 2)) == kh)
+                if (lane < 32 && 2 * b / kBlocks == kh)
                     p.sspart[((size_t)item * kDmaConsumers + cb) * kRowsM + 32 * b + lane] = ssq[b] + ex_ss[(other * kBlocks + b) * 32 + lane];
         }
     }

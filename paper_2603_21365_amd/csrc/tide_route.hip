@@ -385,9 +385,11 @@ template <int DT, int kBlocks, bool kRagged> int launch_splitk(float* part, int6
     unsigned cus = 0;
     const int rc = resident_cus(&cus);
     if (rc) return rc;
-    // as many k-tiles as a workgroup has, while the workgroups that share a CU have room for them (at least four)
-    const int ntile = p.dpad * Storage<DT>::kBytes / kTileBytes, nk = (ntile + p.k_slices - 1) / p.k_slices, per_cu = (int)((items + cus - 1) / cus);
-    p.ring_stages = std::min({kMostStages, std::max(nk, 4), std::max(4, kMostStages / per_cu)});
+    // As many k-tiles as a workgroup has, at least four.  (A workgroup is alone on its CU: twelve waves of 96-168 registers.)  Four where the workgroups take
+    // several rounds: a longer ring is level there or slower (four / eight, us, fp32: C = 2, d = 8192, T = 4500 119 / 123, C = 10, T = 1000 124 / 128, width 256, C = 6, d = 4096,
+    // T = 1500 113 / 115; 49 sizes, 0.3 % on average).
+    const int ntile = p.dpad * Storage<DT>::kBytes / kTileBytes, nk = (ntile + p.k_slices - 1) / p.k_slices;
+    p.ring_stages = items > cus ? 4 : std::min(kMostStages, std::max(nk, 4));
     const int lds = splitk_lds_bytes<kBlocks>(p.ring_stages);
     p.zpart = part;
     p.sspart = (float*)((char*)part + z_bytes);
