@@ -77,7 +77,9 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
     constexpr int kStageBytes = kRowsM * kTileBytes;
     constexpr int kInstrPerProducer = kRowsM / 4 / splitk_producers(kFused);   // one transfer = 4 rows x 256 B
     constexpr int kKW = splitk_kwaves(kFused), kConsumers = kKW * kDmaConsumers;
-    constexpr int kPre = kBlocks == 4 ? 1 : 2;                     // k-tiles of W1' a consumer keeps in flight (registers permitting)
+    // k-tiles of W1' a consumer keeps in flight: two while the registers hold them.  (fp32, 64 rows: two are 168 registers and one spilled, one is 96 and faster, us:
+    // C = 2, d = 5120, T = 2200 54.2 / 49.7, C = 8, d = 8192, T = 700 78.3 / 75.2, C = 1, d = 2560, T = 3000 19.2 / 19.0; 2 % over 40 sizes.)
+    constexpr int kPre = kBlocks == 4 || (kBlocks == 2 && DT == kF32) ? 1 : 2;
     constexpr int kPartFloats = splitk_part_floats<kBlocks>();
     char* ring = smem;
     TIDE_FETCH_ARGS16(p.total_tiles, p.tiles_per_ckpt, p.by_tiles.m, p.by_slices.m, p.deal_out, p.k_slices, p.ring_stages, p.T, p.d, p.dpad, p.b,
