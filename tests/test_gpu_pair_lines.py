@@ -21,28 +21,34 @@ def inputs(dtype, C, T, d, b):
     return w, rt, hb, to_device(hb, dtype), routers_to_device(rt)
 
 
-# few rows | pair: one 16-row tile below and above the line
-FEW = [("bf16", 8, T, 1024, 128) for T in (96, 97)] + [("f16", 8, T, 2048, 128) for T in (96, 97)] + [("f32", 4, T, 1024, 128) for T in (192, 193)]
-FEW += [("bf16", 1, T, 2560, 128) for T in (512, 513)] + [("bf16", 1, T, 4096, 128) for T in (448, 449)] + [("f32", 8, T, 2048, 128) for T in (48, 49)]
-FEW += [("bf16", 2, T, 4096, 256) for T in (112, 113)] + [("f16", 8, T, 5120, 128) for T in (16, 17)] + [("f32", 3, T, 2560, 64) for T in (16, 17)]
-FEW += [("bf16", 1, T, 8192, 128) for T in (16, 17, 33)] + [("bf16", 8, T, 2904, 128) for T in (32, 33, 64, 65)] + [("f32", 6, T, 1448, 128) for T in (32, 33, 80, 81)]
-FEW += [("f16", 20, 40, 1000, 128), ("bf16", 8, 97, 1448, 128)] + [("bf16", 1, T, 5120, 128) for T in (96, 97)]
-FEW += [("bf16", 3, T, 6144, 128) for T in (32, 33)] + [("f32", 2, T, 3072, 128) for T in (64, 65)] + [("bf16", 8, T, 6144, 64) for T in (32, 33)]
-# pair | streaming forms, width 256 with fp32 rows beyond a 64-row tile per CU
-PAIR = [("bf16", 1, 3000, 2048, 128), ("f16", 1, 5000, 4096, 128), ("f32", 6, 700, 768, 128), ("f32", 6, 600, 768, 256), ("f32", 5, 1000, 1024, 256),
-        ("f32", 5, 3400, 512, 256), ("f32", 7, 1676, 2560, 256), ("f16", 6, 1500, 8192, 256), ("bf16", 7, 722, 8192, 128)]
+LATENCY, PAIR, STREAM128, STREAM64, FEW = 0, 1, 5, 6, 12          # tide_call_route's kernels
+# (dtype, C, T, d, b): the kernel on 256 CUs
+KERNELS = {}
+# few rows | what lies behind it: one 16-row tile below and above the line
+for dtype, C, d, b, last in (("f16", 8, 2048, 128, 96), ("f32", 4, 1024, 128, 192), ("bf16", 1, 2560, 128, 512), ("bf16", 1, 4096, 128, 448), ("f32", 8, 2048, 128, 48),
+                             ("bf16", 2, 4096, 256, 112), ("f16", 8, 5120, 128, 16), ("bf16", 1, 8192, 128, 16), ("bf16", 8, 2904, 128, 64), ("f32", 6, 1448, 128, 80),
+                             ("bf16", 1, 5120, 128, 96), ("bf16", 3, 6144, 128, 32), ("f32", 2, 3072, 128, 64), ("bf16", 8, 6144, 64, 32)):
+    KERNELS[dtype, C, last, d, b], KERNELS[dtype, C, last + 1, d, b] = FEW, PAIR
+KERNELS["bf16", 8, 96, 1024, 128], KERNELS["bf16", 8, 97, 1024, 128] = FEW, STREAM128
+KERNELS.update({("f32", 3, 16, 2560, 64): FEW, ("f32", 3, 17, 2560, 64): FEW, ("bf16", 8, 32, 2904, 128): FEW, ("bf16", 8, 33, 2904, 128): FEW, ("f32", 6, 32, 1448, 128): FEW,
+                ("f32", 6, 33, 1448, 128): FEW, ("bf16", 1, 33, 8192, 128): PAIR, ("f16", 20, 40, 1000, 128): PAIR, ("bf16", 8, 97, 1448, 128): PAIR})
+# pair | streaming forms
+KERNELS.update({("bf16", 1, 3000, 2048, 128): PAIR, ("f16", 1, 5000, 4096, 128): PAIR, ("f32", 6, 700, 768, 128): PAIR, ("f32", 6, 600, 768, 256): PAIR, ("f32", 5, 1000, 1024, 256): PAIR})
+# ... width 256 with fp32 rows beyond a 64-row tile per CU, long rows: the packed call only
+PACKED_ONLY = {("f32", 5, 3400, 512, 256): STREAM64, ("f32", 7, 1676, 2560, 256): STREAM64, ("f16", 6, 1500, 8192, 256): PAIR, ("bf16", 7, 722, 8192, 128): PAIR}
+CASES = [(*case, False, kernel) for case, kernel in {**KERNELS, **PACKED_ONLY}.items()]
+CASES += [(*case, True, LATENCY if case[2] <= 32 and case[3] % 128 else kernel) for case, kernel in KERNELS.items()]
 
 
-@pytest.mark.parametrize("raw", [False, True])
-@pytest.mark.parametrize("dtype,C,T,d,b", FEW + PAIR)
-def test_either_side_of_a_line(dtype, C, T, d, b, raw):
+@pytest.mark.parametrize("dtype,C,T,d,b,raw,kernel", CASES)
+def test_either_side_of_a_line(dtype, C, T, d, b, raw, kernel):
     import torch
     from paper_2603_21365_amd import tide_route as tr
-    if raw and (dtype, C, T, d, b) in PAIR[5:]:
-        pytest.skip("the packed call covers this size")
     w, rt, hb, h, (g, W1, b1, w2) = inputs(dtype, C, T, d, b)
     tail = (b1, w2, rt.b2, rt.theta, w.layer_ids, 0, w.n_layers)
     pk = None if raw else tr.router_pack(tr.DTYPE_CODES[dtype], g, W1)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert tr.call_route(tr.DTYPE_CODES[dtype], C, T, d, b, raw_weights=raw)["kernel"] == kernel
     call = lambda: tr.select_exit(h, g, w.eps, W1, *tail) if raw else tr.select_exit_packed(h, pk, w.eps, *tail, d=d)
     out = [call() for _ in range(2)]
     torch.cuda.synchronize()
@@ -52,11 +58,20 @@ def test_either_side_of_a_line(dtype, C, T, d, b, raw):
     report(compare_select(w.name, dtype, z, ex, m, z_o, ex_o, m_o, rt.theta, w.layer_ids, 0, w.n_layers))
 
 
-@pytest.mark.parametrize("dtype,C,T,d,b", [("f32", 10, 1763, 512, 256), ("f32", 4, 1056, 8192, 256), ("f16", 8, 669, 8192, 256), ("f16", 8, 64, 4096, 128)])
-def test_the_fixed_scratch_array(dtype, C, T, d, b):
-    """Calls whose cheapest pair keeps more partial results than the array holds take a smaller one."""
+# what the call takes without a limit and within the array (kernel, rows per tile, slices): fewer slices, lower tiles, no pair; and one that fits
+@pytest.mark.parametrize("dtype,C,T,d,b,free,fits", [
+    ("f32", 1, 4151, 8192, 256, (PAIR, 64, 8), (PAIR, 64, 4)), ("f32", 1, 5127, 8192, 256, (PAIR, 128, 8), (PAIR, 64, 4)), ("f32", 10, 1650, 2048, 256, (PAIR, 64, 2), (STREAM64, 64, 1)),
+    ("f16", 10, 796, 8192, 256, (PAIR, 128, 4), (STREAM64, 64, 1)), ("f16", 8, 669, 8192, 256, (PAIR, 128, 2), (PAIR, 128, 2))])
+def test_the_fixed_scratch_array(dtype, C, T, d, b, free, fits):
+    """Calls whose cheapest pair keeps more partial results than the array holds take one that fits, or a form without any."""
     import torch
     from paper_2603_21365_amd import tide_route as tr
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        room = tr.noalloc_scratch_bytes()
+        assert (tr.workspace_bytes(tr.DTYPE_CODES[dtype], C, T, d, b) > room) == (free != fits)
+        for block, want in ((1 << 40, free), (room, fits)):
+            route = tr.call_route(tr.DTYPE_CODES[dtype], C, T, d, b, block_bytes=block)
+            assert (route["kernel"], route["rows_per_tile"], route["k_slices"]) == want
     lib = tr.load_library()
     w, rt, hb, h, (g, W1, b1, w2) = inputs(dtype, C, T, d, b)
     pk = tr.router_pack(tr.DTYPE_CODES[dtype], g, W1)
@@ -84,6 +99,9 @@ def test_captured_without_an_eager_call(dtype, C, T, d, b):
     from paper_2603_21365_amd import tide_route as tr
     w0, rt0, _, h0, (g0, W0, b10, w20) = inputs("bf16", 2, 3100, 256, 128)
     w, rt, hb, h, (g, W1, b1, w2) = inputs(dtype, C, T, d, b)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        route, room = tr.call_route(tr.DTYPE_CODES[dtype], C, T, d, b), max(tr.call_route(tr.BF16, 2, t, 256)["scratch_bytes"] for t in (8, 16, *range(32, 3104, 32)))
+        assert route["kernel"] == PAIR and route["scratch_bytes"] > room
     pk0, pk = tr.router_pack(tr.BF16, g0, W0), tr.router_pack(tr.DTYPE_CODES[dtype], g, W1)
     out = (torch.empty(T, dtype=torch.int32, device="cuda"), torch.empty((C, T), dtype=torch.float32, device="cuda"), torch.empty(T, dtype=torch.int32, device="cuda"))
     call = lambda **kw: tr.select_exit_packed(h, pk, w.eps, b1, w2, rt.b2, rt.theta, w.layer_ids, 0, w.n_layers, d=d, **kw)
