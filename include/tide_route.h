@@ -51,7 +51,10 @@
  *          enough a call only enqueues kernels, so it can be captured in a HIP graph; the graph
  *          holds the workspace's addresses, so make one eager call of the largest shape on the
  *          capturing stream first and neither outgrow nor release the workspace while the graph lives
- *          (an eager call leaves room for every smaller T of its type, C, d, b and kind of weights);
+ *          (an eager call leaves room for every smaller T of its type, C, d, b and kind of weights, at most
+ *          52 MB of partial results at widths 64 and 128, 156 MB at 256).  A call that is captured
+ *          without such an eager call, while the workspace has no room for its partial results, takes a route that
+ *          needs no more than there is: its logits then agree with the eager call's to rounding only, not bit for bit;
  *      (2) the _ws entry points take a caller-owned workspace (tide_workspace_bytes,
  *          tide_workspace_init): nothing is allocated, and calls on different workspaces may run
  *          concurrently on different streams;
@@ -62,11 +65,13 @@
  *    (a caller-owned workspace: by the caller's next tide_workspace_init).
  *  - W1 / packed, w2, and b1 when given, must be 16-byte aligned (TIDE_ERR_ALIGNMENT).
  *  - Small batches (a decode step, or one checkpoint's call on a few hundred rows) run on kernels
- *    that split each router's work over the whole chip: on packed weights the few-rows kernel
- *    (a workgroup per 16 rows and 16 bottleneck columns) while its workgroups fit the chip, a
- *    matrix-core split-k pair beyond; an fp32 latency kernel for raw weights up to 8 rows per
- *    checkpoint (32 for hidden sizes that are not multiples of 128); larger batches on the
- *    streaming kernels.  All of them compute the same function.
+ *    that split each router's work over the whole chip.  Packed weights, up to 16 rows per checkpoint: the few-rows kernel
+ *    (a workgroup per 16 rows and 16 bottleneck columns) while its workgroups fit the chip, the split-k form in one launch
+ *    beyond (many checkpoints, rows above 20 KiB).  More rows: the few-rows kernel while it is faster than two launches -- one and a half
+ *    workgroups per CU for rows of up to 4 KiB, one up to 6 KiB, seven eighths up to 8 KiB, a fifth to three tenths up to
+ *    12 KiB, none above --, then a matrix-core split-k pair.  Raw weights: an fp32 latency kernel up to 8 rows per
+ *    checkpoint (32 for hidden sizes that are not multiples of 128), else the same on weights packed by the call.
+ *    Larger batches run on the streaming kernels.  All of them compute the same function; their sums are taken in different orders.
  */
 #ifndef TIDE_ROUTE_H
 #define TIDE_ROUTE_H
@@ -164,22 +169,27 @@ int tide_select_exit_packed(const void* hidden, int dtype, int64_t C, int64_t T,
 /* ---- Caller-owned workspaces: the same two calls with the scratch memory supplied by the caller
  * (Eq. (2) / Fig. 1 step 3 as above; nothing is allocated, and each stream can have its own).
  *
- * tide_workspace_bytes: bytes a call of this shape needs on the current device under the current
+ * tide_workspace_bytes: bytes a call of this shape makes use of on the current device under the current
  *   variant / prefill-form settings (raw_weights != 0: the call takes W1 and packs it inside the
  *   call).  A multiple of 256; 0 with tide_last_error() set if the shape is unsupported.  On a
  *   machine without a GPU the answer is that for a 256-CU device.  Host arithmetic only.
+ *   A call given less takes the few-rows kernel if that has room, or keeps fewer partial results or none (logits that agree to
+ *   rounding); it is refused with TIDE_ERR_WORKSPACE if its state words, the weights it packs, the rows it copies, the latency kernel's
+ *   part or a forced form's do not fit: a workspace for a program's largest T serves its smaller ones, all but the latency kernel's.
  * tide_workspace_init: zero-fills `workspace` (device, 256-byte aligned, workspace_bytes >= 256) on
  *   `stream` with a kernel and registers it with the library.  Call it once after allocating the
  *   workspace, and again before a call that keeps MORE state at the start of the workspace than
- *   the calls since the last init (more tokens, or an exit_layer output after calls without one);
+ *   an earlier one that left data there (more tokens, or an exit_layer output after calls without one): weights packed or
+ *   rows copied by the call, the latency kernel's part, and up to 16 rows per checkpoint what the split-k form would keep;
  *   the library tracks this per workspace and returns TIDE_ERR_WORKSPACE instead of computing on a
- *   workspace in the wrong state.  Calls of one and the same shape never need a second init.
+ *   workspace in the wrong state.  Other partial results lie at the workspace's end and are cleared where they reach the state
+ *   words of other calls.  Calls of one and the same shape never need a second init.
  *   Calls sharing one workspace must be ordered on one stream (the workspace carries their state);
  *   the library does not check this for caller-owned workspaces.
  * tide_workspace_forget: drops the library's record of a workspace (before freeing it); optional,
  *   the library keeps at most 64 records and replaces the least recently used.
  * The _ws calls: exactly one of W1 (raw fp32 weights, with optional gamma) and packed is non-NULL;
- *   workspace_bytes >= tide_workspace_bytes(...) and <= what tide_workspace_init was given.      */
+ *   workspace_bytes (see tide_workspace_bytes) <= what tide_workspace_init was given.             */
 size_t tide_workspace_bytes(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int raw_weights);
 int tide_workspace_init(void* workspace, size_t workspace_bytes, void* stream);
 int tide_workspace_forget(void* workspace);
@@ -196,12 +206,15 @@ int tide_select_exit_ws(const void* hidden, int dtype, int64_t C, int64_t T, int
                         uint32_t* fire_mask, void* workspace, size_t workspace_bytes, void* stream);
 
 /* tide_select_exit_packed for callers that cannot allocate: code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc.  Same arguments, same results, same kernels; the
+ * serving loops, harnesses that forbid hipMalloc.  Same arguments, same function; the
  * scratch memory is a fixed array of TIDE_NOALLOC_SCRATCH_BYTES inside the library (every GPU the
  * library runs on holds its own copy until the process ends), and the call makes no allocating
- * HIP or library call.  A shape that needs more scratch memory than the array holds
- * (tide_workspace_bytes(..., 0) > tide_noalloc_scratch_bytes()) is refused with
- * TIDE_ERR_WORKSPACE.  All calls on one GPU share that GPU's array: they must be ordered on one
+ * HIP or library call.  A shape that makes use of no more scratch memory than the array holds
+ * (tide_workspace_bytes(..., 0) <= tide_noalloc_scratch_bytes()) runs on the same kernels with the same bits, except that
+ * hidden sizes that are no multiple of 128 take no split-k pair here; a larger one takes fewer slices, another tile height or a form without
+ * partial results, and its logits agree to rounding; it is refused with
+ * TIDE_ERR_WORKSPACE only where no route fits (a forced form, rows that the call has to copy, more than 4 million tokens' state).
+ * All calls on one GPU share that GPU's array: they must be ordered on one
  * stream -- calls that overlap on one GPU race.  The array keeps the last call's contents; the
  * state words a call needs to start from zero are cleared by a small kernel on `stream` whenever
  * an earlier call may have left data there.                                                  */

@@ -1,8 +1,8 @@
 // Calibration labels (paper Sec. 3.1 step 2, Eq. (1)): for every token and checkpoint the
 // cosine similarity between the checkpoint's hidden state and the last layer's, and the label
-// 1[s > tau].  One wave (rows up to 16 KiB) or one workgroup per token keeps the last layer's
-// row in registers and streams the token's C checkpoint rows past it: every row is read once,
-// (C+1)*d elements per token.
+// 1[s > tau].  One, two or four waves per token (rows up to 16 KiB), or one or two workgroups, each keep the
+// last layer's row in registers and stream their share of the token's C checkpoint rows past it: those are
+// read once, the last layer's row once per unit (from L2 after the first), (C+1)*d elements per token from memory.
 #pragma once
 #include "device_utils.hpp"
 

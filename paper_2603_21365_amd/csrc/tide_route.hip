@@ -1031,50 +1031,57 @@ bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, i
 }
 
 // The few-rows kernel (a workgroup per 16 rows and 16 columns, all of k) or the paths above?  Its one launch beats the split-k pair's two
-// (8.3 us from a host that issues them back to back, whatever the kernels take, and 2-3 us more where the exit projection follows) until a workgroup
-// has to walk long rows or the workgroups are more than the CUs; the lines lie where the few-rows kernel takes 9 us (256 CUs, packed weights, bf16
-// unless said, few rows / pair, us, at a share w of the CUs):
-//   rows up to 4 KiB:   C = 8, d = 1024: 7.0 / 9.1 at w = 0.75, 7.5 / 8.3 at 1, 8.8 / 7.8 at 1.5; d = 2048 7.5 / 8.7, 8.8 / 8.5; fp32, d = 1024 7.9 / 8.4,
-//                       9.3 / 7.8; with the exit projection, C = 5, d = 2048, 11.5 / 13.4 at 1.1; d = 1448, C = 8: 8.9 / 7.3 at 1.5, 9.8 / 7.5 at 2 -- 1.5;
-//   up to 6 KiB:        d = 2560: 8.3 / 8.4 at 0.75, 8.9 / 8.2 at 1, 10.7 / 7.9 at 1.5; d = 3072 with the projection 12.4 / 13.5 at 0.94 -- 1;
-//   up to 8 KiB:        d = 4096: 8.3 / 8.9 at 0.66, 8.6 / 8.2 at 0.75, 9.4 / 8.4 at 1, 11.5 / 8.8 at 1.5; fp32, d = 2048 9.1 / 9.1, 9.8 / 9.1 at 1, 12.5 / 9.6; width 64
-//                       with the projection 12.9 / 14.1 at 0.875; width 256, C = 2: 9.0 / 8.6 at 0.5, 10.3 / 9.4 at 1 -- seven eighths;
-//   up to 12 KiB:       16 bits: d = 5120 8.4 / 9.0 at 0.16, 8.8 / 8.3 at 0.22, 9.4 / 8.8 at 0.5; d = 6144 8.6 / 9.3 at 0.125, 8.9 / 9.2 at 0.19, 9.2 / 8.9 at 0.25 (width 64:
-//                       8.9 / 9.7) -- a fifth; fp32: d = 2560 9.3 / 9.7 at 0.19, 9.7 / 9.8 at 0.25, 9.8 / 9.4 at 0.31; d = 3072 9.3 / 10.2 at 0.125, 9.8 / 10.3 at 0.28 -- three tenths;
-//   longer:             d = 8192 10.0 / 10.4 and 9.5 / 8.8 (one checkpoint) at 0.06-0.125, 10.7 / 10.4 at 0.19; fp32, d = 4096 11.0 / 11.3, 10.5 / 10.3, 11.4 / 11.3 -- never.
-// Up to 16 rows per checkpoint the other path is the one-launch split-k form or, at width 256, a pair that is mostly padding, and the lines are:
-// rows up to 20 KiB whenever the workgroups fit the chip (C = 8, d = 4096: 8.7 -> 6.3 at T = 1, 9.5 -> 7.3 at 16);
-//   longer ones: up to 8 rows always (fp32, d = 8192, C = 8: 17.0 -> 16.1; bf16, d = 16384, C = 1 / 8: 12.5 -> 12.3, 14.6 / 14.8);
-//   9 to 16 rows meet the one-launch split-k form at widths 64 / 128 (bf16 at T = 12 / 16: d = 12288 11.8 -> 11.4, but 11.7 / 12.5, d = 16384 13.2 / 13.9, 13.2 / 15.4;
-//   fp32: d = 6144 14.8 -> 13.0, 14.7 -> 14.1; d = 8192 17.2 -> 16.1, but 17.1 / 17.4 and 17.8 / 18.9 at C = 8), not at 256 (fp32, d = 8192, C = 8: 21.1 -> 20.6).
-// Rows of 64 KiB (fp32, d = 16384) are level at best.  Every workgroup of a row tile ticks the tile's counter (14 ns each), which from 128 ticks on costs what
-// the kernel gains against the 128-column split-k forms (width 256, where those take twice the workgroups, does not meet that line: 1.03-1.6 times
-// up to 240 ticks).  17 to 24 checkpoints at width 128: up to 16 rows still for 4 rows or rows of 4 KiB (f16, C = 24: 1.2 times at d = 768, T = 1, 1.05 at T = 4, d = 5120,
-// but bf16, C = 20: 8.6 / 9.1 us at T = 8, 9.4 / 10.1 at 16, d = 2560); more rows for fp32 or rows of 8 KiB (f16, C = 24: 1.12 times at d = 5120, T = 32, but bf16 9.3 / 10.3 us at
-// d = 1024, 11.2 / 12.0 at 2560).  More checkpoints: 9.9 / 11.4 at C = 28, T = 16, d = 2560, 9.3 / 10.4 at T = 8.  Beyond one workgroup per CU rows of up to
-// 2 KiB meet it from 112 ticks on (C = 16, T = 33, d = 1024: 9.2 / 9.6).
-// Hidden sizes that are no multiple of 128 have no split-k form on the calls that would be the latency kernel's (d = 1600 at T <= 32: 25-50 us against 6-9) and
-// none in a block that was sized without it (`pair` false; the register-ring kernel, 18.9 -> 9.3 us at C = 8, T = 100, d = 1600): there up to
-// two workgroups per CU; with the pair they follow the lines above (d = 2904, C = 8: 8.3 / 8.7 at T = 48, 10.7 / 8.2 at 96; d = 4304 14.2 / 9.3).
+// (8.3-8.7 us from a host that issues them back to back, whatever the kernels take, and 2-3 us more where the exit projection follows) until a
+// workgroup has to walk long rows or the workgroups are more than the CUs.  Figures: us, few rows / the other path, 256 CUs, packed weights, bf16 and C = 8 unless
+// said, w = workgroups per CU.
 // kFewWide: a captured call whose pair would have to allocate takes the kernel wherever it is at all reasonable.
+// pair: false where there is no split-k form behind it (see below).
 enum FewRule { kFewNever, kFewByRule, kFewWide };
 bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, bool pair, FewRule rule) {
     if (rule == kFewNever) return false;
     const int64_t tiles = (T + kFewRows - 1) / kFewRows, nbk = b / kFewCols, row_bytes = d * (int64_t)elem_bytes(dtype);
-    if (tiles > kFewMaxTiles || C * nbk >= 256 || row_bytes > 32768) return false;
     const int64_t W = C * tiles * nbk, n = (int64_t)cus;
+    const bool f32 = dtype == TIDE_F32;
+    // (rows of 64 KiB, fp32, d = 16384, are level at best)
+    if (tiles > kFewMaxTiles || C * nbk >= 256 || row_bytes > 32768) return false;
+    // Every workgroup of a row tile ticks the tile's counter (14 ns each).  Beyond one workgroup per CU rows of up to 2 KiB meet that from 112 ticks
+    // on (C = 16, T = 33, d = 1024: 9.6 / 9.2).
     const bool few_ticks = C * nbk <= 112 || row_bytes > 2048;
+
+    // Hidden sizes that are no multiple of 128 have no split-k form on the calls that would be the latency kernel's (d = 1600, T <= 32: 6-9 / 25-50) and none in a
+    // block that was sized without it (the register-ring kernel: d = 1600, T = 100 9.3 / 18.9).  With the pair they follow the lines below
+    // (d = 2904: 8.3 / 8.7 at T = 48, 10.7 / 8.2 at 96; d = 4304 14.2 / 9.3).
     if (d % 128 != 0 && (!pair || C * nbk > 128)) return W <= (few_ticks ? 2 * n : n);
+
+    // Many checkpoints, widths 64 / 128: from 128 ticks on the counter costs what the kernel gains over the 128-column split-k forms (width 256, where those take twice
+    // the workgroups, does not meet that line: 1.03-1.6 times as fast up to 240 ticks).  C = 28: 11.4 / 9.9 at T = 16, d = 2560, 10.4 / 9.3 at T = 8.
     if (b <= 128 && C * nbk >= 200) return false;
     if (rule == kFewWide) return W <= (few_ticks ? 2 * n : n);
-    if (b <= 128 && C * nbk > 128 && !(T <= kFewRows ? T <= 4 || row_bytes <= 4096 : dtype == TIDE_F32 || row_bytes >= 8192)) return false;
-    if (T > kFewRows) {
-        if (row_bytes > 8192) return row_bytes <= 12288 && (dtype == TIDE_F32 ? 10 * W <= 3 * n : b == 64 && row_bytes > 10240 ? 4 * W <= n : 5 * W <= n);
+    // 17 to 24 checkpoints at width 128, up to 16 rows: 4 rows or rows of 4 KiB (f16, C = 24: 1.2 times at d = 768, T = 1, 1.05 at d = 5120, T = 4, but C = 20, d = 2560 9.1 / 8.6 at
+    // T = 8, 10.1 / 9.4 at 16); more: fp32 or rows of 8 KiB (f16, C = 24, d = 5120, T = 32 1.12 times, but 10.3 / 9.3 at d = 1024, 12.0 / 11.2 at 2560).
+    if (b <= 128 && C * nbk > 128 && !(T <= kFewRows ? T <= 4 || row_bytes <= 4096 : f32 || row_bytes >= 8192)) return false;
+
+    if (T > kFewRows) {             // against the pair
+        // above 12 KiB: d = 8192 10.0 / 10.4 and (C = 1) 9.5 / 8.8 at w = 0.06-0.125, 10.7 / 10.4 at 0.19; fp32, d = 4096 11.0 / 11.3, 10.5 / 10.3, 11.4 / 11.3
+        if (row_bytes > 12288) return false;
+        // fp32: d = 2560 9.3 / 9.7 at 0.19, 9.7 / 9.8 at 0.25, 9.8 / 9.4 at 0.31; d = 3072 9.3 / 10.2 at 0.125, 9.8 / 10.3 at 0.28
+        if (row_bytes > 8192 && f32) return 10 * W <= 3 * n;
+        // d = 5120 8.4 / 9.0 at 0.16, 8.8 / 8.3 at 0.22, 9.4 / 8.8 at 0.5; d = 6144 8.6 / 9.3 at 0.125, 8.9 / 9.2 at 0.19, 9.2 / 8.9 at 0.25, but width 64 8.9 / 9.7 there
+        if (row_bytes > 8192) return b == 64 && row_bytes > 10240 ? 4 * W <= n : 5 * W <= n;
+        // d = 4096 8.3 / 8.9 at 0.66, 8.6 / 8.2 at 0.75, 9.4 / 8.4 at 1, 11.5 / 8.8 at 1.5; fp32, d = 2048 9.1 / 9.1, 9.8 / 9.1 at 1, 12.5 / 9.6; width 64 with the projection
+        // 12.9 / 14.1 at 0.875; width 256, C = 2: 9.0 / 8.6 at 0.5, 10.3 / 9.4 at 1
         if (row_bytes > 6144) return 8 * W <= 7 * n;
-        return W <= n || (row_bytes <= 4096 && few_ticks && 2 * W <= 3 * n);
+        // d = 2560 8.3 / 8.4 at 0.75, 8.9 / 8.2 at 1, 10.7 / 7.9 at 1.5; d = 3072 with the projection 12.4 / 13.5 at 0.94
+        if (row_bytes > 4096) return W <= n;
+        // d = 1024 7.0 / 9.1 at 0.75, 7.5 / 8.3 at 1, 8.8 / 7.8 at 1.5; d = 2048 7.5 / 8.7, 8.8 / 8.5; fp32, d = 1024 7.9 / 8.4, 9.3 / 7.8; with the projection, C = 5,
+        // d = 2048 11.5 / 13.4 at 1.1; d = 1448 8.9 / 7.3 at 1.5, 9.8 / 7.5 at 2
+        return W <= n || (few_ticks && 2 * W <= 3 * n);
     }
+    // Up to 16 rows per checkpoint against the one-launch split-k form or, at width 256, a pair that is mostly padding:
+    // d = 4096 6.3 / 8.7 at T = 1, 7.3 / 9.5 at 16; up to 8 rows of any length fp32, d = 8192 16.1 / 17.0, d = 16384, C = 1 / 8 12.3 / 12.5, 14.8 / 14.6; width 256, fp32, d = 8192 20.6 / 21.1
     if (row_bytes <= 20480 || T <= 8 || b == 256) return W <= n;
-    return W <= n && (dtype == TIDE_F32 ? T <= 12 || row_bytes <= 24576 : T <= 12 && row_bytes <= 24576);
+    // 9 to 16 rows, T = 12 / 16: d = 12288 11.4 / 11.8, 12.5 / 11.7; d = 16384 13.9 / 13.2, 15.4 / 13.2; fp32: d = 6144 13.0 / 14.8, 14.1 / 14.7; d = 8192 16.1 / 17.2, 17.4 / 17.1 (18.9 / 17.8 at C = 8)
+    return W <= n && (f32 ? T <= 12 || row_bytes <= 24576 : T <= 12 && row_bytes <= 24576);
 }
 
 // ---- What a router call needs of scratch memory, and which path it takes: host arithmetic only.
