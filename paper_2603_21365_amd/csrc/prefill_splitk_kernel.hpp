@@ -77,8 +77,8 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
     constexpr int kStageBytes = kRowsM * kTileBytes;
     constexpr int kInstrPerProducer = kRowsM / 4 / splitk_producers(kFused);   // one transfer = 4 rows x 256 B
     constexpr int kKW = splitk_kwaves(kFused), kConsumers = kKW * kDmaConsumers;
-    // k-tiles of W1' a consumer keeps in flight: two while the registers hold them.  (fp32, 64 rows: two are 168 registers and one spilled, one is 96 and faster, us:
-    // C = 2, d = 5120, T = 2200 54.2 / 49.7, C = 8, d = 8192, T = 700 78.3 / 75.2, C = 1, d = 2560, T = 3000 19.2 / 19.0; 2 % over 40 sizes.)
+    // k-tiles of W1' a consumer keeps in flight: two while the registers hold them.  (fp32, 64 rows: one, 96 registers instead of 145, us, two / one: in several
+    // rounds C = 1, d = 8192, T = 4500 113.8 / 108.0, C = 6, d = 5120, T = 400, width 256 50.0 / 46.8; level in one round.)
     constexpr int kPre = kBlocks == 4 || (kBlocks == 2 && DT == kF32) ? 1 : 2;
     constexpr int kPartFloats = splitk_part_floats<kBlocks>();
     char* ring = smem;
@@ -267,13 +267,22 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
                 k_tile(next_stage(), breg[j], kt0 + k + j + kPre, std::true_type{});
             }
         }
-#pragma unroll
-        for (int j = 0; j < 2 * kPre - 1; ++j) {   // fewer than 2 kPre k-tiles left (k is a multiple of kPre)
-            if (k + j < nk) {
+        // One to 2 kPre - 1 k-tiles are left.  Each count is a straight line of its own: with a test per k-tile the accumulators lived in two register sets
+        // at every join (fp32, 64 rows: 168 and one spilled, now 145 with two k-tiles in flight; 16 bits, 32 rows 110 / 93; a few-tile call 2-4 % faster, us:
+        // bf16, C = 5, T = 100, d = 4096 9.1 / 8.5, C = 1, T = 1000, d = 5120 9.9 / 9.4, one launch, C = 28, T = 8, d = 2560 10.0 / 9.7).
+        if (kPre == 2 && k + 2 < nk) {             // three: the last one goes where the first of them was
+            ring_barrier();
+            k_tile(next_stage(), breg[0], kt0 + k + 2, std::true_type{});
+            ring_barrier();
+            k_tile(next_stage(), breg[kPre - 1], 0, std::false_type{});
+            ring_barrier();
+            k_tile(next_stage(), breg[0], 0, std::false_type{});
+        } else {
+            ring_barrier();
+            k_tile(next_stage(), breg[0], 0, std::false_type{});
+            if (kPre == 2 && k + 1 < nk) {
                 ring_barrier();
-                const char* st = next_stage();
-                if (k + j + kPre < nk) k_tile(st, breg[j % kPre], kt0 + k + j + kPre, std::true_type{});
-                else k_tile(st, breg[j % kPre], 0, std::false_type{});
+                k_tile(next_stage(), breg[kPre - 1], 0, std::false_type{});
             }
         }
 
