@@ -68,7 +68,7 @@
  *    that split each router's work over the whole chip.  Packed weights, up to 16 rows per checkpoint: the few-rows kernel
  *    (a workgroup per 16 rows and 16 bottleneck columns) while its workgroups fit the chip, the split-k form in one launch
  *    beyond (many checkpoints, rows above 20 KiB).  More rows: the few-rows kernel while it is faster than two launches -- one and a half
- *    workgroups per CU for rows of up to 4 KiB, one up to 6 KiB, seven eighths up to 8 KiB, a fifth to three tenths up to
+ *    workgroups per CU for rows of up to 4 KiB, one up to 6 KiB, seven eighths up to 8 KiB, a fifth or a quarter up to
  *    12 KiB, none above --, then a matrix-core split-k pair.  Raw weights: an fp32 latency kernel up to 8 rows per
  *    checkpoint (32 for hidden sizes that are not multiples of 128), else the same on weights packed by the call.
  *    Larger batches run on the streaming kernels.  All of them compute the same function; their sums are taken in different orders.

@@ -1062,12 +1062,13 @@ bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigne
     if (b <= 128 && C * nbk > 128 && !(T <= kFewRows ? T <= 4 || row_bytes <= 4096 : f32 || row_bytes >= 8192)) return false;
 
     if (T > kFewRows) {             // against the pair
-        // above 12 KiB: d = 8192 10.0 / 10.4 and (C = 1) 9.5 / 8.8 at w = 0.06-0.125, 10.7 / 10.4 at 0.19; fp32, d = 4096 11.0 / 11.3, 10.5 / 10.3, 11.4 / 11.3
+        // above 12 KiB: d = 8192 10.0 / 10.2 (C = 2) and 9.8 / 9.0 (C = 1) at w = 0.06-0.125, 10.7 / 10.3 at 0.19; fp32, d = 4096 11.0 / 11.3, 10.5 / 10.3, 11.4 / 11.3
         if (row_bytes > 12288) return false;
-        // fp32: d = 2560 9.3 / 9.7 at 0.19, 9.7 / 9.8 at 0.25, 9.8 / 9.4 at 0.31; d = 3072 9.3 / 10.2 at 0.125, 9.8 / 10.3 at 0.28
-        if (row_bytes > 8192 && f32) return 10 * W <= 3 * n;
-        // d = 5120 8.4 / 9.0 at 0.16, 8.8 / 8.3 at 0.22, 9.4 / 8.8 at 0.5; d = 6144 8.6 / 9.3 at 0.125, 8.9 / 9.2 at 0.19, 9.2 / 8.9 at 0.25, but width 64 8.9 / 9.7 there
-        if (row_bytes > 8192) return b == 64 && row_bytes > 10240 ? 4 * W <= n : 5 * W <= n;
+        // d = 5376 8.6 / 8.9 at 0.125, 8.8 / 8.9 at 0.19, 9.3 / 8.8 at 0.25; d = 6144 8.6 / 9.0, 9.0 / 9.0, 9.4 / 8.9, but width 64 8.9 / 9.2 at 0.25; fp32: d = 2688 9.2 / 9.9 at
+        // 0.125, 9.7 / 10.0 at 0.25, 10.1 / 9.9 at 0.375; d = 3072 9.3 / 10.1 at 0.125
+        if (row_bytes > 10240) return f32 || b == 64 ? 4 * W <= n : 5 * W <= n;
+        // d = 5120 8.1 / 8.2 at 0.06, 8.6 / 8.5 at 0.19, 9.1 / 8.5 at 0.25; fp32, d = 2560 9.2 / 9.4 at 0.125, 9.3 / 9.5 at 0.19, 9.7 / 9.5 at 0.25, 10.0 / 9.4 at 0.375
+        if (row_bytes > 8192) return 5 * W <= n;
         // d = 4096 8.3 / 8.9 at 0.66, 8.6 / 8.2 at 0.75, 9.4 / 8.4 at 1, 11.5 / 8.8 at 1.5; fp32, d = 2048 9.1 / 9.1, 9.8 / 9.1 at 1, 12.5 / 9.6; width 64 with the projection
         // 12.9 / 14.1 at 0.875; width 256, C = 2: 9.0 / 8.6 at 0.5, 10.3 / 9.4 at 1
         if (row_bytes > 6144) return 8 * W <= 7 * n;

@@ -96,8 +96,8 @@ def test_few_rows_of_many_checkpoints(dtype, T, d, kernel, slices):
 
 
 # the most rows of C checkpoints that the few-rows kernel takes before the split-k pair does
-@pytest.mark.parametrize("dtype,C,d,b,most", [(tr.BF16, 1, 5120, 128, 96), (tr.F16, 2, 5376, 128, 48), (tr.BF16, 3, 6144, 128, 32), (tr.BF16, 8, 6144, 64, 32), (tr.BF16, 4, 5120, 64, 48),
-                                              (tr.F32, 1, 2560, 128, 144), (tr.F32, 2, 3072, 128, 64), (tr.F32, 3, 2688, 128, 48), (tr.F32, 8, 3072, 64, 32), (tr.BF16, 1, 8192, 128, 16),
+@pytest.mark.parametrize("dtype,C,d,b,most", [(tr.BF16, 1, 5120, 128, 96), (tr.F16, 2, 5376, 128, 48), (tr.BF16, 3, 6144, 128, 32), (tr.BF16, 8, 6144, 64, 32), (tr.BF16, 4, 5120, 64, 48), (tr.F32, 4, 2560, 64, 48),
+                                              (tr.F32, 1, 2560, 128, 96), (tr.F32, 2, 3072, 128, 64), (tr.F32, 3, 2688, 128, 32), (tr.F32, 8, 3072, 64, 32), (tr.BF16, 1, 8192, 128, 16),
                                               (tr.F32, 2, 4096, 128, 16)])
 def test_the_line_between_few_rows_and_the_pair(dtype, C, d, b, most):
     assert tr.call_route(dtype, C, most, d, b)["kernel"] == tr.ROUTE_FEW_ROWS
