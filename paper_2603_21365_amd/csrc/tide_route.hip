@@ -385,7 +385,7 @@ template <int DT, int kBlocks, bool kRagged> int launch_splitk(float* part, int6
     unsigned cus = 0;
     const int rc = resident_cus(&cus);
     if (rc) return rc;
-    // As many k-tiles as a workgroup has, at least four.  (A workgroup is alone on its CU: twelve waves of 96-168 registers.)  Four where the workgroups take
+    // As many k-tiles as a workgroup has, at least four.  (A workgroup is alone on its CU: twelve waves of 93-151 registers.)  Four where the workgroups take
     // several rounds: a longer ring is level there or slower (four / eight, us, fp32: C = 2, d = 8192, T = 4500 119 / 123, C = 10, T = 1000 124 / 128, width 256, C = 6, d = 4096,
     // T = 1500 113 / 115; 49 sizes, 0.3 % on average).
     const int ntile = p.dpad * Storage<DT>::kBytes / kTileBytes, nk = (ntile + p.k_slices - 1) / p.k_slices;
@@ -530,7 +530,8 @@ struct PrefillPlan {
     PlannedLaunch launch[2];
 };
 
-// The split-k pair's cost (see plan_prefill), us: for 16-bit and fp32 rows, tiles of 32, 64 and 128 rows.
+// The split-k pair's cost (see plan_prefill), us: for 16-bit and fp32 rows, tiles of 32, 64 and 128 rows.  (Fitted before the last k-tiles of a slice ran in straight
+// lines: tiles of 32 and 64 rows take 1-4 % less since.)
 struct PairCost { double launch, chain, row, slice; };
 constexpr PairCost kPairCost[2][3] = {{{4.7, 0.59, 0.0063, 0.0087}, {4.8, 0.77, 0.0111, 0.0070}, {5.9, 1.07, 0.0119, 0.0059}},
                                       {{5.3, 0.58, 0.0101, 0.0103}, {6.1, 0.84, 0.0098, 0.0081}, {7.0, 1.47, 0.0095, 0.0070}}};
