@@ -1844,6 +1844,7 @@ int label_unit_bits(bool wave_per_row, int64_t row_chunks, int64_t C, int64_t T,
         // d = 4096: 14.7 / 9.4 / 8.1 at 500, 15.8 / 11.9 / 12.6 at 900, 19.0 / 16.8 / 16.8 at 1300, 20.2 / 22.1 / 20.8 at 1550, 20.8 / 23.0 / 21.0 at 1700 (C = 5 14.9 / 16.2 / 15.4,
         // C = 16 36.2 / 40.9 / 37.8), 28.9 / 28.3 / 26.6 at 2200; d = 8192 37.6 / 39.6 / 38.5 at 1550, 62.2 / 53.2 / 49.9 at 2200.
         bits = t <= 700 ? 2 : t <= 1500 ? 1 : t <= 1900 ? 0 : 2;
+    // Never more units than checkpoints: a unit requests its first row before it looks whether there is another.
     // Two or three checkpoints: two units at most, and one where many waves would only be the better balanced (d = 4096, C = 3: 17.2 / 17.5 at 3000).
     return C >= 4 ? bits : bits == 2 && t > 1500 && row_chunks > 256 ? 0 : std::min(bits, 1);
 }
