@@ -206,7 +206,7 @@ __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const Pre
     // bytes apart: atomics on one line take 14 ns each.
     uint32_t* counter = p.counters + ((tile & 3) << 4) + (tile >> 2);
     uint32_t prev = 0;
-    if (lane == 0) prev = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0) prev = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     prev = __builtin_amdgcn_readfirstlane(prev);
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     if (prev != (uint32_t)per_row - 1) return;
