@@ -15,6 +15,8 @@
 // the pair beyond): 8.7 -> 6.4 at T = 1, 8.8 -> 6.9 at 8, 9.6 -> 7.4 at 16, 11.5 -> 8.6 at 48; width 256, T = 8: 12.7 -> 8.8;
 // fp32 rows, T = 4: 12.4 -> 9.4; d = 768, T = 4: 10.0 -> 6.3; d = 1600 (no multiple of 128), C = 12, T = 48: 18.4 -> 8.8.  kFull against the latency kernel: 34.6 -> 8.6 at C = 4, T = 32, d = 1608, 12.2 -> 7.5
 // at C = 8, T = 4, 13.2 -> 9.9 at C = 1, T = 1, d = 4104 (terms rounded to the nearest instead: 9.0, 8.0 and 11.8).
+// Later: the tick without an L2 invalidate 8.5 -> 7.9 at T = 48; waves without a share of the row load nothing instead of zeros, which cost as much as
+// data (6.2 -> 5.7 at C = 5, T = 33, d = 1024, 5.5 -> 5.1 at d = 768, T = 4, 7.3 -> 6.8 at C = 6, T = 20, d = 3072); eight or sixteen waves (launch_few_rows).
 // Every storage type, every width, every hidden size whose rows are whole 16-byte chunks.
 #pragma once
 #include <type_traits>
@@ -24,8 +26,6 @@
 
 namespace tide {
 
-constexpr int kFewWaves = 8;
-constexpr int kFewThreads = kFewWaves * kWave;
 constexpr int kFewRows = 16, kFewCols = 16;
 constexpr int kFewMaxTiles = 64;         // row tiles of a call: one counter each
 
@@ -35,8 +35,8 @@ template <int DT> constexpr int few_groups() { return DT == kF32 ? 4 : 8; }
 constexpr int kFewChunks = 32;           // 16-byte chunks of a row per wave and turn: 512 bytes
 constexpr int kFewRowsPerTransfer = kWave / kFewChunks;
 // dynamic LDS: every wave's share of a turn of `rows` rows (rounded up to whole transfers)
-constexpr int few_lds_bytes(int rows) {
-    return kFewWaves * ((rows + kFewRowsPerTransfer - 1) / kFewRowsPerTransfer * kFewRowsPerTransfer) * kFewChunks * 16;
+constexpr int few_lds_bytes(int waves, int rows) {
+    return waves * ((rows + kFewRowsPerTransfer - 1) / kFewRowsPerTransfer * kFewRowsPerTransfer) * kFewChunks * 16;
 }
 
 // acc[16x16] += A[16 x 32] * B[32 x 16]: lane l supplies row / column l % 16 and the 8 consecutive k of quarter l / 16.
@@ -56,8 +56,8 @@ template <> __device__ __forceinline__ f32x4 mma_k32<kF16>(u32x4 a, u32x4 b, f32
 // that are its otherwise.  x = hi + mid + lo, each the upper 16 bits of what the one before leaves: exact (24 bits in three times 8), and fewer vector
 // instructions, which bound this form, than rounding to the nearest.  The five small products of the six have an accumulator
 // of their own and do not lose bits against the large sum.
-template <int DT, bool kFull = false>
-__global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const PrefillParams p) {
+template <int DT, int kWaves, bool kFull = false>
+__global__ __launch_bounds__(kWaves * kWave, 4) void tide_few_rows_kernel(const PrefillParams p) {
     typedef __attribute__((address_space(3))) char lds_char;
     typedef __attribute__((address_space(1))) const char glb_char;
     constexpr int kE = Storage<DT>::kBytes, kPl = Compute<DT>::kPlanes;
@@ -66,8 +66,8 @@ __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const Pre
     static_assert(kU * 32 * kE == kFewChunks * 16, "a wave's turn is kFewChunks chunks of a row");
     static_assert(!kFull || DT == kF32, "16-bit rows are exact in one term");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ __attribute__((aligned(16))) f32x4 part[kFewWaves][kWave];
-    __shared__ float ssq_part[kFewWaves][kFewRows];
+    __shared__ __attribute__((aligned(16))) f32x4 part[kWaves][kWave];
+    __shared__ float ssq_part[kWaves][kFewRows];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const Pre
     const uint32_t woff = (uint32_t)(((q >> 1) * 4 + cb) * 64 + (q & 1) * 32 + j0 + r) * 16;
     const char* zeros = reinterpret_cast<const char*>(g_zeros);
     const char* rbase = p.hidden + (int64_t)c * p.ckpt_stride_bytes + (int64_t)row0 * p.row_stride_bytes;
-    char* mine = smem + wave * (few_lds_bytes(rows) / kFewWaves);              // this wave's share of the rows
+    char* mine = smem + wave * (few_lds_bytes(1, rows));                // this wave's share of the rows
     // this lane's columns of the second layer (16 nb + 4 q + 0..3), first so that nothing waits for them later
     const int col = c * p.b + nb * kFewCols + 4 * q;
     const f32x4 w2v = *reinterpret_cast<const f32x4*>(p.w2 + col);
@@ -102,13 +102,14 @@ __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const Pre
     f32x4 acc = f32x4{0, 0, 0, 0};
     [[maybe_unused]] f32x4 small = f32x4{0, 0, 0, 0};            // kFull
     float ssq = 0.0f;
-    const int turns = (ng + kFewWaves * kU - 1) / (kFewWaves * kU);
+    const int turns = (ng + kWaves * kU - 1) / (kWaves * kU);
     const int rl = lane / kFewChunks, slot = lane % kFewChunks;  // transfer: row within it, chunk slot
     const int rr = min(r, rows - 1);                             // rows that do not exist repeat the last one; never stored
     const char* a_lds = mine + rr * (kFewChunks * 16);
     const int ax = (q * kLd) ^ rr;                               // chunk slot = chunk ^ row: conflict-free reads
     for (int i = 0; i < turns; ++i) {
-        const int g0 = (i * kFewWaves + wave) * kU;              // this wave's groups (uniform)
+        const int g0 = (i * kWaves + wave) * kU;                 // this wave's groups (uniform)
+        if (g0 >= ng) break;                                     // (nothing is left for this wave: no loads of zeros)
         u32x4 w[kU][kPl];
 #pragma unroll
         for (int u = 0; u < kU; ++u)
@@ -191,7 +192,7 @@ __global__ __launch_bounds__(kFewThreads, 4) void tide_few_rows_kernel(const Pre
         f32x4 s = part[0][lane];
         float ss = ssq_part[0][r];
 #pragma unroll
-        for (int w = 1; w < kFewWaves; ++w) { s += part[w][lane]; ss += ssq_part[w][r]; }
+        for (int w = 1; w < kWaves; ++w) { s += part[w][lane]; ss += ssq_part[w][r]; }
         if (!p.b1) b1v = f32x4{0, 0, 0, 0};
         const float inv = inv_rms_f32(ss, p.inv_d, p.eps);
         float z = 0.0f;

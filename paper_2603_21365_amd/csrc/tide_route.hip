@@ -928,16 +928,16 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
 }
 
 // The few-rows kernel: a workgroup per 16 rows and 16 columns of the bottleneck.  full: fp32 rows with all their bits.
-template <int DT, bool kFull = false> int launch_few(unsigned grid, hipStream_t st, const PrefillParams& p) {
+template <int DT, int kWaves, bool kFull = false> int launch_few(unsigned grid, hipStream_t st, const PrefillParams& p) {
     static bool raised[kMaxDevices] = {};
     int dev = 0;
     TIDE_HIP(hipGetDevice(&dev));
     if (!raised[dev]) {
-        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_few_rows_kernel<DT, kFull>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, few_lds_bytes(kFewRows)));
+        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_few_rows_kernel<DT, kWaves, kFull>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, few_lds_bytes(kWaves, kFewRows)));
         raised[dev] = true;
     }
-    hipLaunchKernelGGL((tide_few_rows_kernel<DT, kFull>), dim3(grid), dim3(kFewThreads), few_lds_bytes(std::min(p.T, kFewRows)), st, p);
+    hipLaunchKernelGGL((tide_few_rows_kernel<DT, kWaves, kFull>), dim3(grid), dim3(kWaves * kWave), few_lds_bytes(kWaves, std::min(p.T, kFewRows)), st, p);
     return TIDE_OK;
 }
 int launch_few_rows(const Scratch& sc, PrefillParams p, int dtype, bool full, hipStream_t st) {
@@ -947,8 +947,20 @@ int launch_few_rows(const Scratch& sc, PrefillParams p, int dtype, bool full, hi
     p.zpart = sc.part;
     p.counters = sc.counters;
     const unsigned grid = 8u * (unsigned)((p.total_tiles * p.k_slices + 7) / 8);
-    const int rc = dtype == TIDE_F32 && full ? launch_few<kF32, true>(grid, st, p)
-                                             : by_dtype(dtype, [&](auto dt) { return launch_few<decltype(dt)::value>(grid, st, p); });
+    // Sixteen waves where eight would take a second turn of the k loop (a dependent round trip) and a CU has one workgroup at most (its LDS holds one): us,
+    // eight / sixteen: 7.3 / 7.2 at C = 8, T = 16, d = 4096, f16, 9.9 / 9.3 at C = 4, T = 16, d = 8192, 8.7 / 8.5 at C = 10, T = 1; fp32, d = 4096, T = 1 / 8 9.0 / 8.7 and 10.1 / 9.7,
+    // d = 8192, C = 10, T = 1 14.2 / 13.0; but where one turn is enough 6.1 / 6.3 at d = 2048, T = 16, 5.7 / 6.0 at d = 1024, T = 33.
+    unsigned cus = 0;
+    int rc = resident_cus(&cus);
+    if (rc) return rc;
+    const int one_turn = 8 * (dtype == TIDE_F32 ? few_groups<kF32>() : few_groups<kBF16>()) * 32;      // elements of a row
+    const bool wide = p.dpad > one_turn && (int64_t)p.total_tiles * p.k_slices <= (int64_t)cus;
+    auto go = [&](auto waves_tag) {
+        constexpr int kWaves = decltype(waves_tag)::value;
+        return dtype == TIDE_F32 && full ? launch_few<kF32, kWaves, true>(grid, st, p)
+                                         : by_dtype(dtype, [&](auto dt) { return launch_few<decltype(dt)::value, kWaves>(grid, st, p); });
+    };
+    rc = wide ? go(std::integral_constant<int, 16>{}) : go(std::integral_constant<int, 8>{});
     if (rc) return rc;
     TIDE_HIP(hipGetLastError());
     return TIDE_OK;
