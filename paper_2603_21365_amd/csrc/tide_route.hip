@@ -470,18 +470,29 @@ template <bool kRagged, int kMaxBlocks> int launch_band_f32(unsigned grid, hipSt
 }
 
 // The one-tile kernel: a workgroup per 128-row tile from p.tile_begin on.
-template <int DT, int kHalves, bool kRagged = false> int launch_tile(hipStream_t st, const PrefillParams& p) {
+template <int DT, int kHalves, bool kRagged, int kRowsM, bool kBurst> int launch_tile_form(hipStream_t st, const PrefillParams& p) {
     static bool raised[kMaxDevices] = {};
     int dev = 0;
     TIDE_HIP(hipGetDevice(&dev));
+    constexpr int lds = tile_lds_bytes(kHalves, kRowsM, kBurst);
     if (!raised[dev]) {
-        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_prefill_tile_kernel<DT, kHalves, kRagged>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds_bytes(kHalves)));
+        TIDE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tide_prefill_tile_kernel<DT, kHalves, kRagged, kRowsM, kBurst>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         raised[dev] = true;
     }
     const unsigned grid = 8u * (unsigned)((p.total_tiles - p.tile_begin + 7) / 8);
-    hipLaunchKernelGGL((tide_prefill_tile_kernel<DT, kHalves, kRagged>), dim3(grid), dim3(tile_threads(kHalves)), tile_lds_bytes(kHalves), st, p);
+    hipLaunchKernelGGL((tide_prefill_tile_kernel<DT, kHalves, kRagged, kRowsM, kBurst>), dim3(grid), dim3(tile_threads(kHalves)), lds, st, p);
     return TIDE_OK;
+}
+// In bursts up to three quarters of the CUs (64 rows: always); figures at the kernel.
+template <int DT, int kHalves, bool kRagged = false, int kRowsM = kTileRows> int launch_tile(hipStream_t st, const PrefillParams& p) {
+    if constexpr (kHalves == 1) {
+        unsigned cus = 0;
+        const int rc = resident_cus(&cus);
+        if (rc) return rc;
+        if (kRowsM == 64 || 4 * (int64_t)(p.total_tiles - p.tile_begin) <= 3 * (int64_t)cus) return launch_tile_form<DT, 1, kRagged, kRowsM, true>(st, p);
+    }
+    if constexpr (kRowsM == kTileRows) return launch_tile_form<DT, kHalves, kRagged, kRowsM, false>(st, p);
 }
 
 // The streaming kernels use more LDS than the default per-kernel limit: raise it once.
@@ -509,7 +520,8 @@ enum PrefillKernel : int {
     kKernelWideF32 = 3,    // prefill_wide32_kernel.hpp
     kKernelTile = 4,       // prefill_tile_kernel.hpp
     kKernelStream128 = 5,  // prefill_dma_kernel.hpp, 128 rows per workgroup
-    kKernelStream64 = 6,   // prefill_dma_kernel.hpp, 64 rows per workgroup (width 256: both column halves per wave)
+    kKernelStream64 = 6,   // 64 rows per workgroup: prefill_tile_kernel.hpp where no workgroup has a second tile (16-bit rows, widths 64 / 128), else
+                           // prefill_dma_kernel.hpp (width 256: both column halves per wave)
     kKernelRing = 7,       // prefill_kernel.hpp
     kKernelBand = 8,       // prefill_band_kernel.hpp: rows_per_tile = 32 (the unit its bands are counted in)
     kKernelSplitKFused = 9,// prefill_splitk_kernel.hpp in one launch: 32-row tiles, the last workgroup of a tile finishes it
@@ -555,7 +567,7 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     // 128 rows as CUs: 25.7 against 29.6 us at 64 tiles on 256 CUs, measured); from there on 64-row
     // tiles are faster as long as every CU holds at most one (30.3 against 32.8 us at 80 tiles of 128
     // rows, 32.9 against 39.5 us at 128; with a second workgroup on some CUs 55 us at 129, where the
-    // one-tile kernel takes 43.6 us).  `form` overrides for tests and tuning.
+    // one-tile kernel takes 43.6 us; 16-bit rows of that kind are another 4-12 % faster since they run on the one-tile kernel).  `form` overrides for tests and tuning.
     const int64_t tiles128 = C * ((T + 127) / 128), tiles64 = C * ((T + 63) / 64);
     int rows_per_wg = (4 * tiles128 > (int64_t)cus && tiles64 <= (int64_t)cus) ? 64 : 128;
     if (form == 1) rows_per_wg = 64;
@@ -907,9 +919,19 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
                 // (rows above 7 KiB: "nt" is as fast or faster here, us default / nt, C = 4, T = 3232 and C = 10, T = 1300: 16.2 / 18.0 and 16.3 / 18.3 at d = 1752,
                 // 21.3 / 23.9 and 22.0 / 24.3 at 2600, but 33.3 / 32.9 and 34.6 / 33.2 at 3848, 38.5 / 37.3 and 40.0 / 37.6 at 4568)
                 if (p.d * (int)elem_bytes(dtype) > 7168) p.shared_lines = 0;
-                if (two_halves) rc = R ? no_form() : launch_dma<DT, 64, 2>(L.grid, st, p);
-                else if constexpr (DT != kF32 || !R) rc = launch_dma<DT, 64, 1, R>(L.grid, st, p);
-                else rc = no_form();
+                if (two_halves) {
+                    rc = R ? no_form() : launch_dma<DT, 64, 2>(L.grid, st, p);
+                } else if constexpr (DT != kF32) {
+                    // Where no workgroup has a second tile there is nothing to schedule: the one-tile kernel on 64 rows, 5-12 % faster
+                    // (figures there).  (The automatic choice is always that; a forced form may be more tiles.)
+                    if (p.total_tiles - p.tile_begin <= (int)L.grid) rc = launch_tile<DT, 1, R, 64>(st, p);
+                    else if constexpr (!R) rc = launch_dma<DT, 64, 1>(L.grid, st, p);
+                    else rc = no_form();
+                } else if constexpr (!R) {
+                    rc = launch_dma<DT, 64, 1>(L.grid, st, p);
+                } else {
+                    rc = no_form();
+                }
                 break;
             default:
                 if (ntile >= kMaxDepth)
