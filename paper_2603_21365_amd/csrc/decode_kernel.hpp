@@ -2,10 +2,10 @@
 // every decode step evaluates the routers on the new token's checkpoint states) for a
 // handful of rows per call, where the cost is reading C routers' weights and latency.
 //
-// The d-long contraction of each checkpoint is split over S = d/128 workgroups (times the
-// 128-column halves of the bottleneck: one for widths 64 and 128, two for 256) so that the
+// The d-long contraction of each checkpoint is split over slices of k and groups of columns (raw weights: up to
+// 512 k values and 32 columns per workgroup; packed: 128 k values and a 128-column half) so that the
 // whole chip pulls the weights at once (raw fp32 W1, no packing pass: with so few rows the
-// matrix cores have nothing to amortise).  Each workgroup writes its partial 128-vector and
+// matrix cores have nothing to amortise).  Each workgroup writes its partial sums of its columns and
 // partial sum of squares per token (device-scope stores, no fences); the last workgroup of a
 // checkpoint (device-scope counter) reduces them in a fixed order and finishes the router; the last checkpoint to
 // report a token selects its earliest exit.  One launch, no host round trip, deterministic sums.
@@ -25,7 +25,8 @@ struct DecodeParams {
     int dpad;             // rows of the packed weights (d rounded up to whole k-tiles)
     const float* b1;      // [C][b] or null
     const float* w2;      // [C][b]
-    int C, T, d, S;       // S = ceil(d / kDecodeSlice); the last slice may be partial (any d with 16-byte rows)
+    int C, T, d, S;       // S slices of k; the last one may be partial (any d with 16-byte rows)
+    int slice;            // raw weights: k values per slice, a multiple of 128, at most kDecodeRawSlice (packed weights: kDecodeSlice)
     int b, halves;        // bottleneck width (64, 128, 256) and its 128-column halves
     float eps;
     int32_t min_layer, no_exit;
@@ -38,7 +39,9 @@ struct DecodeParams {
 };
 
 constexpr int kDecodeThreads = 256;
-constexpr int kDecodeSlice = 128;    // k values per workgroup
+constexpr int kDecodeSlice = 128;    // k values per workgroup of the packed kernel
+constexpr int kDecodeRawSlice = 512; // most k values per workgroup of the raw kernel, ...
+constexpr int kDecodeRawCols = 32;   // ... and its columns
 constexpr int kDecodeTB = 8;         // tokens per pass
 constexpr int kPartPad = 4;          // the partial sum of squares, padded to 16 bytes
 
@@ -70,12 +73,12 @@ template <> __device__ __forceinline__ void chunk_to_f32<kBF16>(u32x4 c, float* 
 __device__ __forceinline__ uint32_t* decode_counter(const DecodeParams& p, int c) { return p.counter + ((c & 3) << 4) + (c >> 2); }
 
 template <int kHalves, int kTB>
-__device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int* flag, float* lds) {
+__device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int workgroups, int* flag, float* lds) {
     constexpr int part_stride = kHalves * kBottleneck + kPartPad;
     constexpr int kG = kDecodeThreads / (32 * kTB);      // threads per (token, quad): 8, 4, 2 or 1
     const int tid = threadIdx.x;
     stage_writes_done();
-    if (!last_arrival(decode_counter(p, c), (uint32_t)(p.S * kHalves), flag)) return;
+    if (!last_arrival(decode_counter(p, c), (uint32_t)workgroups, flag)) return;
 
     const int q = tid & 31, tl = (tid >> 5) % kTB, g = (tid >> 5) / kTB;
     f32x4 b1v[kHalves], w2v[kHalves];
@@ -91,6 +94,7 @@ __device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int*
     }
     const int s_begin = g * p.S / kG, s_end = (g + 1) * p.S / kG;
     const float* pc = p.part + (size_t)c * p.S * p.T * part_stride;
+    const StageBlock pb(pc);                                     // (a checkpoint's partial results are far below 4 GiB)
     f32x4* shares = reinterpret_cast<f32x4*>(lds);               // [kHalves][kG][kTB][32]
     float* ss_shares = lds + kHalves * kG * kTB * 128;           // [kG][kTB]
     for (int t0 = 0; t0 < p.T; t0 += kTB) {
@@ -111,9 +115,9 @@ __device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int*
             for (int hf = 0; hf < kHalves; ++hf)
 #pragma unroll
                 for (int u = 0; u < kBatch; ++u) {
-                    const float* at = pc + ((size_t)(kExact ? s0 + u : min(s0 + u, s_end - 1)) * p.T + ts) * part_stride + hf * kBottleneck + 4 * q;
+                    const uint32_t at = ((uint32_t)(kExact ? s0 + u : min(s0 + u, s_end - 1)) * p.T + ts) * part_stride + hf * kBottleneck + 4 * q;
                     if constexpr (kExact) v[hf][u] = f32x4{0, 0, 0, 0};
-                    if (!kExact || s0 + u < s_end) v[hf][u] = stage_load4(at);
+                    if (!kExact || s0 + u < s_end) v[hf][u] = pb.load4(4 * at);
                 }
             // lane q's slice of the batch
             const float sv = stage_load(pc + ((size_t)min(s0 + min(q, kBatch - 1), s_end - 1) * p.T + ts) * part_stride + kHalves * kBottleneck);
@@ -162,6 +166,9 @@ __device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int*
                 for (int i = 0; i < kG; ++i) a[hf] += shares[((hf * kG + i) * kTB + tl) * 32 + q];
             }
         }
+#pragma unroll
+        for (int hf = 0; hf < kHalves; ++hf)                     // (columns beyond the width: nobody may have written them)
+            if (hf * kBottleneck + 4 * q >= p.b) a[hf] = f32x4{0, 0, 0, 0};
         const float r = 1.0f / sqrtf(ssum / (float)p.d + p.eps);
         float term = 0.0f;
 #pragma unroll
@@ -185,53 +192,58 @@ __device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int*
     if (tid == 0) __hip_atomic_store(decode_counter(p, c), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Raw fp32 weights: a workgroup takes 32 columns (128 bytes of a row of W1: whole lines) and up to 512 k values, so that with the same number of workgroups
+// as 128 columns x 128 k makes, a checkpoint's last one has a quarter as many partial results to read.
 // kHalves = p.halves as a compile-time value (1 or 2): the width-128 kernel carries no code or
 // registers for a second column half.  kTB = tokens per pass: 1, 2, 4 or 8, the smallest that holds T (8 beyond).
 // What bounds it: 16 MiB of weights on the whole chip (C = 8, d = 4096: 2-3 us), then the hand-over's round trips.  Measured (fp16, C = 8,
 // d = 4096, us per call back to back, weights in the caches): 13.7 / 13.7 / 13.8 / 15.1 at T = 1 / 2 / 4 / 8 with eight tokens' arithmetic always, the weights queued before the rows (loads return in
 // order, so nothing was staged until the last weight was there), the counters of all checkpoints in one line and one thread per
-// (token, quad) in the finish; now 9.0 / 9.5 / 10.6 / 13.1, width 256 24.8 -> 16.1 at T = 4.
+// (token, quad) in the finish; 10.3 / 11.2 / 12.4 / 14.9 with 128 columns x 128 k per workgroup (the last one of a checkpoint then reads 66 KiB past every cache at
+// T = 4, now 17) and partial results read 8 bytes at a time; now 9.3 / 9.9 / 10.4 / 12.2.  d = 8192, C = 6, T = 8 19.2 -> 13.6; width 256, T = 4 18.8 -> 14.0; width 64,
+// T = 8 13.1 -> 9.8; C = 4, T = 2, d = 2048 7.7 -> 7.2; fp32, d = 3072, T = 4 11.4 -> 9.9.
 template <int DT, int kHalves, int kTB>
 __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const DecodeParams p) {
     constexpr int E = Storage<DT>::kElems;
-    constexpr int kChunksPerTok = kDecodeSlice / E;          // 16 or 32 lanes share a token
-    constexpr int kLoads = kDecodeSlice / 8;                 // float4 weight loads per thread
-    constexpr int kXLoads = (kTB * kChunksPerTok + kDecodeThreads - 1) / kDecodeThreads;
-    __shared__ __attribute__((aligned(16))) float xs[kTB][kDecodeSlice];   // gamma-scaled inputs of this slice
-    __shared__ float ss_lds[kTB];
-    __shared__ __attribute__((aligned(16))) float red[4][kTB][kBottleneck];
+    constexpr int kChunksPerTok = kDecodeRawSlice / E;       // 64 or 128 chunks of a row at most
+    constexpr int kLoads = kDecodeRawSlice / 32;             // float4 weight loads per thread
+    constexpr int kXLoads = kTB * kChunksPerTok / kDecodeThreads > 0 ? kTB * kChunksPerTok / kDecodeThreads : 1;
+    __shared__ __attribute__((aligned(16))) float xs[kTB][kDecodeRawSlice];   // gamma-scaled inputs of this slice
+    __shared__ float ss_lds[kTB][kChunksPerTok / kWave];
+    __shared__ __attribute__((aligned(16))) float red[4][kTB][kDecodeRawCols];
     __shared__ __attribute__((aligned(16))) float fin[kHalves * kDecodeThreads * 4 + kDecodeThreads / 32];
     __shared__ int flag;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // consecutive workgroup ids land on consecutive XCDs: keep one checkpoint's weights on
     // one XCD (and in its L2 across calls) whenever the counts allow it
-    const int nblk = p.C * p.S * kHalves;
+    const int groups = p.b / kDecodeRawCols;
+    const int nblk = p.C * p.S * groups;
     const int per_xcd = (nblk + 7) >> 3;
     const int work = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if ((int)(blockIdx.x >> 3) >= per_xcd || work >= nblk) return;
-    const int c = work / (p.S * kHalves);
-    const int rest = work - c * p.S * kHalves;
-    const int s = rest / kHalves, half = rest - s * kHalves;
-    const int k0 = s * kDecodeSlice;
+    const int c = work / (p.S * groups);
+    const int rest = work - c * p.S * groups;
+    const int s = rest / groups, grp = rest - s * groups;
+    const int k0 = s * p.slice, k_end = min(k0 + p.slice, p.d);
     constexpr int part_stride = kHalves * kBottleneck + kPartPad;
 
-    const char* base = p.hidden + (int64_t)c * p.ckpt_stride_bytes + (int64_t)k0 * Storage<DT>::kBytes;
-    const float* g = p.gamma ? p.gamma + (size_t)c * p.d + k0 : nullptr;
+    const char* base = p.hidden + (int64_t)c * p.ckpt_stride_bytes;
+    const float* g = p.gamma ? p.gamma + (size_t)c * p.d : nullptr;
     // rows first: loads return in order.  Branch-free (a load that does not count goes to a clamped address and its value is
-    // dropped), so that all of them stay in flight together.
+    // dropped), so that all of them stay in flight together.  Chunks beyond the slice or the row: zeros.
     u32x4 xv[kXLoads];
     float gv[kXLoads][E];
     auto load_rows = [&](int t0, int nt) {
 #pragma unroll
         for (int i = 0; i < kXLoads; ++i) {
-            const int qq = tid + i * kDecodeThreads, t = min(qq / kChunksPerTok, nt - 1), ch = qq % kChunksPerTok;
-            const bool inside = k0 + ch * E < p.d;              // the last slice of a ragged d is partial
-            const int chs = inside ? ch : 0;
-            xv[i] = *reinterpret_cast<const u32x4*>(base + (int64_t)(t0 + t) * p.row_stride_bytes + chs * 16);
+            const int qq = tid + i * kDecodeThreads, t = min(qq / kChunksPerTok, nt - 1), k = k0 + qq % kChunksPerTok * E;
+            const bool inside = k < k_end;
+            const int ks = inside ? k : k0;
+            xv[i] = *reinterpret_cast<const u32x4*>(base + (int64_t)(t0 + t) * p.row_stride_bytes + (int64_t)ks * Storage<DT>::kBytes);
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                const float ge = g ? g[chs * E + e] : 1.0f;
+                const float ge = g ? g[ks + e] : 1.0f;
                 gv[i][e] = inside ? ge : 1.0f;
             }
             if (!inside) xv[i] = u32x4{0, 0, 0, 0};
@@ -239,17 +251,13 @@ __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const Decod
     };
     load_rows(0, min(kTB, p.T));
 
-    // ---- this thread's weights: rows k0 + 16*kk + i, columns 4*jq .. 4*jq+3 of this half ----
-    const int kk = tid >> 5, jq = tid & 31;
-    // columns beyond the width and rows beyond d read as zeros: branch-free, as above
-    const bool live = half * kBottleneck + 4 * jq < p.b;
-    const float* w = p.W1 + (size_t)c * p.d * p.b + (live ? half * kBottleneck + 4 * jq : 0);
+    // ---- this thread's weights: rows k0 + 16*kk + i, columns 4*jq .. 4*jq+3 of this group; a shorter slice leaves the last threads of k without any ----
+    const int kk = tid >> 3, jq = tid & 7;
+    const float* w = p.W1 + (size_t)c * p.d * p.b + grp * kDecodeRawCols + 4 * jq;
+    const int kw = k0 + kLoads * kk;
     f32x4 wreg[kLoads];
 #pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-        const int k = k0 + kLoads * kk + i;
-        wreg[i] = *reinterpret_cast<const f32x4*>(w + (size_t)(k < p.d ? k : p.d - 1) * p.b);
-    }
+    for (int i = 0; i < kLoads; ++i) wreg[i] = *reinterpret_cast<const f32x4*>(w + (size_t)min(kw + i, k_end - 1) * p.b);
 
     for (int t0 = 0; t0 < p.T; t0 += kTB) {
         const int nt = min(kTB, p.T - t0);
@@ -267,56 +275,68 @@ __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const Decod
 #pragma unroll
                 for (int e = 0; e < E; ++e) xs[t][ch * E + e] = f[e] * gv[i][e];
             }
-            sq = xor_reduce_sum<(kChunksPerTok == 16 ? 4 : 5)>(sq);
-            if (ch == 0 && t < kTB) ss_lds[t] = sq;
+            sq = wave_sum(sq);                                   // a wave's 64 chunks are one token's
+            if (lane == 0 && t < kTB) ss_lds[t][ch / kWave] = sq;
         }
         __syncthreads();
 
         // ---- partial products over this thread's 16 k values ----
+        // (in two halves of eight, added at the end: shorter chains of roundings)
         float acc[kTB][4];
 #pragma unroll
         for (int t = 0; t < kTB; ++t)
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[t][j] = 0.0f;
+        float first[kTB][4];
 #pragma unroll
         for (int i4 = 0; i4 < kLoads / 4; ++i4) {
+            if (i4 == kLoads / 8) {
+#pragma unroll
+                for (int t = 0; t < kTB; ++t)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) { first[t][j] = acc[t][j]; acc[t][j] = 0.0f; }
+            }
 #pragma unroll
             for (int t = 0; t < kTB; ++t) {
                 const f32x4 x = *reinterpret_cast<const f32x4*>(&xs[t][kLoads * kk + 4 * i4]);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int k = k0 + kLoads * kk + 4 * i4 + i;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[t][j] = fmaf(x[i], (live && k < p.d) ? wreg[4 * i4 + i][j] : 0.0f, acc[t][j]);
+                    for (int j = 0; j < 4; ++j) acc[t][j] = fmaf(x[i], kw + 4 * i4 + i < k_end ? wreg[4 * i4 + i][j] : 0.0f, acc[t][j]);
                 }
             }
         }
-        // lanes l and l^32 hold the two k phases of a wave; then the four waves meet in LDS
+        // lanes 8 apart hold the eight k phases of a wave; then the four waves meet in LDS
 #pragma unroll
-        for (int t = 0; t < kTB; ++t)
+        for (int t = 0; t < kTB; ++t) {
+            f32x4 v;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float v = acc[t][j] + __shfl_xor(acc[t][j], 32, kWave);
-                if (lane < 32) red[wave][t][4 * jq + j] = v;
-            }
+            for (int j = 0; j < 4; ++j) v[j] = add_xor<32>(add_xor<16>(add_xor<8>(first[t][j] + acc[t][j])));
+            if (lane < 8) *reinterpret_cast<f32x4*>(&red[wave][t][4 * jq]) = v;
+        }
         __syncthreads();
-        // thread (tl, q) owns token tl and columns 4q..4q+3 from here on
+        // thread (tl, q) owns token tl and columns 4q..4q+3 of the group from here on
         {
-            const int tl = tid >> 5, q = tid & 31;
+            const int tl = tid >> 3, q = tid & 7;
             if (tl < nt) {
                 float* dst = p.part + (((size_t)c * p.S + s) * p.T + t0 + tl) * part_stride;
                 f32x4 v;
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     v[j] = (red[0][tl][4 * q + j] + red[1][tl][4 * q + j]) + (red[2][tl][4 * q + j] + red[3][tl][4 * q + j]);
-                stage_store4(dst + half * kBottleneck + 4 * q, v);
-                if (q == 0 && half == 0) stage_store(dst + kHalves * kBottleneck, ss_lds[tl]);
+                stage_store4(dst + grp * kDecodeRawCols + 4 * q, v);
+                if (q == 0 && grp == 0) {
+                    float sum = ss_lds[tl][0];
+#pragma unroll
+                    for (int i = 1; i < kChunksPerTok / kWave; ++i) sum += ss_lds[tl][i];
+                    stage_store(dst + kHalves * kBottleneck, sum);
+                }
             }
         }
         __syncthreads();
     }
 
-    decode_finish<kHalves, kTB>(p, c, &flag, fin);
+    decode_finish<kHalves, kTB>(p, c, p.S * groups, &flag, fin);
 }
 
 // The same with pre-packed weights (the serving loop's form: gamma already folded in, half the
@@ -431,7 +451,7 @@ __global__ __launch_bounds__(kDecodeThreads) void tide_decode_packed_kernel(cons
         }
         __syncthreads();
     }
-    decode_finish<kHalves, kDecodeTB>(p, c, &flag, fin);
+    decode_finish<kHalves, kDecodeTB>(p, c, p.S * kHalves, &flag, fin);
 }
 
 }  // namespace tide

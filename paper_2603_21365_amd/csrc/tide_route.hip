@@ -1006,7 +1006,10 @@ int launch_decode(const Scratch& sc, const void* hidden, int dtype, int64_t C, i
     p.C = (int)C;
     p.T = (int)T;
     p.d = (int)d;
-    p.S = (int)((d + kDecodeSlice - 1) / kDecodeSlice);
+    // raw weights: as few slices as hold the row, as equal as whole 128s allow
+    const int blocks = (int)((d + kDecodeSlice - 1) / kDecodeSlice), most = kDecodeRawSlice / kDecodeSlice;
+    p.slice = packed ? kDecodeSlice : (blocks + (blocks + most - 1) / most - 1) / ((blocks + most - 1) / most) * kDecodeSlice;
+    p.S = (int)((d + p.slice - 1) / p.slice);
     p.b = (int)b;
     p.halves = halves_of(b);
     p.eps = eps;
@@ -1021,7 +1024,7 @@ int launch_decode(const Scratch& sc, const void* hidden, int dtype, int64_t C, i
     p.counter = sc.counters;
     p.part = sc.part;
     p.arrive = o.exit_layer ? sc.arrive : nullptr;
-    const int nblk = p.C * p.S * p.halves;
+    const int nblk = p.C * p.S * (packed ? p.halves : p.b / kDecodeRawCols);
     const unsigned grid = 8u * (unsigned)((nblk + 7) / 8);
     by_dtype(dtype, [&](auto dt) {
         constexpr int DT = decltype(dt)::value;
@@ -1051,8 +1054,8 @@ int launch_decode(const Scratch& sc, const void* hidden, int dtype, int64_t C, i
 // d = 4096, C = 1 / 8, fp16: 9.5 / 10.6 us against 10.8 / 13.9 us at T = 1, 13.5 / 15.9 us at T = 8
 // and 40 us at T = 32; fp32 rows: 13.3 / 14.7 us against 11.3 / 14.4 us at T = 1 and 13.6 / 16.4 us at
 // T = 8).  With raw weights that form needs the packing pass first (7.5 us at C = 8), so the latency
-// kernel, which reads W1 as it is, keeps T <= 8 (fp16, C = 8, d = 4096: 9.1 / 10.7 / 12.2 / 13.2 us at T = 1 / 4 / 5 / 8, against the packing pass and
-// the few-rows kernel's 12.3 at T = 12: nearly level at the line, but the latency kernel multiplies the fp32 weights, not their 16-bit
+// kernel, which reads W1 as it is, keeps T <= 8 (fp16, C = 8, d = 4096: 9.3 / 10.4 / 12.1 / 12.2 us at T = 1 / 4 / 5 / 8, against the packing pass and
+// the few-rows kernel's 12.3 at T = 12: level at the line, but the latency kernel multiplies the fp32 weights, not their 16-bit
 // rounding, so a call does not lose those bits below it); it also keeps, up to
 // T = 32, what the split-k form does not cover (hidden sizes that are not multiples of 128).  Calls that would pack or have
 // packed weights go to the few-rows kernel instead where use_few_rows says so.
