@@ -135,7 +135,7 @@ _PACK = {np.float32: "%df", np.int32: "%di"}
 
 def _host_once(a, C, np_dtype):
     """_host for the arguments of one call: Python numbers, C of them or one for all, are packed without numpy's conversions (three
-    arguments: 22.8 -> 14.9 us of host time per select_exit_packed).  Anything else, and what struct refuses, goes the other way."""
+    arguments: 22.8 -> 14.9 us of host time per select_exit_packed, and 11.7 since the stream's handle is fetched directly).  Anything else, and what struct refuses, goes the other way."""
     try:
         if type(a) in _PLAIN:
             a = (a,) * C
@@ -147,8 +147,15 @@ def _host_once(a, C, np_dtype):
     return _host(a, C, np_dtype)
 
 
+# The handle of the current device's current stream without a Stream object around it (2.7 -> 0.3 us a call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or _raw_device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_raw_device())
 
 
 def _rows(hidden: torch.Tensor, ndim: int):
