@@ -14,6 +14,8 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
     # hipcc must not form packed-fp32 instructions from ordinary float code on this target
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # scalar kernel arguments in registers when a wave starts (14 dwords: 16 user registers less the argument block's address)
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
 ]
 
 

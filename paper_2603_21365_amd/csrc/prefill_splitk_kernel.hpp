@@ -32,6 +32,21 @@
 namespace tide {
 
 constexpr int kFinishThreads = 256;
+
+// The arguments that a launch of the pair needs before its first load, as scalars in front of the parameter block: the first 14 dwords of scalar arguments are
+// in registers when a wave starts (the compiler's kernarg preload, see build.py), where the block is a round trip of some 0.2 us away.  What is needed later is fetched while the first loads are
+// under way.  us, before / after: C = 1, T = 3000, d = 4096 13.3 / 12.8, T = 1000 8.7 / 8.1, C = 8, T = 200, d = 2048 8.3 / 7.9, T = 322, d = 4096 13.5 / 13.0 (without the preload 13.4).
+struct SplitkTiling {          // 64 bits
+    uint32_t total_tiles, tiles_per_ckpt, slices, stages, halves, deal_out, shared_lines;
+    __host__ __device__ static uint64_t pack(const PrefillParams& p) {
+        return (uint64_t)(uint32_t)p.total_tiles | (uint64_t)(uint32_t)p.tiles_per_ckpt << 20 | (uint64_t)(uint32_t)p.k_slices << 40 | (uint64_t)(uint32_t)p.ring_stages << 44 |
+               (uint64_t)(p.b > kBottleneck) << 48 | (uint64_t)(p.deal_out != 0) << 49 | (uint64_t)(p.shared_lines != 0) << 50;
+    }
+    __device__ static SplitkTiling unpack(uint64_t v) {
+        const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+        return SplitkTiling{lo & 0xfffff, (uint32_t)(v >> 20) & 0xfffff, hi >> 8 & 15, hi >> 12 & 15, 1 + (hi >> 16 & 1), hi >> 17 & 1, hi >> 18 & 1};
+    }
+};
 constexpr int kSplitkMaxS = 8;           // most workgroups that share a tile's k range (the single-launch form unrolls over them)
 
 template <int kBlocks> constexpr int splitk_lds_bytes(int stages) { return stages * kBlocks * 32 * kTileBytes; }   // the ring
@@ -46,7 +61,7 @@ template <int kBlocks> constexpr int splitk_part_floats() { return kBlocks * 32 
 //   - two consumer waves per SIMD, each one half of every k-tile; the two of a column block exchange halves of their accumulators at the end;
 //   - up to eight k-tiles in the ring, four in flight (a producer that asks for all eight at once is held up 3.3 us in doing so and hands
 //     the first one over at 3.5 us instead of 1.5);
-//   - in both launches the kernel arguments in one round trip, divisions by multiplication, and in the second one 32-bit offsets, no load
+//   - in both launches the first kernel arguments in registers and the rest in one round trip, divisions by multiplication, and in the second one 32-bit offsets, no load
 //     under a condition and vector-ALU exchanges.
 // us per call, before / after: 14.7 / 13.5 at C = 1, T = 3000; 14.0 / 13.5 at C = 8, T = 322; 10.5 / 9.3 at C = 1, T = 1000; fp32, C = 1, T = 3000 24.8 / 23.3;
 // width 256, C = 8, T = 200 14.3 / 13.4.  (Rotating the k order of a slice from tile to tile: 0.3 us slower; channels are hashed.)
@@ -68,7 +83,9 @@ constexpr int kSplitkMaxStages = 8;     // k-tiles of rows in the ring at most (
 // 8 bytes at a time, and lost to the second launch; with the rows in use only it wins at decode sizes (see the host's
 // choice).  Ordering is by completion, as in the latency kernel (device_utils.hpp: stage_store / last_arrival).
 template <int DT, int kBlocks, bool kFused = false, bool kRagged = false>
-__global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk_kernel(const PrefillParams p) {
+__global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk_kernel(
+    const char* hidden, const u32x4* packed, int64_t ckpt_stride_bytes, int64_t row_stride_bytes, uint64_t tiling, uint32_t by_slices_m, uint32_t by_tiles_m,
+    int T, int d, const PrefillParams p) {
     static_assert(!kFused || kBlocks == 1, "the single-launch form has 32-row tiles");
     typedef __attribute__((address_space(3))) char lds_char;
     typedef __attribute__((address_space(1))) const char glb_char;
@@ -82,43 +99,42 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
     constexpr int kPre = kBlocks == 4 || (kBlocks == 2 && DT == kF32) ? 1 : 2;
     constexpr int kPartFloats = splitk_part_floats<kBlocks>();
     char* ring = smem;
-    TIDE_FETCH_ARGS16(p.total_tiles, p.tiles_per_ckpt, p.by_tiles.m, p.by_slices.m, p.deal_out, p.k_slices, p.ring_stages, p.T, p.d, p.dpad, p.b,
-                      p.hidden, p.ckpt_stride_bytes, p.row_stride_bytes, p.packed, p.zpart);
+    const SplitkTiling tl = SplitkTiling::unpack(tiling);
+    const FastDiv by_slices{tl.slices, by_slices_m}, by_tiles{tl.tiles_per_ckpt, by_tiles_m};
+    const int dpad = (d + 127) & ~127;                           // rows of the packed weights
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int S = p.k_slices, stages = p.ring_stages;
-    const int halves = (p.b + kBottleneck - 1) / kBottleneck;
+    const int S = (int)tl.slices, stages = (int)tl.stages, halves = (int)tl.halves;
     // XCD x (workgroup id mod 8) takes the x-th eighth of the tile-major list: a tile's partial results come from one XCD, and the
     // second launch, cut the same way, finds them in that XCD's L2 (dealt out round-robin, the slices of a tile were on eight XCDs;
     // us per call: 17.0 -> 15.3 at C = 8, T = 322, d = 4096, 16.9 -> 15.5 at C = 1, T = 3000, 18.8 -> 17.2 at 4096; width 256, C = 8, T = 200 18.8 -> 15.5).
     // Every XCD then reads the whole W1' of its tiles: few tiles of long rows are dealt out instead (p.deal_out, see deals_out in tide_route.hip),
     // and so is the one-launch form, which hands over past every cache (C = 4, T = 16, bf16: 13.0 -> 12.3 at d = 12288, 15.5 -> 13.7 at 16384).
-    const int items = p.total_tiles * halves * S, per_xcd = (items + 7) >> 3;
-    const bool dealt = kFused || p.deal_out;
+    const int items = (int)tl.total_tiles * halves * S, per_xcd = (items + 7) >> 3;
+    const bool dealt = kFused || tl.deal_out;
     const int item = dealt ? (int)blockIdx.x : (int)((blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3));
     if (item >= items || (!dealt && (int)(blockIdx.x >> 3) >= per_xcd)) return;
-    const int th = p.by_slices(item), slice = item - th * S;
+    const int th = by_slices(item), slice = item - th * S;
     const int tile = halves == 2 ? th >> 1 : th, half = th - tile * halves;
-    const int ntile = p.dpad * Storage<DT>::kBytes / kTileBytes;
-    const int kt0 = p.by_slices(slice * ntile), nk = p.by_slices((slice + 1) * ntile) - kt0;
-    const int c = p.by_tiles(tile);
-    const int row0 = (tile - c * p.tiles_per_ckpt) * kRowsM;
+    const int ntile = dpad * Storage<DT>::kBytes / kTileBytes;
+    const int kt0 = by_slices(slice * ntile), nk = by_slices((slice + 1) * ntile) - kt0;
+    const int c = by_tiles(tile);
+    const int row0 = (tile - c * (int)tl.tiles_per_ckpt) * kRowsM;
     const int cb = wave & 3;                                       // a consumer's column block
-    float* zmine = p.zpart + (size_t)item * kPartFloats + (size_t)(cb * kBlocks) * 1024 + lane * 4;
 
     if (wave >= kConsumers) {
         // ------------------------------------------------------------------ producers
         const int pw = wave - kConsumers;
         const int rl = lane >> 4, slot = lane & 15;
-        const char* base = p.hidden + (int64_t)c * p.ckpt_stride_bytes + (int64_t)kt0 * kTileBytes;
+        const char* base = hidden + (int64_t)c * ckpt_stride_bytes + (int64_t)kt0 * kTileBytes;
         const char* gp[kInstrPerProducer];
-        const int row_bytes = p.d * Storage<DT>::kBytes, whole = row_bytes / kTileBytes;   // kRagged: k-tiles from `whole` on reach beyond the rows' end
+        const int row_bytes = d * Storage<DT>::kBytes, whole = row_bytes / kTileBytes;   // kRagged: k-tiles from `whole` on reach beyond the rows' end
 #pragma unroll
         for (int i = 0; i < kInstrPerProducer; ++i) {
             const int row = (pw * kInstrPerProducer + i) * 4 + rl;          // row within the tile
             int r = row0 + row;
-            r = r < p.T ? r : p.T - 1;                                      // ragged tail: re-read the last row
-            gp[i] = base + (int64_t)r * p.row_stride_bytes + ((slot ^ (row & 15)) << 4);
+            r = r < T ? r : T - 1;                                      // ragged tail: re-read the last row
+            gp[i] = base + (int64_t)r * row_stride_bytes + ((slot ^ (row & 15)) << 4);
         }
         int issued = 0, slot_in = 0;
         auto issue_next = [&]() {
@@ -134,7 +150,7 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
                                                      (lds_char*)(dst + (pw * kInstrPerProducer + i) * 1024), 16, 0, 0);
                 }
             } else {
-                row_transfers<kRagged>(p.shared_lines, [&](auto policy) {
+                row_transfers<kRagged>(tl.shared_lines, [&](auto policy) {
 #pragma unroll
                     for (int i = 0; i < kInstrPerProducer; ++i)
                         __builtin_amdgcn_global_load_lds((glb_char*)(gp[i] + (int64_t)issued * kTileBytes),
@@ -171,11 +187,11 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
         const int r = lane & 31;
         const int a_base = r * kTileBytes;
         const int y16 = (((lane >> 5) ^ (r & 15)) << 4) ^ (kh << 7);   // see prefill_dma_kernel.hpp; a half k-tile is 128 bytes of a row
-        const size_t ckpt_chunks = (size_t)p.dpad * kBottleneck / Storage<DT>::kElems;
+        const size_t ckpt_chunks = (size_t)dpad * kBottleneck / Storage<DT>::kElems;
         constexpr int kGroups = Compute<DT>::kMmaGroups / kKW, kPlanes = Compute<DT>::kPlanes;   // 16-k groups of a k-tile that this wave takes
         constexpr int kFrags = kGroups * kPlanes;                    // their W1' fragments
-        const u32x4* bptr = p.packed + ((size_t)c * halves + half) * ckpt_chunks + (size_t)(kh * kGroups) * 256 + cb * 64 + lane;
-        const size_t plane_chunks = (size_t)p.dpad * 16;                // fp32 rows: the hi and the mid plane of W1'
+        const u32x4* bptr = packed + ((size_t)c * halves + half) * ckpt_chunks + (size_t)(kh * kGroups) * 256 + cb * 64 + lane;
+        const size_t plane_chunks = (size_t)dpad * 16;                // fp32 rows: the hi and the mid plane of W1'
         const int yf16 = ((((lane >> 5) << 1) ^ (r & 15)) << 4) ^ (kh << 7);       // fp32 rows: see prefill_dma_kernel.hpp
         auto b_fragment = [&](int kt, int g, int pl) { return bptr[pl * plane_chunks + (size_t)(kt * Compute<DT>::kMmaGroups + g) * 256]; };
         // W1' fragments of kPre k-tiles in flight: with few k-tiles per workgroup nothing else hides
@@ -189,6 +205,7 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
 #pragma unroll
                 for (int pl = 0; pl < kPlanes; ++pl) breg[j][g * kPlanes + pl] = b_fragment(kt, g, pl);
         }
+        if constexpr (!kFused) asm volatile("" ::"s"(p.zpart), "s"(p.sspart));      // fetched while the first loads are under way
         f32x16 acc[kBlocks];
         float ssq[kBlocks];
 #pragma unroll
@@ -286,6 +303,7 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
             }
         }
 
+        float* zmine = p.zpart + (size_t)item * kPartFloats + (size_t)(cb * kBlocks) * 1024 + lane * 4;
         // ---- what this workgroup leaves behind: its accumulators as they are, and per wave one
         // partial sum of squares per row (lanes l and l^32 hold the two chunk phases)
 #pragma unroll
@@ -293,7 +311,7 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
             const float s2 = ssq[b] + __shfl_xor(ssq[b], 32, kWave);
             if constexpr (kFused) {
                 // register quad q holds rows 8 q + 4 (lane / 32) + (0..3): the quads below the tile's last row in use
-                const int quads = (min(p.T - row0, 32) + 7) >> 3;
+                const int quads = (min(T - row0, 32) + 7) >> 3;
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     if (q < quads) stage_store4(zmine + q * 256, f32x4{acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]});
@@ -342,7 +360,7 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
         int* flag = reinterpret_cast<int*>(z_part + 4 * 32);
         stage_writes_done();
         if (!last_arrival(p.counters + tile, (uint32_t)S, flag)) return;
-        const int quads = (min(p.T - row0, 32) + 7) >> 3;
+        const int quads = (min(T - row0, 32) + 7) >> 3;
         const size_t first_item = (size_t)tile * S;
         if (wave < kDmaConsumers) {
             // this lane's column of the second layer, fetched first so that the epilogue does not wait for it
@@ -403,7 +421,7 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
         if (tid == 0) __hip_atomic_store(p.counters + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // zero for the next call
         if (tid < 32) {
             const int t = row0 + tid;
-            if (t < p.T) {
+            if (t < T) {
                 const float z = p.tab.b2[c] + ((z_part[tid] + z_part[32 + tid]) + (z_part[64 + tid] + z_part[96 + tid]));
                 emit_router_result(p, c, t, z);
             }
@@ -418,29 +436,29 @@ __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk
 // launch: an eighth of the loads per lane and a quarter of the SiLUs, which took 0.5-1 us off a call (12.5 -> 11.6 us at C = 1, T = 1024,
 // 14.6 -> 13.6 at 2048, 17.4 -> 16.9 at 3000; width 256, C = 8, T = 200 21.2 -> 18.9).
 template <int kBlocks, int kHalves, int kQ, int kS>
-__global__ __launch_bounds__(kFinishThreads * kHalves) void tide_splitk_finish_kernel(const PrefillParams p) {
+__global__ __launch_bounds__(kFinishThreads * kHalves) void tide_splitk_finish_kernel(
+    const float* zpart, const float* b1, const float* w2, uint64_t tiling, uint32_t by_tiles_m, float inv_d, int T, int b, const PrefillParams p) {
     constexpr int kRows8 = 8 * kQ;
     __shared__ float z_part[4 * kHalves][kRows8];
     __shared__ float ss_part[4][kRows8];
     constexpr uint32_t kRowsM = kBlocks * 32;
     constexpr uint32_t kPartBytes = splitk_part_floats<kBlocks>() * sizeof(float);
-    TIDE_FETCH_ARGS16(p.total_tiles, p.tiles_per_ckpt, p.by_tiles.m, p.deal_out, p.k_slices, p.T, p.b, p.b1, p.w2, p.zpart, p.sspart, p.eps, p.C,
-                      p.logits, p.exit_layer, p.arrive);
+    const SplitkTiling tl = SplitkTiling::unpack(tiling);
+    const FastDiv by_tiles{tl.tiles_per_ckpt, by_tiles_m};
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = wave >> 2, w = wave & 3;
-    const uint32_t groups = (uint32_t)p.total_tiles * kBlocks * (4 / kQ), per_xcd = (groups + 7) >> 3;
-    const uint32_t item = p.deal_out ? blockIdx.x : (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);           // (see the first launch)
-    if (item >= groups || (!p.deal_out && (blockIdx.x >> 3) >= per_xcd)) return;
+    const uint32_t groups = tl.total_tiles * kBlocks * (4 / kQ), per_xcd = (groups + 7) >> 3;
+    const uint32_t item = tl.deal_out ? blockIdx.x : (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);           // (see the first launch)
+    if (item >= groups || (!tl.deal_out && (blockIdx.x >> 3) >= per_xcd)) return;
     const uint32_t quad = (item % (4 / kQ)) * kQ, tb = item / (4 / kQ);
     const uint32_t tile = tb / kBlocks, blk = tb - tile * kBlocks;
-    const uint32_t c = p.by_tiles((int)tile);
-    const uint32_t row0 = (tile - c * p.tiles_per_ckpt) * kRowsM + 32 * blk + 8 * quad;
-    if (row0 >= (uint32_t)p.T) return;             // padding rows only
-    const float b2c = p.tab.b2[c], thr = p.tab.thr_logit[c];
-    const uint32_t S = p.k_slices;                 // at most kS
+    const uint32_t c = by_tiles((int)tile);
+    const uint32_t row0 = (tile - c * tl.tiles_per_ckpt) * kRowsM + 32 * blk + 8 * quad;
+    if (row0 >= (uint32_t)T) return;             // padding rows only
+    const uint32_t S = tl.slices;                 // at most kS
     // partial accumulators: rows 8 q + 4 (lane / 32) + (0..3) of the block per quad, one column per lane; all slices' loads in
     // flight (a surplus load re-reads the last slice).  Offsets into the partial results have 32 bits: they are 512 MiB at most.
-    const char* zp = reinterpret_cast<const char*>(p.zpart) + ((tile * kHalves + half) * S * kPartBytes + (w * kBlocks + blk) * 4096 + quad * 1024);
+    const char* zp = reinterpret_cast<const char*>(zpart) + ((tile * kHalves + half) * S * kPartBytes + (w * kBlocks + blk) * 4096 + quad * 1024);
     f32x4 v[kS][kQ];
 #pragma unroll
     for (uint32_t j = 0; j < kS; ++j) {
@@ -453,16 +471,19 @@ __global__ __launch_bounds__(kFinishThreads * kHalves) void tide_splitk_finish_k
     const uint32_t sl = tid >> 5;
     float ss[kQ];
     if (squares) {
-        const char* sp = reinterpret_cast<const char*>(p.sspart) +
+        const char* sp = reinterpret_cast<const char*>(zpart) + (size_t)tl.total_tiles * kHalves * S * kPartBytes +
                          ((tile * kHalves * S + (sl < S ? sl : S - 1)) * kDmaConsumers + ((tid >> 3) & 3)) * (kRowsM * 4) + (32 * blk + 8 * quad + (tid & 7)) * 4;
 #pragma unroll
         for (int q = 0; q < kQ; ++q) ss[q] = *reinterpret_cast<const float*>(sp + 32 * q);
     }
     // this lane's column of the second layer (columns at and beyond the bottleneck width are zero padding: their w2 is zero), branch-free
-    const uint32_t col = kBottleneck * half + 32 * w + (lane & 31), at = c * p.b + (col < (uint32_t)p.b ? col : 0);
-    float b1c = (p.b1 ? p.b1 : p.w2)[at], w2c = p.w2[at];
-    if (!p.b1) b1c = 0.0f;
-    if (col >= (uint32_t)p.b) w2c = 0.0f;
+    const uint32_t col = kBottleneck * half + 32 * w + (lane & 31), at = c * b + (col < (uint32_t)b ? col : 0);
+    float b1c = (b1 ? b1 : w2)[at], w2c = w2[at];
+    if (!b1) b1c = 0.0f;
+    if (col >= (uint32_t)b) w2c = 0.0f;
+    // what the end needs, fetched while the partial results are under way
+    const float b2c = p.tab.b2[c], thr = p.tab.thr_logit[c];
+    TIDE_FETCH_ARGS8(p.eps, p.C, p.logits, p.exit_layer, p.arrive, p.fire_mask, b2c, thr);
     if (squares) {
 #pragma unroll
         for (int q = 0; q < kQ; ++q) {
@@ -485,7 +506,7 @@ __global__ __launch_bounds__(kFinishThreads * kHalves) void tide_splitk_finish_k
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int row = 8 * q + 4 * h + e;
-            const float inv = inv_rms_f32((ss_part[0][row] + ss_part[1][row]) + (ss_part[2][row] + ss_part[3][row]), p.inv_d, p.eps);
+            const float inv = inv_rms_f32((ss_part[0][row] + ss_part[1][row]) + (ss_part[2][row] + ss_part[3][row]), inv_d, p.eps);
             x[e] = w2c * silu_f32(fmaf(inv, sum[q][e], b1c));
         }
         const float total = reduce_scatter4(x, lane);     // of row 4 h + 2 (bit 3 of the lane) + (bit 2), in every lane of it
@@ -494,7 +515,7 @@ __global__ __launch_bounds__(kFinishThreads * kHalves) void tide_splitk_finish_k
     __syncthreads();
     if (tid < kRows8) {
         const int t = row0 + tid;
-        if (t < p.T) {
+        if (t < T) {
             float zsum = (z_part[0][tid] + z_part[1][tid]) + (z_part[2][tid] + z_part[3][tid]);
             if constexpr (kHalves == 2) zsum += (z_part[4][tid] + z_part[5][tid]) + (z_part[6][tid] + z_part[7][tid]);
             emit_router_result(p, c, t, b2c + zsum, thr);

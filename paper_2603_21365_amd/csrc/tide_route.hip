@@ -393,13 +393,15 @@ template <int DT, int kBlocks, bool kRagged> int launch_splitk(float* part, int6
     const int lds = splitk_lds_bytes<kBlocks>(p.ring_stages);
     p.zpart = part;
     p.sspart = (float*)((char*)part + z_bytes);
-    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, kBlocks, false, kRagged>), dim3(8u * (unsigned)((items + 7) / 8)), dim3(splitk_threads(false)), lds, st, p);
+    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, kBlocks, false, kRagged>), dim3(8u * (unsigned)((items + 7) / 8)), dim3(splitk_threads(false)), lds, st,
+                       p.hidden, p.packed, p.ckpt_stride_bytes, p.row_stride_bytes, SplitkTiling::pack(p), p.by_slices.m, p.by_tiles.m, p.T, p.d, p);
     // 8 rows per workgroup of the second launch while that is at most one and a half workgroups per CU, else 16 (8 / 16 rows, us): 11.5 / 12.7 at
     // C = 1, T = 1024, 16.9 / 17.4 at C = 8, T = 322 (384 workgroups of 8 rows), 19.8 / 18.8 at C = 1, T = 4096 (512)
+    const uint64_t tiling = SplitkTiling::pack(p);
     auto finish = [&](auto halves_tag, auto quads_tag) {
         constexpr int kH = decltype(halves_tag)::value, kQ = decltype(quads_tag)::value;
-        if (p.k_slices <= 4) hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, kH, kQ, 4>), dim3(8u * (unsigned)((tiles * kBlocks * (4 / kQ) + 7) / 8)), dim3(kH * kFinishThreads), 0, st, p);
-        else hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, kH, kQ, kSplitkMaxS>), dim3(8u * (unsigned)((tiles * kBlocks * (4 / kQ) + 7) / 8)), dim3(kH * kFinishThreads), 0, st, p);
+        if (p.k_slices <= 4) hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, kH, kQ, 4>), dim3(8u * (unsigned)((tiles * kBlocks * (4 / kQ) + 7) / 8)), dim3(kH * kFinishThreads), 0, st, p.zpart, p.b1, p.w2, tiling, p.by_tiles.m, p.inv_d, p.T, p.b, p);
+        else hipLaunchKernelGGL((tide_splitk_finish_kernel<kBlocks, kH, kQ, kSplitkMaxS>), dim3(8u * (unsigned)((tiles * kBlocks * (4 / kQ) + 7) / 8)), dim3(kH * kFinishThreads), 0, st, p.zpart, p.b1, p.w2, tiling, p.by_tiles.m, p.inv_d, p.T, p.b, p);
     };
     const bool fine = 2 * tiles * kBlocks * 4 <= 3 * (int64_t)cus;
     using std::integral_constant;
@@ -422,7 +424,8 @@ template <int DT, bool kRagged> int launch_splitk_fused(float* part, uint32_t* c
     p.sspart = (float*)((char*)part + items * splitk_part_floats<1>() * sizeof(float));
     p.counters = counters;
     p.ring_stages = kDmaStages;
-    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, 1, true, kRagged>), dim3(8u * (unsigned)((items + 7) / 8)), dim3(splitk_threads(true)), splitk_lds_bytes<1>(kDmaStages), st, p);
+    hipLaunchKernelGGL((tide_prefill_splitk_kernel<DT, 1, true, kRagged>), dim3(8u * (unsigned)((items + 7) / 8)), dim3(splitk_threads(true)), splitk_lds_bytes<1>(kDmaStages), st,
+                       p.hidden, p.packed, p.ckpt_stride_bytes, p.row_stride_bytes, SplitkTiling::pack(p), p.by_slices.m, p.by_tiles.m, p.T, p.d, p);
     return TIDE_OK;
 }
 
