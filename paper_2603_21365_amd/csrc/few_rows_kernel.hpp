@@ -16,7 +16,8 @@
 // fp32 rows, T = 4: 12.4 -> 9.4; d = 768, T = 4: 10.0 -> 6.3; d = 1600 (no multiple of 128), C = 12, T = 48: 18.4 -> 8.8.  kFull against the latency kernel: 34.6 -> 8.6 at C = 4, T = 32, d = 1608, 12.2 -> 7.5
 // at C = 8, T = 4, 13.2 -> 9.9 at C = 1, T = 1, d = 4104 (terms rounded to the nearest instead: 9.0, 8.0 and 11.8).
 // Later: the tick without an L2 invalidate 8.5 -> 7.9 at T = 48; waves without a share of the row load nothing instead of zeros, which cost as much as
-// data (6.2 -> 5.7 at C = 5, T = 33, d = 1024, 5.5 -> 5.1 at d = 768, T = 4, 7.3 -> 6.8 at C = 6, T = 20, d = 3072); eight or sixteen waves (launch_few_rows).
+// data (6.2 -> 5.7 at C = 5, T = 33, d = 1024, 5.5 -> 5.1 at d = 768, T = 4, 7.3 -> 6.8 at C = 6, T = 20, d = 3072); eight or sixteen waves (launch_few_rows); the first arguments
+// as scalars, the last ones fetched during the first loads (6.11 -> 6.01 at T = 1, d = 4096, 5.15 -> 4.92 at d = 768, T = 4, 9.4 -> 9.1 at C = 4, T = 16, d = 8192, fp32 9.75 -> 9.44 at T = 8).
 // Every storage type, every width, every hidden size whose rows are whole 16-byte chunks.
 #pragma once
 #include <type_traits>
@@ -56,8 +57,10 @@ template <> __device__ __forceinline__ f32x4 mma_k32<kF16>(u32x4 a, u32x4 b, f32
 // that are its otherwise.  x = hi + mid + lo, each the upper 16 bits of what the one before leaves: exact (24 bits in three times 8), and fewer vector
 // instructions, which bound this form, than rounding to the nearest.  The five small products of the six have an accumulator
 // of their own and do not lose bits against the large sum.
+// What the first loads need comes in scalar arguments (see SplitkTiling); dims = T | C << 16 | log2(b / 16) << 24, T at most 16 kFewMaxTiles.
 template <int DT, int kWaves, bool kFull = false>
-__global__ __launch_bounds__(kWaves * kWave, 4) void tide_few_rows_kernel(const PrefillParams p) {
+__global__ __launch_bounds__(kWaves * kWave, 4) void tide_few_rows_kernel(
+    const char* hidden, const u32x4* packed, int64_t ckpt_stride_bytes, int64_t row_stride_bytes, int d, uint32_t dims, const float* b1, const float* w2, const PrefillParams p) {
     typedef __attribute__((address_space(3))) char lds_char;
     typedef __attribute__((address_space(1))) const char glb_char;
     constexpr int kE = Storage<DT>::kBytes, kPl = Compute<DT>::kPlanes;
@@ -71,33 +74,35 @@ __global__ __launch_bounds__(kWaves * kWave, 4) void tide_few_rows_kernel(const 
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nbk = p.k_slices, shift = __builtin_ctz(nbk);
-    const int items = p.total_tiles << shift;
+    const int T = dims & 0xffff, C = dims >> 16 & 0xff, shift = dims >> 24, nbk = 1 << shift, b = nbk * kFewCols;
+    const int tiles_per_ckpt = (T + kFewRows - 1) / kFewRows;
+    const int items = (C * tiles_per_ckpt) << shift;
     const int per_xcd = (items + 7) >> 3;
     const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if ((int)(blockIdx.x >> 3) >= per_xcd || item >= items) return;
     const int ct = item >> shift, nb = item & (nbk - 1);
-    const int c = p.tiles_per_ckpt == 1 ? ct : ct / p.tiles_per_ckpt;
-    const int tile = ct - c * p.tiles_per_ckpt;
+    const int c = tiles_per_ckpt == 1 ? ct : ct / tiles_per_ckpt;
+    const int tile = ct - c * tiles_per_ckpt;
     const int row0 = tile * kFewRows;
-    const int rows = min(p.T - row0, kFewRows);                  // rows in use (at least one)
+    const int rows = min(T - row0, kFewRows);                  // rows in use (at least one)
 
     const int q = lane >> 4, r = lane & 15;
-    const int row_bytes = p.d * kE;
-    const int ng = p.dpad >> 5;                                  // 32-k groups of the packed weights
+    const int row_bytes = d * kE;
+    const int dpad = (d + 127) & ~127;                           // rows of the packed weights
+    const int ng = dpad >> 5;                                    // 32-k groups of the packed weights
     // the packed layout (pack_kernel.hpp) in 32-k groups: quarter q of group g is half q % 2 of 16-k group 2 g + q / 2
     const int half = nb >> 3, cb = (nb >> 1) & 3, j0 = (nb & 1) * 16;
-    const size_t plane_bytes = (size_t)p.dpad * 256;
-    const int halves = (p.b + kBottleneck - 1) / kBottleneck;
-    const char* wbase = reinterpret_cast<const char*>(p.packed) + ((size_t)c * halves + half) * kPl * plane_bytes;
+    const size_t plane_bytes = (size_t)dpad * 256;
+    const int halves = (b + kBottleneck - 1) / kBottleneck;
+    const char* wbase = reinterpret_cast<const char*>(packed) + ((size_t)c * halves + half) * kPl * plane_bytes;
     const uint32_t woff = (uint32_t)(((q >> 1) * 4 + cb) * 64 + (q & 1) * 32 + j0 + r) * 16;
     const char* zeros = reinterpret_cast<const char*>(g_zeros);
-    const char* rbase = p.hidden + (int64_t)c * p.ckpt_stride_bytes + (int64_t)row0 * p.row_stride_bytes;
+    const char* rbase = hidden + (int64_t)c * ckpt_stride_bytes + (int64_t)row0 * row_stride_bytes;
     char* mine = smem + wave * (few_lds_bytes(1, rows));                // this wave's share of the rows
     // this lane's columns of the second layer (16 nb + 4 q + 0..3), first so that nothing waits for them later
-    const int col = c * p.b + nb * kFewCols + 4 * q;
-    const f32x4 w2v = *reinterpret_cast<const f32x4*>(p.w2 + col);
-    f32x4 b1v = *reinterpret_cast<const f32x4*>((p.b1 ? p.b1 : p.w2) + col);
+    const int col = c * b + nb * kFewCols + 4 * q;
+    const f32x4 w2v = *reinterpret_cast<const f32x4*>(w2 + col);
+    f32x4 b1v = *reinterpret_cast<const f32x4*>((b1 ? b1 : w2) + col);
 
     f32x4 acc = f32x4{0, 0, 0, 0};
     [[maybe_unused]] f32x4 small = f32x4{0, 0, 0, 0};            // kFull
@@ -122,10 +127,11 @@ __global__ __launch_bounds__(kWaves * kWave, 4) void tide_few_rows_kernel(const 
         const bool whole = k0 + kFewChunks * 16 <= row_bytes;    // else: chunks beyond the end of the row are zeros
         for (int t = 0; t < rows; t += kFewRowsPerTransfer) {
             const int row = t + rl, off = k0 + ((slot ^ (row & 15)) << 4);
-            const char* src = rbase + (int64_t)min(row, rows - 1) * p.row_stride_bytes + off;
+            const char* src = rbase + (int64_t)min(row, rows - 1) * row_stride_bytes + off;
             if (!whole) src = off < row_bytes ? src : zeros;
             __builtin_amdgcn_global_load_lds((glb_char*)src, (lds_char*)(mine + t * kFewChunks * 16), 16, 0, 0);
         }
+        TIDE_FETCH_ARGS8(p.zpart, p.counters, p.inv_d, p.eps, p.exit_layer, p.logits, p.fire_mask, p.no_exit);     // for the end, while the loads are under way
         __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));        // vmcnt(0): the transfers have landed (no other wave reads them)
         asm volatile("" ::: "memory");
 #pragma unroll
@@ -176,7 +182,7 @@ __global__ __launch_bounds__(kWaves * kWave, 4) void tide_few_rows_kernel(const 
         asm volatile("" ::: "memory");
     }
 
-    // ---- the eight waves' shares of k meet in LDS; wave 0 finishes
+    // ---- the waves' shares of k meet in LDS; wave 0 finishes
     if constexpr (kFull) acc += small;
     part[wave][lane] = acc;
     ssq += __shfl_xor(ssq, 16, kWave);
@@ -185,15 +191,15 @@ __global__ __launch_bounds__(kWaves * kWave, 4) void tide_few_rows_kernel(const 
     __syncthreads();
     if (wave != 0) return;
     const int t = row0 + r;
-    const bool live = t < p.T;
-    const int per_row = p.C << shift;                            // partial logits of a row
+    const bool live = t < T;
+    const int per_row = C << shift;                            // partial logits of a row
     float* ztile = p.zpart + (size_t)row0 * per_row;
     {
         f32x4 s = part[0][lane];
         float ss = ssq_part[0][r];
 #pragma unroll
         for (int w = 1; w < kWaves; ++w) { s += part[w][lane]; ss += ssq_part[w][r]; }
-        if (!p.b1) b1v = f32x4{0, 0, 0, 0};
+        if (!b1) b1v = f32x4{0, 0, 0, 0};
         const float inv = inv_rms_f32(ss, p.inv_d, p.eps);
         float z = 0.0f;
 #pragma unroll
@@ -220,13 +226,13 @@ __global__ __launch_bounds__(kWaves * kWave, 4) void tide_few_rows_kernel(const 
     auto finish = [&](auto quads_tag) {
         constexpr int kQ = decltype(quads_tag)::value;           // quads of partial logits per row and checkpoint: b / 64
         constexpr int kBatch = kQ == 4 ? 2 : 4;                  // checkpoints whose loads are in flight together
-        for (int cb0 = 0; cb0 < p.C; cb0 += 4 * kBatch) {
+        for (int cb0 = 0; cb0 < C; cb0 += 4 * kBatch) {
             f32x4 v[kBatch][kQ];
             float b2[kBatch], thr[kBatch];
             int lid[kBatch];
 #pragma unroll
             for (int k = 0; k < kBatch; ++k) {
-                const int cc = min(cb0 + 4 * k + q, p.C - 1);
+                const int cc = min(cb0 + 4 * k + q, C - 1);
 #pragma unroll
                 for (int m = 0; m < kQ; ++m) v[k][m] = stage_load4(zr + (cc << shift) + 4 * m);
                 b2[k] = p.tab.b2[cc];
@@ -237,7 +243,7 @@ __global__ __launch_bounds__(kWaves * kWave, 4) void tide_few_rows_kernel(const 
 #pragma unroll
             for (int k = 0; k < kBatch; ++k) {
                 const int cc = cb0 + 4 * k + q;
-                if (live && cc < p.C) {
+                if (live && cc < C) {
 #pragma unroll
                     for (int m = 0; m < kQ; ++m) *reinterpret_cast<f32x4*>(zr + (cc << shift) + 4 * m) = f32x4{0, 0, 0, 0};
                 }
@@ -249,8 +255,8 @@ __global__ __launch_bounds__(kWaves * kWave, 4) void tide_few_rows_kernel(const 
 #pragma unroll
                 for (int m = 0; m < kQ; ++m) z += (v[k][m][0] + v[k][m][1]) + (v[k][m][2] + v[k][m][3]);
                 z += b2[k];
-                if (live && cc < p.C) {
-                    const int64_t o = (int64_t)cc * p.T + t;
+                if (live && cc < C) {
+                    const int64_t o = (int64_t)cc * T + t;
                     const bool f = z > thr[k];
                     if (p.logits) p.logits[o] = z;
                     if (p.prob) p.prob[o] = sigmoid_f32(z);

@@ -962,7 +962,8 @@ template <int DT, int kWaves, bool kFull = false> int launch_few(unsigned grid, 
                                      hipFuncAttributeMaxDynamicSharedMemorySize, few_lds_bytes(kWaves, kFewRows)));
         raised[dev] = true;
     }
-    hipLaunchKernelGGL((tide_few_rows_kernel<DT, kWaves, kFull>), dim3(grid), dim3(kWaves * kWave), few_lds_bytes(kWaves, std::min(p.T, kFewRows)), st, p);
+    hipLaunchKernelGGL((tide_few_rows_kernel<DT, kWaves, kFull>), dim3(grid), dim3(kWaves * kWave), few_lds_bytes(kWaves, std::min(p.T, kFewRows)), st, p.hidden, p.packed,
+                       p.ckpt_stride_bytes, p.row_stride_bytes, p.d, (uint32_t)p.T | (uint32_t)p.C << 16 | (uint32_t)__builtin_ctz((unsigned)p.k_slices) << 24, p.b1, p.w2, p);
     return TIDE_OK;
 }
 int launch_few_rows(const Scratch& sc, PrefillParams p, int dtype, bool full, hipStream_t st) {
@@ -1795,10 +1796,12 @@ int tide_exit_project(const void* hidden, int dtype, int64_t C, int64_t T, int64
             constexpr int kChunks = decltype(chunks)::value;
             if constexpr (kAhead && kChunks > 4)
                 if (!gain_ahead) {
-                    hipLaunchKernelGGL((tide_project_kernel<DT, kWpr, kGain, kChunks, false>), dim3(grid), dim3(kProjectThreads), 0, st, p);
+                    hipLaunchKernelGGL((tide_project_kernel<DT, kWpr, kGain, kChunks, false>), dim3(grid), dim3(kProjectThreads), 0, st, p.exit_layer, p.hidden,
+                       p.ckpt_stride_bytes, p.row_stride_bytes, p.final_hidden, p.final_row_stride_bytes, p.T, p.d, p);
                     return;
                 }
-            hipLaunchKernelGGL((tide_project_kernel<DT, kWpr, kGain, kChunks, kAhead>), dim3(grid), dim3(kProjectThreads), 0, st, p);
+            hipLaunchKernelGGL((tide_project_kernel<DT, kWpr, kGain, kChunks, kAhead>), dim3(grid), dim3(kProjectThreads), 0, st, p.exit_layer, p.hidden,
+                       p.ckpt_stride_bytes, p.row_stride_bytes, p.final_hidden, p.final_row_stride_bytes, p.T, p.d, p);
         };
         auto pick_chunks = [&](auto wpr, auto gain) {
             if constexpr (!decltype(wpr)::value) {
@@ -1931,7 +1934,8 @@ int tide_cosine_labels(const void* hidden, int dtype, int64_t C, int64_t T, int6
         constexpr int DT = decltype(dt)::value;
         auto go = [&](auto wpr, auto chunks) {
             hipLaunchKernelGGL((tide_cosine_kernel<DT, decltype(wpr)::value, decltype(chunks)::value>), dim3(grid),
-                               dim3(kCosineThreads), 0, st, p);
+                               dim3(kCosineThreads), 0, st, p.hidden, p.ckpt_stride_bytes, p.row_stride_bytes, p.final_hidden, p.final_row_stride_bytes, p.T, p.d,
+                               (uint32_t)p.C | (uint32_t)p.group_bits << 16, p);
         };
         auto pick = [&](auto wpr) {
             if (per_thread <= 2) go(wpr, std::integral_constant<int, 2>{});
