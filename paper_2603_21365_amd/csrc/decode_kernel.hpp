@@ -200,7 +200,7 @@ __device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int 
 // d = 4096, us per call back to back, weights in the caches): 13.7 / 13.7 / 13.8 / 15.1 at T = 1 / 2 / 4 / 8 with eight tokens' arithmetic always, the weights queued before the rows (loads return in
 // order, so nothing was staged until the last weight was there), the counters of all checkpoints in one line and one thread per
 // (token, quad) in the finish; 10.3 / 11.2 / 12.4 / 14.9 with 128 columns x 128 k per workgroup (the last one of a checkpoint then reads 66 KiB past every cache at
-// T = 4, now 17) and partial results read 8 bytes at a time; now 9.3 / 9.9 / 10.4 / 12.2.  d = 8192, C = 6, T = 8 19.2 -> 13.6; width 256, T = 4 18.8 -> 14.0; width 64,
+// T = 4, now 17) and partial results read 8 bytes at a time; now 9.2 / 9.7 / 10.3 / 12.3.  d = 8192, C = 6, T = 8 19.2 -> 13.7; width 256, T = 4 18.8 -> 13.1; width 64,
 // T = 8 13.1 -> 9.8; C = 4, T = 2, d = 2048 7.7 -> 7.2; fp32, d = 3072, T = 4 11.4 -> 9.9.
 template <int DT, int kHalves, int kTB>
 __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const DecodeParams p) {
@@ -258,6 +258,9 @@ __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const Decod
     f32x4 wreg[kLoads];
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) wreg[i] = *reinterpret_cast<const f32x4*>(w + (size_t)min(kw + i, k_end - 1) * p.b);
+
+    // for the end, while the loads are under way (9.3 -> 9.2 us at T = 1, 10.5 -> 10.3 at 4, width 256 14.0 -> 13.1; with eight tokens 2 % either way)
+    if constexpr (kTB < 8) TIDE_FETCH_ARGS8(p.part, p.counter, p.b1, p.w2, p.eps, p.logits, p.exit_layer, p.arrive);
 
     for (int t0 = 0; t0 < p.T; t0 += kTB) {
         const int nt = min(kTB, p.T - t0);

@@ -1058,7 +1058,7 @@ int launch_decode(const Scratch& sc, const void* hidden, int dtype, int64_t C, i
 // d = 4096, C = 1 / 8, fp16: 9.5 / 10.6 us against 10.8 / 13.9 us at T = 1, 13.5 / 15.9 us at T = 8
 // and 40 us at T = 32; fp32 rows: 13.3 / 14.7 us against 11.3 / 14.4 us at T = 1 and 13.6 / 16.4 us at
 // T = 8).  With raw weights that form needs the packing pass first (7.5 us at C = 8), so the latency
-// kernel, which reads W1 as it is, keeps T <= 8 (fp16, C = 8, d = 4096: 9.3 / 10.4 / 12.1 / 12.2 us at T = 1 / 4 / 5 / 8, against the packing pass and
+// kernel, which reads W1 as it is, keeps T <= 8 (fp16, C = 8, d = 4096: 9.2 / 10.3 / 12.2 / 12.3 us at T = 1 / 4 / 5 / 8, against the packing pass and
 // the few-rows kernel's 12.3 at T = 12: level at the line, but the latency kernel multiplies the fp32 weights, not their 16-bit
 // rounding, so a call does not lose those bits below it); it also keeps, up to
 // T = 32, what the split-k form does not cover (hidden sizes that are not multiples of 128).  Calls that would pack or have
