@@ -356,11 +356,9 @@ __device__ __forceinline__ bool last_arrival(uint32_t* counter, uint32_t expecte
     return *flag_lds != 0;
 }
 
-// Kernel arguments fetched together: the compiler loads each where it is first used, and every 64-byte line of the argument block
+// Kernel arguments fetched together, behind a kernel's first loads: the compiler loads each where it is first used, and every 64-byte line of the argument block
 // touched for the first time is a round trip of some 500 cycles, one after the other at the start of a small call.
 #define TIDE_FETCH_ARGS8(a, b, c, d, e, f, g, h) asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g), "s"(h))
-#define TIDE_FETCH_ARGS16(a, b, c, d, e, f, g, h, i, j, k, l, m, n, o, q)                                                                   \
-    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g), "s"(h), "s"(i), "s"(j), "s"(k), "s"(l), "s"(m), "s"(n), "s"(o), "s"(q))
 
 // Division of a workgroup's index by a launch constant: the compiler's own sequence is some thirty dependent instructions, and at the
 // start of a small call nothing runs beside them.  Exact for x * d < 2^32.

@@ -49,8 +49,8 @@ template <> __device__ __forceinline__ f32x4 mma_k32<kF16>(u32x4 a, u32x4 b, f32
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), acc, 0, 0, 0);
 }
 
-// p.tiles_per_ckpt = ceil(T / 16) <= kFewMaxTiles, p.total_tiles = C * that, p.k_slices = b / 16 column blocks (4, 8 or 16);
-// p.zpart: [16 * tiles_per_ckpt][C][b / 16] floats; p.counters: kFewMaxTiles words, zero on entry and on exit.
+// ceil(T / 16) <= kFewMaxTiles row tiles per checkpoint, b / 16 column blocks (4, 8 or 16);
+// p.zpart: [16 * row tiles][C][b / 16] floats; p.counters: kFewMaxTiles words, zero on entry and on exit.
 // blockIdx.x -> (checkpoint, row tile, column block), XCD x taking the x-th eighth of that list: a checkpoint's rows and
 // weights stay in one or two L2s.
 // kFull (fp32 rows): the whole fp32 value of a row times both terms of the weight, as the latency kernel multiplies them, for the calls
