@@ -992,6 +992,14 @@ int launch_few_rows(const Scratch& sc, PrefillParams p, int dtype, bool full, hi
     return TIDE_OK;
 }
 
+// The latency kernel's cut of a row of d values: raw weights in as few slices as hold it, as equal as whole 128s allow; packed ones in slices of 128.
+struct DecodeCut { int slice, S; };
+DecodeCut decode_cut(int64_t d, bool packed) {
+    const int blocks = (int)((d + kDecodeSlice - 1) / kDecodeSlice), most = kDecodeRawSlice / kDecodeSlice, least = (blocks + most - 1) / most;
+    const int per_slice = packed ? 1 : (blocks + least - 1) / least;
+    return DecodeCut{per_slice * kDecodeSlice, (blocks + per_slice - 1) / per_slice};
+}
+
 int launch_decode(const Scratch& sc, const void* hidden, int dtype, int64_t C, int64_t T, int64_t d, int64_t b, int64_t ckpt_stride,
                   int64_t row_stride, const float* gamma, const float* W1, const void* packed, float eps, const float* b1, const float* w2,
                   const CheckpointTable& tab, int32_t min_layer, int32_t no_exit, const Outputs& o, hipStream_t st) {
@@ -1010,10 +1018,9 @@ int launch_decode(const Scratch& sc, const void* hidden, int dtype, int64_t C, i
     p.C = (int)C;
     p.T = (int)T;
     p.d = (int)d;
-    // raw weights: as few slices as hold the row, as equal as whole 128s allow
-    const int blocks = (int)((d + kDecodeSlice - 1) / kDecodeSlice), most = kDecodeRawSlice / kDecodeSlice;
-    p.slice = packed ? kDecodeSlice : (blocks + (blocks + most - 1) / most - 1) / ((blocks + most - 1) / most) * kDecodeSlice;
-    p.S = (int)((d + p.slice - 1) / p.slice);
+    const DecodeCut cut = decode_cut(d, packed != nullptr);
+    p.slice = cut.slice;
+    p.S = cut.S;
     p.b = (int)b;
     p.halves = halves_of(b);
     p.eps = eps;
@@ -1162,7 +1169,7 @@ CallNeed call_need(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, bool r
     n.decode = !repack && use_decode(T, dtype, d, b, !raw_weights, variant, form_word);
     const int halves = halves_of(b);
     if (n.decode) {
-        const size_t S = (size_t)((d + kDecodeSlice - 1) / kDecodeSlice);
+        const size_t S = (size_t)decode_cut(d, !raw_weights).S;
         n.part_bytes = round256((size_t)C * S * (size_t)T * (size_t)(halves * kBottleneck + kPartPad) * sizeof(float));
     }
     // (the other paths' needs are counted all the same for a caller's block: what a caller has to bring does not depend on this choice)

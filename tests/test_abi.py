@@ -192,8 +192,10 @@ def test_workspace_size_query():
     assert tr.workspace_bytes(tr.BF16, 8, 4096, 4096, raw_weights=True) == 256 + 4096 * 8 + 8 * tr.packed_router_bytes(tr.BF16, 4096)
     # a decode step on packed weights: split-k pair, 32-row tiles x 8 slices -> 16.5 KiB per workgroup
     assert tr.workspace_bytes(tr.F16, 8, 8, 4096) == 256 + 256 + 8 * 8 * (32 * 128 + 4 * 32) * 4
-    # ... on raw weights: the latency kernel, d/128 slices of 128 + 4 floats per row
-    assert tr.workspace_bytes(tr.F16, 8, 1, 4096, raw_weights=True) == 256 + 256 + 8 * 32 * 1 * 132 * 4
+    # ... on raw weights: the latency kernel, d/512 slices of 128 + 4 floats per row
+    assert tr.workspace_bytes(tr.F16, 8, 1, 4096, raw_weights=True) == 256 + 256 + 8 * 8 * 1 * 132 * 4
+    # (five blocks of 128: two slices, of three and of two)
+    assert tr.workspace_bytes(tr.F16, 8, 1, 640, raw_weights=True) == 256 + 256 + 8 * 2 * 1 * 132 * 4
     # multiples of 256, monotone in T for a fixed path, zero for unsupported shapes
     for T in (1, 33, 500, 4096, 16384):
         assert tr.workspace_bytes(tr.BF16, 9, T, 4096) % 256 == 0

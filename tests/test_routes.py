@@ -102,3 +102,14 @@ def test_few_rows_of_many_checkpoints(dtype, T, d, kernel, slices):
 def test_the_line_between_few_rows_and_the_pair(dtype, C, d, b, most):
     assert tr.call_route(dtype, C, most, d, b)["kernel"] == tr.ROUTE_FEW_ROWS
     assert tr.call_route(dtype, C, most + 1, d, b)["kernel"] == SPLITK
+
+
+def test_raw_weights_on_few_rows_fit_the_fixed_array():
+    """The latency kernel on raw weights keeps partial results of d / 512 slices: its largest call fits where d / 128 would not."""
+    shape = (tr.BF16, 32, 8, 16384, 256)
+    need = state_bytes(8) + 32 * 32 * 8 * (256 + 4) * 4
+    assert tr.workspace_bytes(*shape, raw_weights=True) == need
+    route = tr.call_route(*shape, raw_weights=True, block_bytes=tr.noalloc_scratch_bytes())
+    assert route["kernel"] == tr.ROUTE_LATENCY and route["scratch_bytes"] == need
+    assert tr.call_route(*shape, raw_weights=True, block_bytes=need)["kernel"] == tr.ROUTE_LATENCY
+    assert refused(*shape, raw_weights=True, block_bytes=need - 256)
