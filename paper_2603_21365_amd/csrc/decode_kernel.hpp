@@ -42,6 +42,7 @@ constexpr int kDecodeThreads = 256;
 constexpr int kDecodeSlice = 128;    // k values per workgroup of the packed kernel
 constexpr int kDecodeRawSlice = 512; // most k values per workgroup of the raw kernel, ...
 constexpr int kDecodeRawCols = 32;   // ... and its columns
+constexpr int kDecodeRawMaxSlices = kMaxHidden / kDecodeRawSlice;    // (decode_cut: as few slices as hold the row)
 constexpr int kDecodeTB = 8;         // tokens per pass
 constexpr int kPartPad = 4;          // the partial sum of squares, padded to 16 bytes
 
@@ -141,15 +142,20 @@ __device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int 
                 else { add_batch(s0, integral_constant<int, 4>{}, std::false_type{}); s0 += 4; }
             }
         } else {
-            // fewer tokens: as small a batch as covers the thread's share
+            // fewer tokens (raw weights only): as small a batch as covers the thread's share.  No batch is compiled in that no share needs: with
+            // all up to 32 the kernels for 1 / 2 / 4 tokens, widths up to 128, had 196 / 172 / 172 registers, now 128 / 134 / 163 at most (us, C = 32, f16, T = 1:
+            // 7.7 -> 7.4 at d = 640; fp32, T = 4, d = 8192: 41 -> 35).
+            constexpr int kMostShare = (kDecodeRawMaxSlices + kG - 1) / kG;          // 4, 8 or 16
             auto add_slices = [&](auto batch_tag) {
                 for (int s0 = s_begin; s0 < s_end; s0 += decltype(batch_tag)::value) add_batch(s0, batch_tag, std::false_type{});
             };
             const int share = (p.S + kG - 1) / kG;
-            if (share <= 4) add_slices(integral_constant<int, 4>{});
-            else if (share <= 8) add_slices(integral_constant<int, 8>{});
-            else if (share <= 16 || kHalves == 2) add_slices(integral_constant<int, kHalves == 2 ? 8 : 16>{});
-            else add_slices(integral_constant<int, 32>{});
+            if (kMostShare <= 4 || share <= 4) {
+                add_slices(integral_constant<int, 4>{});
+            } else if constexpr (kMostShare > 4) {
+                if (kMostShare <= 8 || kHalves == 2 || share <= 8) add_slices(integral_constant<int, 8>{});
+                else if constexpr (kMostShare > 8 && kHalves == 1) add_slices(integral_constant<int, 16>{});
+            }
         }
         if constexpr (kG > 1) {
 #pragma unroll

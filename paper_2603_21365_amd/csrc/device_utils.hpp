@@ -7,6 +7,7 @@
 namespace tide {
 
 constexpr int kBottleneck = 128;
+constexpr int kMaxHidden = 16384;       // longest row of hidden states
 constexpr int kWave = 64;
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;

@@ -60,6 +60,7 @@ constexpr int kDecodeAutoMaxT = 32;
 constexpr int kDecodeRawMaxT = 8;          // raw weights where the split-k prefill form applies
 constexpr int kDecodeMaxT = 64;
 static_assert(kFewMaxTiles <= (int)kCounterSlots, "the few-rows kernel: a counter per row tile");
+static_assert((uint64_t)kMaxHidden / kDecodeSlice * kDecodeMaxT * (2 * kBottleneck + kPartPad) * sizeof(float) < (1ull << 32), "decode_finish: 32-bit offsets");
 constexpr int kSplitkMaxSlices = 8;        // workgroups that share a tile's k range in the split-k prefill form
 constexpr int kSplitkRingBytes = 128 * 1024;   // most LDS for its ring
 constexpr int kSplitkMaxTiles = 128;       // most 128-row tiles' worth of rows (x column halves) the split-k form is considered for ...
@@ -218,7 +219,7 @@ bool supported_bottleneck(int64_t b) { return b == 64 || b == 128 || b == 256; }
 // rows (repack_kernel.hpp) and then takes the tuned kernels.
 bool supported_hidden(int dtype, int64_t d) {
     (void)dtype;
-    return d >= 1 && d <= 16384;
+    return d >= 1 && d <= kMaxHidden;
 }
 bool chunked_rows(int dtype, int64_t d) { return (d * (int64_t)(dtype == TIDE_F32 ? 4 : 2)) % 16 == 0; }
 bool needs_repack(int dtype, int64_t d, int64_t b) { return !chunked_rows(dtype, d) || (d % 128 != 0 && b == 256); }
