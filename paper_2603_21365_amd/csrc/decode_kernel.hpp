@@ -235,27 +235,26 @@ __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const Decod
     constexpr int part_stride = kHalves * kBottleneck + kPartPad;
 
     const char* base = p.hidden + (int64_t)c * p.ckpt_stride_bytes;
-    const float* g = p.gamma ? p.gamma + (size_t)c * p.d : nullptr;
-    // rows first: loads return in order.  Branch-free (a load that does not count goes to a clamped address and its value is
+    // rows first: loads return in order.  Branch-free (a load that does not count goes to a clamped address or beyond the end of its block, and its value is
     // dropped), so that all of them stay in flight together.  Chunks beyond the slice or the row: zeros.
+    // (With the gain's loads under a condition -- there may be none -- each of them was waited for by itself, four to a thread, eight at T > 4.
+    // us in a graph of calls, f16, C = 8, d = 4096: 7.6 -> 6.9 at T = 1, 8.3 -> 7.9 at 4, 10.2 -> 9.6 at 8; width 256, C = 28, T = 1 25.2 -> 23.5.  A barrier to the
+    // scheduler behind the rows' loads only: with one behind the weights' too the last case takes 24.7.)
+    const bool gain = p.gamma != nullptr;
+    const BoundedBlock g((gain ? p.gamma : p.W1) + (size_t)c * p.d, gain ? (uint32_t)p.d * 4 : 0);
     u32x4 xv[kXLoads];
-    float gv[kXLoads][E];
+    f32x4 gv[kXLoads][E / 4];
     auto load_rows = [&](int t0, int nt) {
 #pragma unroll
         for (int i = 0; i < kXLoads; ++i) {
-            const int qq = tid + i * kDecodeThreads, t = min(qq / kChunksPerTok, nt - 1), k = k0 + qq % kChunksPerTok * E;
-            const bool inside = k < k_end;
-            const int ks = inside ? k : k0;
+            const int qq = tid + i * kDecodeThreads, t = min(qq / kChunksPerTok, nt - 1), k = k0 + qq % kChunksPerTok * E, ks = k < k_end ? k : k0;
             xv[i] = *reinterpret_cast<const u32x4*>(base + (int64_t)(t0 + t) * p.row_stride_bytes + (int64_t)ks * Storage<DT>::kBytes);
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const float ge = g ? g[ks + e] : 1.0f;
-                gv[i][e] = inside ? ge : 1.0f;
-            }
-            if (!inside) xv[i] = u32x4{0, 0, 0, 0};
+            for (int e = 0; e < E; e += 4) gv[i][e / 4] = g.load4((uint32_t)(ks + e) * 4);       // (gamma is aligned to a float only)
         }
     };
     load_rows(0, min(kTB, p.T));
+    __builtin_amdgcn_sched_barrier(0);
 
     // ---- this thread's weights: rows k0 + 16*kk + i, columns 4*jq .. 4*jq+3 of this group; a shorter slice leaves the last threads of k without any ----
     const int kk = tid >> 3, jq = tid & 7;
@@ -275,14 +274,15 @@ __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const Decod
 #pragma unroll
         for (int i = 0; i < kXLoads; ++i) {
             const int qq = tid + i * kDecodeThreads, t = qq / kChunksPerTok, ch = qq % kChunksPerTok;
+            const bool inside = k0 + ch * E < k_end;
             float f[E];
-            chunk_to_f32<DT>(xv[i], f);
+            chunk_to_f32<DT>(inside ? xv[i] : u32x4{0, 0, 0, 0}, f);
             float sq = 0.0f;
 #pragma unroll
             for (int e = 0; e < E; ++e) sq = fmaf(f[e], f[e], sq);
             if (t < kTB) {
 #pragma unroll
-                for (int e = 0; e < E; ++e) xs[t][ch * E + e] = f[e] * gv[i][e];
+                for (int e = 0; e < E; ++e) xs[t][ch * E + e] = f[e] * (gain && inside ? gv[i][e / 4][e % 4] : 1.0f);
             }
             sq = wave_sum(sq);                                   // a wave's 64 chunks are one token's
             if (lane == 0 && t < kTB) ss_lds[t][ch / kWave] = sq;

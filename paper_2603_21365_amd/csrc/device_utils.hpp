@@ -334,6 +334,14 @@ struct StageBlock {
         return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, byte, 0, kDeviceScope));
     }
 };
+// A block of `bytes` bytes from an address that is the same in every lane: what is loaded beyond its end is zero and costs no memory access.
+struct BoundedBlock {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ BoundedBlock(const void* base, uint32_t bytes) : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000)) {}
+    __device__ __forceinline__ f32x4 load4(uint32_t byte) const {        // byte a multiple of 4
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, byte, 0, 0));
+    }
+};
 // Wait until every memory operation this wave has issued is complete (stores acknowledged).
 __device__ __forceinline__ void stage_writes_done() {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
