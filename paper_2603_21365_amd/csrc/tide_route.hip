@@ -974,14 +974,19 @@ int launch_few_rows(const Scratch& sc, PrefillParams p, int dtype, bool full, hi
     p.zpart = sc.part;
     p.counters = sc.counters;
     const unsigned grid = 8u * (unsigned)((p.total_tiles * p.k_slices + 7) / 8);
-    // Sixteen waves where eight would take a second turn of the k loop (a dependent round trip) and a CU has one workgroup at most (its LDS holds one): us,
-    // eight / sixteen: 7.3 / 7.2 at C = 8, T = 16, d = 4096, f16, 9.9 / 9.3 at C = 4, T = 16, d = 8192, 8.7 / 8.5 at C = 10, T = 1; fp32, d = 4096, T = 1 / 8 9.0 / 8.7 and 10.1 / 9.7,
-    // d = 8192, C = 10, T = 1 14.2 / 13.0; but where one turn is enough 6.1 / 6.3 at d = 2048, T = 16, 5.7 / 6.0 at d = 1024, T = 33.
+    // Sixteen waves where eight would take a second turn of the k loop (a dependent round trip), a CU has one workgroup at most (its LDS holds one) and there
+    // is enough to read: a workgroup of sixteen starts and ends 0.2 us later.  us in a graph of calls, eight / sixteen, C = 4 where not said: rows of 8 KiB
+    // (16-bit, d = 4096): C = 1, T = 1 5.3 / 5.55, T = 4 5.85 / 6.1, C = 8, T = 8 6.5 / 6.55, T = 16 7.2 / 6.9; 10 KiB: T = 4 6.2 / 6.4, T = 16 7.65 / 7.55; 12 KiB: T = 4 6.65 / 6.7,
+    // C = 8, T = 8 7.5 / 7.35, T = 16 8.45 / 7.95; fp32, 10 KiB: T = 2 6.3 / 6.65, T = 8 level, C = 8, T = 16 8.3 / 8.2; 12 KiB: C = 1, T = 1 level, C = 8, T = 4 7.7 / 7.55, T = 8 8.3 / 7.75;
+    // 16 KiB (fp32, d = 4096): C = 1, T = 1 7.95 / 7.45, T = 8 9.0 / 8.3; 16-bit: C = 1, T = 1 level, C = 8, T = 16 10.15 / 9.55; 32 KiB, C = 8: T = 1 11.4 / 10.7, fp32 13.4 / 11.9.
+    // Never where one turn is enough: 6.1 / 6.3 at d = 2048, T = 16, 5.7 / 6.0 at d = 1024, T = 33.
     unsigned cus = 0;
     int rc = resident_cus(&cus);
     if (rc) return rc;
     const int one_turn = 8 * (dtype == TIDE_F32 ? few_groups<kF32>() : few_groups<kBF16>()) * 32;      // elements of a row
-    const bool wide = p.dpad > one_turn && (int64_t)p.total_tiles * p.k_slices <= (int64_t)cus;
+    const int row_bytes = p.dpad * (int)elem_bytes(dtype);
+    const bool wide = p.dpad > one_turn && (int64_t)p.total_tiles * p.k_slices <= (int64_t)cus &&
+                      (row_bytes >= (dtype == TIDE_F32 ? 12288 : 16384) || std::min(p.T, kFewRows) * row_bytes > 81920);
     auto go = [&](auto waves_tag) {
         constexpr int kWaves = decltype(waves_tag)::value;
         return dtype == TIDE_F32 && full ? launch_few<kF32, kWaves, true>(grid, st, p)
