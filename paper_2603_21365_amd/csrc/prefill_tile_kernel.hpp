@@ -45,7 +45,8 @@ constexpr int tile_threads(int kHalves) { return (tile_consumers(kHalves) + kDma
 // registers), the rows in a burst of their own, and no more of them ahead than two stages (four stages instead of three: 2-4 % slower).  Tiles of 64 rows, which read
 // twice as much W1' as rows, take two k-tiles per stage, and their producers let W1' go first (some 640 cycles).  us, without / with, bf16, C = 8, rows from memory:
 //   64 rows (the streaming kernel before): d = 4096 29.7 / 27.1 at T = 1203, 38.4 / 33.9 at 2040, d = 5120 35.8 / 33.5 at 1250, d = 8192 53.1 / 47.2, d = 1024 12.3 / 11.6 at
-//   1500 (one k-tile per stage: 29.1, 37.1 at d = 4096);
+//   1500 (one k-tile per stage: 29.1, 37.1 at d = 4096); an odd number of k-tiles: d = 640 9.45 / 9.15 at 1500, 1600 17.5 / 16.3 at 2040, d = 384 level (its last stage
+//   asks for the W1' of its one k-tile twice; a branch round the second half of a stage's requests: 6 % faster there, up to 5 % slower from d = 1920 on);
 //   128 rows: d = 4096 43.5 / 41.0 at T = 2100, 47.4 / 45.7 at 3000, but 50.9 / 51.1 at 3500, 55.4 / 56.4 at 4096; d = 2048 24.8 / 23.7, 27.0 / 26.4, 28.4 / 28.7, 30.4 / 32.6; d = 8192
 //   79.6 / 75.4, 86.8 / 86.3, 93.2 / 95.5, 102.8 / 107.4 (d = 5120 60.5 / 57.7 at 3000, 68.6 / 68.3 at 4096): with most of the CUs at work HBM bounds it, and
 //   the finer mixture keeps that busier -- hence bursts up to three quarters of the CUs (launch_tile).
@@ -112,8 +113,9 @@ __global__ __launch_bounds__(tile_threads(kHalves), 1) void tide_prefill_tile_ke
             if (issued >= nstage) return;
 #pragma unroll
             for (int h = 0; h < kT; ++h) {
+                if (h > 0 && issued * kT + h >= ntile) break;               // (an odd number of k-tiles: the last stage has one)
                 char* dst = ring + (issued % kStages) * kStageBytes + h * kTileOfRows;
-                const int kt = kt_of(min(issued * kT + h, ntile - 1));      // (an odd number of k-tiles: the last stage repeats one, nobody reads it)
+                const int kt = kt_of(issued * kT + h);
                 if (kRagged && kt >= whole) {
 #pragma unroll
                     for (int i = 0; i < kInstrPerProducer; ++i) {
@@ -138,11 +140,13 @@ __global__ __launch_bounds__(tile_threads(kHalves), 1) void tide_prefill_tile_ke
         for (int k = 0; k < nstage; ++k) {
             // stage k has landed once only the transfers of the younger stages are outstanding (loads complete in issue order)
             const int younger = issued - k - 1;
-            if (younger >= 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kPerStage));
+            static_assert(kT == 1 || kStages == 3, "at most one stage of two k-tiles is younger");
+            if (kT == 1 && younger >= 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kPerStage));
+            else if (kT > 1 && younger == 1 && (k + 2) * kT > ntile) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kInstrPerProducer));      // (the last stage, with one k-tile)
             else if (younger == 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kPerStage));
             else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             ring_barrier();                        // stage k handed over; the slot of stage k-1 is free
-            if constexpr (kRowsM == 64) __builtin_amdgcn_s_sleep(10);       // (the consumers' W1' first)
+            if (kRowsM == 64 && issued < nstage) __builtin_amdgcn_s_sleep(10);      // (the consumers' W1' first)
             issue_next();
         }
         ring_barrier();                            // the two barriers of the consumers' epilogue
