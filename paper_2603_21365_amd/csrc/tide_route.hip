@@ -473,7 +473,7 @@ template <bool kRagged, int kMaxBlocks> int launch_band_f32(unsigned grid, hipSt
     return TIDE_OK;
 }
 
-// The one-tile kernel: a workgroup per 128-row tile from p.tile_begin on.
+// The one-tile kernel: a workgroup per tile of kRowsM rows from p.tile_begin on.
 template <int DT, int kHalves, bool kRagged, int kRowsM, bool kBurst> int launch_tile_form(hipStream_t st, const PrefillParams& p) {
     static bool raised[kMaxDevices] = {};
     int dev = 0;
@@ -488,13 +488,14 @@ template <int DT, int kHalves, bool kRagged, int kRowsM, bool kBurst> int launch
     hipLaunchKernelGGL((tide_prefill_tile_kernel<DT, kHalves, kRagged, kRowsM, kBurst>), dim3(grid), dim3(tile_threads(kHalves)), lds, st, p);
     return TIDE_OK;
 }
-// In bursts up to three quarters of the CUs (64 rows: always); figures at the kernel.
+// In bursts up to three quarters of the CUs, but not on rows of two k-tiles, whose second burst is the last (d = 256, C = 8, without / with: 7.7 / 8.0 us at T = 2080,
+// 8.0 / 8.2 at 3000; level at d = 128 and 384, 10.5 / 10.3 at 512) (64 rows: always); figures at the kernel.
 template <int DT, int kHalves, bool kRagged = false, int kRowsM = kTileRows> int launch_tile(hipStream_t st, const PrefillParams& p) {
     if constexpr (kHalves == 1) {
         unsigned cus = 0;
         const int rc = resident_cus(&cus);
         if (rc) return rc;
-        if (kRowsM == 64 || 4 * (int64_t)(p.total_tiles - p.tile_begin) <= 3 * (int64_t)cus) return launch_tile_form<DT, 1, kRagged, kRowsM, true>(st, p);
+        if (kRowsM == 64 || (p.dpad > 256 && 4 * (int64_t)(p.total_tiles - p.tile_begin) <= 3 * (int64_t)cus)) return launch_tile_form<DT, 1, kRagged, kRowsM, true>(st, p);
     }
     if constexpr (kRowsM == kTileRows) return launch_tile_form<DT, kHalves, kRagged, kRowsM, false>(st, p);
 }
