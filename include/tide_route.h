@@ -314,7 +314,7 @@ int tide_set_prefill_form(int form);
  * launch).  out: HOST int32 [2][7], per launch {kernel, rows_per_tile, tiles_per_ckpt, total_tiles,
  * tile_begin, k_slices, workgroups}: the launch covers tiles tile_begin .. total_tiles-1 of the
  * checkpoint-major list of tiles of rows_per_tile rows (tiles_per_ckpt per checkpoint, the last one
- * of a checkpoint possibly ragged).  kernel: 1 split-k pair, 2 wide-tile, 3 wide-tile fp32, 4 one-tile,
+ * of a checkpoint possibly ragged).  kernel: 1 split-k pair, 2 wide-tile, 3 wide-tile fp32, 4 one-tile (of 128 or 64 rows),
  * 5 / 6 streaming with 128 / 64 rows, 7 register-ring, 8 band (rows_per_tile = 32: the blocks its
  * bands are counted in, see tide_band_schedule), 9 split-k in one launch, 10 square, 11 band for fp32 rows.  Hidden sizes
  * whose rows are copied first (see the conventions) are planned at the padded size.  Other hidden sizes that are not multiples of

@@ -523,10 +523,9 @@ enum PrefillKernel : int {
     kKernelSplitK = 1,     // prefill_splitk_kernel.hpp: the pair
     kKernelWide = 2,       // prefill_wide_kernel.hpp (16-bit rows; width 256: 128-row tiles)
     kKernelWideF32 = 3,    // prefill_wide32_kernel.hpp
-    kKernelTile = 4,       // prefill_tile_kernel.hpp
+    kKernelTile = 4,       // prefill_tile_kernel.hpp, 128 or (widths 64 / 128) 64 rows per workgroup
     kKernelStream128 = 5,  // prefill_dma_kernel.hpp, 128 rows per workgroup
-    kKernelStream64 = 6,   // 64 rows per workgroup: prefill_tile_kernel.hpp where no workgroup has a second tile (16-bit rows, widths 64 / 128), else
-                           // prefill_dma_kernel.hpp (width 256: both column halves per wave)
+    kKernelStream64 = 6,   // prefill_dma_kernel.hpp, 64 rows per workgroup (width 256: both column halves per wave)
     kKernelRing = 7,       // prefill_kernel.hpp
     kKernelBand = 8,       // prefill_band_kernel.hpp: rows_per_tile = 32 (the unit its bands are counted in)
     kKernelSplitKFused = 9,// prefill_splitk_kernel.hpp in one launch: 32-row tiles, the last workgroup of a tile finishes it
@@ -572,7 +571,7 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     // 128 rows as CUs: 25.7 against 29.6 us at 64 tiles on 256 CUs, measured); from there on 64-row
     // tiles are faster as long as every CU holds at most one (30.3 against 32.8 us at 80 tiles of 128
     // rows, 32.9 against 39.5 us at 128; with a second workgroup on some CUs 55 us at 129, where the
-    // one-tile kernel takes 43.6 us; 16-bit rows of that kind are another 4-12 % faster since they run on the one-tile kernel).  `form` overrides for tests and tuning.
+    // one-tile kernel takes 43.6 us; 16-bit rows of that kind are another 5-12 % faster on the one-tile kernel).  `form` overrides for tests and tuning.
     const int64_t tiles128 = C * ((T + 127) / 128), tiles64 = C * ((T + 63) / 64);
     int rows_per_wg = (4 * tiles128 > (int64_t)cus && tiles64 <= (int64_t)cus) ? 64 : 128;
     if (form == 1) rows_per_wg = 64;
@@ -794,10 +793,11 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     unsigned grid = 8u * (unsigned)((left + 7) / 8);
     int kernel = kKernelRing;
     if (!ring_form) {
-        // One whole 128-row tile for every CU or none (more than half as many tiles as CUs, at most as
-        // many): the one-tile kernel, 1-3 % faster than the persistent one on such batches.
-        const bool one_tile_each = dtype != TIDE_F32 && rows_per_wg == 128 &&
-                                   (form == 6 || tile256 || (form == 0 && !two_halves && 2 * left > (int64_t)cus && left <= (int64_t)cus));
+        // One whole tile for every CU or none (128 rows: more than half as many tiles as CUs, at most as many; 64 rows, widths 64 / 128: always): there is
+        // nothing to schedule, and the one-tile kernel is 1-3 % faster than the persistent one on such batches, on 64 rows 5-12 % (figures there).
+        const bool one_tile_each = dtype != TIDE_F32 &&
+                                   (rows_per_wg == 128 ? form == 6 || tile256 || (form == 0 && !two_halves && 2 * left > (int64_t)cus && left <= (int64_t)cus)
+                                                       : form == 0 && !two_halves && left <= (int64_t)cus);
         kernel = one_tile_each ? kKernelTile : rows_per_wg == 128 ? kKernelStream128 : kKernelStream64;
         if (!one_tile_each) {
             // The streaming kernels are persistent: at most one (128-row; width 256: the two-halves
@@ -897,8 +897,15 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
                 else rc = no_form();
                 break;
             case kKernelTile:
-                if constexpr (DT != kF32) rc = !two_halves ? launch_tile<DT, 1, R>(st, p) : R ? no_form() : launch_tile<DT, 2>(st, p);
-                else rc = no_form();
+                if constexpr (DT != kF32) {
+                    // (64 rows, rows above 7 KiB: "nt" is as fast or faster here, us default / nt, C = 4, T = 3232 and C = 10, T = 1300, on the streaming kernel: 16.2 / 18.0 and
+                    // 16.3 / 18.3 at d = 1752, 21.3 / 23.9 and 22.0 / 24.3 at 2600, but 33.3 / 32.9 and 34.6 / 33.2 at 3848, 38.5 / 37.3 and 40.0 / 37.6 at 4568)
+                    if (L.rows_per_tile == 64 && p.d * (int)eb > 7168) p.shared_lines = 0;
+                    if (two_halves) rc = R || L.rows_per_tile != kTileRows ? no_form() : launch_tile<DT, 2>(st, p);
+                    else rc = L.rows_per_tile == 64 ? launch_tile<DT, 1, R, 64>(st, p) : launch_tile<DT, 1, R>(st, p);
+                } else {
+                    rc = no_form();
+                }
                 break;
             case kKernelBand:
                 if constexpr (DT != kF32) rc = launch_band<DT, R>(L.grid, st, p);
@@ -921,22 +928,8 @@ int launch_prefill(const Scratch& sc, const PrefillPlan& plan, PrefillParams p, 
                 else rc = no_form();
                 break;
             case kKernelStream64:
-                // (rows above 7 KiB: "nt" is as fast or faster here, us default / nt, C = 4, T = 3232 and C = 10, T = 1300: 16.2 / 18.0 and 16.3 / 18.3 at d = 1752,
-                // 21.3 / 23.9 and 22.0 / 24.3 at 2600, but 33.3 / 32.9 and 34.6 / 33.2 at 3848, 38.5 / 37.3 and 40.0 / 37.6 at 4568)
-                if (p.d * (int)elem_bytes(dtype) > 7168) p.shared_lines = 0;
-                if (two_halves) {
-                    rc = R ? no_form() : launch_dma<DT, 64, 2>(L.grid, st, p);
-                } else if constexpr (DT != kF32) {
-                    // Where no workgroup has a second tile there is nothing to schedule: the one-tile kernel on 64 rows, 5-12 % faster
-                    // (figures there).  (The automatic choice is always that; a forced form may be more tiles.)
-                    if (p.total_tiles - p.tile_begin <= (int)L.grid) rc = launch_tile<DT, 1, R, 64>(st, p);
-                    else if constexpr (!R) rc = launch_dma<DT, 64, 1>(L.grid, st, p);
-                    else rc = no_form();
-                } else if constexpr (!R) {
-                    rc = launch_dma<DT, 64, 1>(L.grid, st, p);
-                } else {
-                    rc = no_form();
-                }
+                if constexpr (!R) rc = two_halves ? launch_dma<DT, 64, 2>(L.grid, st, p) : launch_dma<DT, 64, 1>(L.grid, st, p);
+                else rc = no_form();
                 break;
             default:
                 if (ntile >= kMaxDepth)

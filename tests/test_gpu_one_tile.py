@@ -8,20 +8,21 @@ from parity import compare_select, oracle_select, report, routers_to_device, to_
 
 pytestmark = pytest.mark.gpu
 
-STREAM64, TILE = 6, 4
+TILE = 4
 
 
-@pytest.mark.parametrize("C,dtype,T,d,b,kernel", [
-    (22, "bf16", 380, 128, 128, STREAM64), (22, "f16", 380, 256, 64, STREAM64), (22, "bf16", 380, 384, 128, STREAM64), (22, "bf16", 333, 640, 128, STREAM64),
-    (17, "f16", 449, 1000, 128, STREAM64), (2, "f16", 5000, 72, 128, STREAM64), (9, "bf16", 1025, 2304, 128, STREAM64), (1, "bf16", 16384, 1152, 128, STREAM64),
-    (3, "bf16", 5470, 128, 128, TILE), (3, "f16", 8192, 256, 64, TILE), (3, "bf16", 8193, 384, 128, TILE), (10, "bf16", 2250, 648, 128, TILE),
-    (8, "bf16", 3072, 512, 128, TILE), (8, "bf16", 3073, 512, 128, TILE), (8, "f16", 3000, 1000, 128, TILE), (8, "f16", 3100, 1000, 128, TILE)])
-def test_one_tile(C, dtype, T, d, b, kernel):
+@pytest.mark.parametrize("C,dtype,T,d,b,rows", [
+    (22, "bf16", 380, 128, 128, 64), (22, "f16", 380, 256, 64, 64), (22, "bf16", 380, 384, 128, 64), (22, "bf16", 333, 640, 128, 64),
+    (17, "f16", 449, 1000, 128, 64), (2, "f16", 5000, 72, 128, 64), (9, "bf16", 1025, 2304, 128, 64), (1, "bf16", 16384, 1152, 128, 64),
+    (3, "bf16", 5470, 128, 128, 128), (3, "f16", 8192, 256, 64, 128), (3, "bf16", 8193, 384, 128, 128), (10, "bf16", 2250, 648, 128, 128),
+    (8, "bf16", 3072, 512, 128, 128), (8, "bf16", 3073, 512, 128, 128), (8, "f16", 3000, 1000, 128, 128), (8, "f16", 3100, 1000, 128, 128)])
+def test_one_tile(C, dtype, T, d, b, rows):
     import torch
     from paper_2603_21365_amd import tide_route as tr
     w = synth.Workload(f"one_tile_{dtype}_C{C}_T{T}_d{d}_b{b}", 97, dtype, d, 4 * C, 4, T, None, b=b)
     print(f"[gpu-case] {w.name}", flush=True)
-    assert tr.call_route(tr.DTYPE_CODES[dtype], C, T, d, b)["kernel"] == kernel
+    route = tr.call_route(tr.DTYPE_CODES[dtype], C, T, d, b)
+    assert (route["kernel"], route["rows_per_tile"]) == (TILE, rows)
     rt, hb = w.routers(), w.hidden()
     g, W1, b1, w2 = routers_to_device(rt)
     dev, pk = to_device(hb, dtype), tr.router_pack(tr.DTYPE_CODES[dtype], g, W1)

@@ -9,7 +9,7 @@ import pytest
 from paper_2603_21365_amd import tide_route as tr
 
 SPLITK, WIDE, WIDE_F32, TILE, STREAM128, STREAM64, RING, BAND, SPLITK_FUSED, SQUARE, BAND_F32 = 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11
-ZERO_FILLS = (SPLITK, SPLITK_FUSED, TILE, STREAM128, STREAM64, RING, BAND, BAND_F32)      # kernels with a form for rows that are no whole k-tiles
+ZERO_FILLS = (SPLITK, SPLITK_FUSED, TILE, STREAM128, RING, BAND, BAND_F32)      # kernels with a form for rows that are no whole k-tiles
 ELEM = {tr.F32: 4, tr.F16: 2, tr.BF16: 2}
 
 
@@ -72,12 +72,13 @@ def check_plan(dtype, C, T, d, b, cus, form):
                     rem = all_tiles % cus
                     assert 2 * all_tiles > cus and (all_tiles <= cus or rem == 0 or 2 * rem > cus), what
         if k == TILE:
-            assert R == 128 and dtype != tr.F32, what
+            assert dtype != tr.F32 and (R == 128 or (R == 64 and form == 0 and halves == 1 and L["total_tiles"] - L["tile_begin"] <= cus)), what   # 64 rows: one per CU at most
             assert wg == 8 * -(-(L["total_tiles"] - L["tile_begin"]) // 8), what
         if k in (STREAM128, STREAM64):
             assert R == (128 if k == STREAM128 else 64), what
             assert wg % 8 == 0 and wg <= cus * (1 if (R == 128 or halves == 2) else 2), what
             assert halves == 1 or k == STREAM64, what
+            assert k == STREAM128 or halves == 2 or dtype == tr.F32 or form != 0, what            # 16-bit rows, widths 64 / 128: 64-row tiles are the one-tile kernel's unless forced
         if k == RING:
             assert R == 64 and halves == 1, what
         if k == BAND:
@@ -263,8 +264,8 @@ def test_generic_hidden_sizes_on_random_shapes():
         if d % 128 == 0:
             d += 8
         plan = check_plan(dtype, C, T, d, int(rng.choice([64, 128])), int(rng.choice([8, 32, 64, 256, 256, 304])), 0)
-        kinds |= {L["kernel"] for L in plan}
-    assert kinds >= {SPLITK, STREAM128, STREAM64, TILE, BAND, BAND_F32}, kinds
+        kinds |= {(L["kernel"], L["rows_per_tile"]) for L in plan}
+    assert kinds >= {(SPLITK, 64), (STREAM128, 128), (TILE, 64), (TILE, 128), (BAND, 32), (BAND_F32, 32)}, kinds
 
 
 def test_the_choices_on_the_named_workloads():
@@ -298,7 +299,9 @@ def test_the_choices_on_the_named_workloads():
     assert kinds(tr.prefill_plan(tr.BF16, 1, 1024, 1024)) == [(STREAM128, 128)]                   # short rows: the chain is short already
     assert kinds(tr.prefill_plan(tr.BF16, 8, 4096, 4096, 256)) == [(TILE, 128)]                   # width 256: one 128-row tile per CU, eight consumer waves
     assert kinds(tr.prefill_plan(tr.BF16, 8, 2048, 4096, 256)) == [(STREAM64, 64)]                # ... 128 tiles: a 64-row workgroup per CU
-    assert kinds(tr.prefill_plan(tr.BF16, 8, 2048, 4096)) == [(STREAM64, 64)]                     # 128 tiles of 128 rows: a 64-row workgroup per CU
+    assert kinds(tr.prefill_plan(tr.BF16, 8, 2048, 4096)) == [(TILE, 64)]                         # 128 tiles of 128 rows: a 64-row workgroup per CU, the one-tile kernel
+    assert kinds(tr.prefill_plan(tr.BF16, 8, 2048, 4096, form=1)) == [(STREAM64, 64)]             # ... the streaming kernel when forced
+    assert kinds(tr.prefill_plan(tr.F16, 10, 1600, 1000)) == [(TILE, 64)]                         # ... rows that are no whole k-tiles
     assert kinds(tr.prefill_plan(tr.BF16, 8, 2080, 4096)) == [(TILE, 128)]                        # 136 tiles: the 64-row kernel would need two per CU
     assert kinds(tr.prefill_plan(tr.BF16, 8, 6144, 4096)) == [(BAND, 32)]                         # 6 blocks per CU
     assert kinds(tr.prefill_plan(tr.BF16, 8, 6144, 4096, form=4)) == [(WIDE, 256)]                # 192 wide tiles: three quarters of a round
