@@ -321,15 +321,12 @@ __device__ __forceinline__ f32x4 stage_load4(const float* p) {
     q[1] = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return __builtin_bit_cast(f32x4, q);
 }
-// The same 16 bytes at a time (an atomic has 8 at most), at 32-bit offsets from an address that is the same in every lane: buffer accesses with the
+// The same load 16 bytes at a time (an atomic has 8 at most), at 32-bit offsets from an address that is the same in every lane: buffer loads with the
 // device-scope bit, performed where the 8-byte ones above are.
 struct StageBlock {
-    static constexpr int kDeviceScope = 16;      // the buffer instructions' cache policy: sc1
+    static constexpr int kDeviceScope = 16;      // the buffer loads' cache policy: sc1
     __amdgpu_buffer_rsrc_t r;
     __device__ __forceinline__ explicit StageBlock(const void* base) : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0xffffffffu, 0x00020000)) {}
-    __device__ __forceinline__ void store4(uint32_t byte, f32x4 v) const {
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, byte, 0, kDeviceScope);
-    }
     __device__ __forceinline__ f32x4 load4(uint32_t byte) const {
         return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, byte, 0, kDeviceScope));
     }
