@@ -38,6 +38,7 @@ constexpr int kFinishThreads = 256;
 // under way.  us, before / after: C = 1, T = 3000, d = 4096 13.3 / 12.8, T = 1000 8.7 / 8.1, C = 8, T = 200, d = 2048 8.3 / 7.9, T = 322, d = 4096 13.5 / 13.0 (without the preload 13.4).
 struct SplitkTiling {          // 64 bits
     uint32_t total_tiles, tiles_per_ckpt, slices, stages, halves, deal_out, shared_lines;
+    static constexpr uint32_t kMostTiles = (1 << 20) - 1, kMostSlices = 15, kMostStages = 15;      // what the fields hold
     __host__ __device__ static uint64_t pack(const PrefillParams& p) {
         return (uint64_t)(uint32_t)p.total_tiles | (uint64_t)(uint32_t)p.tiles_per_ckpt << 20 | (uint64_t)(uint32_t)p.k_slices << 40 | (uint64_t)(uint32_t)p.ring_stages << 44 |
                (uint64_t)(p.b > kBottleneck) << 48 | (uint64_t)(p.deal_out != 0) << 49 | (uint64_t)(p.shared_lines != 0) << 50;

@@ -365,6 +365,9 @@ template <int DT, bool kRagged> int launch_band(unsigned grid, hipStream_t st, P
 
 // The split-k pair: `tiles` tiles of kBlocks*32 rows times p.k_slices workgroups leave their partial
 // results in `part`, then one small workgroup per 32-row block adds them and finishes the router.
+// (SplitkTiling: what the argument word holds)
+static_assert(std::max(kSplitkForcedMaxTiles * 4, kSplitkMaxTiles * 10) <= (int)SplitkTiling::kMostTiles, "tiles: at most the 32-row blocks a pair is considered for");
+static_assert(kSplitkMaxSlices <= (int)SplitkTiling::kMostSlices && kSplitkMaxStages <= (int)SplitkTiling::kMostStages && kDmaStages <= (int)SplitkTiling::kMostStages, "slices and stages");
 // Bytes of partial results the pair leaves for `tiles` tiles of kBlocks*32 rows in `halves` column halves and S slices.
 size_t splitk_part_bytes(int blocks, int64_t tiles, int halves, int64_t S) {
     const size_t items = (size_t)tiles * halves * S;
@@ -957,6 +960,7 @@ template <int DT, int kWaves, bool kFull = false> int launch_few(unsigned grid, 
                                      hipFuncAttributeMaxDynamicSharedMemorySize, few_lds_bytes(kWaves, kFewRows)));
         raised[dev] = true;
     }
+    static_assert(kFewMaxTiles * kFewRows < 1 << 16 && TIDE_MAX_CHECKPOINTS < 1 << 8, "the fields of dims");
     hipLaunchKernelGGL((tide_few_rows_kernel<DT, kWaves, kFull>), dim3(grid), dim3(kWaves * kWave), few_lds_bytes(kWaves, std::min(p.T, kFewRows)), st, p.hidden, p.packed,
                        p.ckpt_stride_bytes, p.row_stride_bytes, p.d, (uint32_t)p.T | (uint32_t)p.C << 16 | (uint32_t)__builtin_ctz((unsigned)p.k_slices) << 24, p.b1, p.w2, p);
     return TIDE_OK;
@@ -1939,6 +1943,7 @@ int tide_cosine_labels(const void* hidden, int dtype, int64_t C, int64_t T, int6
     hipStream_t st = (hipStream_t)stream;
     by_dtype(dtype, [&](auto dt) {
         constexpr int DT = decltype(dt)::value;
+        static_assert(TIDE_MAX_CHECKPOINTS < 1 << 16, "the fields of ckpts");
         auto go = [&](auto wpr, auto chunks) {
             hipLaunchKernelGGL((tide_cosine_kernel<DT, decltype(wpr)::value, decltype(chunks)::value>), dim3(grid),
                                dim3(kCosineThreads), 0, st, p.hidden, p.ckpt_stride_bytes, p.row_stride_bytes, p.final_hidden, p.final_row_stride_bytes, p.T, p.d,
