@@ -83,6 +83,9 @@ constexpr int kSplitkMaxStages = 8;     // k-tiles of rows in the ring at most (
 // not depend on who is last) and finishes the router.  An earlier version of this hand-over read whole 16 KiB blocks,
 // 8 bytes at a time, and lost to the second launch; with the rows in use only it wins at decode sizes (see the host's
 // choice).  Ordering is by completion, as in the latency kernel (device_utils.hpp: stage_store / last_arrival).
+// (fp32: 175 registers since its first arguments are scalars, 156 before: one workgroup per CU instead of two where a forced call or other work asks for two.  Held to three
+// waves per SIMD it spills six and is 5 % slower, up to 18; as it is it is 5 % faster than with 156, us, 156 / 175 / held: C = 29, T = 8, d = 4096 15.8 / 15.3 / 16.5, C = 32, T = 16,
+// d = 2048 12.65 / 11.3 / 12.75, and forced on more workgroups than CUs, C = 8, T = 200, d = 4096, 29.3 / 27.4 / 27.5.)
 template <int DT, int kBlocks, bool kFused = false, bool kRagged = false>
 __global__ __launch_bounds__(splitk_threads(kFused), 1) void tide_prefill_splitk_kernel(
     const char* hidden, const u32x4* packed, int64_t ckpt_stride_bytes, int64_t row_stride_bytes, uint64_t tiling, uint32_t by_slices_m, uint32_t by_tiles_m,
