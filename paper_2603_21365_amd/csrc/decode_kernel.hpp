@@ -131,8 +131,8 @@ __device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int 
         using std::integral_constant;
         if constexpr (kG == 1) {
             // Eight tokens per pass: a thread has all slices of its token.  As few loads as cover them, batch after batch, and none for a token
-            // that does not exist: a surplus load is a round trip past every cache too (us, all of 32 slices loaded against this: 57 / 47 at C = 12, T = 25,
-            // d = 4296, 34 slices; 15.0 / 14.1 at C = 16, T = 5, 19 slices).  (Width 256: two workgroups per CU, so smaller batches.)
+            // that does not exist: a surplus load is a round trip past every cache too (us, all of 32 slices loaded against this, raw weights: 29.3 / 28.0 at C = 12, T = 25,
+            // d = 4296, 9 slices; 12.2 / 11.9 at C = 16, T = 5, 8 slices).  (Width 256: two workgroups per CU, so smaller batches.)
             constexpr int kMost = kHalves == 2 ? 8 : 32;
             for (int s0 = s_begin; valid && s0 < s_end;) {
                 const int left = s_end - s0;
@@ -206,8 +206,9 @@ __device__ __forceinline__ void decode_finish(const DecodeParams& p, int c, int 
 // d = 4096, us per call back to back, weights in the caches): 13.7 / 13.7 / 13.8 / 15.1 at T = 1 / 2 / 4 / 8 with eight tokens' arithmetic always, the weights queued before the rows (loads return in
 // order, so nothing was staged until the last weight was there), the counters of all checkpoints in one line and one thread per
 // (token, quad) in the finish; 10.3 / 11.2 / 12.4 / 14.9 with 128 columns x 128 k per workgroup (the last one of a checkpoint then reads 66 KiB past every cache at
-// T = 4, now 17) and partial results read 8 bytes at a time; now 9.2 / 9.7 / 10.3 / 12.3.  d = 8192, C = 6, T = 8 19.2 -> 13.7; width 256, T = 4 18.8 -> 13.1; width 64,
-// T = 8 13.1 -> 9.8; C = 4, T = 2, d = 2048 7.7 -> 7.2; fp32, d = 3072, T = 4 11.4 -> 9.9.
+// T = 4, now 17) and partial results read 8 bytes at a time; now 7.3 / 7.7 / 8.2 / 10.0 (of which the gain's loads, see below, and registers, see decode_finish, about 0.6).
+// Before this cut / now: d = 8192, C = 6, T = 8 17.2 / 10.9; width 256, T = 4 16.0 / 9.9; width 64, T = 8 13.1 / 9.4; C = 4, T = 2, d = 2048 7.9 / 6.9; fp32, d = 3072, T = 4 10.2 / 8.1.
+// (W1 through bounded loads, so that a slice shorter than 512 costs no surplus ones: 1-3 % faster on few workgroups, up to 8 % slower at width 256 on several per CU.)
 template <int DT, int kHalves, int kTB>
 __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const DecodeParams p) {
     constexpr int E = Storage<DT>::kElems;
@@ -264,7 +265,7 @@ __global__ __launch_bounds__(kDecodeThreads) void tide_decode_kernel(const Decod
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) wreg[i] = *reinterpret_cast<const f32x4*>(w + (size_t)min(kw + i, k_end - 1) * p.b);
 
-    // for the end, while the loads are under way (9.3 -> 9.2 us at T = 1, 10.5 -> 10.3 at 4, width 256 14.0 -> 13.1; with eight tokens 2 % either way)
+    // for the end, while the loads are under way (1 % at T = 1, 2 % at 4, 6 % at width 256; with eight tokens 2 % either way)
     if constexpr (kTB < 8) TIDE_FETCH_ARGS8(p.part, p.counter, p.b1, p.w2, p.eps, p.logits, p.exit_layer, p.arrive);
 
     for (int t0 = 0; t0 < p.T; t0 += kTB) {

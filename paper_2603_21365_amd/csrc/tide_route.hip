@@ -558,7 +558,7 @@ constexpr PairCost kPairCost[2][3] = {{{4.7, 0.59, 0.0063, 0.0087}, {4.8, 0.77, 
 // Up to 8 rows; 0.8 more beyond, as much as the streaming form's.
 constexpr PairCost kOneLaunchCost[2] = {{5.8, 0.41, 0.057, 0.0099}, {5.9, 0.59, 0.033, 0.0121}};
 int64_t splitk_max_blocks(int dtype, int halves) { return (int64_t)kSplitkMaxTiles * (halves == 1 ? 4 : dtype == TIDE_F32 ? 10 : 6); }
-constexpr double kPairLaunches = 8.3;      // two launches from a host that issues them back to back
+constexpr double kPairLaunches = 8.3;      // two launches from a host that issues them back to back (6.3-8.5, by host)
 
 PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigned cus, int form_word, bool ragged = false, bool split_k = true,
                          size_t most_part = SIZE_MAX, bool behind_few = false) {
@@ -571,10 +571,10 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     // Rows per workgroup (streaming form).  128 rows fetch each W1' fragment once per 128 rows and
     // is the choice whenever the tiles fill most of the chip.  With few tiles it wins again, because
     // every CU is launched and the tiles are cut into 32-row pieces (up to a quarter as many tiles of
-    // 128 rows as CUs: 25.7 against 29.6 us at 64 tiles on 256 CUs, measured); from there on 64-row
-    // tiles are faster as long as every CU holds at most one (30.3 against 32.8 us at 80 tiles of 128
-    // rows, 32.9 against 39.5 us at 128; with a second workgroup on some CUs 55 us at 129, where the
-    // one-tile kernel takes 43.6 us; 16-bit rows of that kind are another 5-12 % faster on the one-tile kernel).  `form` overrides for tests and tuning.
+    // 128 rows as CUs: 24.9 against 27.1 us at 64 tiles on 256 CUs, d = 4096, measured, 15.4 / 15.6 at d = 2048); from there on 64-row
+    // tiles are faster as long as every CU holds at most one (27.6 against 33.7 us at 80 tiles of 128
+    // rows, 33.7 against 42.9 us at 128; with a second workgroup on some CUs 55.5 us at 136, where the
+    // one-tile kernel takes 41.3 us).  `form` overrides for tests and tuning.
     const int64_t tiles128 = C * ((T + 127) / 128), tiles64 = C * ((T + 63) / 64);
     int rows_per_wg = (4 * tiles128 > (int64_t)cus && tiles64 <= (int64_t)cus) ? 64 : 128;
     if (form == 1) rows_per_wg = 64;
@@ -584,8 +584,8 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     // so of these two the ring form is the faster one for fp32 (measured 4.1 vs 3.6 TB/s); whole rounds
     // of 256-row tiles go to the fp32 wide-tile kernel further down (4.7 TB/s).
     // Width 256 (two column halves per wave) exists in the streaming form with 64 rows per
-    // workgroup only.  With 128 rows the accumulators (256 values per lane) leave room for half a
-    // k-tile of W1' in flight, too little to cover the L2 round trip: measured slower.
+    // workgroup only.  With 128 rows the accumulators (128 values per lane) and two halves' fragments left too
+    // little of W1' in flight to cover the L2 round trip: measured slower.
     // Rows that are no whole k-tiles (ragged), 16 bits, more than one 128-row tile per CU: it also keeps the batches whose checkpoints end in
     // short tiles, so that the 64-row tiles are two per CU at most (bf16, C = 7, T = 4650, 511 tiles of 64 rows: 60 / 73 us at d = 3080 / 4072 against
     // 64 / 79 in bands, level at d = 1608); from a third one on bands are faster (C = 9, T = 3600, 513 tiles: 79 / 96 us against 62 / 77).
@@ -618,11 +618,11 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     //   split-k pair:          launch + chain ceil(n / S) ceil(W / CUs) + (row n / 32 + slice S) R   (kPairCost, by type and B),
     //                          and no less than the host takes to issue two launches (where they are two)
     // The pair has to be 8 % cheaper, twice what the estimates are good for; the one launch just cheaper (kOneLaunchCost; bf16, streaming / one launch:
-    // C = 28: 7.4 / 7.3 us at d = 512, 8.4 / 7.7 at 768, 9.2 / 7.8 at 1024, T = 8; two slices or four where eight would share a CU's
-    // time: C = 28, T = 8, d = 2560 10.6 / 10.1 at eight / four).  What the pair's line moved (us, before / after):
-    // bf16, C = 1: d = 5120, T = 5000 24.5 / 21.1, d = 2048, T = 3000 12.7 / 9.9, d = 4096, T = 5000 20.8 / 18.4; C = 8, d = 8192, T = 700 36.3 / 31.4;
-    // fp32, C = 6: d = 5120, T = 700 47.9 / 41.3, d = 768, T = 700 16.6 / 14.2; fp32, width 256, C = 6: d = 1024, T = 600 31.8 / 17.9, d = 4096 121 / 70 at
-    // T = 1000 and 125 / 110 at 1500 (the streaming form's 64-row tiles leave CUs idle there, and past one round it takes two: five times
+    // C = 28: 7.6 / 7.7 us at d = 512, 9.0 / 8.0 at 768, 9.3 / 7.7 at 1024, T = 8; two slices or four where eight would share a CU's
+    // time).  Streaming form / pair (us):
+    // bf16, C = 1: d = 5120, T = 5000 27.0 / 20.5, d = 2048, T = 3000 12.6 / 9.8, d = 4096, T = 5000 22.1 / 18.3; C = 8, d = 8192, T = 700 39.9 / 31.5;
+    // fp32, C = 6: d = 5120, T = 700 79 / 47, d = 768, T = 700 16.7 / 14.1; fp32, width 256, C = 6: d = 1024, T = 600 31.4 / 18.0, d = 4096 120 / 72 at
+    // T = 1000 and 125 / 106 at 1500 (the streaming form's 64-row tiles leave CUs idle there, and past one round it takes two: five times
     // as many blocks as otherwise are the pair's to compare).
     // Forced (form 5) the cheapest shape is taken whatever the streaming estimate says, and the form
     // word may fix the tile height (bits 8-15) and the slice count (bits 16-23).
@@ -1069,9 +1069,9 @@ int launch_decode(const Scratch& sc, const void* hidden, int dtype, int64_t C, i
 // d = 4096, C = 1 / 8, fp16: 9.5 / 10.6 us against 10.8 / 13.9 us at T = 1, 13.5 / 15.9 us at T = 8
 // and 40 us at T = 32; fp32 rows: 13.3 / 14.7 us against 11.3 / 14.4 us at T = 1 and 13.6 / 16.4 us at
 // T = 8).  With raw weights that form needs the packing pass first (7.5 us at C = 8), so the latency
-// kernel, which reads W1 as it is, keeps T <= 8 (fp16, C = 8, d = 4096: 9.2 / 10.3 / 12.2 / 12.3 us at T = 1 / 4 / 5 / 8, against the packing pass and
-// the few-rows kernel's 12.3 at T = 12: level at the line, but the latency kernel multiplies the fp32 weights, not their 16-bit
-// rounding, so a call does not lose those bits below it); it also keeps, up to
+// kernel, which reads W1 as it is, keeps T <= 8 (fp16, C = 8, d = 4096: 7.3 / 8.2 / 9.9 / 10.0 us at T = 1 / 4 / 5 / 8, against the packing pass and
+// the few-rows kernel's 11.5 at T = 9, 11.8 at 12; the latency kernel also multiplies the fp32 weights, not their 16-bit
+// rounding, so a call does not lose those bits below the line); it also keeps, up to
 // T = 32, what the split-k form does not cover (hidden sizes that are not multiples of 128).  Calls that would pack or have
 // packed weights go to the few-rows kernel instead where use_few_rows says so.
 bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, int variant, int form_word) {
@@ -1084,9 +1084,10 @@ bool use_decode(int64_t T, int dtype, int64_t d, int64_t b, bool packed_given, i
 }
 
 // The few-rows kernel (a workgroup per 16 rows and 16 columns, all of k) or the paths above?  Its one launch beats the split-k pair's two
-// (8.3-8.7 us from a host that issues them back to back, whatever the kernels take, and 2-3 us more where the exit projection follows) until a
-// workgroup has to walk long rows or the workgroups are more than the CUs.  Figures: us, few rows / the other path, 256 CUs, packed weights, bf16 and C = 8 unless
-// said, w = workgroups per CU.
+// (7.8-8.5 us from a host that issues them back to back, whatever the kernels take, and 2-3 us more where the exit projection follows) until a
+// workgroup has to walk long rows or the workgroups are more than the CUs.  Figures: us, few rows / the other path, back to back from a host, [in a graph of calls, where
+// the host does not hold the pair up], 256 CUs, packed weights, bf16 and C = 8 unless said, w = workgroups per CU.  Both sides have become faster since the lines were
+// drawn; they stay where the two ways of calling do not agree, and on the pair's side where few rows would gain some 5-10 % more.
 // kFewWide: a captured call whose pair would have to allocate takes the kernel wherever it is at all reasonable.
 // pair: false where there is no split-k form behind it (see below).
 enum FewRule { kFewNever, kFewByRule, kFewWide };
@@ -1095,46 +1096,51 @@ bool use_few_rows(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, unsigne
     const int64_t tiles = (T + kFewRows - 1) / kFewRows, nbk = b / kFewCols, row_bytes = d * (int64_t)elem_bytes(dtype);
     const int64_t W = C * tiles * nbk, n = (int64_t)cus;
     const bool f32 = dtype == TIDE_F32;
-    // (rows of 64 KiB, fp32, d = 16384, are level at best)
+    // (rows of 64 KiB: fp32, d = 16384, T = 8 21.6 / 26.3 at C = 1, 24.0 / 26.8 at C = 8)
     if (tiles > kFewMaxTiles || C * nbk >= 256 || row_bytes > 32768) return false;
     // Every workgroup of a row tile ticks the tile's counter (14 ns each).  Beyond one workgroup per CU rows of up to 2 KiB meet that from 112 ticks
-    // on (C = 16, T = 33, d = 1024: 9.6 / 9.2).
+    // on (C = 16, T = 33, d = 1024: 7.7 / 7.9 [7.1 / 6.6]).
     const bool few_ticks = C * nbk <= 112 || row_bytes > 2048;
 
-    // Hidden sizes that are no multiple of 128 have no split-k form on the calls that would be the latency kernel's (d = 1600, T <= 32: 6-9 / 25-50) and none in a
+    // Hidden sizes that are no multiple of 128 have no split-k form on the calls that would be the latency kernel's (d = 1600, T = 16: 6.6 / 17.2) and none in a
     // block that was sized without it (the register-ring kernel: d = 1600, T = 100 9.3 / 18.9).  With the pair they follow the lines below
-    // (d = 2904: 8.3 / 8.7 at T = 48, 10.7 / 8.2 at 96; d = 4304 14.2 / 9.3).
+    // (d = 2904: 7.7 / 7.9 [7.3 / 6.8] at T = 48, 9.2 / 8.2 at 96; d = 4304 10.6 / 9.0).
     if (d % 128 != 0 && (!pair || C * nbk > 128)) return W <= (few_ticks ? 2 * n : n);
 
     // Many checkpoints, widths 64 / 128: from 128 ticks on the counter costs what the kernel gains over the 128-column split-k forms (width 256, where those take twice
-    // the workgroups, does not meet that line: 1.03-1.6 times as fast up to 240 ticks).  C = 28: 11.4 / 9.9 at T = 16, d = 2560, 10.4 / 9.3 at T = 8.
+    // the workgroups, does not meet that line: 1.03-1.6 times as fast up to 240 ticks).  C = 28: 10.3 / 9.7 at T = 16, d = 2560, 9.0 / 9.0 at T = 8.
     if (b <= 128 && C * nbk >= 200) return false;
     if (rule == kFewWide) return W <= (few_ticks ? 2 * n : n);
-    // 17 to 24 checkpoints at width 128, up to 16 rows: 4 rows or rows of 4 KiB (f16, C = 24: 1.2 times at d = 768, T = 1, 1.05 at d = 5120, T = 4, but C = 20, d = 2560 9.1 / 8.6 at
-    // T = 8, 10.1 / 9.4 at 16); more: fp32 or rows of 8 KiB (f16, C = 24, d = 5120, T = 32 1.12 times, but 10.3 / 9.3 at d = 1024, 12.0 / 11.2 at 2560).
-    if (b <= 128 && C * nbk > 128 && !(T <= kFewRows ? T <= 4 || row_bytes <= 4096 : f32 || row_bytes >= 8192)) return false;
+    // 17 to 24 checkpoints at width 128, up to 16 rows: 4 rows or rows of 4 KiB (f16, C = 24: 7.4 / 7.7 at d = 768, T = 1, 9.2 / 9.7 at d = 5120, T = 4, but C = 20, d = 2560 8.2 / 8.2 at
+    // T = 8, 8.9 / 9.0 at 16); more: fp32, as far as the lines below take it (C = 20, T = 17, d = 768 8.5 / 8.3, C = 24, T = 32, d = 1024 9.3 / 8.5; f16, C = 24, T = 32 8.8 / 8.1 at d = 1024, 10.0 / 8.5
+    // at 2560, 13.6 / 10.2 at 5120).
+    if (b <= 128 && C * nbk > 128 && !(T <= kFewRows ? T <= 4 || row_bytes <= 4096 : f32)) return false;
 
     if (T > kFewRows) {             // against the pair
-        // above 12 KiB: d = 8192 10.0 / 10.2 (C = 2) and 9.8 / 9.0 (C = 1) at w = 0.06-0.125, 10.7 / 10.3 at 0.19; fp32, d = 4096 11.0 / 11.3, 10.5 / 10.3, 11.4 / 11.3
+        // above 12 KiB: d = 8192 9.0 / 9.0 [9.0 / 8.6] at w = 0.06, 9.2 / 10.2 [9.4 / 9.3] at 0.125, 9.5 / 10.2 [9.7 / 9.4] at 0.19; fp32, d = 4096 9.6 / 10.2 [9.8 / 9.6], 9.9 / 11.0 [10.1 / 10.3],
+        // 10.1 / 11.0 [10.3 / 10.4]
         if (row_bytes > 12288) return false;
-        // d = 5376 8.6 / 8.9 at 0.125, 8.8 / 8.9 at 0.19, 9.3 / 8.8 at 0.25; d = 6144 8.6 / 9.0, 9.0 / 9.0, 9.4 / 8.9, but width 64 8.9 / 9.2 at 0.25; fp32: d = 2688 9.2 / 9.9 at
-        // 0.125, 9.7 / 10.0 at 0.25, 10.1 / 9.9 at 0.375; d = 3072 9.3 / 10.1 at 0.125
+        // d = 5376 8.2 / 8.7 [7.8 / 8.0] at 0.125, 8.2 / 9.0 [8.1 / 8.1] at 0.19, 8.2 / 9.0 [7.9 / 8.1] at 0.25; d = 6144 8.3 / 9.0 [8.1 / 8.1], 8.5 / 9.1 [8.4 / 8.2], 8.3 / 9.2 [8.2 / 8.2], width 64
+        // 8.4 / 9.0 [8.3 / 7.9] at 0.25; fp32: d = 2688 8.5 / 9.8 [8.4 / 9.0] at 0.125, 8.6 / 9.9 [8.5 / 9.1] at 0.25, 8.8 / 10.1 [8.8 / 9.2] at 0.375; d = 3072 8.6 / 9.9 [8.5 / 9.2] at 0.125
         if (row_bytes > 10240) return f32 || b == 64 ? 4 * W <= n : 5 * W <= n;
-        // d = 5120 8.1 / 8.2 at 0.06, 8.6 / 8.5 at 0.19, 9.1 / 8.5 at 0.25; fp32, d = 2560 9.2 / 9.4 at 0.125, 9.3 / 9.5 at 0.19, 9.7 / 9.5 at 0.25, 10.0 / 9.4 at 0.375
+        // d = 5120 7.7 / 8.0 [7.2 / 7.0] at 0.06, 8.1 / 8.6 [7.8 / 7.7] at 0.19, 8.0 / 8.8 [7.8 / 7.7] at 0.25; fp32, d = 2560 8.4 / 9.3 [8.1 / 8.6] at 0.125, 8.5 / 9.6 [8.5 / 8.6] at 0.19, 8.5 / 9.5 [8.2 / 8.6] at
+        // 0.25, 8.5 / 9.7 [8.6 / 8.7] at 0.375
         if (row_bytes > 8192) return 5 * W <= n;
-        // d = 4096 8.3 / 8.9 at 0.66, 8.6 / 8.2 at 0.75, 9.4 / 8.4 at 1, 11.5 / 8.8 at 1.5; fp32, d = 2048 9.1 / 9.1, 9.8 / 9.1 at 1, 12.5 / 9.6; width 64 with the projection
-        // 12.9 / 14.1 at 0.875; width 256, C = 2: 9.0 / 8.6 at 0.5, 10.3 / 9.4 at 1
+        // d = 4096 8.3 / 8.5 [7.8 / 7.6] at 0.66, 8.2 / 8.2 [8.1 / 7.3] at 0.75, 8.2 / 8.5 [8.4 / 7.7] at 0.875, 8.6 / 8.3 [8.4 / 7.3] at 1, 10.0 / 8.7 at 1.5; fp32, d = 2048 8.4 / 9.2 [8.3 / 8.4],
+        // 8.4 / 9.1 [8.4 / 8.2], 8.5 / 9.2 [8.5 / 8.5], 8.7 / 9.2 [8.8 / 8.1], 10.9 / 9.5; width 64 with the projection 13.0 / 13.7 at 0.875; width 256, C = 2: 7.8 / 8.6 [7.6 / 7.7] at 0.5,
+        // 8.4 / 8.5 [8.4 / 7.4] at 1
         if (row_bytes > 6144) return 8 * W <= 7 * n;
-        // d = 2560 8.3 / 8.4 at 0.75, 8.9 / 8.2 at 1, 10.7 / 7.9 at 1.5; d = 3072 with the projection 12.4 / 13.5 at 0.94
+        // d = 2560 7.6 / 7.8 [7.2 / 6.6] at 0.75, 7.9 / 8.0 [7.7 / 6.8] at 1, 8.9 / 8.2 [9.0 / 7.2] at 1.5; d = 3072 with the projection 12.5 / 12.8 at 0.94
         if (row_bytes > 4096) return W <= n;
-        // d = 1024 7.0 / 9.1 at 0.75, 7.5 / 8.3 at 1, 8.8 / 7.8 at 1.5; d = 2048 7.5 / 8.7, 8.8 / 8.5; fp32, d = 1024 7.9 / 8.4, 9.3 / 7.8; with the projection, C = 5,
-        // d = 2048 11.5 / 13.4 at 1.1; d = 1448 8.9 / 7.3 at 1.5, 9.8 / 7.5 at 2
+        // d = 1024 6.4 / 9.3 [6.0 / 8.5] at 0.75, 6.8 / 9.3 [6.3 / 8.5] at 1, 7.5 / 9.3 [7.2 / 8.5] at 1.5; d = 2048 7.4 / 7.9 [6.8 / 6.3] at 1, 8.1 / 7.8 [7.9 / 6.7] at 1.5; fp32, d = 1024 7.3 / 8.2
+        // [6.8 / 7.0] at 0.75, 7.6 / 8.1 [7.2 / 6.8] at 1, 8.4 / 8.4 [8.3 / 7.2] at 1.5; with the projection, C = 5, d = 2048 11.6 / 12.4 at 1.1; d = 1448 8.1 / 7.9 [7.7 / 6.7] at 1.5, 8.4 / 7.9 at 2
         return W <= n || (few_ticks && 2 * W <= 3 * n);
     }
     // Up to 16 rows per checkpoint against the one-launch split-k form or, at width 256, a pair that is mostly padding:
-    // d = 4096 6.3 / 8.7 at T = 1, 7.3 / 9.5 at 16; up to 8 rows of any length fp32, d = 8192 16.1 / 17.0, d = 16384, C = 1 / 8 12.3 / 12.5, 14.8 / 14.6; width 256, fp32, d = 8192 20.6 / 21.1
+    // d = 4096 6.3 / 8.5 at T = 1, 7.5 / 9.1 at 16; up to 8 rows of any length fp32, d = 8192 14.2 / 16.9, d = 16384, C = 1 / 8 10.7 / 12.4, 13.5 / 14.2; width 256, fp32, d = 8192 16.5 / 16.2 at T = 8
+    // (18.7 / 16.4 at 16: the pair has overtaken there since the line was drawn)
     if (row_bytes <= 20480 || T <= 8 || b == 256) return W <= n;
-    // 9 to 16 rows, T = 12 / 16: d = 12288 11.4 / 11.8, 12.5 / 11.7; d = 16384 13.9 / 13.2, 15.4 / 13.2; fp32: d = 6144 13.0 / 14.8, 14.1 / 14.7; d = 8192 16.1 / 17.2, 17.4 / 17.1 (18.9 / 17.8 at C = 8)
+    // 9 to 16 rows, T = 12 / 16: d = 12288 10.9 / 12.9, 11.9 / 13.0; d = 16384 14.8 / 15.3, 16.2 / 15.6; fp32: d = 6144 12.2 / 15.1, 13.1 / 15.1; d = 8192 15.5 / 17.5, 16.9 / 17.5 (C = 4 14.0 / 17.2, 15.3 / 17.2)
     return W <= n && (f32 ? T <= 12 || row_bytes <= 24576 : T <= 12 && row_bytes <= 24576);
 }
 
