@@ -4,8 +4,8 @@
 //
 // Why another form.  When a batch gives every CU one whole tile or none (between half as many
 // tiles as CUs and as many), the streaming kernel's schedule has nothing to decide, but its
-// code for walking tile lists and for 64- and 32-row pieces still costs registers (243 against
-// 139 here) and set-up time: this form is 1-3 % faster on such batches (measured at d = 2048,
+// code for walking tile lists and for 64- and 32-row pieces still costs registers (241 and 19 spilled scalars against
+// 181 here; the forms in bursts, below, spend 237-242 on a second set of W1') and set-up time: this form is 1-3 % faster on such batches (measured at d = 2048,
 // 4096 and 8192 on the same box; the 8B-shaped prefill of 8 x 4096 rows is one).  There, keeping W1' two
 // k-tiles ahead instead of one, or filling all four ring slots at the start, changes nothing.
 // 16-bit storage types, d a multiple of 128 (kRagged: any rows of whole 16-byte chunks, zeros fetched beyond their end).
@@ -39,8 +39,8 @@ constexpr int kTileRows = 128;
 // L2, once per workgroup; the ring holds rows only.
 constexpr int tile_consumers(int kHalves) { return kDmaConsumers * kHalves; }
 constexpr int tile_threads(int kHalves) { return (tile_consumers(kHalves) + kDmaProducers) * kWave; }          // 384 / 640
-// What bounds the form while HBM does not: a CU has about 32 KiB of loads outstanding, answered in order, whatever they are.  So its rate is 32 KiB per
-// latency of the slowest in the queue (measured: 180 GB/s per CU from L2 alone, 62 from memory alone, 55 for the two mixed finely), and W1' from L2 pays
+// What bounds the form while HBM does not: a CU has about 32 KiB of loads outstanding, answered in order, whatever they are.  So its rate from memory is 32 KiB per
+// latency (measured: 62 GB/s per CU from memory alone, 55 with L2's mixed in finely, where L2 alone gives 180, a limit of its own), and W1' from L2 pays
 // the rows' memory latency whenever both are requested in turns.  kBurst: a stage's W1' fragments are requested all at once at its start (two sets of
 // registers), the rows in a burst of their own, and no more of them ahead than two stages (four stages instead of three: 2-4 % slower).  Tiles of 64 rows, which read
 // twice as much W1' as rows, take two k-tiles per stage, and their producers let W1' go first (some 640 cycles).  us, without / with, bf16, C = 8, rows from memory:

@@ -1,6 +1,6 @@
 """Per-workgroup timeline of the one-tile prefill kernel on the 8B-shaped bf16 prefill (C=8, T=4096, d=4096).
 
-    python -m paper_2603_21365_amd.timeline --build     # here or on the GPU machine: the instrumented library
+    python -m paper_2603_21365_amd.timeline --build     # the instrumented library; needs no GPU
     python -m paper_2603_21365_amd.timeline             # on the GPU: run it and print the summary
 
 The instrumented build (-DTIDE_TILE_TIMELINE) is the product kernel plus one read of the 100 MHz
