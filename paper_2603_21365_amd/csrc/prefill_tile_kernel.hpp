@@ -45,7 +45,7 @@ constexpr int tile_threads(int kHalves) { return (tile_consumers(kHalves) + kDma
 // registers), the rows in a burst of their own, and no more of them ahead than two stages (four stages instead of three: 2-4 % slower).  Tiles of 64 rows, which read
 // twice as much W1' as rows, take two k-tiles per stage, and their producers let W1' go first (some 640 cycles).  us, without / with, bf16, C = 8, rows from memory:
 //   64 rows (the streaming kernel before): d = 4096 29.7 / 27.1 at T = 1203, 38.4 / 33.9 at 2040, d = 5120 35.8 / 33.5 at 1250, d = 8192 53.1 / 47.2, d = 1024 12.3 / 11.6 at
-//   1500 (one k-tile per stage: 29.1, 37.1 at d = 4096); an odd number of k-tiles: d = 640 9.45 / 9.15 at 1500, 1600 17.5 / 16.3 at 2040, d = 384 level (its last stage
+//   1500 (one k-tile per stage: 29.1, 37.1 at d = 4096; without the 640 cycles / with: 34.4 / 33.6 at d = 4096, T = 2040, 21.5 / 21.3 at d = 2176, 0.5 % on short rows); an odd number of k-tiles: d = 640 9.45 / 9.15 at 1500, 1600 17.5 / 16.3 at 2040, d = 384 level (its last stage
 //   asks for the W1' of its one k-tile twice; a branch round the second half of a stage's requests: 6 % faster there, up to 5 % slower from d = 1920 on);
 //   128 rows: d = 4096 43.5 / 41.0 at T = 2100, 47.4 / 45.7 at 3000, but 50.9 / 51.1 at 3500, 55.4 / 56.4 at 4096; d = 2048 24.8 / 23.7, 27.0 / 26.4, 28.4 / 28.7, 30.4 / 32.6; d = 8192
 //   79.6 / 75.4, 86.8 / 86.3, 93.2 / 95.5, 102.8 / 107.4 (d = 5120 60.5 / 57.7 at 3000, 68.6 / 68.3 at 4096): with most of the CUs at work HBM bounds it, and

@@ -797,7 +797,7 @@ PrefillPlan plan_prefill(int dtype, int64_t C, int64_t T, int64_t d, int64_t b, 
     int kernel = kKernelRing;
     if (!ring_form) {
         // One whole tile for every CU or none (128 rows: more than half as many tiles as CUs, at most as many; 64 rows, widths 64 / 128: always): there is
-        // nothing to schedule, and the one-tile kernel is 1-3 % faster than the persistent one on such batches, on 64 rows 5-12 % (figures there).
+        // nothing to schedule, and the one-tile kernel is 1-3 % faster than the persistent one on such batches, on 64 rows 2-13 %, level on rows of three k-tiles (figures there).
         const bool one_tile_each = dtype != TIDE_F32 &&
                                    (rows_per_wg == 128 ? form == 6 || tile256 || (form == 0 && !two_halves && 2 * left > (int64_t)cus && left <= (int64_t)cus)
                                                        : form == 0 && !two_halves && left <= (int64_t)cus);
